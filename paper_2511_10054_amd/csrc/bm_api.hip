@@ -517,8 +517,9 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
     sp.T = T; sp.E = E; sp.n_shared = desc->n_shared;
     sp.n_tiles = (T + fp.tile_tokens - 1) / fp.tile_tokens;   // tiles of the front kernel (per-tile statistics)
     const bool persistent = !skinny && bf16 && persistent_device();
-    const int mode_gu = skinny ? (1 << 20) : tile_mode(desc, false, persistent);   // skinny: one table entry per live group
-    const int mode_dn = skinny ? (1 << 20) : tile_mode(desc, true, persistent);
+    const bool per_group = skinny || !bf16;              // decode and fp32 projections: one table entry per live group
+    const int mode_gu = per_group ? (1 << 30) : tile_mode(desc, false, persistent);
+    const int mode_dn = per_group ? (1 << 30) : tile_mode(desc, true, persistent);
     // the plain table serves whichever projection runs a single tile height (both, unless one is mixed)
     sp.BM = mode_gu != TILES_MIXED ? mode_gu : (mode_dn != TILES_MIXED ? mode_dn : 256);
     if (mode_gu == TILES_MIXED || mode_dn == TILES_MIXED) {
@@ -528,7 +529,7 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
         sp.mt_group_s = at<int32_t>(ws, L.mt_group_s); sp.mt_row0_s = at<int32_t>(ws, L.mt_row0_s);
         sp.n_mtiles_s = at<int32_t>(ws, L.n_mtiles_s);
     }
-    sp.largest_first = skinny ? 1 : 0;
+    sp.largest_first = per_group ? 1 : 0;
     sp.tile_counts = fp.tile_counts; sp.tile_base = at<int32_t>(ws, L.tile_base);
     sp.tile_stats = fp.tile_stats;
     sp.offsets = at<int32_t>(ws, L.offsets);
@@ -566,7 +567,7 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
         ScanParams sq = sp;
         sq.tile_stats = nullptr; sq.stats = nullptr;      // written by the substitution kernel
         err |= launch_grouping(sq, cp, st);
-    } else if (desc->dtype == BM_BF16 && sp.n_tiles == 1) {
+    } else if (sp.n_tiles == 1) {
         fp.tail = 1;                           // a single tile: its workgroup finishes the grouping too
         fp.scan = sp;
         fp.scat = cp;
@@ -635,9 +636,9 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
         mark(2);
         err |= launch_down_bf16(dp, st);
     } else {
-        err |= launch_gateup_f32(gp, L.rows_max, st);
+        err |= launch_gateup_f32(gp, L.rows_max, T, st);
         mark(2);
-        err |= launch_down_f32(dp, L.rows_max, st);
+        err |= launch_down_f32(dp, L.rows_max, T, st);
     }
     mark(3);
 

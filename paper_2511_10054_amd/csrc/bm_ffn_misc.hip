@@ -1,71 +1,7 @@
-// fp32 expert projections (plain fp32 FMA, one workgroup per row) and the
-// gate-weighted aggregation  y[t] = sum_k w[t][k] * o[pos(t,k)] + shared rows.
+// The gate-weighted aggregation  y[t] = sum_k w[t][k] * o[pos(t,k)] + shared rows.
 #include "bm_kernels.h"
 
 namespace bm {
-
-__device__ __forceinline__ float silu_precise(float a) { return a / (1.0f + expf(-a)); }
-
-// group of a row: offsets is non-decreasing with G+1 entries
-__device__ __forceinline__ int find_group(const int32_t *offsets, int G, int pos) {
-    int lo = 0, hi = G;               // offsets[lo] <= pos < offsets[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (offsets[mid] <= pos) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
-template <bool DUAL>
-__global__ void __launch_bounds__(256) rowwise_f32_kernel(GemmParams p) {
-    extern __shared__ float s_row[];
-    __shared__ int s_g;
-    const int pos = blockIdx.x;
-    if (pos >= p.n_mtiles[1]) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) s_g = find_group(p.offsets, p.n_groups, pos);
-    const int src = p.row_map ? p.row_map[pos] : pos;
-    const float *arow = static_cast<const float *>(p.a) + (size_t)src * p.Kd;
-    for (int j = tid; j < p.Kd; j += blockDim.x) s_row[j] = arow[j];
-    __syncthreads();
-    const int g = s_g;
-    const float *b0 = (g < p.E) ? static_cast<const float *>(p.b0) + (size_t)g * p.N * p.Kd
-                                : static_cast<const float *>(p.sb0) + (size_t)(g - p.E) * p.N * p.Kd;
-    const float *b1 = nullptr;
-    if (DUAL)
-        b1 = (g < p.E) ? static_cast<const float *>(p.b1) + (size_t)g * p.N * p.Kd
-                       : static_cast<const float *>(p.sb1) + (size_t)(g - p.E) * p.N * p.Kd;
-    float *c = static_cast<float *>(p.c) + (size_t)pos * p.N;
-    for (int n = wave; n < p.N; n += 4) {
-        const float *r0 = b0 + (size_t)n * p.Kd;
-        float s0 = 0.0f, s1 = 0.0f;
-        if (DUAL) {
-            const float *r1 = b1 + (size_t)n * p.Kd;
-            for (int j = lane; j < p.Kd; j += WAVE) {
-                s0 = fmaf(r0[j], s_row[j], s0);
-                s1 = fmaf(r1[j], s_row[j], s1);
-            }
-            s0 = wave_sum(s0);
-            s1 = wave_sum(s1);
-            if (lane == 0) c[n] = silu_precise(s0) * s1;
-        } else {
-            for (int j = lane; j < p.Kd; j += WAVE) s0 = fmaf(r0[j], s_row[j], s0);
-            s0 = wave_sum(s0);
-            if (lane == 0) c[n] = s0;
-        }
-    }
-}
-
-int launch_gateup_f32(const GemmParams &p, int max_rows, hipStream_t st) {
-    if (max_rows > 0)
-        hipLaunchKernelGGL(rowwise_f32_kernel<true>, dim3(max_rows), dim3(256), (size_t)p.Kd * sizeof(float), st, p);
-    return launch_status(__func__);
-}
-int launch_down_f32(const GemmParams &p, int max_rows, hipStream_t st) {
-    if (max_rows > 0)
-        hipLaunchKernelGGL(rowwise_f32_kernel<false>, dim3(max_rows), dim3(256), (size_t)p.Kd * sizeof(float), st, p);
-    return launch_status(__func__);
-}
 
 // ---------------------------------------------------------------------------
 // Aggregation: a gather per token in slot order, then the shared experts, so

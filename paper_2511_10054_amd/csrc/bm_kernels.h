@@ -69,8 +69,8 @@ struct FrontParams {
     int32_t *tile_counts;   // [E][n_tiles]
     int32_t *tile_stats;    // [n_tiles][4]
     int fused;              // one workgroup walks all tiles and also does the scan and the scatter
-    int tail;               // not fused, a single tile: the workgroup also finishes the grouping (bf16 kernel)
-    int tile_tokens;        // tokens per workgroup: TILE_T, or 16 for small batches (bf16 kernel, see front_tile_tokens)
+    int tail;               // not fused, a single tile: the workgroup also finishes the grouping
+    int tile_tokens;        // tokens per workgroup: TILE_T, or 16 for small batches and fp32 (see front_tile_tokens)
     ScanParams scan;        // used when fused or tail
     ScatterParams scat;     // used when fused or tail
 };
@@ -147,9 +147,9 @@ int launch_down_bf16(const GemmParams &p, hipStream_t st);     // c = a b0^T, bf
 bool persistent_device();       // the current device has the shape the persistent prefill kernels are laid out for
 bool down_split_tail(int Kd);   // the down projection of this reduction width may use p.splitk (its split tail)
 
-// fp32 FMA projections (one workgroup per row)
-int launch_gateup_f32(const GemmParams &p, int max_rows, hipStream_t st);
-int launch_down_f32(const GemmParams &p, int max_rows, hipStream_t st);
+// fp32 projections (the row-tile table lists each live group once); max_rows bounds the rows of all groups
+int launch_gateup_f32(const GemmParams &p, int max_rows, int T, hipStream_t st);
+int launch_down_f32(const GemmParams &p, int max_rows, int T, hipStream_t st);
 
 bool skinny_p_ok(int Kd, int ch);       // shape fits the persistent decode kernel with ring depth ch
 bool skinny_lds_ok(int Kd, int ksplit); // shape fits the LDS-staged decode kernel
