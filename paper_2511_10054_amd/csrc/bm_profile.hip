@@ -10,117 +10,143 @@
 
 namespace bm {
 
-// index of the pair (i < j) in a row-major strict upper triangle of an E x E matrix
-__device__ __forceinline__ int tri_index(int i, int j, int E) { return i * (2 * E - i - 1) / 2 + (j - i - 1); }
+// Co-activation counts by bit sets.  A workgroup takes CO_TOK tokens and CO_ROWS pivots: it writes, per expert, the
+// set of its chunk's tokens that hold the expert (one bit per token, LDS atomic OR - an expert listed twice sets one
+// bit twice, ids out of range set none; neighbouring lanes own different words, so that a popular expert's bits do
+// not queue on one), then counts every pair (pivot i, expert j) as the population count of
+// the two sets' intersection and adds it to the global int64 totals; the pair (i, i) is the activation count.
+// Bound by latency: one read of the chunk's ids, two barriers, the LDS reads of a thread's pairs (4 pivots: 7.1 us for
+// 4096 tokens of 8 out of 128 experts; 8 pivots 7.9, 16 pivots 15.3; 6.4 without the global atomics).  The kernel it
+// replaces walked a token per wave with lane permutes and flushed a whole triangle every 64 tokens: 41 us.
+constexpr int CO_TOK = 1024, CO_ROWS = 4, CO_WORDS = CO_TOK / 64;
 
-// One wave per token.  Lane k holds slot k's expert; a repeated or out-of-range id is dropped (an expert
-// counts once per token).  Counts are gathered in LDS (strict upper triangle, one int per pair) and added
-// to the global int64 totals once per workgroup, so the global atomics are per touched pair, not per token.
-template <int EMAX>
-__global__ void __launch_bounds__(256) coact_kernel(const int32_t *ids, int T, int K, int E, int tokens_per_wg,
-                                                    unsigned long long *A, unsigned long long *M) {
-    __shared__ int32_t s_pair[EMAX * (EMAX - 1) / 2];
-    __shared__ int32_t s_act[EMAX];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n_pair = E * (E - 1) / 2;
-    for (int i = tid; i < n_pair; i += blockDim.x) s_pair[i] = 0;
-    for (int i = tid; i < E; i += blockDim.x) s_act[i] = 0;
-    __syncthreads();
-    const int t_begin = blockIdx.x * tokens_per_wg, t_end = min(T, t_begin + tokens_per_wg);
-    for (int t = t_begin + wave; t < t_end; t += (int)(blockDim.x >> 6)) {
-        int e = lane < K ? ids[(size_t)t * K + lane] : -1;
-        bool valid = (unsigned)e < (unsigned)E;
-        for (int k = 0; k < K; ++k) {                      // drop repeats: keep the first occurrence
-            const int ek = __shfl(e, k, WAVE);
-            if (lane > k && ek == e) valid = false;
+__global__ void __launch_bounds__(CO_TOK) coact_kernel(const int32_t *ids, int T, int K, int E, unsigned long long *A,
+                                                       unsigned long long *M) {
+    __shared__ unsigned long long bits[BM_MAX_E][CO_WORDS + 1];         // padded: rows start in different banks
+    constexpr int PAIRS = CO_ROWS * BM_MAX_E / CO_TOK;                  // pairs of a thread
+    const int tid = threadIdx.x, row0 = blockIdx.x * CO_ROWS;
+    const int n_pairs = min(CO_ROWS, E - row0) * E;
+    const int chunks = T / CO_TOK + (T % CO_TOK ? 1 : 0);
+    int n[PAIRS] = {};
+    for (int c = blockIdx.y; c < chunks; c += gridDim.y) {
+        for (int i = tid; i < E * (CO_WORDS + 1); i += CO_TOK) (&bits[0][0])[i] = 0ull;
+        __syncthreads();
+        if (tid < T - c * CO_TOK) {
+            const int32_t *row = ids + ((size_t)c * CO_TOK + tid) * K;
+            for (int k0 = 0; k0 < K; k0 += 8) {                         // eight loads in flight
+                int e[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) e[i] = k0 + i < K ? row[k0 + i] : -1;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if ((unsigned)e[i] < (unsigned)E)
+                        atomicOr(reinterpret_cast<unsigned *>(bits[e[i]]) + (tid & 31), 1u << (tid >> 5));
+            }
         }
-        if (valid) atomicAdd(&s_act[e], 1);
-        for (int k = 0; k < K; ++k) {
-            const int ek = __shfl(e, k, WAVE);
-            const bool vk = __shfl((int)valid, k, WAVE) != 0;
-            if (vk && valid && lane > k) atomicAdd(&s_pair[tri_index(min(e, ek), max(e, ek), E)], 1);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PAIRS; ++q) {
+            const int idx = tid + q * CO_TOK;
+            if (idx >= n_pairs) break;
+            const unsigned long long *bi = bits[row0 + idx / E], *bj = bits[idx % E];
+#pragma unroll
+            for (int w = 0; w < CO_WORDS; ++w) n[q] += __popcll(bi[w] & bj[w]);
         }
+        __syncthreads();                                                // the next chunk clears the sets
     }
-    __syncthreads();
-    for (int i = tid; i < E; i += blockDim.x)
-        if (s_act[i]) atomicAdd(&A[i], (unsigned long long)s_act[i]);
-    for (int idx = tid; idx < E * E; idx += blockDim.x) {
-        const int i = idx / E, j = idx - i * E;
-        if (i >= j) continue;
-        const int v = s_pair[tri_index(i, j, E)];
-        if (v) {
-            atomicAdd(&M[(size_t)i * E + j], (unsigned long long)v);
-            atomicAdd(&M[(size_t)j * E + i], (unsigned long long)v);
-        }
+#pragma unroll
+    for (int q = 0; q < PAIRS; ++q) {
+        const int idx = tid + q * CO_TOK;
+        if (idx >= n_pairs) break;
+        const int i = row0 + idx / E, j = idx % E;
+        if (n[q]) atomicAdd(i == j ? &A[i] : &M[(size_t)i * E + j], (unsigned long long)n[q]);
     }
 }
 
-// One wave per pivot i.  Lane l owns peers l, l+64, ...; a peer's rank is the number of peers with a
-// larger count, or the same count and a lower index (the order of q = count / row sum); peers of rank r
-// form the sequence pi_i.  Lane 0 then walks the prefix sums: the list ends at the first t with
+// One workgroup per pivot i, thread j owns peer j.  A peer's rank is the number of peers with a larger count, or the
+// same count and a lower index (the order of q = count / row sum); peers of rank r form the sequence pi_i.  The
+// first wave then scans the prefix sums, four ranks per lane: the list ends at the first t with
 //   count(pi_i(1..t)) >= alpha * row sum         (one fp64 product, one comparison)
-// cut to at most R entries, at least one if the row sum is positive.
-__global__ void __launch_bounds__(64) buddy_build_kernel(const long long *M, int E, int R, float alpha,
-                                                         int32_t *table, int32_t *list_len, float *q_out) {
+// cut to at most R entries, at least one if the row sum is positive.  Bound by latency: E broadcast reads of the
+// counts per thread (one wave ranking two experts per lane and lane 0 walking the prefix sums: 14 us for 128 experts).
+__global__ void __launch_bounds__(BM_MAX_E) buddy_build_kernel(const long long *M, int E, int R, float alpha,
+                                                               int32_t *table, int32_t *list_len, float *q_out) {
     __shared__ long long s_cnt[BM_MAX_E];
     __shared__ int32_t s_order[BM_MAX_E];
-    const int i = blockIdx.x, lane = threadIdx.x;
-    long long total = 0;
-    for (int j = lane; j < E; j += WAVE) {
-        const long long c = (j == i) ? 0 : M[(size_t)i * E + j];
-        s_cnt[j] = c;
-        total += c;
-    }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) total += __shfl_xor(total, m, WAVE);
-    for (int j = lane; j < E; j += WAVE) s_order[j] = -1;
+    const int i = blockIdx.x, j = threadIdx.x;
+    const long long mine = (j < E && j != i) ? M[(size_t)i * E + j] : 0;
+    s_cnt[j] = mine;
+    s_order[j] = -1;
     __syncthreads();
-    for (int j = lane; j < E; j += WAVE) {
-        const long long c = s_cnt[j];
-        if (c <= 0) continue;
+    if (mine > 0) {
         int rank = 0;
+#pragma unroll 16
         for (int o = 0; o < E; ++o) {
             const long long co = s_cnt[o];
-            rank += (co > c) || (co == c && o < j);
+            rank += (int)(co > mine) | ((int)(co == mine) & (int)(o < j));
         }
         s_order[rank] = j;
     }
     __syncthreads();
-    if (lane == 0) {
-        int t_i = 0;
-        long long cum = 0;
-        const double need = (double)alpha * (double)total;
-        for (int r = 0; r < E && s_order[r] >= 0; ++r) {
-            cum += s_cnt[s_order[r]];
-            t_i = r + 1;
-            if ((double)cum >= need) break;
-        }
-        if (t_i > R) t_i = R;
-        for (int r = 0; r < R; ++r) {
-            table[(size_t)i * R + r] = r < t_i ? s_order[r] : -1;
-            if (q_out) q_out[(size_t)i * R + r] = r < t_i ? (float)((double)s_cnt[s_order[r]] / (double)total) : 0.0f;
-        }
-        if (list_len) list_len[i] = t_i;
+    if (j >= WAVE) return;
+    constexpr int PER = BM_MAX_E / WAVE;
+    int ord[PER];
+    long long cnt[PER], own = 0, total = 0;
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        ord[c] = s_order[j * PER + c];
+        cnt[c] = ord[c] >= 0 ? s_cnt[ord[c]] : 0;
+        own += cnt[c];
+        total += s_cnt[j * PER + c];
     }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) total += __shfl_xor(total, m, WAVE);
+    long long cum = own;                             // inclusive scan of the listed counts over the lanes
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+        const long long o = __shfl_up(cum, d, WAVE);
+        if (j >= d) cum += o;
+    }
+    cum -= own;
+    const double need = (double)alpha * (double)total;
+    int reach = E;                                   // first rank of this lane whose prefix sum reaches the threshold
+    int listed = 0;
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        cum += cnt[c];
+        if (ord[c] >= 0) {
+            ++listed;
+            if ((double)cum >= need && reach == E) reach = j * PER + c;
+        }
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        reach = min(reach, __shfl_xor(reach, m, WAVE));
+        listed += __shfl_xor(listed, m, WAVE);
+    }
+    const int t_i = min(min(reach + 1, listed), R);
+    for (int r = j; r < R; r += WAVE) {
+        const int o = r < t_i ? s_order[r] : -1;
+        table[(size_t)i * R + r] = o;
+        if (q_out) q_out[(size_t)i * R + r] = o >= 0 ? (float)((double)s_cnt[o] / (double)total) : 0.0f;
+    }
+    if (j == 0 && list_len) list_len[i] = t_i;
 }
 
 int launch_coactivation(const int32_t *ids, int T, int K, int E, long long *A, long long *M, hipStream_t st) {
     if (T > 0) {
-        // enough workgroups to fill the chip, enough tokens per workgroup to amortise the LDS flush
-        int per = (T + 511) / 512;
-        if (per < 64) per = 64;
-        const int grid = (T + per - 1) / per;
-        unsigned long long *a = reinterpret_cast<unsigned long long *>(A), *m = reinterpret_cast<unsigned long long *>(M);
-        if (E <= 64) hipLaunchKernelGGL(coact_kernel<64>, dim3(grid), dim3(256), 0, st, ids, T, K, E, per, a, m);
-        else if (E <= 128) hipLaunchKernelGGL(coact_kernel<128>, dim3(grid), dim3(256), 0, st, ids, T, K, E, per, a, m);
-        else hipLaunchKernelGGL(coact_kernel<256>, dim3(grid), dim3(256), 0, st, ids, T, K, E, per, a, m);
+        // up to two workgroups per unit; those of a longer batch walk several chunks before they add their counts up
+        const int rows = (E + CO_ROWS - 1) / CO_ROWS, chunks = T / CO_TOK + (T % CO_TOK ? 1 : 0), most = 512 / rows;
+        const dim3 grid(rows, chunks < most ? chunks : most);
+        hipLaunchKernelGGL(coact_kernel, grid, dim3(CO_TOK), 0, st, ids, T, K, E,
+                           reinterpret_cast<unsigned long long *>(A), reinterpret_cast<unsigned long long *>(M));
     }
     return launch_status(__func__);
 }
 
 int launch_buddy_build(const long long *M, int E, int R, float alpha, int32_t *table, int32_t *list_len, float *q,
                        hipStream_t st) {
-    hipLaunchKernelGGL(buddy_build_kernel, dim3(E), dim3(64), 0, st, M, E, R, alpha, table, list_len, q);
+    hipLaunchKernelGGL(buddy_build_kernel, dim3(E), dim3(BM_MAX_E), 0, st, M, E, R, alpha, table, list_len, q);
     return launch_status(__func__);
 }
 

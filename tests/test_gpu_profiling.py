@@ -49,6 +49,20 @@ def test_coactivation_counts(T, E, K):
     np.testing.assert_array_equal(M.cpu().numpy(), M_ref)
 
 
+@pytest.mark.parametrize("T,E,K", [(1023, 17, 3), (1024, 16, 1), (1025, 33, 9), (64, 1, 1), (20000, 250, 16)])
+def test_coactivation_at_the_edges_of_its_chunks(T, E, K):
+    """1024 tokens and 4 pivots make a workgroup: one less, exactly one, one more of either, and a batch that a
+    workgroup walks in several chunks (250 experts: 8 workgroups for 20 chunks).  Whole numbers, exact."""
+    print("coactivation edges", T, E, K, flush=True)
+    g = np.random.default_rng(T)
+    ids = np.stack([g.permutation(E)[:K] for _ in range(T)]).astype(np.int32)
+    ids[::5, 0] = E                                     # out of range
+    A_ref, M_ref = oracle.coactivation(np.where(ids < E, ids, -1), E)
+    A, M = _device_counts([ids], E, K)
+    np.testing.assert_array_equal(A.cpu().numpy(), A_ref)
+    np.testing.assert_array_equal(M.cpu().numpy(), M_ref)
+
+
 @pytest.mark.parametrize("E,K,R", [(8, 2, 3), (64, 6, 8), (128, 8, 8), (256, 8, 32), (37, 5, 1)])
 def test_buddy_table_builder(E, K, R):
     torch = _torch()
