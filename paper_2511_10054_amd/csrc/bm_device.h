@@ -58,25 +58,22 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 // Largest 32-bit key over the wave, returned to every lane as a wave-uniform value.  Within a row of
 // 16 lanes: four DPP exchanges (lane ^ 1, lane ^ 2, mirror inside a half row, mirror inside the row);
-// the four row results are then read with v_readlane and compared on the scalar side.
+// two more hand the row results on to lane 63, which one v_readlane fetches (four v_readlane and scalar
+// maxima cost more than the two exchanges).
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#define BM_DPP_MAX(ctrl_)                                                                             \
+#define BM_DPP_MAX(ctrl_, rows_)                                                                      \
     {                                                                                                 \
-        const uint32_t o_ = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl_, 0xF, 0xF, false); \
+        const uint32_t o_ = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl_, rows_, 0xF, false); \
         v = o_ > v ? o_ : v;                                                                          \
     }
-    BM_DPP_MAX(0xB1)     // quad_perm [1, 0, 3, 2]
-    BM_DPP_MAX(0x4E)     // quad_perm [2, 3, 0, 1]
-    BM_DPP_MAX(0x141)    // row_half_mirror
-    BM_DPP_MAX(0x140)    // row_mirror
+    BM_DPP_MAX(0xB1, 0xF)     // quad_perm [1, 0, 3, 2]
+    BM_DPP_MAX(0x4E, 0xF)     // quad_perm [2, 3, 0, 1]
+    BM_DPP_MAX(0x141, 0xF)    // row_half_mirror
+    BM_DPP_MAX(0x140, 0xF)    // row_mirror
+    BM_DPP_MAX(0x142, 0xA)    // lane 15 of each row into the next row (rows 1 and 3)
+    BM_DPP_MAX(0x143, 0xC)    // lane 31 into rows 2 and 3
 #undef BM_DPP_MAX
-    uint32_t best = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)v, 16 * r);
-        best = o > best ? o : best;
-    }
-    return best;
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // Order-preserving map of finite floats (and infinities) to unsigned integers, and back.  -0 is mapped

@@ -19,43 +19,55 @@
 namespace bm {
 
 // ---------------------------------------------------------------------------
-// Algorithm 1 for one token.  Slots are visited in order; the scan over a
-// buddy row has a fixed trip count H and selects the first acceptable entry
-// without an early exit.  `bitmap` is the residency mask (LDS), `table` the
-// buddy table (LDS or global), `ids` the token's K slots (read, then
-// overwritten in place), `w` its gate weights (nullable).
+// Sets of experts (the residency mask, a token's U_t) in W words of 64; W = ceil(E / 64) is known at compile time,
+// because picking one of four words costs most of a test.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool test_bit4(const uint64_t (&m)[4], int b) {
-    const int wi = b >> 6;
-    uint64_t wv = wi == 0 ? m[0] : wi == 1 ? m[1] : wi == 2 ? m[2] : m[3];
+template <int W>
+__device__ __forceinline__ bool test_bit(const uint64_t (&m)[W], int b) {
+    uint64_t wv = m[0];
+#pragma unroll
+    for (int i = 1; i < W; ++i) wv = (b >> 6) == i ? m[i] : wv;
     return (wv >> (b & 63)) & 1ull;
 }
-__device__ __forceinline__ void set_bit4(uint64_t (&m)[4], int b) {
-    const int wi = b >> 6;
+template <int W>
+__device__ __forceinline__ void set_bit(uint64_t (&m)[W], int b) {
     const uint64_t bit = 1ull << (b & 63);
-    m[0] |= wi == 0 ? bit : 0ull;
-    m[1] |= wi == 1 ? bit : 0ull;
-    m[2] |= wi == 2 ? bit : 0ull;
-    m[3] |= wi == 3 ? bit : 0ull;
+#pragma unroll
+    for (int i = 0; i < W; ++i) m[i] |= (W == 1 || (b >> 6) == i) ? bit : 0ull;
 }
 
 // Gates in front of the substitution (Section 3.1: TAE, Eq. 1, and probability margin;
 // Section 5.1: replacement budget).  From the token's K gate weights renormalised to sum 1:
 // the token may be given substitutes unless (BM_GATE_TAE and TAE <= tau) or (BM_GATE_MARGIN and
 // largest - second largest >= gamma); returns how many slots may be replaced (0 = none).
+// (eight weights at a time, so that their reads, divisions and logarithms overlap; the sums stay in slot order)
 __device__ __forceinline__ int replacement_budget(int K, uint32_t flags, float tau, float gamma, int rho,
                                                   const float *w) {
     int budget = (flags & BM_REPLACE_BUDGET) ? rho : 0x7fffffff;
     if (flags & (BM_GATE_TAE | BM_GATE_MARGIN)) {
         float sum = 0.0f;
-        for (int k = 0; k < K; ++k) sum += w[k];
+        for (int k0 = 0; k0 < K; k0 += 8) {
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = w[min(k0 + i, K - 1)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum = k0 + i < K ? sum + v[i] : sum;
+        }
         float h = 0.0f, p1 = 0.0f, p2 = 0.0f;
-        for (int k = 0; k < K; ++k) {
-            const float pk = w[k] / sum;
-            h -= pk > 0.0f ? pk * logf(pk) : 0.0f;
-            const float lo = fminf(p1, pk);
-            p1 = fmaxf(p1, pk);
-            p2 = fmaxf(p2, lo);
+        for (int k0 = 0; k0 < K; k0 += 8) {
+            float pk[8], t[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) pk[i] = w[min(k0 + i, K - 1)] / sum;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[i] = pk[i] > 0.0f ? pk[i] * logf(pk[i]) : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (k0 + i >= K) break;
+                h -= t[i];
+                const float lo = fminf(p1, pk[i]);
+                p1 = fmaxf(p1, pk[i]);
+                p2 = fmaxf(p2, lo);
+            }
         }
         const float tae = K > 1 ? h / logf((float)K) : 0.0f;
         if ((flags & BM_GATE_TAE) && tae <= tau) budget = 0;
@@ -71,80 +83,149 @@ __device__ __forceinline__ bool dist_bypass(int n_req, int n_cpu, float beta) {
 }
 
 // Token-aware buddy priority (Section 3.1, Eq. 3 with kappa = 0): how the normalised router logit of
-// expert b (its softmax probability over all experts) is obtained for the token at hand.
+// expert b (its softmax probability over all experts) is obtained for token t of the tile at hand.
 struct PsiSource {
     const float *q;        // [E][R] q[j|i] of every table entry; null: priority = table order
     float eta;
-    const float *logits;   // the token's logit row (bias included), with zmax and inv_den; or null
-    float zmax, inv_den;
-    const float *probs;    // the token's probability row; used when logits is null
-    __device__ __forceinline__ float zhat(int b) const {
-        return logits != nullptr ? __expf(logits[b] - zmax) * inv_den : probs[b];
+    int stride;            // between the tokens of logits or probs
+    const float *logits;   // logit rows (bias included), with zmax and inv_den per token; or null
+    const float *zmax, *inv_den;
+    const float *probs;    // probability rows; used when logits is null
+    __device__ __forceinline__ float zhat(int t, int b) const {
+        return logits != nullptr ? __expf(logits[t * stride + b] - zmax[t]) * inv_den[t] : probs[(size_t)t * stride + b];
     }
 };
 
-__device__ __forceinline__ void remap_token(int K, int E, int R, int H, uint32_t flags, float tau, float gamma,
-                                            int rho, const uint64_t *bitmap, const int32_t *table,
-                                            const int32_t *ids_in, int32_t *ids_out, float *w,
-                                            int &n_miss, int &n_sub, int &n_drop, const PsiSource &psi) {
-    const bool unique = (flags & BM_REMAP_UNIQUE) != 0;
-    int budget = 0x7fffffff;
-    if (flags & BM_GATE_ANY) budget = replacement_budget(K, flags, tau, gamma, rho, w);   // before any drop
-    uint64_t used[4] = {0ull, 0ull, 0ull, 0ull};   // U_t
-    for (int k = 0; k < K; ++k) {
-        int e = ids_in[k];
-        if ((unsigned)e < (unsigned)E) set_bit4(used, e);
+// Entries of a buddy row that may stand in for its expert: bit r set if entry r < H is in [0, E) and resident.
+// (8 entries at a time: the reads of a batch go out together)
+template <int W>
+__device__ __forceinline__ uint32_t acceptable_entries(const int32_t *row, int H, int E, const uint64_t (&resident)[W]) {
+    uint32_t m = 0;
+    for (int r0 = 0; r0 < H; r0 += 8) {
+        int b[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[i] = row[min(r0 + i, H - 1)];       // (no branches between the reads)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (r0 + i < H && (unsigned)b[i] < (unsigned)E && test_bit<W>(resident, b[i])) m |= 1u << (r0 + i);
     }
-    for (int k = 0; k < K; ++k) {
-        const int e = ids_in[k];
-        const bool valid = (unsigned)e < (unsigned)E;
-        const bool res = valid && ((bitmap[e >> 6 & 3] >> (e & 63)) & 1ull);
-        int out = res ? e : -1;
-        if (valid && !res) {
-            ++n_miss;
-            bool found = false;
-            const int32_t *row = table + (size_t)e * R;
-            const int depth = budget > 0 ? H : 0;          // budget used up or token gated: no search
-            if (psi.q == nullptr) {
-                for (int r = 0; r < depth; ++r) {
-                    const int b = row[r];
-                    const bool bvalid = (unsigned)b < (unsigned)E;
-                    const int bc = bvalid ? b : 0;
-                    bool ok = bvalid && ((bitmap[bc >> 6] >> (bc & 63)) & 1ull);
-                    ok = ok && !(unique && test_bit4(used, bc));
-                    out = (ok && !found) ? b : out;
-                    found = found || ok;
-                }
-            } else {
-                // the acceptable entry of largest q * (1 + eta * zhat); equal scores keep the earlier entry
-                const float *qrow = psi.q + (size_t)e * R;
-                float best = 0.0f;
-                for (int r = 0; r < depth; ++r) {
-                    const int b = row[r];
-                    const bool bvalid = (unsigned)b < (unsigned)E;
-                    const int bc = bvalid ? b : 0;
-                    bool ok = bvalid && ((bitmap[bc >> 6] >> (bc & 63)) & 1ull);
-                    ok = ok && !(unique && test_bit4(used, bc));
-                    const float score = qrow[r] * (1.0f + psi.eta * psi.zhat(bc));
-                    const bool take = ok && (!found || score > best);
-                    out = take ? b : out;
-                    best = take ? score : best;
-                    found = found || ok;
+    return m;
+}
+
+// Algorithm 1 for a tile of tokens; every thread of the workgroup calls it.  ids [ntok][K] sits in LDS, the router's
+// choice in, the substituted ids (-1 dropped) out; `accept` holds acceptable_entries() of every expert; `used`
+// is LDS scratch of ntok * W words (U_t: the tokens' original ids; read with BM_REMAP_UNIQUE only).
+//   1. a thread per assignment finds the candidate: the first acceptable entry that is not one of the token's
+//      original ids.  The assignment becomes expert | candidate << 8 | entry << 16 | PICK_* flags.
+//   2. a lane per token walks its slots in order: budget, and - where an earlier slot has just been given the
+//      candidate - the row's next acceptable entry.  What the walk reads is fetched eight slots at a time.
+// One lane's walk is a chain of dependent instructions of a few cycles each, so as much as possible happens in step 1
+// (8 tokens, 8 slots each, 128 experts: all of it in the walk 4.7 us).
+constexpr int PICK_RESIDENT = 1 << 24, PICK_CANDIDATE = 1 << 25, PICK_VALID = 1 << 26;
+
+template <int W>
+__device__ __forceinline__ void remap_tile(int ntok, int K, int E, int R, uint32_t flags, float tau, float gamma, int rho,
+                                           const uint64_t (&resident)[W], const uint32_t *accept, const int32_t *table,
+                                           int32_t *ids, float *w, unsigned long long *used, int32_t *stats,
+                                           const PsiSource &psi) {
+    const int tid = threadIdx.x, n = ntok * K;
+    const bool unique = (flags & BM_REMAP_UNIQUE) != 0;
+    if (unique) {
+        for (int i = tid; i < ntok * W; i += blockDim.x) used[i] = 0ull;
+        __syncthreads();
+        for (int idx = tid; idx < n; idx += blockDim.x) {
+            const int e = ids[idx];
+            if ((unsigned)e < (unsigned)E) atomicOr(&used[(idx / K) * W + (e >> 6)], 1ull << (e & 63));
+        }
+        __syncthreads();
+    }
+    for (int idx = tid; idx < n; idx += blockDim.x) {
+        const int e = ids[idx];
+        int v = 0;
+        if ((unsigned)e < (unsigned)E) {
+            v = e | PICK_VALID;
+            if (test_bit<W>(resident, e)) v |= PICK_RESIDENT;
+            else if (psi.q == nullptr) {
+                const unsigned long long *u = used + (idx / K) * W;
+                for (uint32_t m = accept[e]; m != 0u; m &= m - 1) {
+                    const int r = __builtin_ctz(m), b = table[(size_t)e * R + r];
+                    if (unique && ((u[b >> 6] >> (b & 63)) & 1ull)) continue;
+                    v |= PICK_CANDIDATE | b << 8 | r << 16;
+                    break;
                 }
             }
-            if (found) { ++n_sub; --budget; set_bit4(used, out); } else { ++n_drop; }
         }
-        ids_out[k] = out;
-        if (w != nullptr && out < 0) w[k] = 0.0f;
+        ids[idx] = v;
     }
+    __syncthreads();
+    if (tid < ntok) {
+        int32_t *tok = ids + tid * K;
+        float *tw = w != nullptr ? w + (size_t)tid * K : nullptr;
+        const unsigned long long *u = used + tid * W;
+        int n_miss = 0, n_sub = 0, budget = 0x7fffffff;
+        if (flags & BM_GATE_ANY) budget = replacement_budget(K, flags, tau, gamma, rho, tw);      // before any drop
+        uint64_t given[W] = {};                            // substitutes of the earlier slots
+        for (int k0 = 0; k0 < K; k0 += 8) {
+            int v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = tok[min(k0 + i, K - 1)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (k0 + i >= K) break;
+                const bool miss = (v[i] & (PICK_VALID | PICK_RESIDENT)) == PICK_VALID;
+                const int32_t *row = table + (size_t)(v[i] & 255) * R;
+                int cand = (v[i] >> 8) & 255;
+                bool ok = miss && (v[i] & PICK_CANDIDATE) != 0 && budget > 0;      // else used up or gated: no search
+                if (psi.q != nullptr) {
+                    // the acceptable entry of largest q * (1 + eta * zhat); equal scores keep the earlier entry
+                    if (miss && budget > 0) {
+                        const float *qrow = psi.q + (size_t)(v[i] & 255) * R;
+                        float best = 0.0f;
+                        for (uint32_t m = accept[v[i] & 255]; m != 0u; m &= m - 1) {
+                            const int r = __builtin_ctz(m), b = row[r];
+                            if (unique && (((u[b >> 6] >> (b & 63)) & 1ull) || test_bit<W>(given, b))) continue;
+                            const float score = qrow[r] * (1.0f + psi.eta * psi.zhat(tid, b));
+                            if (!ok || score > best) { cand = b; best = score; ok = true; }
+                        }
+                    }
+                } else if (unique && __any(ok && test_bit<W>(given, cand))) {      // rare: one branch for the wave
+                    if (ok && test_bit<W>(given, cand)) {
+                        ok = false;
+                        for (uint32_t m = accept[v[i] & 255] & ~((2u << ((v[i] >> 16) & 31)) - 1u); m != 0u; m &= m - 1) {
+                            const int b = row[__builtin_ctz(m)];
+                            if (((u[b >> 6] >> (b & 63)) & 1ull) || test_bit<W>(given, b)) continue;
+                            cand = b;
+                            ok = true;
+                            break;
+                        }
+                    }
+                }
+                if (unique) {                              // without U_t nobody asks
+#pragma unroll
+                    for (int c = 0; c < W; ++c) given[c] |= ok && (W == 1 || (cand >> 6) == c) ? 1ull << (cand & 63) : 0ull;
+                }
+                n_miss += miss ? 1 : 0;
+                n_sub += ok ? 1 : 0;
+                budget -= ok ? 1 : 0;
+                const int out = ok ? cand : (v[i] & PICK_RESIDENT) ? (v[i] & 255) : -1;
+                tok[k0 + i] = out;
+                if (tw != nullptr && out < 0) tw[k0 + i] = 0.0f;
+            }
+        }
+        if (n_miss) atomicAdd(&stats[0], n_miss);
+        if (n_sub) atomicAdd(&stats[1], n_sub);
+        if (n_miss - n_sub) atomicAdd(&stats[2], n_miss - n_sub);
+    }
+    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
 // Shared LDS block of the front kernels.
 // ---------------------------------------------------------------------------
 struct FrontLds {
-    int32_t ids[TILE_T * BM_MAX_K];
+    alignas(16) int32_t ids[TILE_T * BM_MAX_K];
     float w[TILE_T * BM_MAX_K];
+    unsigned long long used[TILE_T * 4];
     int32_t counts[BM_MAX_E];
     int32_t lut[BM_MAX_E];
     int32_t stats[4];
@@ -204,6 +285,8 @@ __device__ void tile_epilogue(const FrontParams &p, float *logits, int stride, i
             uint32_t key[EC];
 #pragma unroll
             for (int c = 0; c < EC; ++c) key[c] = (lane + 64 * c < E) ? float_to_ordered(myv[c]) : 0u;
+            int win = 0;                                   // lane r: the winner of round r
+            uint32_t won = 0u;
             for (int r = 0; r < K; ++r) {
                 uint32_t mine = key[0];
 #pragma unroll
@@ -218,24 +301,29 @@ __device__ void tile_epilogue(const FrontParams &p, float *logits, int stride, i
 #pragma unroll
                 for (int c = 0; c < EC; ++c)
                     if (lane + 64 * c == e_win) key[c] = 0u;
-                if (lane == 0) {
-                    s.ids[i * K + r] = e_win;
-                    s.w[i * K + r] = ordered_to_float(best);
-                }
+                win = lane == r ? e_win : win;
+                won = lane == r ? best : won;
+            }
+            if (lane < K) {
+                s.ids[i * K + lane] = win;
+                s.w[i * K + lane] = ordered_to_float(won);
             }
         }
         __builtin_amdgcn_wave_barrier();
-        const float zmax = s.w[i * K];
+        // lane k < K: the gate weight of slot k
+        const float zk = lane < K ? s.w[i * K + lane] : 0.0f;
+        const float zmax = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, zk)));
+        const float pk = (lane < K) ? expf(zk - zmax) : 0.0f;
         float denom = 0.0f;
         if (p.flags & BM_RENORM_TOPK) {
-            for (int k = 0; k < K; ++k) denom += expf(s.w[i * K + k] - zmax);     // same order in every lane
+            for (int k = 0; k < K; ++k)                    // in slot order
+                denom += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pk), k));
         } else {
             float part = 0.0f;
 #pragma unroll
             for (int c = 0; c < EC; ++c) part += (myv[c] == -INFINITY) ? 0.0f : expf(myv[c] - zmax);
             denom = wave_sum(part);
         }
-        const float pk = (lane < K) ? expf(s.w[i * K + lane] - zmax) : 0.0f;
         if (p.flags & BM_PSI_TOKEN) {
             // token-aware buddy priority needs every expert's softmax probability for this token: keep
             // (zmax, 1 / sum over all experts) for the substitution below, or write the probabilities out
@@ -296,43 +384,29 @@ __device__ void tile_epilogue(const FrontParams &p, float *logits, int stride, i
         if (tid == 0) { s.dist[0] = n_req; s.dist[1] = n_cpu; s.dist[2] = bypass ? 1 : 0; }
     }
 
+    const int32_t *tab = tab_in_lds ? s_table : p.table;
+    uint64_t resident[EC];
+#pragma unroll
+    for (int i = 0; i < EC; ++i) resident[i] = s.bitmap[i];
     if (p.flags & (BM_REMAP_UNIQUE | BM_GATE_ANY | BM_PSI_TOKEN)) {
         // Algorithm 1 proper (and its per-token gates and priorities): a lane walks its token's slots in order
-        if (tid < ntok) {
-            int n_miss = 0, n_sub = 0, n_drop = 0;
-            int32_t *tok_ids = &s.ids[tid * K];
-            float *tok_w = &s.w[tid * K];
-            PsiSource psi{};
-            if (psi_mode) {
-                psi.q = p.q; psi.eta = p.eta;
-                psi.logits = logits + tid * stride; psi.zmax = s.zmax[tid]; psi.inv_den = s.inv_den[tid];
-            }
-            remap_token(K, E, p.R, H, p.flags, p.tau, p.gamma, p.rho, s.bitmap,
-                        tab_in_lds ? s_table : p.table, tok_ids, tok_ids, tok_w, n_miss, n_sub, n_drop, psi);
-            if (n_miss) atomicAdd(&s.stats[0], n_miss);
-            if (n_sub) atomicAdd(&s.stats[1], n_sub);
-            if (n_drop) atomicAdd(&s.stats[2], n_drop);
-            for (int k = 0; k < K; ++k) {
-                const int e = tok_ids[k];
-                if (e >= 0) atomicAdd(&s.counts[e], 1);
-            }
+        uint32_t *accept = reinterpret_cast<uint32_t *>(s.lut);
+        for (int e = tid; e < E; e += blockDim.x) accept[e] = acceptable_entries<EC>(tab + (size_t)e * p.R, H, E, resident);
+        __syncthreads();
+        PsiSource psi{};
+        if (psi_mode) { psi.q = p.q; psi.eta = p.eta; psi.stride = stride; psi.logits = logits; psi.zmax = s.zmax; psi.inv_den = s.inv_den; }
+        remap_tile<EC>(ntok, K, E, p.R, p.flags, p.tau, p.gamma, p.rho, resident, accept, tab, s.ids, s.w, s.used, s.stats, psi);
+        for (int idx = tid; idx < n; idx += blockDim.x) {
+            const int e = s.ids[idx];
+            if (e >= 0) atomicAdd(&s.counts[e], 1);
         }
     } else {
-        // without the U_t test the substitute depends on the expert alone: one lane per expert scans
-        // its buddy row once (same fixed-trip select scan), then every assignment is a table lookup
-        const int32_t *tab = tab_in_lds ? s_table : p.table;
+        // without the U_t test the substitute depends on the expert alone: one lane per expert looks up its
+        // row's first acceptable entry, then every assignment is a table lookup
         for (int e = tid; e < E; e += blockDim.x) {
-            const bool res = (s.bitmap[e >> 6] >> (e & 63)) & 1ull;
-            int out = res ? e : -1;
-            bool found = res;
-            for (int r = 0; r < H; ++r) {
-                const int b = tab[e * p.R + r];
-                const bool bvalid = (unsigned)b < (unsigned)E;
-                const int bc = bvalid ? b : 0;
-                const bool ok = bvalid && ((s.bitmap[bc >> 6] >> (bc & 63)) & 1ull);
-                out = (ok && !found) ? b : out;
-                found = found || ok;
-            }
+            const bool res = test_bit<EC>(resident, e);
+            const uint32_t m = res ? 0u : acceptable_entries<EC>(tab + (size_t)e * p.R, H, E, resident);
+            const int out = res ? e : m != 0u ? tab[(size_t)e * p.R + __builtin_ctz(m)] : -1;
             s.lut[e] = out | (res ? 0 : 0x40000000);       // bit 30 marks "was not resident"
         }
         __syncthreads();
@@ -370,7 +444,7 @@ __device__ void tile_epilogue(const FrontParams &p, float *logits, int stride, i
 constexpr int FUSED_TILES = 1;
 
 struct FusedLds {
-    int32_t ids[FUSED_TILES][TILE_T * BM_MAX_K];   // substituted ids of every tile
+    alignas(16) int32_t ids[FUSED_TILES][TILE_T * BM_MAX_K];   // substituted ids of every tile
     int32_t counts[FUSED_TILES][BM_MAX_E];         // per-tile histograms
     int32_t stats[FUSED_TILES][4];
     int32_t dist[4];                               // distribution gate counters (single-tile batches)
@@ -378,43 +452,53 @@ struct FusedLds {
     int32_t tstart[BM_MAX_E + 16];                 // first row tile of each group
 };
 
-// exclusive prefix sum over the wave; `total` = sum over all lanes
+// exclusive prefix sum over the wave; `total` = sum over all lanes.  Four shifts inside each row of 16 lanes, then
+// the row sums handed on (DPP moves of a few cycles each; a lane permute through LDS takes over a hundred)
 __device__ __forceinline__ int wave_excl_scan(int v, int &total) {
-    const int lane = threadIdx.x & 63;
     int incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(incl, d, WAVE);
-        if (lane >= d) incl += o;
-    }
-    total = __shfl(incl, 63, WAVE);
+#define BM_DPP_ADD(ctrl_, rows_) incl += __builtin_amdgcn_update_dpp(0, incl, ctrl_, rows_, 0xF, false);
+    BM_DPP_ADD(0x111, 0xF)     // row_shr 1
+    BM_DPP_ADD(0x112, 0xF)     // row_shr 2
+    BM_DPP_ADD(0x114, 0xF)     // row_shr 4
+    BM_DPP_ADD(0x118, 0xF)     // row_shr 8
+    BM_DPP_ADD(0x142, 0xA)     // lane 15 of each row into the next row (rows 1 and 3)
+    BM_DPP_ADD(0x143, 0xC)     // lane 31 into rows 2 and 3
+#undef BM_DPP_ADD
+    total = __builtin_amdgcn_readlane(incl, 63);
     return incl - v;
 }
 
-// Stable placement of A assignments whose substituted ids sit in LDS (-1 = dropped): the position of
-// assignment a is start[e] plus the number of earlier assignments with the same expert e.  One wave
-// per expert walks the assignments 64 at a time; the rank inside a step is a ballot and a popcount.
-__device__ void place_assignments(const int32_t *ids, int A, int E, int K, const int32_t *start,
-                                  const ScatterParams &c) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-    for (int e = wave; e < E; e += nw) {
-        int run = start[e];
-        if (start[e + 1] == run) continue;             // nothing routed to this expert
-        for (int base = 0; base < A; base += WAVE) {
-            const int a = base + lane;
-            const bool mine = a < A && ids[a] == e;
-            const unsigned long long m = __ballot(mine);
-            if (mine) {
-                const int pos = run + __popcll(m & ((1ull << lane) - 1ull));
-                c.perm[pos] = a;
-                if (c.row_token) c.row_token[pos] = a / K;
-                c.inv_perm[a] = pos;
-            }
-            run += __popcll(m);
-        }
-    }
+// Per expert, the set of the assignments that hold it: bit a % 64 of masks[e * words + a / 64] for assignment a of A
+// whose substituted ids sit in LDS (-1 = dropped), words = ceil(A / 64).  The number of earlier assignments with the
+// same expert - the rank that a stable placement needs - is then a few population counts instead of a walk over the
+// assignments.  Every thread of the workgroup calls it; ends with a barrier.
+__device__ __forceinline__ void assignment_sets(const int32_t *ids, int A, int E, unsigned long long *masks) {
+    const int tid = threadIdx.x, words = (A + 63) >> 6;
+    for (int i = tid; i < E * words; i += blockDim.x) masks[i] = 0ull;
+    __syncthreads();
     for (int a = tid; a < A; a += blockDim.x)
-        if (ids[a] < 0) c.inv_perm[a] = -1;
+        if ((unsigned)ids[a] < (unsigned)E) atomicOr(&masks[ids[a] * words + (a >> 6)], 1ull << (a & 63));
+    __syncthreads();
+}
+__device__ __forceinline__ int earlier_assignments(const unsigned long long *masks, int words, int e, int a) {
+    const unsigned long long *m = masks + e * words;
+    int rank = __popcll(m[a >> 6] & ((1ull << (a & 63)) - 1ull));
+    for (int w = 0; w < (a >> 6); ++w) rank += __popcll(m[w]);
+    return rank;
+}
+
+// Stable placement: the position of assignment a is start[e] plus its rank in its expert's set.
+__device__ __forceinline__ void place_assignments(const int32_t *ids, int A, int E, int K, const int32_t *start,
+                                                  const unsigned long long *masks, const ScatterParams &c) {
+    for (int a = threadIdx.x; a < A; a += blockDim.x) {
+        const int e = ids[a];
+        const int pos = (unsigned)e < (unsigned)E ? start[e] + earlier_assignments(masks, (A + 63) >> 6, e, a) : -1;
+        if (pos >= 0) {
+            c.perm[pos] = a;
+            if (c.row_token) c.row_token[pos] = a / K;
+        }
+        c.inv_perm[a] = pos;
+    }
 }
 
 // The two row-tile lists of a projection that runs both tile heights in one launch (p.mixed): a group of n rows
@@ -469,16 +553,26 @@ __device__ void write_group_tables(const ScanParams &p, const int32_t *start, co
     const int tid = threadIdx.x, G = p.E + p.n_shared;
     for (int g = tid; g <= G; g += blockDim.x) p.offsets[g] = start[g];
     if (p.largest_first) {
-        for (int g = tid; g < G; g += blockDim.x) {
+        // eight lanes per group share the comparisons: group h comes first when it has more rows, or as many and a
+        // lower index, i.e. when rows * 512 - index is larger (one signed 64-bit difference, no chain of conditions)
+        const int part = tid & 7;
+        for (int g0 = 0; g0 < G; g0 += blockDim.x >> 3) {
+            const int g = min(g0 + (tid >> 3), G - 1);
             const int n = start[g + 1] - start[g];
-            if (n == 0) continue;
+            const long long mine = (long long)n * 512 - g;
             int rank = 0;
-            for (int h = 0; h < G; ++h) {
-                const int m = start[h + 1] - start[h];
-                rank += (m > n || (m == n && h < g)) ? 1 : 0;
+#pragma unroll 4
+            for (int h = part; h < G; h += 8) {
+                const long long d = mine - ((long long)(start[h + 1] - start[h]) * 512 - h);
+                rank += (int)((unsigned long long)d >> 63);
             }
-            p.mt_group[rank] = g;
-            p.mt_row0[rank] = start[g];
+            rank += __shfl_xor(rank, 1, WAVE);
+            rank += __shfl_xor(rank, 2, WAVE);
+            rank += __shfl_xor(rank, 4, WAVE);
+            if (part == 0 && n > 0 && g0 + (tid >> 3) < G) {
+                p.mt_group[rank] = g;
+                p.mt_row0[rank] = start[g];
+            }
         }
     } else {
         for (int g = tid; g < G; g += blockDim.x) {
@@ -494,10 +588,11 @@ __device__ void write_group_tables(const ScanParams &p, const int32_t *start, co
 // Everything after the per-expert counts of a batch whose substituted ids sit in LDS (one workgroup):
 // group offsets, the list of row tiles (or of live groups, largest first, for the decode projections),
 // statistics, stable placement.  counts: E entries in LDS; start / tstart: LDS scratch of G + 1 entries;
-// local_stats: the three substitution counters in LDS, or null to add up the per-tile ones.  Every thread of
-// the workgroup calls it, after a barrier behind the writes of ids and counts.
+// masks: assignment_sets() of the ids; local_stats: the three substitution counters in LDS, or null to add up the
+// per-tile ones.  Every thread of the workgroup calls it, after a barrier behind the writes of ids, counts and masks.
 __device__ void finish_groups(const ScanParams &p, const ScatterParams &c, const int32_t *ids, int A,
-                              const int32_t *counts, int32_t *start, int32_t *tstart, const int32_t *local_stats) {
+                              const int32_t *counts, int32_t *start, int32_t *tstart, const unsigned long long *masks,
+                              const int32_t *local_stats) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int E = p.E, G = p.E + p.n_shared, K = c.K;
     if (wave == 0) {                               // exclusive scans over the groups, a few consecutive groups per lane
@@ -537,7 +632,7 @@ __device__ void finish_groups(const ScanParams &p, const ScatterParams &c, const
         }
         if (lane == 0) { p.stats[wave] = sum; p.stats[3 + wave] = 0; }
     }
-    place_assignments(ids, A, E, K, start, c);
+    place_assignments(ids, A, E, K, start, masks, c);
     const int live = start[E];
     for (int pos = live + tid; pos < A; pos += blockDim.x) c.perm[pos] = -1;
     if (c.row_token)
@@ -545,7 +640,7 @@ __device__ void finish_groups(const ScanParams &p, const ScatterParams &c, const
             for (int t = tid; t < p.T; t += blockDim.x) c.row_token[start[E + sidx] + t] = t;
 }
 
-__device__ void fused_tail(const FrontParams &p, FusedLds &fs, int n_tiles) {
+__device__ void fused_tail(const FrontParams &p, FusedLds &fs, int n_tiles, unsigned long long *masks) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int E = p.E, K = p.K, n_shared = p.scan.n_shared, G = E + n_shared, BM = p.scan.BM;
     // group offsets and row-tile starts: one wave, up to 5 consecutive groups per lane
@@ -592,7 +687,8 @@ __device__ void fused_tail(const FrontParams &p, FusedLds &fs, int n_tiles) {
     }
     // stable placement (the batch is one tile)
     const int live = fs.start[E];
-    place_assignments(fs.ids[0], p.T * K, E, K, fs.start, p.scat);
+    assignment_sets(fs.ids[0], p.T * K, E, masks);
+    place_assignments(fs.ids[0], p.T * K, E, K, fs.start, masks, p.scat);
     for (int pos = live + tid; pos < p.T * K; pos += blockDim.x) p.scat.perm[pos] = -1;
     if (p.scat.row_token)
         for (int sidx = 0; sidx < n_shared; ++sidx)
@@ -618,11 +714,12 @@ __device__ void fused_tail(const FrontParams &p, FusedLds &fs, int n_tiles) {
 template <int NB, int NW, int U, bool FUSED>
 __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     static_assert(TILE_T == 32, "two 16-token row blocks per tile");
-    constexpr int STRIDE = NB * 16 + 1;
+    constexpr int STRIDE = NB * 16 + 4;                  // the four row groups of a partial tile start 16 banks apart
     constexpr int TILE = TILE_T * STRIDE;
     constexpr int NS_FIT = (68 * 1024) / (TILE * 4);
     constexpr int NS = NS_FIT >= NW ? NW : (NS_FIT < 1 ? 1 : NS_FIT);   // partial tiles kept side by side
-    __shared__ float part[NS * TILE];
+    __shared__ __attribute__((aligned(16))) float part[NS * TILE];
+    static_assert(sizeof(part) >= NB * 16 * (TILE_T * BM_MAX_K / 64) * 8, "holds the assignment sets as well");
     constexpr bool CAN_STAGE = !FUSED && U >= 2 && U % 2 == 0;
     __shared__ u32x4 stage[CAN_STAGE ? NW * 256 : 1];            // 4 KB per wave (see the staged product below)
     __shared__ FrontLds s;
@@ -640,6 +737,9 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     for (int nb = 0; nb < NB; ++nb) wb[nb] = wr + (size_t)min(nb * 16 + r16, p.E - 1) * p.d + kq * 8;
     const int ksteps = p.d >> 5;
     const int nbatch = ksteps / U;
+    static_assert((NW * 64) % (NB * 16) == 0, "a thread adds up logits of one expert only");
+    const int my_e = tid % (NB * 16);
+    const float my_bias = (p.bias != nullptr && my_e < p.E) ? p.bias[my_e] : 0.0f;
 
     for (int tile = tile_begin; tile < tile_end; ++tile) {
         const int t0 = tile * p.tile_tokens;
@@ -753,13 +853,17 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
         }
 
         // D[i][j] of a 16x16 block: lane holds column j = l % 16 and rows i = 4 * (l / 16) + v.
-        // NS partial tiles sit side by side in LDS; wave w adds into slot w % NS in round w / NS,
-        // then the slots are added in slot order: one fixed association, reproducible.
-        for (int r = 0; r < (NW + NS - 1) / NS; ++r) {
-            if (wave / NS == r) {
-                float *mine = part + (wave % NS) * TILE;
+        // ns partial tiles sit side by side in LDS (twice as many when the tile has 16 rows only); wave w adds
+        // into slot w % ns in round w / ns, then the slots are added in slot order: one fixed association,
+        // reproducible.
+        constexpr int NS2 = 2 * NS < NW ? 2 * NS : NW;
+        const int ns = two ? NS : NS2, slot_size = two ? TILE : 16 * STRIDE;
+        for (int r = 0; r < (NW + ns - 1) / ns; ++r) {
+            if (wave / ns == r) {
+                float *mine = part + (wave % ns) * slot_size;
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb)
+                for (int tb = 0; tb < 2; ++tb) {
+                    if (tb == 1 && !two) break;
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -767,15 +871,31 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                             float *q = &mine[(tb * 16 + 4 * kq + v) * STRIDE + nb * 16 + r16];
                             *q = (r == 0 ? 0.0f : *q) + acc[tb][nb][v];
                         }
+                }
             }
             __syncthreads();
         }
-        for (int idx = tid; idx < TILE_T * NB * 16; idx += NW * 64) {
-            const int i = idx / (NB * 16), e = idx - i * (NB * 16);
-            float sum = (p.bias != nullptr && e < p.E) ? p.bias[e] : 0.0f;
+        constexpr int STEP = NW * 64 / (NB * 16);
+        if (two) {
 #pragma unroll
-            for (int w = 0; w < NS; ++w) sum += part[w * TILE + i * STRIDE + e];
-            part[i * STRIDE + e] = sum;                // slot 0 becomes the logit tile (own element only)
+            for (int i0 = 0; i0 < 32; i0 += STEP) {
+                const int i = i0 + tid / (NB * 16);
+                float sum = my_bias;
+                if (i >= 32) break;
+#pragma unroll
+                for (int w = 0; w < NS; ++w) sum += part[w * TILE + i * STRIDE + my_e];
+                part[i * STRIDE + my_e] = sum;         // slot 0 becomes the logit tile (own element only)
+            }
+        } else {
+#pragma unroll
+            for (int i0 = 0; i0 < 16; i0 += STEP) {
+                const int i = i0 + tid / (NB * 16);
+                float sum = my_bias;
+                if (i >= 16) break;
+#pragma unroll
+                for (int w = 0; w < NS2; ++w) sum += part[w * (16 * STRIDE) + i * STRIDE + my_e];
+                part[i * STRIDE + my_e] = sum;
+            }
         }
         __syncthreads();
         tile_epilogue<(NB + 3) / 4>(p, part, STRIDE, TILE, s, tile);
@@ -788,12 +908,14 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
             __syncthreads();
         }
     }
-    if (FUSED) fused_tail(p, fs, n_tiles);
+    if (FUSED) fused_tail(p, fs, n_tiles, reinterpret_cast<unsigned long long *>(part));
     // a batch of one tile: this workgroup holds every substituted id and the histogram, and finishes the
     // grouping itself instead of leaving it to a launch of its own
     if (!FUSED && p.tail) {
         __syncthreads();
-        finish_groups(p.scan, p.scat, s.ids, p.T * p.K, s.counts, fs.start, fs.tstart, s.stats);
+        unsigned long long *masks = reinterpret_cast<unsigned long long *>(part);    // the logits and the table are done
+        assignment_sets(s.ids, p.T * p.K, p.E, masks);
+        finish_groups(p.scan, p.scat, s.ids, p.T * p.K, s.counts, fs.start, fs.tstart, masks, s.stats);
     }
 }
 
@@ -810,10 +932,11 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
 // ---------------------------------------------------------------------------
 template <int NB, int NW, int KS, bool PRE>
 __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
-    constexpr int TT = 16, STRIDE = NB * 16 + 1, TILE = TT * STRIDE;
+    constexpr int TT = 16, STRIDE = NB * 16 + 4, TILE = TT * STRIDE;
     constexpr int NS_FIT = (68 * 1024) / (TILE * 4);
     constexpr int NS = NS_FIT >= NW ? NW : NS_FIT;                // partial tiles kept side by side
-    __shared__ float part[NS * TILE];
+    __shared__ __attribute__((aligned(16))) float part[NS * TILE];
+    static_assert(sizeof(part) >= NB * 16 * (TT * BM_MAX_K / 64) * 8, "holds the assignment sets as well");
     __shared__ FrontLds s;
     __shared__ int32_t start[BM_MAX_E + 16], tstart[BM_MAX_E + 16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -907,68 +1030,93 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
     tile_epilogue<(NB + 3) / 4>(p, part, STRIDE, NS * TILE, s, tile);
     if (p.tail) {
         __syncthreads();
-        finish_groups(p.scan, p.scat, s.ids, p.T * p.K, s.counts, start, tstart, s.stats);
+        unsigned long long *masks = reinterpret_cast<unsigned long long *>(part);    // the logits and the table are done
+        assignment_sets(s.ids, p.T * p.K, p.E, masks);
+        finish_groups(p.scan, p.scat, s.ids, p.T * p.K, s.counts, start, tstart, masks, s.stats);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Stand-alone substitution kernel: one lane per token, bitmap and table in LDS.
+// Stand-alone substitution kernel: tiles of 64 tokens; table, acceptable entries and ids in LDS.  Bound by latency.  With the distribution gate every workgroup reads all routed ids for the request set (no scratch memory,
+// no grid-wide wait): 16 bytes per load, eight loads in flight per lane (3001 tokens of 8 out of 128 experts: 62 us
+// with one 4-byte load in flight and the buddy rows scanned entry by entry).
+// A single workgroup stores the counters, several add theirs to zeros (launch_remap).
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) remap_kernel(RemapParams p) {
-    extern __shared__ int32_t s_table[];
-    __shared__ uint64_t s_bitmap[4];
-    __shared__ unsigned long long s_req[4];
+constexpr int REMAP_TOK = 64;
+
+template <int W>
+__global__ void __launch_bounds__(1024) remap_kernel(RemapParams p) {
+    extern __shared__ int32_t s_table[];                // E * R entries, then E acceptable-entry masks
+    __shared__ int32_t s_req[64 * W];                   // distribution gate: the expert was routed to
+    __shared__ int32_t s_ids[REMAP_TOK * BM_MAX_K];
+    __shared__ unsigned long long s_used[REMAP_TOK * W];
     __shared__ int32_t s_stats[3];
     const int tid = threadIdx.x;
     const int ec = (p.E + 63) >> 6;
+    uint32_t *accept = reinterpret_cast<uint32_t *>(s_table + p.E * p.R);
     for (int idx = tid; idx < p.E * p.R; idx += blockDim.x) s_table[idx] = p.table[idx];
-    if (tid < 4) { s_bitmap[tid] = (tid < ec) ? p.bitmap[tid] : 0ull; s_req[tid] = 0ull; }
+    uint64_t resident[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) resident[i] = i < ec ? p.bitmap[i] : 0ull;
+    for (int e = tid; e < 64 * W; e += blockDim.x) s_req[e] = 0;
     if (tid < 3) s_stats[tid] = 0;
     __syncthreads();
     int H = p.H;
     if (p.flags & BM_GATE_DIST) {
-        // Eq. 2 over the whole batch, recomputed by every workgroup (no scratch memory, no grid-wide wait)
-        const size_t n = (size_t)p.T * p.K;
-        unsigned long long mine[4] = {0ull, 0ull, 0ull, 0ull};
-        for (size_t a = tid; a < n; a += blockDim.x) {
-            const int e = p.ids_in[a];
-            if ((unsigned)e < (unsigned)p.E) {
-                const unsigned long long bit = 1ull << (e & 63);
-                const int wi = e >> 6;
-                mine[0] |= wi == 0 ? bit : 0ull; mine[1] |= wi == 1 ? bit : 0ull;
-                mine[2] |= wi == 2 ? bit : 0ull; mine[3] |= wi == 3 ? bit : 0ull;
-            }
-        }
+        // Eq. 2 over the whole batch; every lane that meets an expert stores the same 1
+        const size_t n = (size_t)p.T * p.K, n_vec = n >> 2;
+        typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
+        for (size_t v0 = tid; v0 < n_vec; v0 += 8 * (size_t)blockDim.x) {
+            i32x4 v[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) if (mine[i]) atomicOr(&s_req[i], mine[i]);
+            for (int i = 0; i < 8; ++i) {
+                const size_t at = v0 + i * (size_t)blockDim.x;
+                v[i] = at < n_vec ? *(const BM_GLOBAL i32x4 *)(p.ids_in + 4 * at) : i32x4{-1, -1, -1, -1};
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if ((unsigned)v[i][c] < (unsigned)p.E) s_req[v[i][c]] = 1;
+        }
+        if (tid < (int)(n & 3)) {
+            const int e = p.ids_in[n_vec * 4 + tid];
+            if ((unsigned)e < (unsigned)p.E) s_req[e] = 1;
+        }
         __syncthreads();
         int n_req = 0, n_cpu = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            n_req += __popcll(s_req[i]);
-            n_cpu += __popcll(s_req[i] & ~s_bitmap[i]);
+        for (int i = 0; i < W; ++i) {
+            const uint64_t req = __ballot(s_req[64 * i + (tid & 63)] != 0);
+            n_req += __popcll(req);
+            n_cpu += __popcll(req & ~resident[i]);
         }
         const bool bypass = dist_bypass(n_req, n_cpu, p.beta);
         if (bypass) H = 0;
         if (p.stats != nullptr && blockIdx.x == 0 && tid == 0) {
             p.stats[3] = n_req; p.stats[4] = n_cpu; p.stats[5] = bypass ? 1 : 0;
         }
+    } else if (p.stats != nullptr && blockIdx.x == 0 && tid < 3) {
+        p.stats[3 + tid] = 0;
     }
-    int n_miss = 0, n_sub = 0, n_drop = 0;
-    for (int t = blockIdx.x * blockDim.x + tid; t < p.T; t += gridDim.x * blockDim.x) {
-        const int32_t *in = p.ids_in + (size_t)t * p.K;
-        int32_t *out = p.ids_out + (size_t)t * p.K;
-        float *w = p.w ? p.w + (size_t)t * p.K : nullptr;
-        PsiSource psi{};
-        if (p.flags & BM_PSI_TOKEN) { psi.q = p.q; psi.eta = p.eta; psi.probs = p.probs + (size_t)t * p.E; }
-        remap_token(p.K, p.E, p.R, H, p.flags, p.tau, p.gamma, p.rho, s_bitmap, s_table, in, out, w, n_miss,
-                    n_sub, n_drop, psi);
-    }
-    if (n_miss) atomicAdd(&s_stats[0], n_miss);
-    if (n_sub) atomicAdd(&s_stats[1], n_sub);
-    if (n_drop) atomicAdd(&s_stats[2], n_drop);
+    for (int e = tid; e < p.E; e += blockDim.x) accept[e] = acceptable_entries<W>(s_table + e * p.R, H, p.E, resident);
     __syncthreads();
-    if (p.stats != nullptr && tid < 3 && s_stats[tid]) atomicAdd(&p.stats[tid], s_stats[tid]);
+    for (int t0 = blockIdx.x * REMAP_TOK; t0 < p.T; t0 += gridDim.x * REMAP_TOK) {
+        const int ntok = min(REMAP_TOK, p.T - t0), n = ntok * p.K;
+        const int32_t *in = p.ids_in + (size_t)t0 * p.K;
+        for (int idx = tid; idx < n; idx += blockDim.x) s_ids[idx] = in[idx];
+        __syncthreads();
+        PsiSource psi{};
+        if (p.flags & BM_PSI_TOKEN) { psi.q = p.q; psi.eta = p.eta; psi.stride = p.E; psi.probs = p.probs + (size_t)t0 * p.E; }
+        remap_tile<W>(ntok, p.K, p.E, p.R, p.flags, p.tau, p.gamma, p.rho, resident, accept, s_table, s_ids,
+                      p.w != nullptr ? p.w + (size_t)t0 * p.K : nullptr, s_used, s_stats, psi);
+        for (int idx = tid; idx < n; idx += blockDim.x) p.ids_out[(size_t)t0 * p.K + idx] = s_ids[idx];
+        __syncthreads();
+    }
+    if (p.stats != nullptr && tid < 3) {
+        if (gridDim.x == 1) p.stats[tid] = s_stats[tid];
+        else if (s_stats[tid]) atomicAdd(&p.stats[tid], s_stats[tid]);
+    }
 }
 
 __global__ void zero_ints_kernel(int32_t *p, int n) {
@@ -1089,6 +1237,7 @@ __global__ void __launch_bounds__(1024) scan_kernel(ScanParams p) {
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) scatter_kernel(ScatterParams p) {
     __shared__ int32_t s_ids[TILE_T * BM_MAX_K];
+    __shared__ unsigned long long masks[BM_MAX_E * (TILE_T * BM_MAX_K / 64)];
     const int tid = threadIdx.x, tile = blockIdx.x, t0 = tile * p.tile_tokens;
     const int n_tiles_all = (p.T + p.tile_tokens - 1) / p.tile_tokens;
     const int K = p.K, E = p.E;
@@ -1098,16 +1247,14 @@ __global__ void __launch_bounds__(256) scatter_kernel(ScatterParams p) {
         const int e = p.ids[(size_t)t0 * K + idx];
         s_ids[idx] = ((unsigned)e < (unsigned)E) ? e : -1;
     }
-    __syncthreads();
+    assignment_sets(s_ids, n, E, masks);                 // (its first barrier is behind the stores above)
     const int live = p.offsets[E];
     for (int idx = tid; idx < n; idx += blockDim.x) {
         const int e = s_ids[idx];
         const int a = t0 * K + idx;
         int pos = -1;
         if (e >= 0) {
-            int rank = 0;
-            for (int j = 0; j < idx; ++j) rank += (s_ids[j] == e) ? 1 : 0;
-            pos = p.offsets[e] + p.tile_base[(size_t)e * n_tiles_all + tile] + rank;
+            pos = p.offsets[e] + p.tile_base[(size_t)e * n_tiles_all + tile] + earlier_assignments(masks, (n + 63) >> 6, e, idx);
             p.perm[pos] = a;
             if (p.row_token) p.row_token[pos] = a / K;
         }
@@ -1144,6 +1291,7 @@ __global__ void __launch_bounds__(1024) group_tiles_kernel(ScanParams p, Scatter
     __shared__ int32_t start[BM_MAX_E + 9];
     __shared__ int32_t tstart[BM_MAX_E + 9];
     __shared__ int32_t s_ids[TILE_T * BM_MAX_K];
+    __shared__ unsigned long long masks[BM_MAX_E * (TILE_T * BM_MAX_K / 64)];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
     const int tile = blockIdx.x, t0 = tile * c.tile_tokens;
     const int K = c.K, E = p.E, G = p.E + p.n_shared;
@@ -1153,6 +1301,7 @@ __global__ void __launch_bounds__(1024) group_tiles_kernel(ScanParams p, Scatter
         const int e = c.ids[(size_t)t0 * K + idx];
         s_ids[idx] = ((unsigned)e < (unsigned)E) ? e : -1;
     }
+    assignment_sets(s_ids, n, E, masks);                  // (its first barrier is behind the stores above)
     constexpr int EB = 8, SB = 4;                         // every load is a round trip to memory: EB * SB go out together
     for (int e0 = wave; e0 < E; e0 += nw * EB) {          // experts e0, e0 + nw, ..
         int tot[EB], bef[EB];
@@ -1231,9 +1380,7 @@ __global__ void __launch_bounds__(1024) group_tiles_kernel(ScanParams p, Scatter
         const int a = t0 * K + idx;
         int pos = -1;
         if (e >= 0) {
-            int rank = 0;
-            for (int j = 0; j < idx; ++j) rank += (s_ids[j] == e) ? 1 : 0;
-            pos = start[e] + before[e] + rank;
+            pos = start[e] + before[e] + earlier_assignments(masks, (n + 63) >> 6, e, idx);
             c.perm[pos] = a;
             if (c.row_token) c.row_token[pos] = a / K;
         }
@@ -1251,33 +1398,30 @@ __global__ void __launch_bounds__(1024) group_tiles_kernel(ScanParams p, Scatter
 // ---------------------------------------------------------------------------
 // Scan and scatter in one workgroup for small batches (at most SMALL_A
 // assignments): the substituted ids are staged in LDS, every expert's count
-// and the stable positions come from ballots over them (place_assignments).
+// and the stable positions come from its assignment set.
 // Writes what scan_kernel and scatter_kernel write, except the per-tile bases.
 // ---------------------------------------------------------------------------
-constexpr int SMALL_A = 1024;
+constexpr int SMALL_A = 1024, SMALL_SETS = 32768;    // assignments, assignments x experts
 
 __global__ void __launch_bounds__(1024) group_small_kernel(ScanParams p, ScatterParams c) {
     __shared__ int32_t ids[SMALL_A];
+    __shared__ unsigned long long masks[SMALL_SETS / 64 + BM_MAX_E];     // words are rounded up per expert
     __shared__ int32_t total[BM_MAX_E + 8];
     __shared__ int32_t start[BM_MAX_E + 9];
     __shared__ int32_t tstart[BM_MAX_E + 9];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-    const int E = p.E, A = c.T * c.K;
+    const int tid = threadIdx.x, E = p.E, A = c.T * c.K, words = (A + 63) >> 6;
     for (int a = tid; a < A; a += blockDim.x) {
         const int e = c.ids[a];
         ids[a] = ((unsigned)e < (unsigned)E) ? e : -1;
     }
-    __syncthreads();
-    for (int e = wave; e < E; e += nw) {
+    assignment_sets(ids, A, E, masks);                   // (its first barrier is behind the stores above)
+    for (int e = tid; e < E; e += blockDim.x) {
         int cnt = 0;
-        for (int base = 0; base < A; base += WAVE) {
-            const int a = base + lane;
-            cnt += __popcll(__ballot(a < A && ids[a] == e));
-        }
-        if (lane == 0) total[e] = cnt;
+        for (int w = 0; w < words; ++w) cnt += __popcll(masks[e * words + w]);
+        total[e] = cnt;
     }
     __syncthreads();
-    finish_groups(p, c, ids, A, total, start, tstart, nullptr);
+    finish_groups(p, c, ids, A, total, start, tstart, masks, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1329,18 +1473,29 @@ int launch_front(const FrontParams &p, int dtype, hipStream_t st) {
     return launch_status(__func__);
 }
 
+// Workgroups of one tile; up to REMAP_ONE tokens a single workgroup is faster, because it stores the counters itself
+// and needs no launch in front of it that zeroes them.
+constexpr int REMAP_ONE = 4 * REMAP_TOK;
+
 int launch_remap(const RemapParams &p, hipStream_t st) {
-    if (p.stats) hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, p.stats, 6);
-    if (p.T > 0) {
-        const size_t lds = (size_t)p.E * p.R * sizeof(int32_t);
-        int blocks = (p.T + 255) / 256;
-        if (p.flags & BM_GATE_DIST) {
-            // every workgroup reads all ids for the request set: bound their number; in place, a single
-            // workgroup reads the set before it overwrites anything
-            blocks = p.ids_out == p.ids_in ? 1 : (blocks > 256 ? 256 : blocks);
-        }
-        hipLaunchKernelGGL(remap_kernel, dim3(blocks), dim3(256), lds, st, p);
+    if (p.T <= 0) {
+        if (p.stats) hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, p.stats, 6);
+        return launch_status(__func__);
     }
+    const size_t lds = (size_t)p.E * (p.R + 1) * sizeof(int32_t);
+    // with the distribution gate every workgroup reads all ids for the request set: large workgroups, not too many
+    const bool dist = (p.flags & BM_GATE_DIST) != 0;
+    const int threads = dist ? 1024 : 256;
+    int blocks = 1;
+    // in place behind the gate, a single workgroup reads the request set before it overwrites anything
+    if (p.T > REMAP_ONE && !(dist && p.ids_out == p.ids_in)) {
+        blocks = (p.T - 1) / REMAP_TOK + 1;
+        blocks = blocks > (dist ? 256 : 1024) ? (dist ? 256 : 1024) : blocks;
+        if (p.stats) hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, p.stats, 3);
+    }
+    if (p.E <= 64) hipLaunchKernelGGL(remap_kernel<1>, dim3(blocks), dim3(threads), lds, st, p);
+    else if (p.E <= 128) hipLaunchKernelGGL(remap_kernel<2>, dim3(blocks), dim3(threads), lds, st, p);
+    else hipLaunchKernelGGL(remap_kernel<4>, dim3(blocks), dim3(threads), lds, st, p);
     return launch_status(__func__);
 }
 
@@ -1358,7 +1513,7 @@ int launch_scan(const ScanParams &p, hipStream_t st) {
 // The one-workgroup kernel walks every assignment once per expert (a wave per expert, 64 assignments a
 // step): fine for a few experts, slow for many (128 experts x 1024 assignments: 25 us against 12 us for the
 // per-tile kernel).
-bool grouping_small(long long assignments, int E) { return assignments <= SMALL_A && assignments * E <= 32768; }
+bool grouping_small(long long assignments, int E) { return assignments <= SMALL_A && assignments * E <= SMALL_SETS; }
 
 // scan + scatter: one kernel for small batches and for small histograms
 int launch_grouping(const ScanParams &sp, const ScatterParams &cp, hipStream_t st) {
