@@ -61,13 +61,30 @@ int tile_mode(const bm_layer_desc *d, bool down, bool persistent) {
     return ((long long)d->T * d->K / d->E >= 128) ? 256 : 128;
 }
 
+// Layers of many small experts at up to 32 tokens: the LDS-staged streaming kernel with two-wave workgroups
+// (32 weight rows), because 64-row blocks leave compute units without one.  ms with four waves | two waves,
+// Qwen3-shaped layer (E = 128, d = 2048, F = 768) at 2 / 8 / 16 / 32 / 64 tokens: .051 .060 .076 .086 .102 | .047
+// .059 .071 .082 .106; Mixtral-shaped (F = 14336, 224 blocks of 64 rows per expert) at 8 / 32 tokens .234 .319 |
+// .259 .324.  The line between the two lies at matrices of 16 MB; down projections beyond 2048 keep their slices.
+bool narrow_shape(const bm_layer_desc *d) {
+    return d->dtype == BM_BF16 && d->T <= 32 && d->d % 128 == 0 && d->F % 128 == 0 && d->F <= 2048 &&
+           (long long)d->d * d->F <= (1ll << 23);
+}
+// ... and widths that are multiples of 128 but not of 256 take it instead of the tiled path up to 16 tokens
+// (DeepSeek-shaped layer, F = 1408, at 3 / 8 / 16 / 32 tokens: tiled .061 .077 .080 .087, two-wave streaming .053
+// .062 .070 .089), as long as its fp32 down-projection output is small (the tiled path's is bf16): a layer
+// that fits the built-in scratch array on one path then fits it on the other.
+constexpr int NARROW_UNFIT_T = 16;
+constexpr long long NARROW_UNFIT_BYTES = 16ll << 20;
+
 // Few rows per group: every expert group is decode-sized and the projections are bound by reading the
 // weights once.  Up to 256 rows in all, or up to 16 rows per expert on average (Qwen3-shaped layer, 128
 // experts, 64 / 128 / 256 tokens: 0.11 / 0.13 / 0.16 ms against 0.14 / 0.15 / 0.16 ms on the tiled path), when
 // both widths fit the fast streaming kernels (multiples of 256).  Widths that do not (DeepSeek-shaped layer,
 // F = 1408, whose shared experts take every token as well) leave the streaming path to its slower
 // fallbacks: there the persistent tiled kernel is faster from 4 tokens on (4 / 8 / 32 tokens: 0.064 / 0.071 /
-// 0.089 against 0.068 / 0.082 / 0.101 ms), so the streaming path keeps only batches of at most 16 rows.
+// 0.089 against 0.068 / 0.082 / 0.101 ms), so the streaming path keeps only batches of at most 16 rows, unless
+// the two-wave kernel takes the shape (narrow_shape).
 // Mixtral-shaped layer, 8 experts, streaming | tiled, ms: 128 tokens 0.40 | 0.44, 192 tokens 0.55 | 0.47,
 // 256 tokens 0.59 | 0.48 (public weight layout; 0.48 | 0.47 and 0.52 | 0.48 on the packed copies).
 bool use_skinny(const bm_layer_desc *d) {
@@ -75,7 +92,8 @@ bool use_skinny(const bm_layer_desc *d) {
     const int ns = d->n_shared > 0 ? d->n_shared : 0;
     const long long rows = (long long)d->T * (d->K + ns);
     const bool fit = d->d % 256 == 0 && d->F % 256 == 0;
-    if (!fit && k64_shape(d)) return rows <= SKINNY_UNFIT_ROWS;
+    if (!fit && k64_shape(d))
+        return rows <= SKINNY_UNFIT_ROWS || (narrow_shape(d) && d->T <= NARROW_UNFIT_T && rows * (2ll * d->F + 4ll * d->d) <= NARROW_UNFIT_BYTES);
     if (rows <= SKINNY_MAX_ROWS) return true;
     return fit && rows <= (long long)SKINNY_AVG_ROWS * (d->E + ns);
 }
@@ -83,6 +101,7 @@ bool use_skinny(const bm_layer_desc *d) {
 // whose 4 waves split it once more): prefer a count that fits the
 // quarter-split kernel, else up to 8 slices of at least 16 k-steps.
 int skinny_ksplit(const bm_layer_desc *d) {
+    if (narrow_shape(d)) return 1;                       // the two-wave kernel takes the reduction whole
     // small groups: the persistent kernel splits the reduction inside one workgroup, no slices
     if ((long long)d->T * d->K <= 32 && (bm::skinny_p_ok(d->F, 14) || bm::skinny_p_ok(d->F, 8))) return 1;
     if ((long long)d->T * d->K > 32) {
@@ -622,6 +641,7 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
         s2.pk = pk_dn ? wt->wp_down : nullptr; s2.spk = pk_dn ? wt->wsp_down : nullptr;
         s2.c = dp.c; s2.N = desc->d; s2.Kd = desc->F; s2.ksplit = ksplit;
         s2.wide = (T > 64 && (long long)T * K >= 16ll * E) ? 1 : 0;
+        s1.narrow = s2.narrow = narrow_shape(desc) ? 1 : 0;      // where the persistent kernel does not apply
         // small batches on a matrix as many 16-row blocks wide as the device has units: the down kernel
         // aggregates its own results (null y: it writes them out for launch_combine below)
         s2.y = y; s2.w = fp.w; s2.inv_perm = cp.inv_perm; s2.T = T; s2.K = K; s2.n_shared = desc->n_shared;

@@ -289,17 +289,19 @@ static void launch_skinny_q(const SkinnyParams &p, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// Decode kernel for larger groups (up to 64 rows per pass).  A workgroup's 4
+// Decode kernel for larger groups (up to 64 rows per pass).  A workgroup's NWV = 4
 // waves own 4 different 16-row weight blocks and walk the whole reduction
 // together; the activation rows are staged by the workgroup in LDS in chunks
 // of CH k-steps, already in MFMA B-operand order (one 1 KB fragment per
 // k-step and 16-row block: contiguous ds_read_b128), double-buffered, so they
 // cost each wave a quarter of the loads and no ring registers.  Weights run
 // through the same rotating register ring as above.
-// Needs Kd divisible by 256 * ksplit (chunks of 8 k-steps).
+// Needs Kd divisible by 32 * CH * ksplit (chunks of CH = 8 k-steps, or 4).
+// NWV = 2: half as many weight rows per workgroup, for batches whose live groups times 64-row blocks are fewer than
+// the chip has slots (Qwen3-shaped layer, 8 tokens: about 30 live experts x 12 blocks on 512 slots, a unit's
+// streaming rate being capped: gate/up 33.0 -> 28.5 us).  With CH = 4 it also takes reductions that are a multiple of
+// 128 but not of 256 (DeepSeek-shaped F = 1408).
 // ---------------------------------------------------------------------------
-template <int NBT> struct SkinnyChunk { static constexpr int CH = 8; };
-constexpr int KUNIT = 256;                             // one chunk: SkinnyChunk::CH k-steps of 32
 
 // PACKED: the weights come from bm_pack_weights' fragment-major copy, where the 1 KB operand
 // fragment of every (16-row block, k-step) is contiguous (gate and up fragments interleaved), so a
@@ -311,13 +313,12 @@ constexpr int KUNIT = 256;                             // one chunk: SkinnyChunk
 // reads it, and a wave's LDS operations stay in order).  Loading the fragments directly, 16 rows x 64
 // bytes per instruction, touches twice the cache lines, which bounds the kernel: 252 us against 191 us for
 // the gate/up projection of the Mixtral-shaped layer at 64 tokens.
-template <bool DUAL, int NBT, bool PACKED>
+template <bool DUAL, int NBT, bool PACKED, int NWV, int CH>
 __device__ __forceinline__ void skinny_lds_pass(const SkinnyParams &p, const uint16_t *w0, const uint16_t *w1,
                                                 u32x4 *xs, u32x4 *wst, int row_begin, int row_end, int k_begin,
                                                 int k_end, int n0, int kslice, bool active) {
-    constexpr int CH = SkinnyChunk<NBT>::CH;
     constexpr int KSTEP = 512 * (DUAL ? 2 : 1);         // packed copy: weight elements between consecutive k-steps
-    constexpr int XW = CH / 4;                          // k-steps of a chunk each wave stages
+    constexpr int XW = CH / NWV;                        // k-steps of a chunk each wave stages
     BM_OPAQUE_PTR(w0);
     BM_OPAQUE_PTR(w1);
     static_assert(XW % 2 == 0, "a wave stages whole 128-byte lines (two k-steps) of every activation row");
@@ -459,14 +460,15 @@ __device__ __forceinline__ void skinny_lds_pass(const SkinnyParams &p, const uin
     }
 }
 
-// One item of the kernel below: 64 weight rows (a 16-row block per wave) of group g over reduction slice kslice.
-template <bool DUAL, int MAXNBT, bool PACKED>
+// One item of the kernel below: a 16-row weight block per wave of group g over reduction slice kslice.
+template <bool DUAL, int MAXNBT, bool PACKED, int NWV, int CH>
 __device__ __forceinline__ void skinny_lds_item(const SkinnyParams &p, u32x4 *xs, u32x4 *wstage, int g, int blk, int kslice) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int n0w = (blk * 4 + wave) * 16;
+    const int n0w = (blk * NWV + wave) * 16;
     const bool active = n0w < p.N;                    // a wave past the last weight row recomputes block 0 and stores nothing
     const int n0 = active ? n0w : 0;
     const int row_begin = p.offsets[g], row_end = p.offsets[g + 1];
+    constexpr int KUNIT = CH * 32;                    // one chunk
     const int per = (p.Kd / KUNIT) / p.ksplit;        // the host picks ksplit as a divisor
     const int k_begin = kslice * per * KUNIT, k_end = k_begin + per * KUNIT;
 
@@ -487,10 +489,10 @@ __device__ __forceinline__ void skinny_lds_item(const SkinnyParams &p, u32x4 *xs
     for (int rb = row_begin; rb < row_end; rb += PASS_ROWS) {
         const int re = min(row_end, rb + PASS_ROWS);
         const int n_rows = re - rb;
-        if (MAXNBT == 1 || n_rows <= 16) skinny_lds_pass<DUAL, 1, PACKED>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
-        else if (MAXNBT == 2 || n_rows <= 32) skinny_lds_pass<DUAL, 2, PACKED>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
-        else if (MAXNBT == 4 || n_rows <= 64) skinny_lds_pass<DUAL, 4, PACKED>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
-        else skinny_lds_pass<DUAL, MAXNBT, PACKED>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
+        if (MAXNBT == 1 || n_rows <= 16) skinny_lds_pass<DUAL, 1, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
+        else if (MAXNBT == 2 || n_rows <= 32) skinny_lds_pass<DUAL, 2, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
+        else if (MAXNBT == 4 || n_rows <= 64) skinny_lds_pass<DUAL, 4, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
+        else skinny_lds_pass<DUAL, MAXNBT, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
         __syncthreads();                              // the next pass restages the LDS buffers
     }
 }
@@ -502,26 +504,32 @@ __device__ __forceinline__ void skinny_lds_item(const SkinnyParams &p, u32x4 *xs
 // with the slice index outermost, 108 us with one workgroup per unit.  A fixed grid of two
 // workgroups per unit walking the items with a stride took 117 us: the items left for its second
 // round sit on a quarter of the units, and a unit's streaming rate is capped.
-template <bool DUAL, int MAXNBT, bool PACKED>
-__global__ void __launch_bounds__(256, MAXNBT <= 4 ? 2 : 1) skinny_lds_bf16_kernel(SkinnyParams p) {
-    __shared__ u32x4 xs[2 * SkinnyChunk<MAXNBT>::CH * MAXNBT * 64];
-    __shared__ u32x4 wstage[PACKED ? 1 : 4 * (DUAL ? 256 : 128)];    // public layout: 2 KB per wave and matrix
+template <bool DUAL, int MAXNBT, bool PACKED, int NWV, int CH>
+__global__ void __launch_bounds__(NWV * 64, NWV == 2 ? 2 : MAXNBT <= 4 ? 2 : 1) skinny_lds_bf16_kernel(SkinnyParams p) {
+    __shared__ u32x4 xs[2 * CH * MAXNBT * 64];
+    __shared__ u32x4 wstage[PACKED ? 1 : NWV * (DUAL ? 256 : 128)];  // public layout: 2 KB per wave and matrix
     const int gi = blockIdx.z;
     if (gi >= p.n_mtiles[0]) return;
-    skinny_lds_item<DUAL, MAXNBT, PACKED>(p, xs, wstage, p.mt_group[gi], blockIdx.x, blockIdx.y);
+    skinny_lds_item<DUAL, MAXNBT, PACKED, NWV, CH>(p, xs, wstage, p.mt_group[gi], blockIdx.x, blockIdx.y);
 }
 
-bool skinny_lds_ok(int Kd, int ksplit) { return Kd % (KUNIT * ksplit) == 0; }
+bool skinny_lds_ok(int Kd, int ksplit) { return Kd % (256 * ksplit) == 0; }
 
 template <bool DUAL>
 static void launch_skinny_lds(const SkinnyParams &p, hipStream_t st) {
-    dim3 grid((p.N / 16 + 3) / 4, p.ksplit, p.max_groups);
     // groups of more than 64 rows (more than 64 tokens): 128 rows per pass over the weights, at one workgroup
     // per compute unit (128 KB of staged activations), instead of two passes of 64
-    if (p.wide && p.pk != nullptr) hipLaunchKernelGGL((skinny_lds_bf16_kernel<DUAL, 8, true>), grid, dim3(256), 0, st, p);
-    else if (p.wide) hipLaunchKernelGGL((skinny_lds_bf16_kernel<DUAL, 8, false>), grid, dim3(256), 0, st, p);
-    else if (p.pk != nullptr) hipLaunchKernelGGL((skinny_lds_bf16_kernel<DUAL, 4, true>), grid, dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((skinny_lds_bf16_kernel<DUAL, 4, false>), grid, dim3(256), 0, st, p);
+#define BM_LAUNCH_LDS(NBT_, NWV_, CH_)                                                                          \
+    {                                                                                                           \
+        const dim3 grid((p.N / 16 + NWV_ - 1) / NWV_, p.ksplit, p.max_groups), block(NWV_ * 64);                \
+        if (p.pk != nullptr) hipLaunchKernelGGL((skinny_lds_bf16_kernel<DUAL, NBT_, true, NWV_, CH_>), grid, block, 0, st, p); \
+        else hipLaunchKernelGGL((skinny_lds_bf16_kernel<DUAL, NBT_, false, NWV_, CH_>), grid, block, 0, st, p); \
+    }
+    if (p.narrow && p.Kd % 256 == 0) BM_LAUNCH_LDS(2, 2, 8)
+    else if (p.narrow) BM_LAUNCH_LDS(2, 2, 4)
+    else if (p.wide) BM_LAUNCH_LDS(8, 4, 8)
+    else BM_LAUNCH_LDS(4, 4, 8)
+#undef BM_LAUNCH_LDS
 }
 
 // ---------------------------------------------------------------------------
@@ -838,6 +846,8 @@ static void launch_skinny(const SkinnyParams &p, dim3 grid, hipStream_t st) {
 
 int launch_skinny_gateup_bf16(const SkinnyParams &p, hipStream_t st) {
     if (launch_skinny_p<true>(p, st)) {
+    } else if (p.narrow) {
+        launch_skinny_lds<true>(p, st);
     } else if (p.max_rows_per_group > 32 && skinny_lds_ok(p.Kd, 1)) {
         launch_skinny_lds<true>(p, st);
     } else if (skinny_q_ok(p.Kd, 1)) {
@@ -851,6 +861,8 @@ int launch_skinny_gateup_bf16(const SkinnyParams &p, hipStream_t st) {
 
 int launch_skinny_down_bf16(const SkinnyParams &p, hipStream_t st) {
     if (p.ksplit == 1 && launch_skinny_p<false>(p, st)) {
+    } else if (p.narrow) {
+        launch_skinny_lds<false>(p, st);
     } else if (p.max_rows_per_group > 32 && skinny_lds_ok(p.Kd, p.ksplit)) {
         launch_skinny_lds<false>(p, st);
     } else if (skinny_q_ok(p.Kd, p.ksplit)) {
