@@ -954,8 +954,9 @@ __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmP
 }
 
 // Adds the chunks of every split tail tile in chunk order and writes the bf16 result (see TailSplit).
-// Grid (16 tail tiles, 8 XCDs, 16 slices of a tile): a workgroup handles one sixteenth of a tile - the
-// accumulator tiles (i, j) with i * 8 + j in [4 * blockIdx.z, 4 * blockIdx.z + 4) - with the chunk
+// Grid 8 XCDs x 16 slices of a tile x 16 tail tiles, the XCD fastest: workgroups are dealt round-robin to the XCDs, so
+// a tile's chunks are read where they were written and partly still sit in that XCD's L2.  A workgroup handles one
+// sixteenth of a tile - the accumulator tiles (i, j) with i * 8 + j in [4 * slice, 4 * slice + 4) - with the chunk
 // writers' thread -> element mapping, so that the reduction itself is spread over the chip.
 __global__ void __launch_bounds__(256) splitk_fixup_kernel(GemmParams p) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -964,7 +965,7 @@ __global__ void __launch_bounds__(256) splitk_fixup_kernel(GemmParams p) {
     const int n_nt = (p.N + 255) / 256;
     const int total = n_mt * n_nt;
     const int per_xcd = (total + 7) >> 3;
-    const int xcd = blockIdx.y, stride = p.splitk_stride, t = blockIdx.x;
+    const int xcd = blockIdx.x & 7, slice = (blockIdx.x >> 3) & 15, t = blockIdx.x >> 7, stride = p.splitk_stride;
     const TailSplit ts = tail_split(total, per_xcd, xcd, stride, p.Kd / 64, true);
     if (ts.S < 2 || t >= ts.rem) return;
     int mt, nt;
@@ -981,10 +982,10 @@ __global__ void __launch_bounds__(256) splitk_fixup_kernel(GemmParams p) {
 #pragma unroll
         for (int ch = 0; ch < 8; ++ch)
             if (ch < ts.S)
-                part[q][ch] = *(const BM_GLOBAL f32x4 *)(src + (size_t)ch * SPLIT_TILE_FLOATS + (blockIdx.z * 4 + q) * 256);
+                part[q][ch] = *(const BM_GLOBAL f32x4 *)(src + (size_t)ch * SPLIT_TILE_FLOATS + (slice * 4 + q) * 256);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int ij = blockIdx.z * 4 + q, i = ij >> 3, j = ij & 7;
+        const int ij = slice * 4 + q, i = ij >> 3, j = ij & 7;
         f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int ch = 0; ch < 8; ++ch)
@@ -1063,7 +1064,7 @@ int launch_down_bf16(const GemmParams &p, hipStream_t st) {
         GemmParams q = p;
         q.splitk_stride = persistent_grid(p, false) >> 3;
         hipLaunchKernelGGL((grouped_gemm256_k64w_bf16_kernel<false, true>), dim3(persistent_grid(p, false)), dim3(256), 0, st, q);
-        hipLaunchKernelGGL(splitk_fixup_kernel, dim3(16, 8, 16), dim3(256), 0, st, q);
+        hipLaunchKernelGGL(splitk_fixup_kernel, dim3(16 * 8 * 16), dim3(256), 0, st, q);
     } else if (p.BM == 256) {
         hipLaunchKernelGGL((grouped_gemm256_dma_bf16_kernel<false>), dim3(grid_for(p, false)), dim3(256), 0, st, p);
     } else {
