@@ -695,6 +695,19 @@ __device__ void fused_tail(const FrontParams &p, FusedLds &fs, int n_tiles, unsi
             for (int t = tid; t < p.T; t += blockDim.x) p.scat.row_token[fs.start[E + sidx] + t] = t;
 }
 
+// sum of N values `stride` apart, by pairs (log2 N roundings in a row instead of N)
+template <int N>
+__device__ __forceinline__ float add_slots(const float *at, int stride) {
+    float v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = at[i * stride];
+#pragma unroll
+    for (int d = 1; d < N; d *= 2)
+#pragma unroll
+        for (int i = 0; i + d < N; i += 2 * d) v[i] += v[i + d];
+    return v[0];
+}
+
 // ---------------------------------------------------------------------------
 // bf16 front kernel: router product on MFMA 16x16x32 (tokens x experts),
 // operands read from global memory directly in the instruction's layout:
@@ -705,19 +718,22 @@ __device__ void fused_tail(const FrontParams &p, FusedLds &fs, int n_tiles, unsi
 // the kernel; the 32x32x16 form reads 32 bytes per row and instruction.)  The
 // waves split the hidden dimension in batches of U k-steps; the loads of a
 // batch are all issued before its MFMAs.  The partial logit tiles of the waves
-// are written to LDS side by side and added in wave order (reproducible sum),
-// or, when NW tiles do not fit, added into one tile wave after wave.
-// NB = number of 16-expert column blocks, NW = waves per workgroup.
+// are written to LDS side by side and added by pairs (reproducible sum);
+// when NW tiles do not fit, some waves first add into another's tile.
+// NB = number of 16-expert column blocks, NW = waves per workgroup, NH = parts of the expert blocks over the waves (the
+// other factor of NW splits the hidden dimension): 128 experts on 16 waves of 4 blocks each have twice the loads in
+// flight and half the tokens to rank per wave that 8 waves of 8 blocks have, in the same registers.
 // FUSED: one workgroup walks all (<= FUSED_TILES) tiles and finishes the
 // grouping itself.
 // ---------------------------------------------------------------------------
-template <int NB, int NW, int U, bool FUSED>
+template <int NB, int NW, int U, bool FUSED, int NH = 1>
 __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     static_assert(TILE_T == 32, "two 16-token row blocks per tile");
     constexpr int STRIDE = NB * 16 + 4;                  // the four row groups of a partial tile start 16 banks apart
     constexpr int TILE = TILE_T * STRIDE;
-    constexpr int NS_FIT = (68 * 1024) / (TILE * 4);
-    constexpr int NS = NS_FIT >= NW ? NW : (NS_FIT < 1 ? 1 : NS_FIT);   // partial tiles kept side by side
+    constexpr int NS_FIT = (74 * 1024) / (TILE * 4);
+    constexpr int NBW = NB / NH, KW = NW / NH;           // expert blocks of a wave, waves along the hidden dimension
+    constexpr int NS = NS_FIT >= KW ? KW : (NS_FIT < 1 ? 1 : NS_FIT);   // partial tiles kept side by side
     __shared__ __attribute__((aligned(16))) float part[NS * TILE];
     static_assert(sizeof(part) >= NB * 16 * (TILE_T * BM_MAX_K / 64) * 8, "holds the assignment sets as well");
     constexpr bool CAN_STAGE = !FUSED && U >= 2 && U % 2 == 0;
@@ -727,14 +743,15 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     FusedLds &fs = fs_store[0];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, kq = lane >> 4;
+    const int kw = NH == 1 ? wave : wave % KW, nb0 = NH == 1 ? 0 : wave / KW * NBW;
     const uint16_t *x = static_cast<const uint16_t *>(p.x);
     const uint16_t *wr = static_cast<const uint16_t *>(p.wr);
     const int n_tiles = (p.T + p.tile_tokens - 1) / p.tile_tokens;
     const int tile_begin = FUSED ? 0 : blockIdx.x, tile_end = FUSED ? n_tiles : blockIdx.x + 1;
 
-    const uint16_t *wb[NB];
+    const uint16_t *wb[NBW];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) wb[nb] = wr + (size_t)min(nb * 16 + r16, p.E - 1) * p.d + kq * 8;
+    for (int nb = 0; nb < NBW; ++nb) wb[nb] = wr + (size_t)min((nb0 + nb) * 16 + r16, p.E - 1) * p.d + kq * 8;
     const int ksteps = p.d >> 5;
     const int nbatch = ksteps / U;
     static_assert((NW * 64) % (NB * 16) == 0, "a thread adds up logits of one expert only");
@@ -747,11 +764,11 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
         const uint16_t *xa[2];
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb) xa[tb] = x + (size_t)min(t0 + tb * 16 + r16, p.T - 1) * p.d + kq * 8;
-        f32x4 acc[2][NB];
+        f32x4 acc[2][NBW];
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[tb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int nb = 0; nb < NBW; ++nb) acc[tb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
         // Staged product: the operands are fetched as whole 128-byte lines (8 rows per instruction, half as
         // many lines touched as with 64 bytes per row - and with many experts the lines touched bound the
@@ -769,22 +786,22 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
             u32x4 *area = stage + (CAN_STAGE ? wave : 0) * 256;       // [block 0..1][row 0..15][piece 0..7]
             const int lrow = lane >> 3, lpiece = lane & 7;
             const uint16_t *xs_[2][2];
-            int woff[NB][2], wslot[2], rslot[2];
+            int woff[NBW][2], wslot[2], rslot[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int r = 8 * j + lrow;
 #pragma unroll
                 for (int tb = 0; tb < 2; ++tb) xs_[tb][j] = x + (size_t)min(t0 + tb * 16 + r, p.T - 1) * p.d + lpiece * 8;
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) woff[nb][j] = min(nb * 16 + r, p.E - 1) * p.d + lpiece * 8;
+                for (int nb = 0; nb < NBW; ++nb) woff[nb][j] = min((nb0 + nb) * 16 + r, p.E - 1) * p.d + lpiece * 8;
                 wslot[j] = r * 8 + (lpiece ^ (r & 7));
                 rslot[j] = r16 * 8 + ((j * 4 + kq) ^ (r16 & 7));     // fragment of the line's k-step j
             }
             const int nlb = p.d / (64 * LPB);
             ks_done = nlb * 2 * LPB;
-            for (int bt = wave; bt < nlb; bt += NW) {
+            for (int bt = kw; bt < nlb; bt += KW) {
                 const int k0 = bt * 64 * LPB;
-                u32x4 rx[LPB][2][2], rw[LPB][NB][2];                   // [line][operand block][row group]
+                u32x4 rx[LPB][2][2], rw[LPB][NBW][2];                   // [line][operand block][row group]
 #pragma unroll
                 for (int h = 0; h < LPB; ++h)
 #pragma unroll
@@ -792,7 +809,7 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                         rx[h][0][j] = ldg128(xs_[0][j] + k0 + h * 64);
                         if (two) rx[h][1][j] = ldg128(xs_[1][j] + k0 + h * 64);
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) rw[h][nb][j] = ldg128(wr + woff[nb][j] + k0 + h * 64);
+                        for (int nb = 0; nb < NBW; ++nb) rw[h][nb][j] = ldg128(wr + woff[nb][j] + k0 + h * 64);
                     }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -807,7 +824,7 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                         for (int ks = 0; ks < 2; ++ks) fa[tb][ks] = as_bf16x8(area[tb * 128 + rslot[ks]]);
                     }
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
+                    for (int nb = 0; nb < NBW; ++nb) {
                         u32x4 *ar = area + (nb & 1) * 128;
 #pragma unroll
                         for (int j = 0; j < 2; ++j) ar[wslot[j]] = rw[h][nb][j];
@@ -822,30 +839,30 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                 }
             }
         }
-        for (int bt = wave; !staged && bt < nbatch; bt += NW) {
+        for (int bt = kw; !staged && bt < nbatch; bt += KW) {
             const int k0 = bt * U * 32;
-            u32x4 ra[2][U], rb[NB][U];
+            u32x4 ra[2][U], rb[NBW][U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 ra[0][u] = ldg128(xa[0] + k0 + u * 32);
                 if (two) ra[1][u] = ldg128(xa[1] + k0 + u * 32);
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) rb[nb][u] = ldg128(wb[nb] + k0 + u * 32);
+                for (int nb = 0; nb < NBW; ++nb) rb[nb][u] = ldg128(wb[nb] + k0 + u * 32);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
+                for (int nb = 0; nb < NBW; ++nb) {
                     acc[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ra[0][u]), as_bf16x8(rb[nb][u]), acc[0][nb], 0, 0, 0);
                     if (two)
                         acc[1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ra[1][u]), as_bf16x8(rb[nb][u]), acc[1][nb], 0, 0, 0);
                 }
         }
-        for (int ks = ks_done + wave; ks < ksteps; ks += NW) {          // k-steps past the last full batch
+        for (int ks = ks_done + kw; ks < ksteps; ks += KW) {          // k-steps past the last full batch
             const bf16x8 a0 = as_bf16x8(ldg128(xa[0] + ks * 32)), a1 = as_bf16x8(ldg128(xa[1] + ks * 32));
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
+            for (int nb = 0; nb < NBW; ++nb) {
                 const bf16x8 b = as_bf16x8(ldg128(wb[nb] + ks * 32));
                 acc[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b, acc[0][nb], 0, 0, 0);
                 acc[1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b, acc[1][nb], 0, 0, 0);
@@ -853,22 +870,22 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
         }
 
         // D[i][j] of a 16x16 block: lane holds column j = l % 16 and rows i = 4 * (l / 16) + v.
-        // ns partial tiles sit side by side in LDS (twice as many when the tile has 16 rows only); wave w adds
-        // into slot w % ns in round w / ns, then the slots are added in slot order: one fixed association,
+        // ns partial tiles sit side by side in LDS (twice as many when the tile has 16 rows only); wave w of an
+        // expert part adds into slot w % ns in round w / ns, then the slots are added by pairs: one fixed association,
         // reproducible.
-        constexpr int NS2 = 2 * NS < NW ? 2 * NS : NW;
+        constexpr int NS2 = 2 * NS < KW ? 2 * NS : KW;
         const int ns = two ? NS : NS2, slot_size = two ? TILE : 16 * STRIDE;
-        for (int r = 0; r < (NW + ns - 1) / ns; ++r) {
-            if (wave / ns == r) {
-                float *mine = part + (wave % ns) * slot_size;
+        for (int r = 0; r < (KW + ns - 1) / ns; ++r) {
+            if (kw / ns == r) {
+                float *mine = part + (kw % ns) * slot_size;
 #pragma unroll
                 for (int tb = 0; tb < 2; ++tb) {
                     if (tb == 1 && !two) break;
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
+                    for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            float *q = &mine[(tb * 16 + 4 * kq + v) * STRIDE + nb * 16 + r16];
+                            float *q = &mine[(tb * 16 + 4 * kq + v) * STRIDE + (nb0 + nb) * 16 + r16];
                             *q = (r == 0 ? 0.0f : *q) + acc[tb][nb][v];
                         }
                 }
@@ -880,21 +897,15 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
 #pragma unroll
             for (int i0 = 0; i0 < 32; i0 += STEP) {
                 const int i = i0 + tid / (NB * 16);
-                float sum = my_bias;
                 if (i >= 32) break;
-#pragma unroll
-                for (int w = 0; w < NS; ++w) sum += part[w * TILE + i * STRIDE + my_e];
-                part[i * STRIDE + my_e] = sum;         // slot 0 becomes the logit tile (own element only)
+                part[i * STRIDE + my_e] = add_slots<NS>(part + i * STRIDE + my_e, TILE) + my_bias;   // slot 0 becomes the logit tile (own element only)
             }
         } else {
 #pragma unroll
             for (int i0 = 0; i0 < 16; i0 += STEP) {
                 const int i = i0 + tid / (NB * 16);
-                float sum = my_bias;
                 if (i >= 16) break;
-#pragma unroll
-                for (int w = 0; w < NS2; ++w) sum += part[w * (16 * STRIDE) + i * STRIDE + my_e];
-                part[i * STRIDE + my_e] = sum;
+                part[i * STRIDE + my_e] = add_slots<NS2>(part + i * STRIDE + my_e, 16 * STRIDE) + my_bias;
             }
         }
         __syncthreads();
@@ -920,6 +931,56 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
 }
 
 // ---------------------------------------------------------------------------
+// fp32 router product of its own, for few tiles and many experts: the front kernel below has one workgroup per 16
+// tokens, and 16 x 128 x 2048 products are 14 us of matrix instructions (plus the sums between them) on one unit.
+// Here a workgroup takes 16 tokens x 16 experts, its 8 waves split the hidden dimension; the front kernel then
+// starts from the logits (Qwen3-shaped layer, 128 tokens: 48 us -> 11 + 10 us).  Same operand layout and sums as below.
+// ---------------------------------------------------------------------------
+constexpr int ROUTER_NW = 8;
+
+__global__ void __launch_bounds__(ROUTER_NW * 64) router_f32_kernel(FrontParams p) {
+    __shared__ f32x4 part[ROUTER_NW][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, quad = lane >> 4;
+    const int e0 = blockIdx.x * 16, t0 = blockIdx.y * 16, d = p.d;
+    const float *xr = static_cast<const float *>(p.x) + (size_t)min(t0 + r16, p.T - 1) * d + quad * 4;
+    const float *wr = static_cast<const float *>(p.wr) + (size_t)min(e0 + r16, p.E - 1) * d + quad * 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k = wave * 32; k < d; k += ROUTER_NW * 32) {          // (d is a multiple of 32)
+        f32x4 a[2], b[2], c[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            a[s] = *(const BM_GLOBAL f32x4 *)(xr + k + s * 16);
+            b[s] = *(const BM_GLOBAL f32x4 *)(wr + k + s * 16);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            f32x4 q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) q[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i], b[s][i], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            c[s] = (q[0] + q[1]) + (q[2] + q[3]);
+        }
+        acc += c[0] + c[1];
+    }
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
+    f32x4 sum = part[0][lane];
+#pragma unroll
+    for (int w = 1; w < ROUTER_NW; ++w) sum += part[w][lane];
+    const int e = e0 + r16;
+    if (e >= p.E) return;
+    const float bias = p.bias != nullptr ? p.bias[e] : 0.0f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int t = t0 + 4 * quad + v;
+        if (t < p.T) p.logits[(size_t)t * p.E + e] = sum[v] + bias;
+    }
+}
+
+// Up to 64 tiles (a quarter of the units) and from 33 experts on; whole 32-value batches of aligned rows only.
+bool front_wants_logits(int T, int d, int E, int dtype) { return dtype == BM_F32 && T <= 1024 && E > 32 && d % 32 == 0; }
+
+// ---------------------------------------------------------------------------
 // fp32 front kernel: 16 tokens per workgroup, router product (tokens x experts) on v_mfma_f32_16x16x4_f32.
 // Lane l loads four consecutive k of row / column l % 16 (one 16-byte piece, piece l / 16 of a 16-wide k
 // slice); MFMA i of the slice takes component i of every piece, the same k order for both operands.  The
@@ -930,11 +991,12 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
 // Qwen3-shaped layer, 128 tokens 4354 us; tiny layer (8 experts, d = 64) 22 us.
 // NB = number of 16-expert column blocks, NW = waves, KS = 16-wide k slices per batch, PRE: load a batch ahead.
 // ---------------------------------------------------------------------------
-template <int NB, int NW, int KS, bool PRE>
+template <int NB, int NW, int KS, bool PRE, int NH = 1>
 __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
     constexpr int TT = 16, STRIDE = NB * 16 + 4, TILE = TT * STRIDE;
-    constexpr int NS_FIT = (68 * 1024) / (TILE * 4);
-    constexpr int NS = NS_FIT >= NW ? NW : NS_FIT;                // partial tiles kept side by side
+    constexpr int NS_FIT = (74 * 1024) / (TILE * 4);
+    constexpr int NBW = NB / NH, KW = NW / NH;           // as in the bf16 kernel
+    constexpr int NS = NS_FIT >= KW ? KW : NS_FIT;                // partial tiles kept side by side
     __shared__ __attribute__((aligned(16))) float part[NS * TILE];
     static_assert(sizeof(part) >= NB * 16 * (TT * BM_MAX_K / 64) * 8, "holds the assignment sets as well");
     __shared__ FrontLds s;
@@ -943,18 +1005,19 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
     const int r16 = lane & 15, quad = lane >> 4;
     const int tile = blockIdx.x, t0 = tile * TT, d = p.d;
     const float *xr = static_cast<const float *>(p.x) + (size_t)min(t0 + r16, p.T - 1) * d;
-    const float *wr[NB];
+    const int kw = NH == 1 ? wave : wave % KW, nb0 = NH == 1 ? 0 : wave / KW * NBW;
+    const float *wr[NBW];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) wr[nb] = static_cast<const float *>(p.wr) + (size_t)min(nb * 16 + r16, p.E - 1) * d;
+    for (int nb = 0; nb < NBW; ++nb) wr[nb] = static_cast<const float *>(p.wr) + (size_t)min((nb0 + nb) * 16 + r16, p.E - 1) * d;
 
-    f32x4 acc[NB];
+    f32x4 acc[NBW];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nb = 0; nb < NBW; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     constexpr int KB = KS * 16;
-    const int nbatch = (d + KB - 1) / KB;
+    const int nbatch = p.logits != nullptr ? 0 : (d + KB - 1) / KB;       // the product is there already
     const bool aligned = (d & 3) == 0;                            // rows start on 16-byte boundaries
-    f32x4 a[2][KS], b[2][NB][KS];
-    auto load = [&](int bt, f32x4 (&ra)[KS], f32x4 (&rb)[NB][KS]) {
+    f32x4 a[2][KS], b[2][NBW][KS];
+    auto load = [&](int bt, f32x4 (&ra)[KS], f32x4 (&rb)[NBW][KS]) {
         const bool plain = aligned && (bt + 1) * KB <= d;         // uniform
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -962,7 +1025,7 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
             if (plain) {
                 ra[ks] = *(const BM_GLOBAL f32x4 *)(xr + k);
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) rb[nb][ks] = *(const BM_GLOBAL f32x4 *)(wr[nb] + k);
+                for (int nb = 0; nb < NBW; ++nb) rb[nb][ks] = *(const BM_GLOBAL f32x4 *)(wr[nb] + k);
             } else {                                              // past the end: zeros in both operands
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -970,14 +1033,14 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
                     const int kc = in ? k + i : 0;
                     ra[ks][i] = in ? xr[kc] : 0.0f;
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) rb[nb][ks][i] = in ? wr[nb][kc] : 0.0f;
+                    for (int nb = 0; nb < NBW; ++nb) rb[nb][ks][i] = in ? wr[nb][kc] : 0.0f;
                 }
             }
         }
     };
-    auto multiply = [&](const f32x4 (&ra)[KS], const f32x4 (&rb)[NB][KS]) {
+    auto multiply = [&](const f32x4 (&ra)[KS], const f32x4 (&rb)[NBW][KS]) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
+        for (int nb = 0; nb < NBW; ++nb) {
             f32x4 c[KS];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
@@ -991,40 +1054,45 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
         }
     };
     if (PRE) {
-        if (wave < nbatch) load(wave, a[0], b[0]);
-        for (int bt = wave; bt < nbatch; bt += 2 * NW) {
-            if (bt + NW < nbatch) load(bt + NW, a[1], b[1]);
+        if (kw < nbatch) load(kw, a[0], b[0]);
+        for (int bt = kw; bt < nbatch; bt += 2 * KW) {
+            if (bt + KW < nbatch) load(bt + KW, a[1], b[1]);
             multiply(a[0], b[0]);
-            if (bt + NW >= nbatch) break;
-            if (bt + 2 * NW < nbatch) load(bt + 2 * NW, a[0], b[0]);
+            if (bt + KW >= nbatch) break;
+            if (bt + 2 * KW < nbatch) load(bt + 2 * KW, a[0], b[0]);
             multiply(a[1], b[1]);
         }
     } else {
-        for (int bt = wave; bt < nbatch; bt += NW) {
+        for (int bt = kw; bt < nbatch; bt += KW) {
             load(bt, a[0], b[0]);
             multiply(a[0], b[0]);
         }
     }
-    // D of a 16x16 block: lane holds column (expert) r16 and rows (tokens) 4 * quad + v; slots as in the bf16 kernel
-    for (int r = 0; r < (NW + NS - 1) / NS; ++r) {
-        if (wave / NS == r) {
-            float *mine = part + (wave % NS) * TILE;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    float *q = &mine[(4 * quad + v) * STRIDE + nb * 16 + r16];
-                    *q = (r == 0 ? 0.0f : *q) + acc[nb][v];
-                }
+    if (p.logits != nullptr) {
+        const int n = min(TT, p.T - t0) * p.E;
+        for (int idx = tid; idx < n; idx += NW * 64) {
+            const int i = idx / p.E, e = idx - i * p.E;
+            part[i * STRIDE + e] = p.logits[(size_t)t0 * p.E + idx];
         }
-        __syncthreads();
-    }
-    for (int idx = tid; idx < TT * NB * 16; idx += NW * 64) {
-        const int i = idx / (NB * 16), e = idx - i * (NB * 16);
-        float sum = 0.0f;
+    } else {
+        // D of a 16x16 block: lane holds column (expert) r16 and rows (tokens) 4 * quad + v; slots as in the bf16 kernel
+        for (int r = 0; r < (KW + NS - 1) / NS; ++r) {
+            if (kw / NS == r) {
+                float *mine = part + (kw % NS) * TILE;
 #pragma unroll
-        for (int w = 0; w < NS; ++w) sum += part[w * TILE + i * STRIDE + e];
-        part[i * STRIDE + e] = sum + ((p.bias != nullptr && e < p.E) ? p.bias[e] : 0.0f);
+                for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        float *q = &mine[(4 * quad + v) * STRIDE + (nb0 + nb) * 16 + r16];
+                        *q = (r == 0 ? 0.0f : *q) + acc[nb][v];
+                    }
+            }
+            __syncthreads();
+        }
+        for (int idx = tid; idx < TT * NB * 16; idx += NW * 64) {
+            const int i = idx / (NB * 16), e = idx - i * (NB * 16);
+            part[i * STRIDE + e] = add_slots<NS>(part + i * STRIDE + e, TILE) + ((p.bias != nullptr && e < p.E) ? p.bias[e] : 0.0f);
+        }
     }
     __syncthreads();
     tile_epilogue<(NB + 3) / 4>(p, part, STRIDE, NS * TILE, s, tile);
@@ -1037,9 +1105,10 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Stand-alone substitution kernel: tiles of 64 tokens; table, acceptable entries and ids in LDS.  Bound by latency.  With the distribution gate every workgroup reads all routed ids for the request set (no scratch memory,
-// no grid-wide wait): 16 bytes per load, eight loads in flight per lane (3001 tokens of 8 out of 128 experts: 62 us
-// with one 4-byte load in flight and the buddy rows scanned entry by entry).
+// Stand-alone substitution kernel: tiles of 64 tokens; table, acceptable entries and ids in LDS.  Bound by latency.
+// With the distribution gate every workgroup reads all routed ids for the request set (no scratch memory, no
+// grid-wide wait): 16 bytes per load, eight loads in flight per lane (3001 tokens of 8 out of 128 experts: 15 us; 62 us
+// with one 4-byte load in flight, the buddy rows scanned entry by entry and a whole walk per lane).
 // A single workgroup stores the counters, several add theirs to zeros (launch_remap).
 // ---------------------------------------------------------------------------
 constexpr int REMAP_TOK = 64;
@@ -1326,12 +1395,10 @@ __global__ void __launch_bounds__(1024) group_tiles_kernel(ScanParams p, Scatter
         }
 #pragma unroll
         for (int j = 0; j < EB; ++j) {
-#pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) {
-                tot[j] += __shfl_xor(tot[j], m, WAVE);
-                bef[j] += __shfl_xor(bef[j], m, WAVE);
-            }
-            if (lane == 0 && e0 + j * nw < E) { total[e0 + j * nw] = tot[j]; before[e0 + j * nw] = bef[j]; }
+            int t, b;                                     // sums over the wave (DPP moves, not lane permutes)
+            wave_excl_scan(tot[j], t);
+            wave_excl_scan(bef[j], b);
+            if (lane == 0 && e0 + j * nw < E) { total[e0 + j * nw] = t; before[e0 + j * nw] = b; }
         }
     }
     for (int g = E + tid; g < G; g += blockDim.x) total[g] = p.T;
@@ -1427,10 +1494,11 @@ __global__ void __launch_bounds__(1024) group_small_kernel(ScanParams p, Scatter
 // ---------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------
-template <int NB, int NW, int U>
+template <int NB, int NW, int U, int NH = 1>
 static void launch_front_bf16(const FrontParams &p, int n_tiles, hipStream_t st) {
-    if (p.fused) hipLaunchKernelGGL((front_bf16_kernel<NB, NW, U, true>), dim3(1), dim3(NW * 64), 0, st, p);
-    else hipLaunchKernelGGL((front_bf16_kernel<NB, NW, U, false>), dim3(n_tiles), dim3(NW * 64), 0, st, p);
+    // (the fused tail has no registers to spare for more waves)
+    if (p.fused) hipLaunchKernelGGL((front_bf16_kernel<NB, NW / NH, U, true>), dim3(1), dim3(NW / NH * 64), 0, st, p);
+    else hipLaunchKernelGGL((front_bf16_kernel<NB, NW, U, false, NH>), dim3(n_tiles), dim3(NW * 64), 0, st, p);
 }
 
 // One workgroup for the whole front end (router to placement): only with the distribution gate and a
@@ -1456,10 +1524,11 @@ int launch_front(const FrontParams &p, int dtype, hipStream_t st) {
     if (n_tiles == 0) return 0;
     const int nb = (p.E + 15) / 16;
     if (dtype == BM_F32) {
+        if (p.logits != nullptr) hipLaunchKernelGGL(router_f32_kernel, dim3(nb, n_tiles), dim3(ROUTER_NW * 64), 0, st, p);
         if (nb <= 1) hipLaunchKernelGGL((front_f32_kernel<1, 16, 2, true>), dim3(n_tiles), dim3(1024), 0, st, p);
         else if (nb <= 2) hipLaunchKernelGGL((front_f32_kernel<2, 8, 2, true>), dim3(n_tiles), dim3(512), 0, st, p);
         else if (nb <= 4) hipLaunchKernelGGL((front_f32_kernel<4, 8, 2, true>), dim3(n_tiles), dim3(512), 0, st, p);
-        else if (nb <= 8) hipLaunchKernelGGL((front_f32_kernel<8, 8, 2, true>), dim3(n_tiles), dim3(512), 0, st, p);
+        else if (nb <= 8) hipLaunchKernelGGL((front_f32_kernel<8, 16, 2, false, 2>), dim3(n_tiles), dim3(1024), 0, st, p);
         else hipLaunchKernelGGL((front_f32_kernel<16, 8, 1, false>), dim3(n_tiles), dim3(512), 0, st, p);
     } else {
         // a tile is latency-bound: 16 waves split the product and rank two tokens each; U keeps a batch
@@ -1467,7 +1536,7 @@ int launch_front(const FrontParams &p, int dtype, hipStream_t st) {
         if (nb <= 1) launch_front_bf16<1, 16, 4>(p, n_tiles, st);
         else if (nb <= 2) launch_front_bf16<2, 16, 4>(p, n_tiles, st);
         else if (nb <= 4) launch_front_bf16<4, 16, 2>(p, n_tiles, st);
-        else if (nb <= 8) launch_front_bf16<8, 8, 2>(p, n_tiles, st);
+        else if (nb <= 8) launch_front_bf16<8, 16, 2, 2>(p, n_tiles, st);
         else launch_front_bf16<16, 8, 1>(p, n_tiles, st);
     }
     return launch_status(__func__);

@@ -212,15 +212,28 @@ __device__ __forceinline__ void f32_tile(const GemmParams &p, float *smem, const
 }
 
 // The row-tile table lists each live group once, largest first (groups with more rows take longer per tile: the
-// short ones fill the end of the launch).  A unit is a group and a block of output columns; its row tiles are
-// dealt to `chunks` workgroups.  Workgroups go round-robin to the 8 XCDs: the row tiles of a unit take
-// consecutive turns of one XCD, whose L2 then holds the weight block.
+// short ones fill the end of the launch).  A unit is a group and a block of output columns; up to F32_CHUNKS of its
+// row tiles run side by side.  The grid holds the units of the last row tile first and those of the first one last.
+// Only the first max_rows / (64 c) groups can have a row tile c, so there are few workgroups without work, and those
+// do not alternate with the others: workgroups are dealt out in turn to the parts of an XCD, and a launch whose
+// every second workgroup was empty ran on half of the chip (gate/up 201 -> 175 us, down 122 -> 89 us).  A unit's row
+// tiles all go to one XCD, whose L2 then holds the weight block.
+__host__ __device__ __forceinline__ int f32_units(int chunk, int groups, int max_rows, int n_nt) {
+    const int most = chunk == 0 ? groups : max_rows / (F32_ROWS * chunk);
+    return ((most < groups ? most : groups) * n_nt + 7) / 8 * 8;
+}
+
 template <bool DUAL, int CHAIN>
-__global__ void __launch_bounds__(256) grouped_gemm_f32_kernel(GemmParams p, int chunks) {
+__global__ void __launch_bounds__(256) grouped_gemm_f32_kernel(GemmParams p, int chunks, int groups, int max_rows) {
     __shared__ __attribute__((aligned(1024))) float smem[F32_STAGES * (F32_ROWS + 64) * 32];
     constexpr int BLK = DUAL ? 32 : 64;
     const int n_nt = (p.N + BLK - 1) / BLK;
-    const int turn = blockIdx.x >> 3, unit = (turn / chunks) * 8 + (blockIdx.x & 7), chunk = turn % chunks;
+    int unit = blockIdx.x, chunk = chunks - 1;
+    for (; chunk > 0; --chunk) {
+        const int n = f32_units(chunk, groups, max_rows, n_nt);
+        if (unit < n) break;
+        unit -= n;
+    }
     if (unit >= p.n_mtiles[0] * n_nt) return;
     const int mt = unit / n_nt, nt = unit - mt * n_nt;
     const int g = p.mt_group[mt];
@@ -246,9 +259,11 @@ static int launch_f32(const GemmParams &p, int max_rows, int T, hipStream_t st) 
         const int tiles = (T + F32_ROWS - 1) / F32_ROWS;          // a group rarely holds a token twice
         const int chunks = tiles < F32_CHUNKS ? tiles : F32_CHUNKS;
         const int groups = p.n_groups < max_rows ? p.n_groups : max_rows;
-        const int units = (groups * ((p.N + BLK - 1) / BLK) + 7) / 8 * 8;
-        if (p.Kd < 1024) hipLaunchKernelGGL((grouped_gemm_f32_kernel<DUAL, 1>), dim3(units * chunks), dim3(256), 0, st, p, chunks);
-        else hipLaunchKernelGGL((grouped_gemm_f32_kernel<DUAL, 2>), dim3(units * chunks), dim3(256), 0, st, p, chunks);
+        const int n_nt = (p.N + BLK - 1) / BLK;
+        int grid = 0;
+        for (int c = 0; c < chunks; ++c) grid += f32_units(c, groups, max_rows, n_nt);
+        if (p.Kd < 1024) hipLaunchKernelGGL((grouped_gemm_f32_kernel<DUAL, 1>), dim3(grid), dim3(256), 0, st, p, chunks, groups, max_rows);
+        else hipLaunchKernelGGL((grouped_gemm_f32_kernel<DUAL, 2>), dim3(grid), dim3(256), 0, st, p, chunks, groups, max_rows);
     } else {
         hipLaunchKernelGGL(rowwise_f32_kernel<DUAL>, dim3(max_rows), dim3(256), (size_t)p.Kd * sizeof(float), st, p);
     }

@@ -60,6 +60,7 @@ struct FrontParams {
     float beta;             // distribution-gate threshold (BM_GATE_DIST: only when one tile holds the batch)
     const float *q;         // [E][R] q of the table entries (BM_PSI_TOKEN)
     float eta;
+    float *logits;          // [T][E] scratch: the router product runs in a launch of its own (fp32, front_wants_logits), or null
     float *probs_out;       // [T][E]: with BM_PSI_TOKEN, write every expert's probability (or null)
     int32_t *ids;           // [T][K] router's choice
     float *w;               // [T][K]
@@ -134,6 +135,7 @@ int launch_status(const char *what);
 
 bool front_can_fuse(int T, int dtype, uint32_t flags);   // the batch is small enough for the one-workgroup front end
 int front_tile_tokens(int T, int dtype, bool fused);   // tokens per workgroup of the front kernel
+bool front_wants_logits(int T, int d, int E, int dtype);   // FrontParams::logits pays if there is room for it
 int launch_front(const FrontParams &p, int dtype, hipStream_t st);
 int launch_remap(const RemapParams &p, hipStream_t st);
 int launch_count(const int32_t *ids, int T, int K, int E, int tile_tokens, int32_t *tile_counts, hipStream_t st);
