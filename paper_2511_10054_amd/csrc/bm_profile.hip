@@ -29,19 +29,22 @@ __global__ void __launch_bounds__(CO_TOK) coact_kernel(const int32_t *ids, int T
     const int chunks = T / CO_TOK + (T % CO_TOK ? 1 : 0);
     int n[PAIRS] = {};
     for (int c = blockIdx.y; c < chunks; c += gridDim.y) {
+        const bool mine = tid < T - c * CO_TOK;
+        const int32_t *row = ids + ((size_t)c * CO_TOK + tid) * K;
+        int e[8];                                                       // eight loads in flight, the first ones while
+#pragma unroll                                                          // the sets are cleared
+        for (int i = 0; i < 8; ++i) e[i] = mine && i < K ? row[i] : -1;
         for (int i = tid; i < E * (CO_WORDS + 1); i += CO_TOK) (&bits[0][0])[i] = 0ull;
         __syncthreads();
-        if (tid < T - c * CO_TOK) {
-            const int32_t *row = ids + ((size_t)c * CO_TOK + tid) * K;
-            for (int k0 = 0; k0 < K; k0 += 8) {                         // eight loads in flight
-                int e[8];
+        for (int k0 = 0; k0 < K; k0 += 8) {
+            if (k0 > 0) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) e[i] = k0 + i < K ? row[k0 + i] : -1;
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if ((unsigned)e[i] < (unsigned)E)
-                        atomicOr(reinterpret_cast<unsigned *>(bits[e[i]]) + (tid & 31), 1u << (tid >> 5));
+                for (int i = 0; i < 8; ++i) e[i] = mine && k0 + i < K ? row[k0 + i] : -1;
             }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if ((unsigned)e[i] < (unsigned)E)
+                    atomicOr(reinterpret_cast<unsigned *>(bits[e[i]]) + (tid & 31), 1u << (tid >> 5));
         }
         __syncthreads();
 #pragma unroll

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import workloads
-from helpers import to_device
+from helpers import safe_threshold, tae_margin, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -45,6 +45,36 @@ def test_substitution_tiles(T, E, K, R, n_res, in_place, dist):
     req = np.unique(ids[ids >= 0])
     extra = [len(req), int((~res[req]).sum()), 0] if dist else [0, 0, 0]
     assert stats.cpu().tolist() == [st["n_miss"], st["n_substituted"], st["n_dropped"]] + extra
+
+
+# K of the eight-lane form (up to 8) and of the walk (9, 17), budgets from none to more than enough, gates that close
+# about half of the tokens (thresholds in a gap of the tokens' values), with and without U_t
+@pytest.mark.parametrize("T,E,K,R,n_res", [(1, 8, 2, 3, 3), (65, 64, 6, 8, 30), (300, 128, 8, 8, 60), (64, 130, 9, 8, 60), (70, 200, 17, 8, 90)])
+@pytest.mark.parametrize("unique", [False, True])
+@pytest.mark.parametrize("rho", [None, 0, 1, 3, 32])
+def test_gates_and_budget_in_substitution_tiles(T, E, K, R, n_res, unique, rho):
+    import torch
+    import paper_2511_10054_amd as bm
+    print("gated substitution tiles", T, E, K, R, n_res, unique, rho, flush=True)
+    ids, res, table = _problem(7 * T + E, T, E, K, R, n_res)
+    w = np.random.default_rng(T).dirichlet(np.full(K, 0.7), size=T).astype(np.float32) + np.float32(1e-4)
+    tae, margin = tae_margin(w.astype(np.float64))
+    gates = [dict(), dict(tau=safe_threshold(tae, 0.5)), dict(gamma=safe_threshold(margin, 0.5))]
+    for gate in gates:
+        if rho is None and not gate:
+            continue
+        ref, w_ref, st = oracle.buddy_remap_gated(ids, res, table, w=w, H=R, unique=unique, rho=rho, **gate)
+        flags = (bm.BM_REMAP_UNIQUE if unique else 0) | (bm.BM_REPLACE_BUDGET if rho is not None else 0)
+        flags |= (bm.BM_GATE_TAE if "tau" in gate else 0) | (bm.BM_GATE_MARGIN if "gamma" in gate else 0)
+        desc = bm.LayerDesc(T=T, d=32, E=E, F=0, K=K, n_shared=0, R=R, H=R, dtype=bm.BM_BF16, flags=flags, rho=rho or 0,
+                            tae_tau=gate.get("tau", 0.0), margin_gamma=gate.get("gamma", 0.0))
+        d_w, out = to_device(w), torch.full((T, K), -9, dtype=torch.int32, device="cuda")
+        stats = torch.full((6,), -9, dtype=torch.int32, device="cuda")
+        bm.bm_buddy_remap(desc, to_device(workloads.pack_bitmap(res)), to_device(table), to_device(ids), out, d_w, stats)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out.cpu().numpy(), ref)
+        np.testing.assert_array_equal(d_w.cpu().numpy(), np.asarray(w_ref, np.float32))
+        assert stats.cpu().tolist()[:3] == [st["n_miss"], st["n_substituted"], st["n_dropped"]]
 
 
 # assignments around one and several words, one workgroup and a workgroup per tile, the largest batch and sets of both
