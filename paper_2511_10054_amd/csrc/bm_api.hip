@@ -527,9 +527,10 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
     fp.ids2 = at<int32_t>(ws, L.ids2);
     fp.tile_counts = at<int32_t>(ws, L.tile_counts);
     fp.tile_stats = at<int32_t>(ws, L.tile_stats);
-    // the logits borrow the space of h, which nothing holds before the gate/up projection
-    if (front_wants_logits(T, desc->d, E, desc->dtype) && (size_t)T * E <= (size_t)L.rows_max * desc->F) fp.logits = at<float>(ws, L.h);
     const bool fuse = front_can_fuse(T, desc->dtype, desc->flags);
+    // the logits borrow the space of h, which nothing holds before the gate/up projection
+    if (!fuse && front_wants_logits(T, desc->d, E, desc->dtype) && (size_t)T * E * 4 <= (size_t)L.rows_max * desc->F * (bf16 ? 2 : 4))
+        fp.logits = at<float>(ws, L.h);
     fp.tile_tokens = front_tile_tokens(T, desc->dtype, fuse);
 
     // 2. offsets, tile bases, row-tile table, statistics

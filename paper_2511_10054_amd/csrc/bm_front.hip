@@ -893,7 +893,10 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
         // whose direct loads touch few lines anyway; not with 256 experts, whose batch would not fit)
         const bool staged = CAN_STAGE;
         int ks_done = nbatch * U;                                      // k-steps covered by the batched loops
-        if (CAN_STAGE) {
+        const bool given = !FUSED && p.logits != nullptr;              // the product is there already
+        if (given) {
+            ks_done = ksteps;
+        } else if (CAN_STAGE) {
             constexpr int LPB = U / 2 > 0 ? U / 2 : 1;
             u32x4 *area = stage + (CAN_STAGE ? wave : 0) * 256;       // [block 0..1][row 0..15][piece 0..7]
             const int lrow = lane >> 3, lpiece = lane & 7;
@@ -951,7 +954,7 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                 }
             }
         }
-        for (int bt = kw; !staged && bt < nbatch; bt += KW) {
+        for (int bt = kw; !staged && !given && bt < nbatch; bt += KW) {
             const int k0 = bt * U * 32;
             u32x4 ra[2][U], rb[NBW][U];
 #pragma unroll
@@ -987,7 +990,7 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
         // reproducible.
         constexpr int NS2 = 2 * NS < KW ? 2 * NS : KW;
         const int ns = two ? NS : NS2, slot_size = two ? TILE : 16 * STRIDE;
-        for (int r = 0; r < (KW + ns - 1) / ns; ++r) {
+        for (int r = 0; !given && r < (KW + ns - 1) / ns; ++r) {
             if (kw / ns == r) {
                 float *mine = part + (kw % ns) * slot_size;
 #pragma unroll
@@ -1005,7 +1008,13 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
             __syncthreads();
         }
         constexpr int STEP = NW * 64 / (NB * 16);
-        if (two) {
+        if (given) {
+            const int n = min(p.tile_tokens, p.T - t0) * p.E;
+            for (int idx = tid; idx < n; idx += NW * 64) {
+                const int i = idx / p.E, e = idx - i * p.E;
+                part[i * STRIDE + e] = p.logits[(size_t)t0 * p.E + idx];
+            }
+        } else if (two) {
 #pragma unroll
             for (int i0 = 0; i0 < 32; i0 += STEP) {
                 const int i = i0 + tid / (NB * 16);
@@ -1043,10 +1052,12 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 router product of its own, for few tiles and many experts: the front kernel below has one workgroup per 16
-// tokens, and 16 x 128 x 2048 products are 14 us of matrix instructions (plus the sums between them) on one unit.
-// Here a workgroup takes 16 tokens x 16 experts, its 8 waves split the hidden dimension; the front kernel then
-// starts from the logits (Qwen3-shaped layer, 128 tokens: 48 us -> 11 + 10 us).  Same operand layout and sums as below.
+// The router product in a launch of its own, for few tiles and many experts: the front kernels have one workgroup per
+// 16 tokens, which reads the whole router matrix through one unit (bf16, 128 experts: 8 of 18 us) and, in fp32,
+// multiplies 16 x 128 x 2048 on it (14 us of matrix instructions, plus the sums between them).  Here a workgroup
+// takes 16 tokens x 16 experts, its 8 waves split the hidden dimension; the front kernel then starts from the
+// logits.  Same operand layouts as there.  Qwen3-shaped layer: fp32, 128 tokens 48 us -> 11 + 10 us; bf16, 8 tokens
+// 17 us -> 5 + 10 us.
 // ---------------------------------------------------------------------------
 constexpr int ROUTER_NW = 8;
 
@@ -1089,8 +1100,51 @@ __global__ void __launch_bounds__(ROUTER_NW * 64) router_f32_kernel(FrontParams 
     }
 }
 
-// Up to 64 tiles (a quarter of the units) and from 33 experts on; whole 32-value batches of aligned rows only.
-bool front_wants_logits(int T, int d, int E, int dtype) { return dtype == BM_F32 && T <= 1024 && E > 32 && d % 32 == 0; }
+__global__ void __launch_bounds__(ROUTER_NW * 64) router_bf16_kernel(FrontParams p) {
+    __shared__ f32x4 part[ROUTER_NW][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, kq = lane >> 4;
+    const int e0 = blockIdx.x * 16, t0 = blockIdx.y * 16, ksteps = p.d >> 5;
+    const uint16_t *xr = static_cast<const uint16_t *>(p.x) + (size_t)min(t0 + r16, p.T - 1) * p.d + kq * 8;
+    const uint16_t *wr = static_cast<const uint16_t *>(p.wr) + (size_t)min(e0 + r16, p.E - 1) * p.d + kq * 8;
+    constexpr int U = 8;                                   // k-steps of 32 a wave has in flight
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    int ks = wave * U;
+    for (; ks + U <= ksteps; ks += ROUTER_NW * U) {
+        u32x4 a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a[u] = ldg128(xr + (ks + u) * 32);
+            b[u] = ldg128(wr + (ks + u) * 32);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a[u]), as_bf16x8(b[u]), acc, 0, 0, 0);
+    }
+    for (int u = 0; u < U && ks + u < ksteps; ++u)         // the last, partial batch
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ldg128(xr + (ks + u) * 32)), as_bf16x8(ldg128(wr + (ks + u) * 32)), acc, 0, 0, 0);
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
+    f32x4 sum;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sum[v] = add_slots<ROUTER_NW>(reinterpret_cast<const float *>(part) + lane * 4 + v, 64 * 4);
+    const int e = e0 + r16;
+    if (e >= p.E) return;
+    const float bias = p.bias != nullptr ? p.bias[e] : 0.0f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int t = t0 + 4 * kq + v;
+        if (t < p.T) p.logits[(size_t)t * p.E + e] = sum[v] + bias;
+    }
+}
+
+// fp32: from 33 experts on, up to 64 tiles (a quarter of the units), whole 32-value batches of aligned rows only.
+// bf16: from 65 experts on, up to 64 tokens (the layer at 1 / 8 / 32 / 64 / 128 / 2048 tokens, 128 experts, us:
+// 40.0 58.2 80.3 97.6 124.8 259 with the product in the front kernel, 37.6 56.3 79.2 96.7 124.6 266 on its own;
+// 64 experts at 1 / 8 / 32 tokens: 49.2 66.1 90.0 | 49.2 66.6 89.5).
+bool front_wants_logits(int T, int d, int E, int dtype) {
+    return dtype == BM_F32 ? E > 32 && T <= 1024 && d % 32 == 0 : E > 64 && T <= 64;
+}
 
 // ---------------------------------------------------------------------------
 // fp32 front kernel: 16 tokens per workgroup, router product (tokens x experts) on v_mfma_f32_16x16x4_f32.
@@ -1642,13 +1696,14 @@ int launch_front(const FrontParams &p, int dtype, hipStream_t st) {
     if (n_tiles == 0) return 0;
     const int nb = (p.E + 15) / 16;
     if (dtype == BM_F32) {
-        if (p.logits != nullptr) hipLaunchKernelGGL(router_f32_kernel, dim3(nb, n_tiles), dim3(ROUTER_NW * 64), 0, st, p);
+        if (p.logits != nullptr) hipLaunchKernelGGL(router_f32_kernel, dim3(nb, (p.T + 15) / 16), dim3(ROUTER_NW * 64), 0, st, p);
         if (nb <= 1) hipLaunchKernelGGL((front_f32_kernel<1, 16, 2, true>), dim3(n_tiles), dim3(1024), 0, st, p);
         else if (nb <= 2) hipLaunchKernelGGL((front_f32_kernel<2, 8, 2, true>), dim3(n_tiles), dim3(512), 0, st, p);
         else if (nb <= 4) hipLaunchKernelGGL((front_f32_kernel<4, 8, 2, true>), dim3(n_tiles), dim3(512), 0, st, p);
         else if (nb <= 8) hipLaunchKernelGGL((front_f32_kernel<8, 16, 2, false, 2>), dim3(n_tiles), dim3(1024), 0, st, p);
         else hipLaunchKernelGGL((front_f32_kernel<16, 8, 1, false>), dim3(n_tiles), dim3(512), 0, st, p);
     } else {
+        if (p.logits != nullptr) hipLaunchKernelGGL(router_bf16_kernel, dim3(nb, (p.T + 15) / 16), dim3(ROUTER_NW * 64), 0, st, p);
         // a tile is latency-bound: 16 waves split the product and rank two tokens each; U keeps a batch
         // of loads ((2 + NB) * U registers quadruples) inside the 128 registers a wave of 16 has
         if (nb <= 1) launch_front_bf16<1, 16, 4>(p, n_tiles, st);

@@ -60,7 +60,7 @@ struct FrontParams {
     float beta;             // distribution-gate threshold (BM_GATE_DIST: only when one tile holds the batch)
     const float *q;         // [E][R] q of the table entries (BM_PSI_TOKEN)
     float eta;
-    float *logits;          // [T][E] scratch: the router product runs in a launch of its own (fp32, front_wants_logits), or null
+    float *logits;          // [T][E] scratch: the router product runs in a launch of its own (front_wants_logits), or null
     float *probs_out;       // [T][E]: with BM_PSI_TOKEN, write every expert's probability (or null)
     int32_t *ids;           // [T][K] router's choice
     float *w;               // [T][K]
