@@ -1453,14 +1453,7 @@ __global__ void __launch_bounds__(1024) scan_kernel(ScanParams p) {
         if (lane == 0) { p.n_mtiles[0] = tot_t; p.n_mtiles[1] = tot_c; }
     }
     __syncthreads();
-    for (int g = tid; g <= G; g += blockDim.x) p.offsets[g] = start[g];
-    for (int g = tid; g < G; g += blockDim.x) {
-        const int nt = tstart[g + 1] - tstart[g];
-        for (int i = 0; i < nt; ++i) {
-            p.mt_group[tstart[g] + i] = g;
-            p.mt_row0[tstart[g] + i] = start[g] + i * p.BM;
-        }
-    }
+    write_group_tables(p, start, tstart);
     write_mixed_tile_tables(p, start);
     if (p.stats != nullptr && wave < 3) {          // one wave per counter, lanes over the tiles
         int sum = 0;

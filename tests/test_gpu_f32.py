@@ -29,6 +29,8 @@ CASES = [
     (dict(d=66, E=8, F=96, K=2, n_resident=4), 20),
     (dict(d=32, E=8, F=70, K=2, n_resident=4), 40),
     (dict(d=77, E=130, F=33, K=3, n_resident=60, n_shared=1), 18),
+    # a histogram that takes the one-workgroup scan, groups from one to a few hundred rows in no order of size
+    (dict(d=32, E=256, F=32, K=1, R=8, H=8, n_resident=100, zipf_s=1.0, resident="alternate"), 2200),
 ]
 
 
