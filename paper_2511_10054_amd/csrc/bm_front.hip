@@ -1628,16 +1628,17 @@ __global__ void __launch_bounds__(1024) group_tiles_kernel(ScanParams p, Scatter
 }
 
 // ---------------------------------------------------------------------------
-// Scan and scatter in one workgroup for small batches (at most SMALL_A
-// assignments): the substituted ids are staged in LDS, every expert's count
+// Scan and scatter in one workgroup for small batches
+// (grouping_small): the substituted ids are staged in LDS, every expert's count
 // and the stable positions come from its assignment set.
 // Writes what scan_kernel and scatter_kernel write, except the per-tile bases.
 // ---------------------------------------------------------------------------
-constexpr int SMALL_A = 1024, SMALL_SETS = 32768;    // assignments, assignments x experts
+constexpr int SMALL_ANY = 1024, SMALL_A = 2048, SMALL_SETS = 32768;     // see grouping_small
 
 __global__ void __launch_bounds__(1024) group_small_kernel(ScanParams p, ScatterParams c) {
     __shared__ int32_t ids[SMALL_A];
-    __shared__ unsigned long long masks[SMALL_SETS / 64 + BM_MAX_E];     // words are rounded up per expert
+    __shared__ unsigned long long masks[SMALL_ANY / 64 * BM_MAX_E];
+    static_assert(SMALL_ANY / 64 * BM_MAX_E >= SMALL_SETS / 64 + SMALL_SETS / SMALL_ANY, "holds the larger batches' sets, rounded up per expert");
     __shared__ int32_t total[BM_MAX_E + 8];
     __shared__ int32_t start[BM_MAX_E + 9];
     __shared__ int32_t tstart[BM_MAX_E + 9];
@@ -1745,10 +1746,13 @@ int launch_scan(const ScanParams &p, hipStream_t st) {
     return launch_status(__func__);
 }
 
-// The one-workgroup kernel walks every assignment once per expert (a wave per expert, 64 assignments a
-// step): fine for a few experts, slow for many (128 experts x 1024 assignments: 25 us against 12 us for the
-// per-tile kernel).
-bool grouping_small(long long assignments, int E) { return assignments <= SMALL_A && assignments * E <= SMALL_SETS; }
+// The one-workgroup kernel takes up to 1024 assignments, one per thread, whatever the number of experts (128 experts, 512 /
+// 1024 assignments: 3.5 / 6.0 us against 7.8 / 7.9 us for the per-tile histograms and the kernel that sums them), and
+// up to 2048 of few experts (8 experts, 1554 assignments: 4.8 against 6.8 us).  Beyond, a thread's rank adds up too
+// many words (128 experts, 2048 assignments: 15.0 against 8.1 us; 8 experts, 4096: 21.3 against 7.0 us).
+bool grouping_small(long long assignments, int E) {
+    return assignments <= SMALL_ANY || (assignments <= SMALL_A && assignments * E <= SMALL_SETS);
+}
 
 // scan + scatter: one kernel for small batches and for small histograms
 int launch_grouping(const ScanParams &sp, const ScatterParams &cp, hipStream_t st) {

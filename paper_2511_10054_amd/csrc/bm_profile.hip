@@ -15,7 +15,7 @@ namespace bm {
 // bit twice, ids out of range set none; neighbouring lanes own different words, so that a popular expert's bits do
 // not queue on one), then counts every pair (pivot i, expert j) as the population count of
 // the two sets' intersection and adds it to the global int64 totals; the pair (i, i) is the activation count.
-// Bound by latency: one read of the chunk's ids, two barriers, the LDS reads of a thread's pairs (4 pivots: 7.1 us for
+// Bound by latency: one read of the chunk's ids, two barriers, the LDS reads of a thread's pairs (4 pivots: 6.8 us for
 // 4096 tokens of 8 out of 128 experts; 8 pivots 7.9, 16 pivots 15.3; 6.4 without the global atomics).  The kernel it
 // replaces walked a token per wave with lane permutes and flushed a whole triangle every 64 tokens: 41 us.
 constexpr int CO_TOK = 1024, CO_ROWS = 4, CO_WORDS = CO_TOK / 64;

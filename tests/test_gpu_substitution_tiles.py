@@ -79,7 +79,7 @@ def test_gates_and_budget_in_substitution_tiles(T, E, K, R, n_res, unique, rho):
 
 # assignments around one and several words, one workgroup and a workgroup per tile, the largest batch and sets of both
 @pytest.mark.parametrize("T,E,K", [(1, 1, 1), (21, 7, 3), (32, 256, 2), (65, 8, 1), (128, 32, 8), (129, 32, 8), (1024, 32, 1),
-                                   (31, 256, 32), (33, 256, 32), (3001, 128, 8), (9000, 200, 4)])
+                                   (31, 256, 32), (32, 256, 32), (33, 256, 32), (128, 128, 8), (1024, 16, 2), (1024, 17, 2), (683, 15, 3), (3001, 128, 8), (9000, 200, 4)])
 def test_grouping_sets(T, E, K):
     import torch
     import paper_2511_10054_amd as bm
