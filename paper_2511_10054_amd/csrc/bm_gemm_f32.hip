@@ -63,7 +63,8 @@ __global__ void __launch_bounds__(256) rowwise_f32_kernel(GemmParams p) {
 //
 // What bounds it: groups of at most ~30 rows are bound by streaming their weights once, larger ones by the fp32
 // matrix rate.  The kernel it replaces (one workgroup per row, each wave a weight row at a time) read an expert's
-// weights once per ROW: 2786 + 2623 us for the two projections of the Qwen3-shaped layer at 128 tokens.
+// weights once per ROW: 2786 + 2623 us for the two projections of the Qwen3-shaped layer at 128 tokens; here 150 + 91
+// us (floors 96 and 48: 640 and 320 MB at 6.7 TB/s).
 //
 //  - Weights are the first MFMA operand, activations the second: a lane ends up with four consecutive output
 //    columns of one row (16-byte stores).  The four waves are two blocks of 16 weight rows (of each half of the
@@ -85,7 +86,7 @@ __global__ void __launch_bounds__(256) rowwise_f32_kernel(GemmParams p) {
 // ---------------------------------------------------------------------------
 #define BM_LDS __attribute__((address_space(3)))
 constexpr int F32_ROWS = 64;            // activation rows per tile
-constexpr int F32_STAGES = 3;           // 48 KB: three workgroups per unit (4 or 5 stages leave two: 434 / 438 us a layer against 398)
+constexpr int F32_STAGES = 3;           // 48 KB: three workgroups per unit (4 or 5 stages leave two: gate/up 162 / 164 us against 150)
 constexpr int F32_CHUNKS = 8;           // row tiles of a group that run side by side
 
 template <bool DUAL, int NBT, int CHAIN>
