@@ -153,6 +153,8 @@ typedef struct {
  *   renormalised over the K slots when BM_RENORM_TOPK is set.
  * x [T][d] dtype (device), w_router [E][d] dtype (device), bias [E] fp32 or
  * NULL (device), ids [T][K] int32 and w [T][K] fp32 (device, written).
+ * A token's ids and w are the same bits whatever T it is part of, and the same
+ * that bm_moe_forward computes for it (before substitution).
  * Uses T, d, E, K, dtype, flags of desc.  T == 0 is a no-op. */
 int bm_route_topk(const bm_layer_desc *desc, const void *x, const void *w_router,
                   const float *bias, int32_t *ids, float *w, void *stream);

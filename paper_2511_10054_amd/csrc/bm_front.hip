@@ -807,16 +807,30 @@ __device__ void fused_tail(const FrontParams &p, FusedLds &fs, int n_tiles, unsi
             for (int t = tid; t < p.T; t += blockDim.x) p.scat.row_token[fs.start[E + sidx] + t] = t;
 }
 
-// sum of N values `stride` apart, by pairs (log2 N roundings in a row instead of N)
-template <int N>
+// The router product of a token has one order of additions, whatever kernel, batch size or tile it is computed in, so
+// that a token's routing does not depend on what else is in the batch or on the call (an engine that fetches the
+// experts named by bm_route_topk finds the layer asking for the same ones).  KW waves take every KW-th batch of k-steps
+// in turn; their sums w_0 .. w_KW-1 are added as H = partial_tiles<NB, KW, 16>() chains (w_j, w_j+H, w_j+2H, ..), the
+// chains by pairs: H is the number of partial tiles (16 tokens x NB * 16 experts) that the front kernels' LDS holds side
+// by side.  Tiles of 32 tokens add up their two blocks of 16 one after the other.
+template <int NB, int KW, int ROWS>
+__host__ __device__ constexpr int partial_tiles() {
+    constexpr int fit = (74 * 1024) / (ROWS * (NB * 16 + 4) * 4);
+    return fit >= KW ? KW : fit;
+}
+// v_0 .. v_N-1, `stride` apart: chains of every H-th value, the H chains by pairs
+template <int N, int H>
 __device__ __forceinline__ float add_slots(const float *at, int stride) {
+    static_assert(N % H == 0, "whole chains");
     float v[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = at[i * stride];
 #pragma unroll
-    for (int d = 1; d < N; d *= 2)
+    for (int i = H; i < N; ++i) v[i % H] += v[i];
 #pragma unroll
-        for (int i = 0; i + d < N; i += 2 * d) v[i] += v[i + d];
+    for (int d = 1; d < H; d *= 2)
+#pragma unroll
+        for (int i = 0; i + d < H; i += 2 * d) v[i] += v[i + d];
     return v[0];
 }
 
@@ -830,8 +844,8 @@ __device__ __forceinline__ float add_slots(const float *at, int stride) {
 // the kernel; the 32x32x16 form reads 32 bytes per row and instruction.)  The
 // waves split the hidden dimension in batches of U k-steps; the loads of a
 // batch are all issued before its MFMAs.  The partial logit tiles of the waves
-// are written to LDS side by side and added by pairs (reproducible sum);
-// when NW tiles do not fit, some waves first add into another's tile.
+// are written to LDS side by side and added there; when they do not all fit,
+// some waves first add into another's tile (one order of additions in any case, see partial_tiles).
 // NB = number of 16-expert column blocks, NW = waves per workgroup, NH = parts of the expert blocks over the waves (the
 // other factor of NW splits the hidden dimension): 128 experts on 16 waves of 4 blocks each have twice the loads in
 // flight and half the tokens to rank per wave that 8 waves of 8 blocks have, in the same registers.
@@ -843,9 +857,9 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     static_assert(TILE_T == 32, "two 16-token row blocks per tile");
     constexpr int STRIDE = NB * 16 + 4;                  // the four row groups of a partial tile start 16 banks apart
     constexpr int TILE = TILE_T * STRIDE;
-    constexpr int NS_FIT = (74 * 1024) / (TILE * 4);
     constexpr int NBW = NB / NH, KW = NW / NH;           // expert blocks of a wave, waves along the hidden dimension
-    constexpr int NS = NS_FIT >= KW ? KW : (NS_FIT < 1 ? 1 : NS_FIT);   // partial tiles kept side by side
+    constexpr int NS = partial_tiles<NB, KW, TILE_T>(), NS2 = partial_tiles<NB, KW, 16>();   // kept side by side
+    static_assert(NS2 <= 2 * NS, "the partial tiles of 16 tokens fit");
     __shared__ __attribute__((aligned(16))) float part[NS * TILE];
     static_assert(sizeof(part) >= NB * 16 * (TILE_T * BM_MAX_K / 64) * 8, "holds the assignment sets as well");
     constexpr bool CAN_STAGE = !FUSED && U >= 2 && U % 2 == 0;
@@ -985,48 +999,48 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
         }
 
         // D[i][j] of a 16x16 block: lane holds column j = l % 16 and rows i = 4 * (l / 16) + v.
-        // ns partial tiles sit side by side in LDS (twice as many when the tile has 16 rows only); wave w of an
-        // expert part adds into slot w % ns in round w / ns, then the slots are added by pairs: one fixed association,
-        // reproducible.
-        constexpr int NS2 = 2 * NS < KW ? 2 * NS : KW;
-        const int ns = two ? NS : NS2, slot_size = two ? TILE : 16 * STRIDE;
-        for (int r = 0; !given && r < (KW + ns - 1) / ns; ++r) {
-            if (kw / ns == r) {
-                float *mine = part + (kw % ns) * slot_size;
-#pragma unroll
-                for (int tb = 0; tb < 2; ++tb) {
-                    if (tb == 1 && !two) break;
-#pragma unroll
-                    for (int nb = 0; nb < NBW; ++nb)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            float *q = &mine[(tb * 16 + 4 * kq + v) * STRIDE + (nb0 + nb) * 16 + r16];
-                            *q = (r == 0 ? 0.0f : *q) + acc[tb][nb][v];
-                        }
-                }
-            }
-            __syncthreads();
-        }
-        constexpr int STEP = NW * 64 / (NB * 16);
+        // Partial tiles of 16 tokens sit side by side in LDS; wave w of an expert part adds into slot w % NS2 in round
+        // w / NS2, then the slots are added: one fixed association, reproducible.
+        constexpr int STEP = NW * 64 / (NB * 16), ROWS_PER = (16 + STEP - 1) / STEP;   // rows a sweep of the threads adds up
+        const int my_i = tid / (NB * 16);
         if (given) {
             const int n = min(p.tile_tokens, p.T - t0) * p.E;
             for (int idx = tid; idx < n; idx += NW * 64) {
                 const int i = idx / p.E, e = idx - i * p.E;
                 part[i * STRIDE + e] = p.logits[(size_t)t0 * p.E + idx];
             }
-        } else if (two) {
-#pragma unroll
-            for (int i0 = 0; i0 < 32; i0 += STEP) {
-                const int i = i0 + tid / (NB * 16);
-                if (i >= 32) break;
-                part[i * STRIDE + my_e] = add_slots<NS>(part + i * STRIDE + my_e, TILE) + my_bias;   // slot 0 becomes the logit tile (own element only)
-            }
         } else {
+            float sum[2][ROWS_PER];
 #pragma unroll
-            for (int i0 = 0; i0 < 16; i0 += STEP) {
-                const int i = i0 + tid / (NB * 16);
-                if (i >= 16) break;
-                part[i * STRIDE + my_e] = add_slots<NS2>(part + i * STRIDE + my_e, 16 * STRIDE) + my_bias;
+            for (int tb = 0; tb < 2; ++tb) {
+                if (tb == 1 && !two) break;
+                if (tb == 1) __syncthreads();            // the first block's slots have been read
+#pragma unroll
+                for (int r = 0; r < (KW + NS2 - 1) / NS2; ++r) {
+                    if (kw / NS2 == r) {
+                        float *mine = part + (kw % NS2) * (16 * STRIDE);
+#pragma unroll
+                        for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                float *q = &mine[(4 * kq + v) * STRIDE + (nb0 + nb) * 16 + r16];
+                                *q = (r == 0 ? 0.0f : *q) + acc[tb][nb][v];
+                            }
+                    }
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int j = 0; j < ROWS_PER; ++j)
+                    if (my_i + j * STEP < 16)
+                        sum[tb][j] = add_slots<NS2, NS2>(part + (my_i + j * STEP) * STRIDE + my_e, 16 * STRIDE) + my_bias;
+            }
+            // the first two slots become the logit tile (a thread writes only where it alone has read)
+#pragma unroll
+            for (int tb = 0; tb < 2; ++tb) {
+                if (tb == 1 && !two) break;
+#pragma unroll
+                for (int j = 0; j < ROWS_PER; ++j)
+                    if (my_i + j * STEP < 16) part[(tb * 16 + my_i + j * STEP) * STRIDE + my_e] = sum[tb][j];
             }
         }
         __syncthreads();
@@ -1056,40 +1070,54 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
 // 16 tokens, which reads the whole router matrix through one unit (bf16, 128 experts: 8 of 18 us) and, in fp32,
 // multiplies 16 x 128 x 2048 on it (14 us of matrix instructions, plus the sums between them).  Here a workgroup
 // takes 16 tokens x 16 experts, its 8 waves split the hidden dimension; the front kernel then starts from the
-// logits.  Same operand layouts as there.  Qwen3-shaped layer: fp32, 128 tokens 48 us -> 11 + 10 us; bf16, 8 tokens
+// logits.  Same operand layouts, k-step batches and order of additions as there, so the same bits.  Qwen3-shaped layer: fp32, 128 tokens 48 us -> 11 + 10 us; bf16, 8 tokens
 // 17 us -> 5 + 10 us.
 // ---------------------------------------------------------------------------
 constexpr int ROUTER_NW = 8;
 
+// NB: the front kernel's expert blocks, whose k-step batches (32 values, 16 with 256 experts) and sum order this takes
+// (8 serves 33 to 128 experts: 4 and 8 blocks are the same in both)
+static_assert(partial_tiles<4, ROUTER_NW, 16>() == partial_tiles<8, ROUTER_NW, 16>(), "one instantiation for both");
+template <int NB>
 __global__ void __launch_bounds__(ROUTER_NW * 64) router_f32_kernel(FrontParams p) {
     __shared__ f32x4 part[ROUTER_NW][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, quad = lane >> 4;
     const int e0 = blockIdx.x * 16, t0 = blockIdx.y * 16, d = p.d;
     const float *xr = static_cast<const float *>(p.x) + (size_t)min(t0 + r16, p.T - 1) * d + quad * 4;
     const float *wr = static_cast<const float *>(p.wr) + (size_t)min(e0 + r16, p.E - 1) * d + quad * 4;
+    constexpr int KS = NB <= 8 ? 2 : 1, G = 2 / KS, KB = KS * 16, STEP = ROUTER_NW * KB;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k = wave * 32; k < d; k += ROUTER_NW * 32) {          // (d is a multiple of 32)
-        f32x4 a[2], b[2], c[2];
+    for (int k = wave * KB; k < d; k += G * STEP) {               // (d is a multiple of 32)
+        f32x4 a[G][KS], b[G][KS];
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            a[s] = *(const BM_GLOBAL f32x4 *)(xr + k + s * 16);
-            b[s] = *(const BM_GLOBAL f32x4 *)(wr + k + s * 16);
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const int at = min(k + g * STEP, d - KB) + s * 16;
+                a[g][s] = *(const BM_GLOBAL f32x4 *)(xr + at);
+                b[g][s] = *(const BM_GLOBAL f32x4 *)(wr + at);
+            }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (g > 0 && k + g * STEP >= d) break;
+            f32x4 c[KS];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                f32x4 q[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[g][s][i], b[g][s][i], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                c[s] = (q[0] + q[1]) + (q[2] + q[3]);
+            }
+            acc += KS == 2 ? c[0] + c[KS - 1] : c[0];
         }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            f32x4 q[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) q[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i], b[s][i], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            c[s] = (q[0] + q[1]) + (q[2] + q[3]);
-        }
-        acc += c[0] + c[1];
     }
     part[wave][lane] = acc;
     __syncthreads();
     if (wave != 0) return;
-    f32x4 sum = part[0][lane];
+    f32x4 sum;
 #pragma unroll
-    for (int w = 1; w < ROUTER_NW; ++w) sum += part[w][lane];
+    for (int v = 0; v < 4; ++v)
+        sum[v] = add_slots<ROUTER_NW, partial_tiles<NB, ROUTER_NW, 16>()>(reinterpret_cast<const float *>(part) + lane * 4 + v, 64 * 4);
     const int e = e0 + r16;
     if (e >= p.E) return;
     const float bias = p.bias != nullptr ? p.bias[e] : 0.0f;
@@ -1100,34 +1128,47 @@ __global__ void __launch_bounds__(ROUTER_NW * 64) router_f32_kernel(FrontParams 
     }
 }
 
+// NB as above: batches of two k-steps of 32, of one with 256 experts; a wave has eight k-steps in flight
+template <int NB>
 __global__ void __launch_bounds__(ROUTER_NW * 64) router_bf16_kernel(FrontParams p) {
     __shared__ f32x4 part[ROUTER_NW][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, kq = lane >> 4;
     const int e0 = blockIdx.x * 16, t0 = blockIdx.y * 16, ksteps = p.d >> 5;
     const uint16_t *xr = static_cast<const uint16_t *>(p.x) + (size_t)min(t0 + r16, p.T - 1) * p.d + kq * 8;
     const uint16_t *wr = static_cast<const uint16_t *>(p.wr) + (size_t)min(e0 + r16, p.E - 1) * p.d + kq * 8;
-    constexpr int U = 8;                                   // k-steps of 32 a wave has in flight
+    constexpr int U = NB <= 8 ? 2 : 1, G = 8 / U;
+    const int nbatch = ksteps / U;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    int ks = wave * U;
-    for (; ks + U <= ksteps; ks += ROUTER_NW * U) {
-        u32x4 a[U], b[U];
+    int bt = wave;
+    for (; bt + (G - 1) * ROUTER_NW < nbatch; bt += G * ROUTER_NW) {
+        u32x4 a[G][U], b[G][U];
+        const uint16_t *xk = xr + bt * (U * 32), *wk = wr + bt * (U * 32);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a[u] = ldg128(xr + (ks + u) * 32);
-            b[u] = ldg128(wr + (ks + u) * 32);
-        }
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                a[g][u] = ldg128(xk + (g * ROUTER_NW * U + u) * 32);
+                b[g][u] = ldg128(wk + (g * ROUTER_NW * U + u) * 32);
+            }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a[u]), as_bf16x8(b[u]), acc, 0, 0, 0);
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a[g][u]), as_bf16x8(b[g][u]), acc, 0, 0, 0);
     }
-    for (int u = 0; u < U && ks + u < ksteps; ++u)         // the last, partial batch
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ldg128(xr + (ks + u) * 32)), as_bf16x8(ldg128(wr + (ks + u) * 32)), acc, 0, 0, 0);
+    for (; bt < nbatch; bt += ROUTER_NW)                   // the batches past the last full group
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ldg128(xr + (bt * U + u) * 32)), as_bf16x8(ldg128(wr + (bt * U + u) * 32)), acc, 0, 0, 0);
+    for (int ks = nbatch * U + wave; ks < ksteps; ks += ROUTER_NW)     // a k-step past the last full batch
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(ldg128(xr + ks * 32)), as_bf16x8(ldg128(wr + ks * 32)), acc, 0, 0, 0);
     part[wave][lane] = acc;
     __syncthreads();
     if (wave != 0) return;
     f32x4 sum;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) sum[v] = add_slots<ROUTER_NW>(reinterpret_cast<const float *>(part) + lane * 4 + v, 64 * 4);
+    for (int v = 0; v < 4; ++v)
+        sum[v] = add_slots<ROUTER_NW, partial_tiles<NB, ROUTER_NW, 16>()>(reinterpret_cast<const float *>(part) + lane * 4 + v, 64 * 4);
     const int e = e0 + r16;
     if (e >= p.E) return;
     const float bias = p.bias != nullptr ? p.bias[e] : 0.0f;
@@ -1160,9 +1201,8 @@ bool front_wants_logits(int T, int d, int E, int dtype) {
 template <int NB, int NW, int KS, bool PRE, int NH = 1>
 __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
     constexpr int TT = 16, STRIDE = NB * 16 + 4, TILE = TT * STRIDE;
-    constexpr int NS_FIT = (74 * 1024) / (TILE * 4);
     constexpr int NBW = NB / NH, KW = NW / NH;           // as in the bf16 kernel
-    constexpr int NS = NS_FIT >= KW ? KW : NS_FIT;                // partial tiles kept side by side
+    constexpr int NS = partial_tiles<NB, KW, TT>();      // kept side by side
     __shared__ __attribute__((aligned(16))) float part[NS * TILE];
     static_assert(sizeof(part) >= NB * 16 * (TT * BM_MAX_K / 64) * 8, "holds the assignment sets as well");
     __shared__ FrontLds s;
@@ -1257,7 +1297,7 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
         }
         for (int idx = tid; idx < TT * NB * 16; idx += NW * 64) {
             const int i = idx / (NB * 16), e = idx - i * (NB * 16);
-            part[i * STRIDE + e] = add_slots<NS>(part + i * STRIDE + e, TILE) + ((p.bias != nullptr && e < p.E) ? p.bias[e] : 0.0f);
+            part[i * STRIDE + e] = add_slots<NS, NS>(part + i * STRIDE + e, TILE) + ((p.bias != nullptr && e < p.E) ? p.bias[e] : 0.0f);
         }
     }
     __syncthreads();
@@ -1690,14 +1730,22 @@ int launch_front(const FrontParams &p, int dtype, hipStream_t st) {
     if (n_tiles == 0) return 0;
     const int nb = (p.E + 15) / 16;
     if (dtype == BM_F32) {
-        if (p.logits != nullptr) hipLaunchKernelGGL(router_f32_kernel, dim3(nb, (p.T + 15) / 16), dim3(ROUTER_NW * 64), 0, st, p);
+        if (p.logits != nullptr) {
+            const dim3 grid(nb, (p.T + 15) / 16), block(ROUTER_NW * 64);
+            if (nb <= 8) hipLaunchKernelGGL(router_f32_kernel<8>, grid, block, 0, st, p);
+            else hipLaunchKernelGGL(router_f32_kernel<16>, grid, block, 0, st, p);
+        }
         if (nb <= 1) hipLaunchKernelGGL((front_f32_kernel<1, 16, 2, true>), dim3(n_tiles), dim3(1024), 0, st, p);
         else if (nb <= 2) hipLaunchKernelGGL((front_f32_kernel<2, 8, 2, true>), dim3(n_tiles), dim3(512), 0, st, p);
         else if (nb <= 4) hipLaunchKernelGGL((front_f32_kernel<4, 8, 2, true>), dim3(n_tiles), dim3(512), 0, st, p);
         else if (nb <= 8) hipLaunchKernelGGL((front_f32_kernel<8, 16, 2, false, 2>), dim3(n_tiles), dim3(1024), 0, st, p);
         else hipLaunchKernelGGL((front_f32_kernel<16, 8, 1, false>), dim3(n_tiles), dim3(512), 0, st, p);
     } else {
-        if (p.logits != nullptr) hipLaunchKernelGGL(router_bf16_kernel, dim3(nb, (p.T + 15) / 16), dim3(ROUTER_NW * 64), 0, st, p);
+        if (p.logits != nullptr) {
+            const dim3 grid(nb, (p.T + 15) / 16), block(ROUTER_NW * 64);
+            if (nb <= 8) hipLaunchKernelGGL(router_bf16_kernel<8>, grid, block, 0, st, p);
+            else hipLaunchKernelGGL(router_bf16_kernel<16>, grid, block, 0, st, p);
+        }
         // a tile is latency-bound: 16 waves split the product and rank two tokens each; U keeps a batch
         // of loads ((2 + NB) * U registers quadruples) inside the 128 registers a wave of 16 has
         if (nb <= 1) launch_front_bf16<1, 16, 4>(p, n_tiles, st);
