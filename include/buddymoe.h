@@ -235,7 +235,11 @@ int bm_permute_by_expert(const bm_layer_desc *desc, const int32_t *ids_remapped,
  *   for every surviving slot: h = silu(W_g[e] x) * (W_u[e] x), o = W_d[e] h
  *   y[t] = sum_k w[t][k] * o[t][k] + sum_{s<n_shared} FFN^shared_s(x[t])
  * x [T][d] dtype (device), y [T][d] dtype or fp32 with BM_Y_F32 (device,
- * written; must not alias x).  workspace as above.  dbg may be NULL.
+ * written; must not alias x).  workspace: device scratch, 256-byte aligned, of
+ * bm_workspace_bytes(desc) bytes; one sized for a larger T of the same layer is
+ * enough as well.  (Some small bf16 batches use a faster path if its scratch fits
+ * the workspace given, so their y can differ in rounding with the workspace's
+ * size.)  dbg may be NULL.
  * bf16: MFMA with fp32 accumulation, h and o held in bf16 between the two
  * projections; fp32: fp32 FMA throughout. */
 int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *weights,

@@ -72,8 +72,9 @@ bool narrow_shape(const bm_layer_desc *d) {
 }
 // ... and widths that are multiples of 128 but not of 256 take it instead of the tiled path up to 16 tokens
 // (DeepSeek-shaped layer, F = 1408, at 3 / 8 / 16 / 32 tokens: tiled .061 .077 .080 .087, two-wave streaming .053
-// .062 .070 .089), as long as its fp32 down-projection output is small (the tiled path's is bf16): a layer
-// that fits the built-in scratch array on one path then fits it on the other.
+// .062 .070 .089), as long as its fp32 down-projection output is small (the tiled path's is bf16).  A call whose
+// workspace has no room for that output keeps the tiled path (plan_layout): one that is sized for the largest batch
+// of a serving loop, of 17 to 25 tokens for instance, takes every smaller batch.
 constexpr int NARROW_UNFIT_T = 16;
 constexpr long long NARROW_UNFIT_BYTES = 16ll << 20;
 
@@ -87,13 +88,13 @@ constexpr long long NARROW_UNFIT_BYTES = 16ll << 20;
 // the two-wave kernel takes the shape (narrow_shape).
 // Mixtral-shaped layer, 8 experts, streaming | tiled, ms: 128 tokens 0.40 | 0.44, 192 tokens 0.55 | 0.47,
 // 256 tokens 0.59 | 0.48 (public weight layout; 0.48 | 0.47 and 0.52 | 0.48 on the packed copies).
-bool use_skinny(const bm_layer_desc *d) {
+bool use_skinny(const bm_layer_desc *d, bool compact) {
     if (d->dtype != BM_BF16) return false;
     const int ns = d->n_shared > 0 ? d->n_shared : 0;
     const long long rows = (long long)d->T * (d->K + ns);
     const bool fit = d->d % 256 == 0 && d->F % 256 == 0;
     if (!fit && k64_shape(d))
-        return rows <= SKINNY_UNFIT_ROWS || (narrow_shape(d) && d->T <= NARROW_UNFIT_T && rows * (2ll * d->F + 4ll * d->d) <= NARROW_UNFIT_BYTES);
+        return rows <= SKINNY_UNFIT_ROWS || (!compact && narrow_shape(d) && d->T <= NARROW_UNFIT_T && rows * (2ll * d->F + 4ll * d->d) <= NARROW_UNFIT_BYTES);
     if (rows <= SKINNY_MAX_ROWS) return true;
     return fit && rows <= (long long)SKINNY_AVG_ROWS * (d->E + ns);
 }
@@ -125,8 +126,10 @@ int skinny_ksplit(const bm_layer_desc *d) {
 
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
-// Workspace carving: a pure function of desc.
+// Path and workspace carving: a pure function of desc and of whether the workspace is short (plan_layout).
 struct Layout {
+    bool skinny;                // decode-sized: the streaming kernels
+    int ksplit;                 // reduction slices of their down projection
     size_t ids, ids2, w, tile_counts, tile_base, tile_stats, offsets, perm, inv_perm, row_token;
     size_t mt_group, mt_row0, n_mtiles, mt_group_b, mt_row0_b, n_mtiles_b, mt_group_s, mt_row0_s, n_mtiles_s;
     size_t stats, probs, h, o, splitk, total;
@@ -159,8 +162,10 @@ int check_remap_desc(const bm_layer_desc *d) {
     return BM_OK;
 }
 
-Layout make_layout(const bm_layer_desc *d) {
+Layout make_layout(const bm_layer_desc *d, bool compact = false) {
     Layout L{};
+    L.skinny = use_skinny(d, compact);
+    L.ksplit = L.skinny ? skinny_ksplit(d) : 1;
     const size_t A = (size_t)d->T * d->K;
     const int n_shared = d->n_shared > 0 ? d->n_shared : 0;
     const int G = d->E + n_shared;
@@ -185,7 +190,7 @@ Layout make_layout(const bm_layer_desc *d) {
     L.mt_row0 = take((size_t)L.mtiles_max * 4);
     L.n_mtiles = take(16);
     // the two row-tile lists of a launch that runs 256- and 128-row tiles (at most rows / 256 + G and G entries)
-    const bool mixed = !use_skinny(d) && k64_shape(d);
+    const bool mixed = !L.skinny && k64_shape(d);
     L.mt_group_b = take(mixed ? (size_t)L.mtiles_max * 4 : 0);
     L.mt_row0_b = take(mixed ? (size_t)L.mtiles_max * 4 : 0);
     L.n_mtiles_b = take(mixed ? 16 : 0);
@@ -197,12 +202,20 @@ Layout make_layout(const bm_layer_desc *d) {
     L.probs = take(((d->flags & BM_PSI_TOKEN) && (d->flags & BM_GATE_DIST)) ? (size_t)d->T * d->E * 4 : 0);
     const size_t F = d->F > 0 ? d->F : 0;
     L.h = take((size_t)L.rows_max * F * esz);
-    L.o = take(use_skinny(d) ? (size_t)skinny_ksplit(d) * L.rows_max * d->d * 4 : (size_t)L.rows_max * d->d * esz);
+    L.o = take(L.skinny ? (size_t)L.ksplit * L.rows_max * d->d * 4 : (size_t)L.rows_max * d->d * esz);
     // fp32 partial tiles of the down projection's split tail: one 256 x 256 tile per workgroup of the launch
-    L.has_splitk = !use_skinny(d) && k64_shape(d) && down_split_tail(d->F);
+    L.has_splitk = !L.skinny && k64_shape(d) && down_split_tail(d->F);
     L.splitk = take(L.has_splitk ? (size_t)K64_CUS * 256 * 256 * 4 : 0);   // a launch has at most K64_CUS workgroups
     L.total = off;
     return L;
+}
+
+// The layout that a workspace of so many bytes has room for: the preferred one, whose size bm_workspace_bytes gives,
+// or the one that does without the larger down-projection output.
+bool plan_layout(const bm_layer_desc *d, size_t bytes, Layout &L) {
+    L = make_layout(d);
+    if (bytes < L.total) L = make_layout(d, true);
+    return bytes >= L.total;
 }
 
 // Argument checks of the whole-layer entry points (everything but the workspace).
@@ -251,8 +264,7 @@ template <typename T>
 T *at(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(ws) + off); }
 
 int check_ws(const bm_layer_desc *d, void *ws, size_t bytes, Layout &L) {
-    L = make_layout(d);
-    if (!ws || (reinterpret_cast<uintptr_t>(ws) % ALIGN) || bytes < L.total) return BM_ERR_WORKSPACE;
+    if (!plan_layout(d, bytes, L) || !ws || (reinterpret_cast<uintptr_t>(ws) % ALIGN)) return BM_ERR_WORKSPACE;
     return BM_OK;
 }
 
@@ -484,7 +496,8 @@ int bm_moe_forward_static(const bm_layer_desc *desc, const void *x, const bm_wei
     int rc = check_moe_args(desc, x, wt, residency_bitmap, buddy_table, y);
     if (rc) return rc;
     if (desc->T == 0) return BM_OK;
-    if (make_layout(desc).total > (size_t)BM_STATIC_WORKSPACE_BYTES) return BM_ERR_WORKSPACE;
+    Layout L;
+    if (!plan_layout(desc, BM_STATIC_WORKSPACE_BYTES, L)) return BM_ERR_WORKSPACE;
     void *ws = nullptr;
     rc = static_scratch_ptr(&ws);
     if (rc) return rc;
@@ -535,7 +548,7 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
 
     // 2. offsets, tile bases, row-tile table, statistics
     ScanParams sp{};
-    const bool skinny = use_skinny(desc);
+    const bool skinny = L.skinny;
     sp.T = T; sp.E = E; sp.n_shared = desc->n_shared;
     sp.n_tiles = (T + fp.tile_tokens - 1) / fp.tile_tokens;   // tiles of the front kernel (per-tile statistics)
     const bool persistent = !skinny && bf16 && persistent_device();
@@ -623,7 +636,7 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
     int ksplit = 1;
     bool combined = false;                              // the down projection has written y itself
     if (skinny) {
-        ksplit = skinny_ksplit(desc);
+        ksplit = L.ksplit;
         SkinnyParams s1{};
         s1.a = x; s1.row_map = cp.row_token;
         s1.b0 = wt->w_gate; s1.b1 = wt->w_up; s1.sb0 = wt->ws_gate; s1.sb1 = wt->ws_up;

@@ -157,6 +157,37 @@ def test_host_side_argument_errors_launch_nothing():
     assert lib.bm_moe_forward(ctypes.byref(_desc(n_shared=1)), one, ctypes.byref(w2), one, one, one, one, 1 << 30, None, None) == -1
 
 
+def _accepts(desc, nbytes):
+    """bm_moe_forward takes a workspace of so many bytes (it then stops, before any launch, at the half-filled events)."""
+    one = ctypes.c_void_p(256)
+    w = Weights(*([256] * 8 + [0] * 5))
+    dbg = DebugOut()
+    dbg.stage_events[0] = 1
+    rc = bm.load_library().bm_moe_forward(ctypes.byref(desc), one, ctypes.byref(w), one, one, one, one, nbytes, ctypes.byref(dbg), None)
+    assert rc in (-1, -4), rc
+    return rc == -1
+
+
+@pytest.mark.parametrize("shape", [dict(d=2048, E=64, F=1408, K=6, n_shared=2), dict(d=1024, E=16, F=640, K=4),
+                                   dict(d=640, E=128, F=384, K=8), dict(d=4096, E=8, F=14336, K=2),
+                                   dict(d=2048, E=128, F=768, K=8), dict(d=4096, E=32, F=2048, K=4)])
+def test_a_workspace_kept_for_the_largest_batch_takes_every_smaller_one(shape):
+    """A serving loop sizes its workspace once, for its largest batch."""
+    def desc(T):
+        return _desc(T=T, R=8, H=8, dtype=bm.BM_BF16, **shape)
+    for most in range(3, 65):
+        n = bm.bm_workspace_bytes(desc(most))
+        refused = [T for T in range(3, most + 1) if not _accepts(desc(T), n)]
+        assert not refused, (most, refused)
+        assert not _accepts(desc(most), n // 2)
+
+
+def test_workspace_needs_do_not_grow():
+    """What the DeepSeek-shaped layer took for batches of 3 to 25 tokens before its small batches had a streaming path."""
+    for T, n in ((3, 172800), (8, 449280), (16, 893184), (17, 949248), (25, 1393152)):
+        assert _accepts(_desc(T=T, d=2048, E=64, F=1408, K=6, n_shared=2, R=8, H=8, dtype=bm.BM_BF16), n), T
+
+
 def test_product_package_does_not_import_the_oracle():
     import subprocess, sys
     code = ("import sys; sys.path.insert(0, %r); import paper_2511_10054_amd; "
