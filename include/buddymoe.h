@@ -252,8 +252,8 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
  * that forbid hipMalloc.  Same arguments, kernels and results as bm_moe_forward,
  * but the scratch is a BM_STATIC_WORKSPACE_BYTES array built into the library's
  * device code (each GPU the library is loaded on holds one copy until the process
- * ends); the call allocates and frees nothing.  A desc whose
- * bm_workspace_bytes exceeds BM_STATIC_WORKSPACE_BYTES is refused with
+ * ends); the call allocates and frees nothing.  A desc for which a workspace of
+ * BM_STATIC_WORKSPACE_BYTES is too small is refused with
  * BM_ERR_WORKSPACE before anything is launched (decode-sized batches of the large
  * layers and small prefill batches fit; use bm_moe_forward beyond that).  Every
  * call on a GPU shares that GPU's array: calls that overlap on one GPU (different

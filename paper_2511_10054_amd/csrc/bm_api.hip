@@ -2,6 +2,7 @@
 // Nothing here allocates or synchronises; the only state kept between calls is the
 // per-device address of the built-in scratch array of bm_moe_forward_static.
 #include "bm_kernels.h"
+#include "bm_decode_rules.h"
 #include "bm_device_shape.h"
 
 #include <atomic>
@@ -61,16 +62,8 @@ int tile_mode(const bm_layer_desc *d, bool down, bool persistent) {
     return ((long long)d->T * d->K / d->E >= 128) ? 256 : 128;
 }
 
-// Layers of many small experts at up to 32 tokens: the LDS-staged streaming kernel with two-wave workgroups
-// (32 weight rows), because 64-row blocks leave compute units without one.  ms with four waves | two waves,
-// Qwen3-shaped layer (E = 128, d = 2048, F = 768) at 2 / 8 / 16 / 32 / 64 tokens: .051 .060 .076 .086 .102 | .047
-// .059 .071 .082 .106; Mixtral-shaped (F = 14336, 224 blocks of 64 rows per expert) at 8 / 32 tokens .234 .319 |
-// .259 .324.  The line between the two lies at matrices of 16 MB; down projections beyond 2048 keep their slices.
-bool narrow_shape(const bm_layer_desc *d) {
-    return d->dtype == BM_BF16 && d->T <= 32 && d->d % 128 == 0 && d->F % 128 == 0 && d->F <= 2048 &&
-           (long long)d->d * d->F <= (1ll << 23);
-}
-// ... and widths that are multiples of 128 but not of 256 take it instead of the tiled path up to 16 tokens
+// Widths that are multiples of 128 but not of 256 take the two-wave streaming kernel (bm_decode_rules.h) instead of the
+// tiled path up to 16 tokens
 // (DeepSeek-shaped layer, F = 1408, at 3 / 8 / 16 / 32 tokens: tiled .061 .077 .080 .087, two-wave streaming .053
 // .062 .070 .089), as long as its fp32 down-projection output is small (the tiled path's is bf16).  A call whose
 // workspace has no room for that output keeps the tiled path (plan_layout): one that is sized for the largest batch
@@ -101,8 +94,8 @@ bool use_skinny(const bm_layer_desc *d, bool compact) {
 // Reduction slices of the decode down projection (each slice is a workgroup
 // whose 4 waves split it once more): prefer a count that fits the
 // quarter-split kernel, else up to 8 slices of at least 16 k-steps.
-int skinny_ksplit(const bm_layer_desc *d) {
-    if (narrow_shape(d)) return 1;                       // the two-wave kernel takes the reduction whole
+int skinny_ksplit(const bm_layer_desc *d, bool compact) {
+    if (narrow_down_whole(d, compact)) return 1;
     // small groups: the persistent kernel splits the reduction inside one workgroup, no slices
     if ((long long)d->T * d->K <= 32 && (bm::skinny_p_ok(d->F, 14) || bm::skinny_p_ok(d->F, 8))) return 1;
     if ((long long)d->T * d->K > 32) {
@@ -130,6 +123,7 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 struct Layout {
     bool skinny;                // decode-sized: the streaming kernels
     int ksplit;                 // reduction slices of their down projection
+    bool compact;
     size_t ids, ids2, w, tile_counts, tile_base, tile_stats, offsets, perm, inv_perm, row_token;
     size_t mt_group, mt_row0, n_mtiles, mt_group_b, mt_row0_b, n_mtiles_b, mt_group_s, mt_row0_s, n_mtiles_s;
     size_t stats, probs, h, o, splitk, total;
@@ -165,7 +159,8 @@ int check_remap_desc(const bm_layer_desc *d) {
 Layout make_layout(const bm_layer_desc *d, bool compact = false) {
     Layout L{};
     L.skinny = use_skinny(d, compact);
-    L.ksplit = L.skinny ? skinny_ksplit(d) : 1;
+    L.ksplit = L.skinny ? skinny_ksplit(d, compact) : 1;
+    L.compact = compact;
     const size_t A = (size_t)d->T * d->K;
     const int n_shared = d->n_shared > 0 ? d->n_shared : 0;
     const int G = d->E + n_shared;
@@ -657,7 +652,8 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
         s2.pk = pk_dn ? wt->wp_down : nullptr; s2.spk = pk_dn ? wt->wsp_down : nullptr;
         s2.c = dp.c; s2.N = desc->d; s2.Kd = desc->F; s2.ksplit = ksplit;
         s2.wide = (T > 64 && (long long)T * K >= 16ll * E) ? 1 : 0;
-        s1.narrow = s2.narrow = narrow_shape(desc) ? 1 : 0;      // where the persistent kernel does not apply
+        s1.narrow = narrow_gateup(desc) ? 1 : 0;                 // where the persistent kernel does not apply
+        s2.narrow = narrow_down(desc, L.compact) ? 1 : 0;
         // small batches on a matrix as many 16-row blocks wide as the device has units: the down kernel
         // aggregates its own results (null y: it writes them out for launch_combine below)
         s2.y = y; s2.w = fp.w; s2.inv_perm = cp.inv_perm; s2.T = T; s2.K = K; s2.n_shared = desc->n_shared;

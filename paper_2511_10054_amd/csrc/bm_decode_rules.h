@@ -1,0 +1,53 @@
+// Which decode layers take the two-wave form of the LDS-staged streaming kernel, projection by projection.  Plain
+// C++ without HIP, so that a host test can look at the choices.
+#pragma once
+#include "../../include/buddymoe.h"
+
+namespace bm {
+
+// Layers of many small experts at up to 32 tokens: the LDS-staged streaming kernel with two-wave workgroups
+// (32 weight rows), because 64-row blocks leave compute units without one.  ms with four waves | two waves,
+// Qwen3-shaped layer (E = 128, d = 2048, F = 768) at 2 / 8 / 16 / 32 / 64 tokens: .051 .060 .076 .086 .102 | .047
+// .059 .071 .082 .106; Mixtral-shaped (F = 14336, 224 blocks of 64 rows per expert) at 8 / 32 tokens .234 .319 |
+// .259 .324.  The line between the two lies at matrices of 16 MB and F = 2048.
+// With more than some 500 blocks of 64 rows the two are within 5 % of each other either way, by how the live groups
+// (which the host does not know) divide among the units; the mean over 300 shapes is 1.00.
+inline bool narrow_shape(const bm_layer_desc *d) {
+    return d->dtype == BM_BF16 && d->T <= 32 && d->d % 128 == 0 && d->F % 128 == 0 && d->F <= 2048 &&
+           (long long)d->d * d->F <= (1ll << 23);
+}
+
+// The most groups (expert matrices) that a batch reads
+inline long long decode_groups(const bm_layer_desc *d) {
+    const long long rows = (long long)d->T * d->K;
+    return (rows < d->E ? rows : d->E) + (d->n_shared > 0 ? d->n_shared : 0);
+}
+
+// A projection [N][Kd] of few groups whose reduction the quarter-split kernel takes (multiples of 1024, up to 32 rows): its
+// workgroups of 16 rows, four waves along the reduction, are twice as many with twice the waves.  Two-wave | quarter-split
+// layers, us, cold weights: 8 experts, K = 2, d = 1024, F = 1024 at 1 / 2 tokens (64 / 128 two-wave workgroups a
+// projection) 21.1 21.6 | 18.9 19.6; d = 2048 at 1 token (128) 22.6 | 21.2; one expert a token, d = 3072 (96) 28.9 |
+// 26.0, d = 4096 (128) 25.8 | 24.3; d = 1024, K = 5 (160) 23.5 | 24.7, K = 6 (192) 24.4 | 25.7.
+inline bool quarter_split_projection(const bm_layer_desc *d, int N, int Kd) {
+    return Kd % 1024 == 0 && (long long)d->T * d->K <= 32 && decode_groups(d) * (N / 32) <= 128;
+}
+
+// F = 2048 past 32 rows: the down projection is long enough to be split into two slices of the reduction, and from 512
+// gate/up blocks of 64 rows on no unit is without one.  Two waves for both | four waves for both (split) | two-wave gate/up
+// and split down, us: d = 4096, 16 experts, K = 4 at 9 / 16 / 32 tokens 157 165 161 | 144 154 157 | 152 159 156; 32
+// experts at 32 tokens 299 | 282 | 292; d = 3072, 4 experts, K = 2 at 24 tokens 45 | 51 | 46; 8 experts 69 | 69 | 69.
+inline bool long_narrow(const bm_layer_desc *d) { return d->F >= 2048 && (long long)d->T * d->K > 32; }
+
+inline bool narrow_gateup(const bm_layer_desc *d) {
+    return narrow_shape(d) && !quarter_split_projection(d, d->F, d->d) &&
+           !(long_narrow(d) && decode_groups(d) * (d->F / 64) >= 512);
+}
+// the reduction of the down projection stays whole (one fp32 output); compact: whatever needs the least scratch
+inline bool narrow_down_whole(const bm_layer_desc *d, bool compact) {
+    return narrow_shape(d) && (compact || !long_narrow(d));
+}
+inline bool narrow_down(const bm_layer_desc *d, bool compact) {
+    return narrow_down_whole(d, compact) && !quarter_split_projection(d, d->d, d->F);
+}
+
+}  // namespace bm

@@ -229,6 +229,27 @@ def test_persistent_schedule_is_taken_only_on_the_full_part(tmp_path):
     assert subprocess.run([str(exe)], capture_output=True, text=True).stdout.strip() == "0"
 
 
+def test_two_wave_decode_kernel_is_taken_where_it_is_the_faster_one(tmp_path):
+    """The rules of csrc/bm_decode_rules.h (plain C++) at layers that were measured on both sides of each line:
+    few groups with reductions of 1024 go to the quarter-split kernel, F = 2048 past 32 rows to the four-wave one."""
+    import subprocess
+    cases = [  # T, d, E, F, K -> two waves for gate/up, for down
+        ((1, 1024, 8, 1024, 2), 0, 0), ((2, 1024, 8, 1024, 2), 0, 0), ((3, 1024, 8, 1024, 2), 1, 1), ((32, 1024, 4, 1024, 1), 0, 0),
+        ((1, 1024, 16, 1024, 5), 1, 1), ((1, 2048, 8, 1024, 2), 0, 0), ((2, 2048, 8, 1024, 2), 0, 1), ((1, 4096, 4, 1024, 1), 0, 0),
+        ((1, 3072, 8, 1024, 1), 0, 0), ((8, 2048, 128, 768, 8), 1, 1), ((32, 2048, 128, 768, 8), 1, 1), ((33, 2048, 128, 768, 8), 0, 0),
+        ((9, 4096, 16, 2048, 4), 0, 0), ((8, 4096, 16, 2048, 4), 1, 1), ((24, 3072, 4, 2048, 2), 1, 0), ((24, 3072, 8, 2048, 2), 1, 0),
+        ((24, 3072, 16, 2048, 2), 0, 0), ((1, 4096, 8, 14336, 2), 0, 0), ((8, 2048, 64, 1408, 6), 1, 1)]
+    src = tmp_path / "rules.cpp"
+    src.write_text('#include "bm_decode_rules.h"\n#include <cstdio>\nint main() {\n  int bad = 0;\n' + "".join(
+        '  { bm_layer_desc d{}; d.T = %d; d.d = %d; d.E = %d; d.F = %d; d.K = %d; d.dtype = BM_BF16;\n'
+        '    if (bm::narrow_gateup(&d) != %d || bm::narrow_down(&d, false) != %d) { std::printf("T %%d d %%d E %%d F %%d K %%d\\n", d.T, d.d, d.E, d.F, d.K); ++bad; } }\n'
+        % (*shape, gu, dn) for shape, gu, dn in cases) + '  return bad;\n}\n')
+    exe = tmp_path / "rules"
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2511_10054_amd", "csrc"), "-o", str(exe), str(src)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
 def test_small_tile_dealer_hands_out_every_tile_exactly_once(tmp_path):
     """The dealing of 128-row tiles among an XCD's workgroups (csrc/bm_tile_dealer.h, plain C++): for every
     number of 256-row tiles, 128-row tiles and workgroups in a range, each tile goes to exactly one workgroup,
