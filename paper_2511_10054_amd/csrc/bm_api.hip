@@ -537,7 +537,7 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
     fp.tile_stats = at<int32_t>(ws, L.tile_stats);
     const bool fuse = front_can_fuse(T, desc->dtype, desc->flags);
     // the logits borrow the space of h, which nothing holds before the gate/up projection
-    if (!fuse && front_wants_logits(T, desc->d, E, desc->dtype) && (size_t)T * E * 4 <= (size_t)L.rows_max * desc->F * (bf16 ? 2 : 4))
+    if (!fuse && front_wants_logits(fp, desc->dtype) && (size_t)T * E * 4 <= (size_t)L.rows_max * desc->F * (bf16 ? 2 : 4))
         fp.logits = at<float>(ws, L.h);
     fp.tile_tokens = front_tile_tokens(T, desc->dtype, fuse);
 

@@ -46,6 +46,9 @@ __device__ __forceinline__ float ldg_f32(const void *p) { return *(const BM_GLOB
 // to bf16 or feeds an fp32 product)
 __device__ __forceinline__ float silu(float a) { return a * __builtin_amdgcn_rcpf(1.0f + __expf(-a)); }
 
+// Kernels with 16-byte accesses to an array of 4-byte values look at its address and leave other views to 4-byte accesses.
+__host__ __device__ __forceinline__ bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (WAVE - 1)); }
 
 // butterfly sum over the 64 lanes; every lane ends with the same value and

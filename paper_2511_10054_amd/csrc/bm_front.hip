@@ -1183,8 +1183,8 @@ __global__ void __launch_bounds__(ROUTER_NW * 64) router_bf16_kernel(FrontParams
 // bf16: from 65 experts on, up to 64 tokens (the layer at 1 / 8 / 32 / 64 / 128 / 2048 tokens, 128 experts, us:
 // 40.0 58.2 80.3 97.6 124.8 259 with the product in the front kernel, 37.6 56.3 79.2 96.7 124.6 266 on its own;
 // 64 experts at 1 / 8 / 32 tokens: 49.2 66.1 90.0 | 49.2 66.6 89.5).
-bool front_wants_logits(int T, int d, int E, int dtype) {
-    return dtype == BM_F32 ? E > 32 && T <= 1024 && d % 32 == 0 : E > 64 && T <= 64;
+bool front_wants_logits(const FrontParams &p, int dtype) {
+    return dtype == BM_F32 ? p.E > 32 && p.T <= 1024 && p.d % 32 == 0 && aligned16(p.x) && aligned16(p.wr) : p.E > 64 && p.T <= 64;
 }
 
 // ---------------------------------------------------------------------------
@@ -1221,7 +1221,7 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
     for (int nb = 0; nb < NBW; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     constexpr int KB = KS * 16;
     const int nbatch = p.logits != nullptr ? 0 : (d + KB - 1) / KB;       // the product is there already
-    const bool aligned = (d & 3) == 0;                            // rows start on 16-byte boundaries
+    const bool aligned = (d & 3) == 0 && aligned16(p.x) && aligned16(p.wr);    // rows start on 16-byte boundaries
     f32x4 a[2][KS], b[2][NBW][KS];
     auto load = [&](int bt, f32x4 (&ra)[KS], f32x4 (&rb)[NBW][KS]) {
         const bool plain = aligned && (bt + 1) * KB <= d;         // uniform
@@ -1343,14 +1343,17 @@ __global__ void __launch_bounds__(1024) remap_kernel(RemapParams p) {
     int H = p.H;
     if (p.flags & BM_GATE_DIST) {
         // Eq. 2 over the whole batch; every lane that meets an expert stores the same 1
-        const size_t n = (size_t)p.T * p.K, n_vec = n >> 2;
+        // (the ids before the first 16-byte boundary and past the last whole quadruple, at most six, go one by one)
+        const size_t n = (size_t)p.T * p.K, to_boundary = (4 - ((uintptr_t)p.ids_in >> 2 & 3)) & 3;
+        const size_t head = to_boundary < n ? to_boundary : n, n_vec = (n - head) >> 2;
         typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
+        const int32_t *ids4 = p.ids_in + head;
         for (size_t v0 = tid; v0 < n_vec; v0 += 8 * (size_t)blockDim.x) {
             i32x4 v[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const size_t at = v0 + i * (size_t)blockDim.x;
-                v[i] = at < n_vec ? *(const BM_GLOBAL i32x4 *)(p.ids_in + 4 * at) : i32x4{-1, -1, -1, -1};
+                v[i] = at < n_vec ? *(const BM_GLOBAL i32x4 *)(ids4 + 4 * at) : i32x4{-1, -1, -1, -1};
             }
 #pragma unroll
             for (int i = 0; i < 8; ++i)
@@ -1358,8 +1361,8 @@ __global__ void __launch_bounds__(1024) remap_kernel(RemapParams p) {
                 for (int c = 0; c < 4; ++c)
                     if ((unsigned)v[i][c] < (unsigned)p.E) s_req[v[i][c]] = 1;
         }
-        if (tid < (int)(n & 3)) {
-            const int e = p.ids_in[n_vec * 4 + tid];
+        if (tid < (int)(n - 4 * n_vec)) {
+            const int e = p.ids_in[tid < (int)head ? tid : 4 * n_vec + tid];
             if ((unsigned)e < (unsigned)p.E) s_req[e] = 1;
         }
         __syncthreads();

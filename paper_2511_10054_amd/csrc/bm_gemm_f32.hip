@@ -251,11 +251,12 @@ __global__ void __launch_bounds__(256) grouped_gemm_f32_kernel(GemmParams p, int
     }
 }
 
-// The tiles load whole 128-byte lines of every row; other reduction widths keep the row-by-row kernel.
+// The tiles load whole 128-byte lines of every row in 16-byte pieces; other reduction widths, and arrays that do not
+// start on a 16-byte boundary, keep the row-by-row kernel.
 template <bool DUAL>
 static int launch_f32(const GemmParams &p, int max_rows, int T, hipStream_t st) {
     if (max_rows <= 0) return 0;
-    if (p.Kd % 32 == 0) {
+    if (p.Kd % 32 == 0 && aligned16(p.a) && aligned16(p.b0) && aligned16(p.b1) && aligned16(p.sb0) && aligned16(p.sb1)) {
         constexpr int BLK = DUAL ? 32 : 64;
         const int tiles = (T + F32_ROWS - 1) / F32_ROWS;          // a group rarely holds a token twice
         const int chunks = tiles < F32_CHUNKS ? tiles : F32_CHUNKS;

@@ -135,7 +135,7 @@ int launch_status(const char *what);
 
 bool front_can_fuse(int T, int dtype, uint32_t flags);   // the batch is small enough for the one-workgroup front end
 int front_tile_tokens(int T, int dtype, bool fused);   // tokens per workgroup of the front kernel
-bool front_wants_logits(int T, int d, int E, int dtype);   // FrontParams::logits pays if there is room for it
+bool front_wants_logits(const FrontParams &p, int dtype);   // FrontParams::logits pays if there is room for it
 int launch_front(const FrontParams &p, int dtype, hipStream_t st);
 int launch_remap(const RemapParams &p, hipStream_t st);
 int launch_count(const int32_t *ids, int T, int K, int E, int tile_tokens, int32_t *tile_counts, hipStream_t st);
