@@ -1343,17 +1343,14 @@ __global__ void __launch_bounds__(1024) remap_kernel(RemapParams p) {
     int H = p.H;
     if (p.flags & BM_GATE_DIST) {
         // Eq. 2 over the whole batch; every lane that meets an expert stores the same 1
-        // (the ids before the first 16-byte boundary and past the last whole quadruple, at most six, go one by one)
-        const size_t n = (size_t)p.T * p.K, to_boundary = (4 - ((uintptr_t)p.ids_in >> 2 & 3)) & 3;
-        const size_t head = to_boundary < n ? to_boundary : n, n_vec = (n - head) >> 2;
+        const size_t n = (size_t)p.T * p.K, n_vec = aligned16(p.ids_in) ? n >> 2 : 0;     // others one by one
         typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
-        const int32_t *ids4 = p.ids_in + head;
         for (size_t v0 = tid; v0 < n_vec; v0 += 8 * (size_t)blockDim.x) {
             i32x4 v[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const size_t at = v0 + i * (size_t)blockDim.x;
-                v[i] = at < n_vec ? *(const BM_GLOBAL i32x4 *)(ids4 + 4 * at) : i32x4{-1, -1, -1, -1};
+                v[i] = at < n_vec ? *(const BM_GLOBAL i32x4 *)(p.ids_in + 4 * at) : i32x4{-1, -1, -1, -1};
             }
 #pragma unroll
             for (int i = 0; i < 8; ++i)
@@ -1361,8 +1358,8 @@ __global__ void __launch_bounds__(1024) remap_kernel(RemapParams p) {
                 for (int c = 0; c < 4; ++c)
                     if ((unsigned)v[i][c] < (unsigned)p.E) s_req[v[i][c]] = 1;
         }
-        if (tid < (int)(n - 4 * n_vec)) {
-            const int e = p.ids_in[tid < (int)head ? tid : 4 * n_vec + tid];
+        for (size_t a = 4 * n_vec + tid; a < n; a += blockDim.x) {
+            const int e = p.ids_in[a];
             if ((unsigned)e < (unsigned)p.E) s_req[e] = 1;
         }
         __syncthreads();
