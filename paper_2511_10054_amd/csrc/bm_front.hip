@@ -26,7 +26,10 @@ template <int W>
 __device__ __forceinline__ bool test_bit(const uint64_t (&m)[W], int b) {
     uint64_t wv = m[0];
 #pragma unroll
-    for (int i = 1; i < W; ++i) wv = (b >> 6) == i ? m[i] : wv;
+    for (int i = 1; i < W; ++i) {
+        const uint64_t mi = m[i];        // read whatever the condition: the conditional read of one of four becomes an
+        wv = (b >> 6) == i ? mi : wv;    // indexed one, which puts the array into scratch memory
+    }
     return (wv >> (b & 63)) & 1ull;
 }
 template <int W>
@@ -867,7 +870,7 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     __shared__ FrontLds s;
     __shared__ FusedLds fs_store[FUSED ? 1 : 0 + 1];
     FusedLds &fs = fs_store[0];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, kq = lane >> 4;
     const int kw = NH == 1 ? wave : wave % KW, nb0 = NH == 1 ? 0 : wave / KW * NBW;
     const uint16_t *x = static_cast<const uint16_t *>(p.x);
@@ -875,21 +878,14 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     const int n_tiles = (p.T + p.tile_tokens - 1) / p.tile_tokens;
     const int tile_begin = FUSED ? 0 : blockIdx.x, tile_end = FUSED ? n_tiles : blockIdx.x + 1;
 
-    const uint16_t *wb[NBW];
-#pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) wb[nb] = wr + (size_t)min((nb0 + nb) * 16 + r16, p.E - 1) * p.d + kq * 8;
     const int ksteps = p.d >> 5;
     const int nbatch = ksteps / U;
     static_assert((NW * 64) % (NB * 16) == 0, "a thread adds up logits of one expert only");
     const int my_e = tid % (NB * 16);
-    const float my_bias = (p.bias != nullptr && my_e < p.E) ? p.bias[my_e] : 0.0f;
 
     for (int tile = tile_begin; tile < tile_end; ++tile) {
         const int t0 = tile * p.tile_tokens;
         const bool two = min(p.tile_tokens, p.T - t0) > 16;   // the tile's second 16-token block holds tokens (uniform)
-        const uint16_t *xa[2];
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb) xa[tb] = x + (size_t)min(t0 + tb * 16 + r16, p.T - 1) * p.d + kq * 8;
         f32x4 acc[2][NBW];
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb)
@@ -968,6 +964,12 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                 }
             }
         }
+        // operand rows of the direct loads (set up behind the staged product, which has no registers to spare for them)
+        const uint16_t *xa[2], *wb[NBW];
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) xa[tb] = x + (size_t)min(t0 + tb * 16 + r16, p.T - 1) * p.d + kq * 8;
+#pragma unroll
+        for (int nb = 0; nb < NBW; ++nb) wb[nb] = wr + (size_t)min((nb0 + nb) * 16 + r16, p.E - 1) * p.d + kq * 8;
         for (int bt = kw; !staged && !given && bt < nbatch; bt += KW) {
             const int k0 = bt * U * 32;
             u32x4 ra[2][U], rb[NBW][U];
@@ -1010,6 +1012,7 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                 part[i * STRIDE + e] = p.logits[(size_t)t0 * p.E + idx];
             }
         } else {
+            const float my_bias = (p.bias != nullptr && my_e < p.E) ? p.bias[my_e] : 0.0f;
             float sum[2][ROWS_PER];
 #pragma unroll
             for (int tb = 0; tb < 2; ++tb) {

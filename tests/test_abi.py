@@ -297,6 +297,24 @@ int main() {
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout
 
 
+def test_front_end_kernels_stay_out_of_scratch_memory(tmp_path):
+    """Routing, substitution and grouping kernels hold their values in registers: a spilled value or an array that is
+    indexed at run time (the residency words of more than 128 experts) is a round trip to memory in a chain that is bound
+    by latency.  Left out: the one-workgroup form behind the distribution gate, which has the grouping in it as well and
+    spills in its tail.  Checked on the assembly the build's compiler emits for the build's flags (own code)."""
+    import re
+    import subprocess
+    from paper_2511_10054_amd import build
+    out = tmp_path / "front.s"
+    flags = [f for f in build.FLAGS if f != "-fPIC"]
+    subprocess.run([build.HIPCC, *flags, "-S", "--cuda-device-only", "-o", str(out),
+                    os.path.join(build.CSRC, "bm_front.hip")], check=True, capture_output=True)
+    kernels = re.findall(r"^(_ZN2bm\w+):[^\n]*\n(.*?)\.end_amdhsa_kernel", out.read_text(), flags=re.S | re.M)
+    assert len(kernels) >= 20, [k for k, _ in kernels]
+    spilling = [name for name, body in kernels if "scratch_" in body and not re.search(r"front_bf16_kernelI.*Lb1E", name)]
+    assert not spilling, spilling
+
+
 def test_prefill_kernels_keep_the_hand_managed_register_to_themselves(tmp_path):
     """The persistent prefill kernels park the pending result of one vector load in v255, a register the
     compiler does not manage (csrc/bm_gemm_bf16.hip, BM_LOOKUP / BM_ADOPT): the compiler's own values must
