@@ -2,7 +2,7 @@
 // Nothing here allocates or synchronises; the only state kept between calls is the
 // per-device address of the built-in scratch array of bm_moe_forward_static.
 #include "bm_kernels.h"
-#include "bm_decode_rules.h"
+#include "bm_dispatch_rules.h"
 #include "bm_device_shape.h"
 
 #include <atomic>
@@ -62,7 +62,7 @@ int tile_mode(const bm_layer_desc *d, bool down, bool persistent) {
     return ((long long)d->T * d->K / d->E >= 128) ? 256 : 128;
 }
 
-// Widths that are multiples of 128 but not of 256 take the two-wave streaming kernel (bm_decode_rules.h) instead of the
+// Widths that are multiples of 128 but not of 256 take the two-wave streaming kernel (bm_dispatch_rules.h) instead of the
 // tiled path up to 16 tokens
 // (DeepSeek-shaped layer, F = 1408, at 3 / 8 / 16 / 32 tokens: tiled .061 .077 .080 .087, two-wave streaming .053
 // .062 .070 .089), as long as its fp32 down-projection output is small (the tiled path's is bf16).  A call whose

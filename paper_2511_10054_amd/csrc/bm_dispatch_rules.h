@@ -1,5 +1,6 @@
-// Which decode layers take the two-wave form of the LDS-staged streaming kernel, projection by projection.  Plain
-// C++ without HIP, so that a host test can look at the choices.
+// Rules on sizes that choose between kernels: which decode layers take the two-wave form of the LDS-staged streaming
+// kernel, projection by projection, and where the stand-alone substitution takes one workgroup.  Plain C++ without
+// HIP, so that a host test can look at the choices.
 #pragma once
 #include "../../include/buddymoe.h"
 
@@ -48,6 +49,17 @@ inline bool narrow_down_whole(const bm_layer_desc *d, bool compact) {
 }
 inline bool narrow_down(const bm_layer_desc *d, bool compact) {
     return narrow_down_whole(d, compact) && !quarter_split_projection(d, d->d, d->F);
+}
+
+// Tokens of a tile of the stand-alone substitution kernel, and the most tokens that a single workgroup takes.  It stores
+// the counters itself and needs no launch in front of it that zeroes them (1.8 us), but takes the tiles one after the
+// other.  One workgroup | one per tile, us: 8 of 128 experts, no ties between a token's slots, 65 / 128 / 192 tokens 5.9
+// 6.6 8.3 | 6.7 6.8 6.9; U_t, 65 / 96 / 128 / 192 tokens 8.3 8.4 10.2 13.6 | 8.7 8.3 8.6 8.7; more than eight slots,
+// which a lane walks (16 of 256 experts), 64 / 65 / 96 tokens 22.6 32.4 38.0 | - 24.1 23.7.
+constexpr int REMAP_TOK = 64;
+inline int remap_one_workgroup_tokens(int K, uint32_t flags) {
+    if (!(flags & (BM_REMAP_UNIQUE | BM_GATE_ANY | BM_PSI_TOKEN))) return 2 * REMAP_TOK;
+    return K <= 8 && !(flags & BM_PSI_TOKEN) ? 96 : REMAP_TOK;
 }
 
 }  // namespace bm

@@ -14,6 +14,7 @@
 // the order is the stable one and no atomics decide a position).  Small batches
 // get offsets and placement from one workgroup instead (group_small_kernel), or
 // from the front kernel itself (FUSED).
+#include "bm_dispatch_rules.h"
 #include "bm_kernels.h"
 
 namespace bm {
@@ -1320,8 +1321,6 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
 // with one 4-byte load in flight, the buddy rows scanned entry by entry and a whole walk per lane).
 // A single workgroup stores the counters, several add theirs to zeros (launch_remap).
 // ---------------------------------------------------------------------------
-constexpr int REMAP_TOK = 64;
-
 template <int W>
 __global__ void __launch_bounds__(1024) remap_kernel(RemapParams p) {
     extern __shared__ int32_t s_table[];                // E * R entries, then E acceptable-entry masks
@@ -1760,10 +1759,6 @@ int launch_front(const FrontParams &p, int dtype, hipStream_t st) {
     return launch_status(__func__);
 }
 
-// Workgroups of one tile; up to REMAP_ONE tokens a single workgroup is faster, because it stores the counters itself
-// and needs no launch in front of it that zeroes them.
-constexpr int REMAP_ONE = 4 * REMAP_TOK;
-
 int launch_remap(const RemapParams &p, hipStream_t st) {
     if (p.T <= 0) {
         if (p.stats) hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, p.stats, 6);
@@ -1775,7 +1770,7 @@ int launch_remap(const RemapParams &p, hipStream_t st) {
     const int threads = dist ? 1024 : 256;
     int blocks = 1;
     // in place behind the gate, a single workgroup reads the request set before it overwrites anything
-    if (p.T > REMAP_ONE && !(dist && p.ids_out == p.ids_in)) {
+    if (p.T > remap_one_workgroup_tokens(p.K, p.flags) && !(dist && p.ids_out == p.ids_in)) {
         blocks = (p.T - 1) / REMAP_TOK + 1;
         blocks = blocks > (dist ? 256 : 1024) ? (dist ? 256 : 1024) : blocks;
         if (p.stats) hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, p.stats, 3);

@@ -230,7 +230,7 @@ def test_persistent_schedule_is_taken_only_on_the_full_part(tmp_path):
 
 
 def test_two_wave_decode_kernel_is_taken_where_it_is_the_faster_one(tmp_path):
-    """The rules of csrc/bm_decode_rules.h (plain C++) at layers that were measured on both sides of each line:
+    """The rules of csrc/bm_dispatch_rules.h (plain C++) at layers that were measured on both sides of each line:
     few groups with reductions of 1024 go to the quarter-split kernel, F = 2048 past 32 rows to the four-wave one."""
     import subprocess
     cases = [  # T, d, E, F, K -> two waves for gate/up, for down
@@ -240,11 +240,27 @@ def test_two_wave_decode_kernel_is_taken_where_it_is_the_faster_one(tmp_path):
         ((9, 4096, 16, 2048, 4), 0, 0), ((8, 4096, 16, 2048, 4), 1, 1), ((24, 3072, 4, 2048, 2), 1, 0), ((24, 3072, 8, 2048, 2), 1, 0),
         ((24, 3072, 16, 2048, 2), 0, 0), ((1, 4096, 8, 14336, 2), 0, 0), ((8, 2048, 64, 1408, 6), 1, 1)]
     src = tmp_path / "rules.cpp"
-    src.write_text('#include "bm_decode_rules.h"\n#include <cstdio>\nint main() {\n  int bad = 0;\n' + "".join(
+    src.write_text('#include "bm_dispatch_rules.h"\n#include <cstdio>\nint main() {\n  int bad = 0;\n' + "".join(
         '  { bm_layer_desc d{}; d.T = %d; d.d = %d; d.E = %d; d.F = %d; d.K = %d; d.dtype = BM_BF16;\n'
         '    if (bm::narrow_gateup(&d) != %d || bm::narrow_down(&d, false) != %d) { std::printf("T %%d d %%d E %%d F %%d K %%d\\n", d.T, d.d, d.E, d.F, d.K); ++bad; } }\n'
         % (*shape, gu, dn) for shape, gu, dn in cases) + '  return bad;\n}\n')
     exe = tmp_path / "rules"
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2511_10054_amd", "csrc"), "-o", str(exe), str(src)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+def test_substitution_takes_one_workgroup_only_where_that_is_as_fast(tmp_path):
+    """The rule of csrc/bm_dispatch_rules.h at batches measured on both sides: 2 of 8 and 1 of 64 experts with U_t or
+    gates take 11 to 18 us in one workgroup at 200 to 256 tokens and 6 to 9 us in one per tile."""
+    import subprocess
+    src = tmp_path / "remap.cpp"
+    src.write_text('#include "bm_dispatch_rules.h"\n#include <cstdio>\nint main() {\n'
+                   '  const int plain = bm::remap_one_workgroup_tokens(2, 0), tied = bm::remap_one_workgroup_tokens(2, BM_REMAP_UNIQUE);\n'
+                   '  const int gated = bm::remap_one_workgroup_tokens(1, BM_GATE_TAE), walk = bm::remap_one_workgroup_tokens(16, BM_REMAP_UNIQUE);\n'
+                   '  std::printf("%d %d %d %d\\n", plain, tied, gated, walk);\n'
+                   '  return !(plain >= 128 && plain < 192 && tied >= 64 && tied < 128 && gated >= 64 && gated < 128 && walk == 64);\n}\n')
+    exe = tmp_path / "remap"
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2511_10054_amd", "csrc"), "-o", str(exe), str(src)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout

@@ -77,6 +77,23 @@ def test_gates_and_budget_in_substitution_tiles(T, E, K, R, n_res, unique, rho):
         assert stats.cpu().tolist()[:3] == [st["n_miss"], st["n_substituted"], st["n_dropped"]]
 
 
+# the last batch that a single workgroup takes and the first that it does not, without ties, with U_t and for walks
+@pytest.mark.parametrize("T,E,K", [(128, 24, 3), (129, 24, 3), (96, 24, 8), (97, 24, 8), (64, 40, 9), (65, 40, 9)])
+@pytest.mark.parametrize("unique", [False, True])
+def test_substitution_around_one_workgroup(T, E, K, unique):
+    import torch
+    import paper_2511_10054_amd as bm
+    print("substitution around one workgroup", T, E, K, unique, flush=True)
+    ids, res, table = _problem(T + K, T, E, K, 6, E // 2)
+    ref, _, st = oracle.buddy_remap(ids, res, table, H=6, unique=unique, w=np.ones((T, K), np.float32))
+    desc = bm.LayerDesc(T=T, d=32, E=E, F=0, K=K, n_shared=0, R=6, H=6, dtype=bm.BM_BF16, flags=bm.BM_REMAP_UNIQUE if unique else 0)
+    out, stats = torch.full((T, K), -9, dtype=torch.int32, device="cuda"), torch.full((6,), -9, dtype=torch.int32, device="cuda")
+    bm.bm_buddy_remap(desc, to_device(workloads.pack_bitmap(res)), to_device(table), to_device(ids), out, None, stats)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(out.cpu().numpy(), ref)
+    assert stats.cpu().tolist() == [st["n_miss"], st["n_substituted"], st["n_dropped"], 0, 0, 0]
+
+
 # assignments around one and several words, one workgroup and a workgroup per tile, the largest batch and sets of both
 @pytest.mark.parametrize("T,E,K", [(1, 1, 1), (21, 7, 3), (32, 256, 2), (65, 8, 1), (128, 32, 8), (129, 32, 8), (1024, 32, 1),
                                    (31, 256, 32), (32, 256, 32), (33, 256, 32), (128, 128, 8), (1024, 16, 2), (1024, 17, 2), (683, 15, 3), (3001, 128, 8), (9000, 200, 4)])
