@@ -130,12 +130,13 @@ __device__ __forceinline__ void lanes_of_eight(int v, int (&out)[8]) {
 #undef BM_DPP_MOV
 }
 
-// replacement_budget() for a token held by eight lanes, lane k with the gate weight of slot k: the same operations in the
-// same order, the divisions and logarithms of the slots side by side.
+// replacement_budget() for a token held by eight lanes, lane k with the gate weight of slot k (KC = 1: by one lane): the same
+// operations in the same order, the divisions and logarithms of the slots side by side.
+template <int KC>
 __device__ __forceinline__ int replacement_budget_of_eight(int K, int k, uint32_t flags, float tau, float gamma, int rho, float wk) {
     int budget = (flags & BM_REPLACE_BUDGET) ? rho : 0x7fffffff;
     if (flags & (BM_GATE_TAE | BM_GATE_MARGIN)) {
-        const int first = lane_id() & 56;
+        const int first = KC == 1 ? lane_id() : lane_id() & 56;
         float v[8], sum = 0.0f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = __shfl(wk, first + j, WAVE);
@@ -175,20 +176,21 @@ __device__ __forceinline__ int replacement_budget_of_eight(int K, int k, uint32_
 // moves, and as long as two slots hold the same candidate, the lowest slot that shares one with an earlier slot
 // moves on to its row's next entry (all slots before it are final then, so this is the order of the algorithm;
 // mostly no or one turn).  The budget, from gates evaluated once per token, keeps the first so many substitutes in
-// slot order.  Without U_t and gates any number of slots goes that way, a lane per assignment.  (Substitution of
+// slot order.  Without U_t and gates any number of slots goes that way, a lane per assignment; so does a single slot per
+// token, compiled for it (KC = 1; 1 of 64 experts behind the gates, 1024 / 16384 tokens: 5.5 8.2 us, in eight lanes 8.2 10.7).  (Substitution of
 // 3001 tokens of 8 out of 128 experts with U_t: 6.5 us against 12 us with the walk.)
 constexpr int PICK_RESIDENT = 1 << 24, PICK_CANDIDATE = 1 << 25, PICK_VALID = 1 << 26;
 
-template <int W>
-__device__ __forceinline__ void remap_tile(int ntok, int K, int E, int R, uint32_t flags, float tau, float gamma, int rho,
+template <int W, int KC = 0>
+__device__ __forceinline__ void remap_tile(int ntok, int K_, int E, int R, uint32_t flags, float tau, float gamma, int rho,
                                            const uint64_t (&resident)[W], const uint32_t *accept, const int32_t *table,
                                            int32_t *ids, float *w, unsigned long long *used, int32_t *stats,
                                            const PsiSource &psi) {
-    const int tid = threadIdx.x, n = ntok * K;
+    const int tid = threadIdx.x, K = KC != 0 ? KC : K_, n = ntok * K;
     const bool unique = (flags & BM_REMAP_UNIQUE) != 0;
     const bool tied = unique || (flags & BM_GATE_ANY) != 0;
     if (psi.q == nullptr && (!tied || K <= 8)) {
-        const int per = tied ? 8 : K, total = ntok * per;              // lanes per token
+        const int per = tied && KC != 1 ? 8 : K, total = ntok * per;   // lanes per token
         for (int i0 = 0; i0 < total; i0 += blockDim.x) {
             const int i = i0 + tid, t = i / per, k = i - t * per;
             const bool slot = i < total && k < K;
@@ -197,7 +199,7 @@ __device__ __forceinline__ void remap_tile(int ntok, int K, int E, int R, uint32
             const int32_t *row = table + (size_t)(valid ? e : 0) * R;
             uint32_t m = valid && !res ? accept[e] : 0u;               // entries left to try; the candidate is the lowest
             int cand = m != 0u ? row[__builtin_ctz(m)] : -1;
-            if (unique) {
+            if (unique && KC != 1) {                                   // (a single slot's own id is not resident, so no candidate)
                 int held[8], other[8];                                 // from lane ^ 0 .. lane ^ 7
                 lanes_of_eight(valid ? e : -1, held);
                 auto skip_held = [&]() {                               // the token's original ids stay in U_t
@@ -227,7 +229,7 @@ __device__ __forceinline__ void remap_tile(int ntok, int K, int E, int R, uint32
                 }
             }
             if (flags & BM_GATE_ANY) {
-                const int budget = replacement_budget_of_eight(K, k, flags, tau, gamma, rho, w != nullptr && slot ? w[(size_t)t * K + k] : 0.0f);
+                const int budget = replacement_budget_of_eight<KC>(K, k, flags, tau, gamma, rho, w != nullptr && slot ? w[(size_t)t * K + k] : 0.0f);
                 const unsigned taken = (unsigned)(__ballot(cand >= 0) >> (tid & 56)) & ((1u << k) - 1u);
                 if (__popc(taken) >= budget) cand = -1;
             }
@@ -1321,7 +1323,7 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
 // with one 4-byte load in flight, the buddy rows scanned entry by entry and a whole walk per lane).
 // A single workgroup stores the counters, several add theirs to zeros (launch_remap).
 // ---------------------------------------------------------------------------
-template <int W>
+template <int W, int KC = 0>        // KC = 1: one slot per token, else p.K
 __global__ void __launch_bounds__(1024) remap_kernel(RemapParams p) {
     extern __shared__ int32_t s_table[];                // E * R entries, then E acceptable-entry masks
     __shared__ int32_t s_req[64 * W];                   // distribution gate: the expert was routed to
@@ -1391,7 +1393,7 @@ __global__ void __launch_bounds__(1024) remap_kernel(RemapParams p) {
         }
         PsiSource psi{};
         if (p.flags & BM_PSI_TOKEN) { psi.q = p.q; psi.eta = p.eta; psi.stride = p.E; psi.probs = p.probs + (size_t)t0 * p.E; }
-        remap_tile<W>(ntok, p.K, p.E, p.R, p.flags, p.tau, p.gamma, p.rho, resident, accept, s_table, s_ids,
+        remap_tile<W, KC>(ntok, p.K, p.E, p.R, p.flags, p.tau, p.gamma, p.rho, resident, accept, s_table, s_ids,
                       p.w != nullptr ? p.w + (size_t)t0 * p.K : nullptr, s_used, s_stats, psi);
         for (int idx = tid; idx < n; idx += blockDim.x) p.ids_out[(size_t)t0 * p.K + idx] = s_ids[idx];
         __syncthreads();
@@ -1775,9 +1777,15 @@ int launch_remap(const RemapParams &p, hipStream_t st) {
         blocks = blocks > (dist ? 256 : 1024) ? (dist ? 256 : 1024) : blocks;
         if (p.stats) hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, p.stats, 3);
     }
-    if (p.E <= 64) hipLaunchKernelGGL(remap_kernel<1>, dim3(blocks), dim3(threads), lds, st, p);
-    else if (p.E <= 128) hipLaunchKernelGGL(remap_kernel<2>, dim3(blocks), dim3(threads), lds, st, p);
-    else hipLaunchKernelGGL(remap_kernel<4>, dim3(blocks), dim3(threads), lds, st, p);
+#define BM_REMAP(W_)                                                                                           \
+    {                                                                                                          \
+        if (p.K == 1) hipLaunchKernelGGL((remap_kernel<W_, 1>), dim3(blocks), dim3(threads), lds, st, p);      \
+        else hipLaunchKernelGGL((remap_kernel<W_>), dim3(blocks), dim3(threads), lds, st, p);                  \
+    }
+    if (p.E <= 64) BM_REMAP(1)
+    else if (p.E <= 128) BM_REMAP(2)
+    else BM_REMAP(4)
+#undef BM_REMAP
     return launch_status(__func__);
 }
 

@@ -77,6 +77,33 @@ def test_gates_and_budget_in_substitution_tiles(T, E, K, R, n_res, unique, rho):
         assert stats.cpu().tolist()[:3] == [st["n_miss"], st["n_substituted"], st["n_dropped"]]
 
 
+# one slot a token, which has a form of its own: rows that head the expert itself (U_t holds it), every gate, batches of one
+# and several workgroups, 1 to 4 words of experts
+@pytest.mark.parametrize("T,E", [(1, 3), (64, 64), (97, 65), (300, 128), (257, 200)])
+@pytest.mark.parametrize("unique", [False, True])
+@pytest.mark.parametrize("gate", [dict(), dict(rho=0), dict(rho=1), dict(tau=0.5), dict(gamma=0.5), dict(gamma=1.5), dict(beta=1.5)])
+def test_one_slot_per_token(T, E, unique, gate):
+    import torch
+    import paper_2511_10054_amd as bm
+    print("one slot per token", T, E, unique, gate, flush=True)
+    ids, res, table = _problem(T + E, T, E, 1, 3, (E + 1) // 2)
+    table[:, 0] = np.where(np.arange(E) % 2 == 0, np.arange(E), table[:, 0])
+    w = np.random.default_rng(E).uniform(0.1, 1.0, size=(T, 1)).astype(np.float32)
+    ref, w_ref, st = oracle.buddy_remap_gated(ids, res, table, w=w, H=3, unique=unique, **gate)
+    flags = bm.BM_REMAP_UNIQUE if unique else 0
+    for name, bit in (("rho", bm.BM_REPLACE_BUDGET), ("tau", bm.BM_GATE_TAE), ("gamma", bm.BM_GATE_MARGIN), ("beta", bm.BM_GATE_DIST)):
+        flags |= bit if name in gate else 0
+    desc = bm.LayerDesc(T=T, d=32, E=E, F=0, K=1, n_shared=0, R=3, H=3, dtype=bm.BM_BF16, flags=flags, rho=gate.get("rho", 0),
+                        tae_tau=gate.get("tau", 0.0), margin_gamma=gate.get("gamma", 0.0), dist_beta=gate.get("beta", 0.0))
+    d_w, out = to_device(w), torch.full((T, 1), -9, dtype=torch.int32, device="cuda")
+    stats = torch.full((6,), -9, dtype=torch.int32, device="cuda")
+    bm.bm_buddy_remap(desc, to_device(workloads.pack_bitmap(res)), to_device(table), to_device(ids), out, d_w, stats)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(out.cpu().numpy(), ref)
+    np.testing.assert_array_equal(d_w.cpu().numpy(), np.asarray(w_ref, np.float32))
+    assert stats.cpu().tolist()[:3] == [st["n_miss"], st["n_substituted"], st["n_dropped"]]
+
+
 # the last batch that a single workgroup takes and the first that it does not, without ties, with U_t and for walks
 @pytest.mark.parametrize("T,E,K", [(128, 24, 3), (129, 24, 3), (96, 24, 8), (97, 24, 8), (64, 40, 9), (65, 40, 9)])
 @pytest.mark.parametrize("unique", [False, True])
