@@ -586,20 +586,20 @@ __device__ __forceinline__ int wave_excl_scan(int v, int &total) {
     return incl - v;
 }
 
-// Per expert, the set of the assignments that hold it: bit a % 64 of masks[e * words + a / 64] for assignment a of A
-// whose substituted ids sit in LDS (-1 = dropped), words = ceil(A / 64).  The number of earlier assignments with the
-// same expert - the rank that a stable placement needs - is then a few population counts instead of a walk over the
-// assignments.  Every thread of the workgroup calls it; ends with a barrier.
+// Per expert, the set of the assignments that hold it: bit a % 64 of masks[e * set_stride(A) + a / 64] for assignment a of
+// A whose substituted ids sit in LDS (-1 = dropped).  The number of earlier assignments with the same expert - the rank
+// that a stable placement needs - is then a few population counts instead of a walk over the assignments.  Every thread
+// of the workgroup calls it; ends with a barrier.
 __device__ __forceinline__ void assignment_sets(const int32_t *ids, int A, int E, unsigned long long *masks) {
-    const int tid = threadIdx.x, words = (A + 63) >> 6;
-    for (int i = tid; i < E * words; i += blockDim.x) masks[i] = 0ull;
+    const int tid = threadIdx.x, stride = set_stride(A);
+    for (int i = tid; i < E * stride; i += blockDim.x) masks[i] = 0ull;
     __syncthreads();
     for (int a = tid; a < A; a += blockDim.x)
-        if ((unsigned)ids[a] < (unsigned)E) atomicOr(&masks[ids[a] * words + (a >> 6)], 1ull << (a & 63));
+        if ((unsigned)ids[a] < (unsigned)E) atomicOr(&masks[ids[a] * stride + (a >> 6)], 1ull << (a & 63));
     __syncthreads();
 }
-__device__ __forceinline__ int earlier_assignments(const unsigned long long *masks, int words, int e, int a) {
-    const unsigned long long *m = masks + e * words;
+__device__ __forceinline__ int earlier_assignments(const unsigned long long *masks, int A, int e, int a) {
+    const unsigned long long *m = masks + e * set_stride(A);
     int rank = __popcll(m[a >> 6] & ((1ull << (a & 63)) - 1ull));
     for (int w = 0; w < (a >> 6); ++w) rank += __popcll(m[w]);
     return rank;
@@ -610,7 +610,7 @@ __device__ __forceinline__ void place_assignments(const int32_t *ids, int A, int
                                                   const unsigned long long *masks, const ScatterParams &c) {
     for (int a = threadIdx.x; a < A; a += blockDim.x) {
         const int e = ids[a];
-        const int pos = (unsigned)e < (unsigned)E ? start[e] + earlier_assignments(masks, (A + 63) >> 6, e, a) : -1;
+        const int pos = (unsigned)e < (unsigned)E ? start[e] + earlier_assignments(masks, A, e, a) : -1;
         if (pos >= 0) {
             c.perm[pos] = a;
             if (c.row_token) c.row_token[pos] = a / K;
@@ -867,7 +867,7 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     constexpr int NS = partial_tiles<NB, KW, TILE_T>(), NS2 = partial_tiles<NB, KW, 16>();   // kept side by side
     static_assert(NS2 <= 2 * NS, "the partial tiles of 16 tokens fit");
     __shared__ __attribute__((aligned(16))) float part[NS * TILE];
-    static_assert(sizeof(part) >= NB * 16 * (TILE_T * BM_MAX_K / 64) * 8, "holds the assignment sets as well");
+    static_assert(sizeof(part) >= NB * 16 * set_stride(TILE_T * BM_MAX_K) * 8, "holds the assignment sets as well");
     constexpr bool CAN_STAGE = !FUSED && U >= 2 && U % 2 == 0;
     __shared__ u32x4 stage[CAN_STAGE ? NW * 256 : 1];            // 4 KB per wave (see the staged product below)
     __shared__ FrontLds s;
@@ -1210,7 +1210,7 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
     constexpr int NBW = NB / NH, KW = NW / NH;           // as in the bf16 kernel
     constexpr int NS = partial_tiles<NB, KW, TT>();      // kept side by side
     __shared__ __attribute__((aligned(16))) float part[NS * TILE];
-    static_assert(sizeof(part) >= NB * 16 * (TT * BM_MAX_K / 64) * 8, "holds the assignment sets as well");
+    static_assert(sizeof(part) >= NB * 16 * set_stride(TT * BM_MAX_K) * 8, "holds the assignment sets as well");
     __shared__ FrontLds s;
     __shared__ int32_t start[BM_MAX_E + 16], tstart[BM_MAX_E + 16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1515,7 +1515,7 @@ __global__ void __launch_bounds__(1024) scan_kernel(ScanParams p) {
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) scatter_kernel(ScatterParams p) {
     __shared__ int32_t s_ids[TILE_T * BM_MAX_K];
-    __shared__ unsigned long long masks[BM_MAX_E * (TILE_T * BM_MAX_K / 64)];
+    __shared__ unsigned long long masks[BM_MAX_E * set_stride(TILE_T * BM_MAX_K)];
     const int tid = threadIdx.x, tile = blockIdx.x, t0 = tile * p.tile_tokens;
     const int n_tiles_all = (p.T + p.tile_tokens - 1) / p.tile_tokens;
     const int K = p.K, E = p.E;
@@ -1532,7 +1532,7 @@ __global__ void __launch_bounds__(256) scatter_kernel(ScatterParams p) {
         const int a = t0 * K + idx;
         int pos = -1;
         if (e >= 0) {
-            pos = p.offsets[e] + p.tile_base[(size_t)e * n_tiles_all + tile] + earlier_assignments(masks, (n + 63) >> 6, e, idx);
+            pos = p.offsets[e] + p.tile_base[(size_t)e * n_tiles_all + tile] + earlier_assignments(masks, n, e, idx);
             p.perm[pos] = a;
             if (p.row_token) p.row_token[pos] = a / K;
         }
@@ -1569,7 +1569,7 @@ __global__ void __launch_bounds__(1024) group_tiles_kernel(ScanParams p, Scatter
     __shared__ int32_t start[BM_MAX_E + 9];
     __shared__ int32_t tstart[BM_MAX_E + 9];
     __shared__ int32_t s_ids[TILE_T * BM_MAX_K];
-    __shared__ unsigned long long masks[BM_MAX_E * (TILE_T * BM_MAX_K / 64)];
+    __shared__ unsigned long long masks[BM_MAX_E * set_stride(TILE_T * BM_MAX_K)];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
     const int tile = blockIdx.x, t0 = tile * c.tile_tokens;
     const int K = c.K, E = p.E, G = p.E + p.n_shared;
@@ -1656,7 +1656,7 @@ __global__ void __launch_bounds__(1024) group_tiles_kernel(ScanParams p, Scatter
         const int a = t0 * K + idx;
         int pos = -1;
         if (e >= 0) {
-            pos = start[e] + before[e] + earlier_assignments(masks, (n + 63) >> 6, e, idx);
+            pos = start[e] + before[e] + earlier_assignments(masks, n, e, idx);
             c.perm[pos] = a;
             if (c.row_token) c.row_token[pos] = a / K;
         }
@@ -1681,12 +1681,12 @@ constexpr int SMALL_ANY = 1024, SMALL_A = 2048, SMALL_SETS = 32768;     // see g
 
 __global__ void __launch_bounds__(1024) group_small_kernel(ScanParams p, ScatterParams c) {
     __shared__ int32_t ids[SMALL_A];
-    __shared__ unsigned long long masks[SMALL_ANY / 64 * BM_MAX_E];
-    static_assert(SMALL_ANY / 64 * BM_MAX_E >= SMALL_SETS / 64 + SMALL_SETS / SMALL_ANY, "holds the larger batches' sets, rounded up per expert");
+    __shared__ unsigned long long masks[set_stride(SMALL_ANY) * BM_MAX_E];
+    static_assert(set_stride(SMALL_ANY) * BM_MAX_E >= SMALL_SETS / 64 + 2 * (SMALL_SETS / SMALL_ANY), "holds the larger batches' sets, rounded up per expert");
     __shared__ int32_t total[BM_MAX_E + 8];
     __shared__ int32_t start[BM_MAX_E + 9];
     __shared__ int32_t tstart[BM_MAX_E + 9];
-    const int tid = threadIdx.x, E = p.E, A = c.T * c.K, words = (A + 63) >> 6;
+    const int tid = threadIdx.x, E = p.E, A = c.T * c.K, words = (A + 63) >> 6, stride = set_stride(A);
     for (int a = tid; a < A; a += blockDim.x) {
         const int e = c.ids[a];
         ids[a] = ((unsigned)e < (unsigned)E) ? e : -1;
@@ -1694,7 +1694,7 @@ __global__ void __launch_bounds__(1024) group_small_kernel(ScanParams p, Scatter
     assignment_sets(ids, A, E, masks);                   // (its first barrier is behind the stores above)
     for (int e = tid; e < E; e += blockDim.x) {
         int cnt = 0;
-        for (int w = 0; w < words; ++w) cnt += __popcll(masks[e * words + w]);
+        for (int w = 0; w < words; ++w) cnt += __popcll(masks[e * stride + w]);
         total[e] = cnt;
     }
     __syncthreads();
@@ -1800,10 +1800,11 @@ int launch_scan(const ScanParams &p, hipStream_t st) {
     return launch_status(__func__);
 }
 
-// The one-workgroup kernel takes up to 1024 assignments, one per thread, whatever the number of experts (128 experts, 512 /
-// 1024 assignments: 3.5 / 6.0 us against 7.8 / 7.9 us for the per-tile histograms and the kernel that sums them), and
-// up to 2048 of few experts (8 experts, 1554 assignments: 4.8 against 6.8 us).  Beyond, a thread's rank adds up too
-// many words (128 experts, 2048 assignments: 15.0 against 8.1 us; 8 experts, 4096: 21.3 against 7.0 us).
+// The one-workgroup kernel takes up to 1024 assignments, one per thread, whatever the number of experts, and up to 2048 of
+// few experts; beyond, a thread's rank adds up too many words.  One workgroup | per-tile histograms and the kernel that
+// sums them, us: bm_permute_by_expert (which has to count first in the second form) of 128 experts, 512 / 1024
+// assignments 4.1 4.7 | 8.7 8.7, 8 experts, 1536 / 2048 5.4 6.3 | 8.0 8.0; small layers (whose front kernel has counted) of
+// 128 experts, 1024 / 2048 assignments 33.7 38.0 | 35.1 37.2, 8 experts, 1536 / 2048 / 4096 45.2 46.3 52.8 | 45.7 46.0 47.4.
 bool grouping_small(long long assignments, int E) {
     return assignments <= SMALL_ANY || (assignments <= SMALL_A && assignments * E <= SMALL_SETS);
 }

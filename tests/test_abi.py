@@ -266,6 +266,28 @@ def test_substitution_takes_one_workgroup_only_where_that_is_as_fast(tmp_path):
     assert r.returncode == 0, r.stdout
 
 
+def test_assignment_sets_of_different_experts_meet_in_different_banks(tmp_path):
+    """The same word of 32 consecutive experts' sets falls into 32 different pairs of the 64 LDS banks, for every number of
+    assignments from which a rank reads several words (csrc/bm_dispatch_rules.h, plain C++)."""
+    import subprocess
+    src = tmp_path / "sets.cpp"
+    src.write_text(r'''
+#include "bm_dispatch_rules.h"
+#include <cstdio>
+int main() {
+    for (int A = 449; A <= 2048; ++A) {
+        unsigned seen = 0;
+        for (int e = 0; e < 32; ++e) seen |= 1u << (e * bm::set_stride(A) % 32);
+        if (seen != 0xffffffffu || bm::set_stride(A) * 64 < A) { std::printf("%d\n", A); return 1; }
+    }
+    return 0;
+}
+''')
+    exe = tmp_path / "sets"
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2511_10054_amd", "csrc"), "-o", str(exe), str(src)], check=True)
+    assert subprocess.run([str(exe)]).returncode == 0
+
+
 def test_small_tile_dealer_hands_out_every_tile_exactly_once(tmp_path):
     """The dealing of 128-row tiles among an XCD's workgroups (csrc/bm_tile_dealer.h, plain C++): for every
     number of 256-row tiles, 128-row tiles and workgroups in a range, each tile goes to exactly one workgroup,
