@@ -37,7 +37,9 @@ inline bool quarter_split_projection(const bm_layer_desc *d, int N, int Kd) {
 // gate/up blocks of 64 rows on no unit is without one.  Two waves for both | four waves for both (split) | two-wave gate/up
 // and split down, us: d = 4096, 16 experts, K = 4 at 9 / 16 / 32 tokens 157 165 161 | 144 154 157 | 152 159 156; 32
 // experts at 32 tokens 299 | 282 | 292; d = 3072, 4 experts, K = 2 at 24 tokens 45 | 51 | 46; 8 experts 69 | 69 | 69.
-inline bool long_narrow(const bm_layer_desc *d) { return d->F >= 2048 && (long long)d->T * d->K > 32; }
+// Only where the four-wave form takes the gate/up reduction (multiples of 256): else gate/up has nowhere faster to go, and
+// the split alone is within 4 % either way.
+inline bool long_narrow(const bm_layer_desc *d) { return d->F >= 2048 && d->d % 256 == 0 && (long long)d->T * d->K > 32; }
 
 inline bool narrow_gateup(const bm_layer_desc *d) {
     return narrow_shape(d) && !quarter_split_projection(d, d->F, d->d) &&

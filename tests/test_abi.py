@@ -238,7 +238,7 @@ def test_two_wave_decode_kernel_is_taken_where_it_is_the_faster_one(tmp_path):
         ((1, 1024, 16, 1024, 5), 1, 1), ((1, 2048, 8, 1024, 2), 0, 0), ((2, 2048, 8, 1024, 2), 0, 1), ((1, 4096, 4, 1024, 1), 0, 0),
         ((1, 3072, 8, 1024, 1), 0, 0), ((8, 2048, 128, 768, 8), 1, 1), ((32, 2048, 128, 768, 8), 1, 1), ((33, 2048, 128, 768, 8), 0, 0),
         ((9, 4096, 16, 2048, 4), 0, 0), ((8, 4096, 16, 2048, 4), 1, 1), ((24, 3072, 4, 2048, 2), 1, 0), ((24, 3072, 8, 2048, 2), 1, 0),
-        ((24, 3072, 16, 2048, 2), 0, 0), ((1, 4096, 8, 14336, 2), 0, 0), ((8, 2048, 64, 1408, 6), 1, 1)]
+        ((24, 3072, 16, 2048, 2), 0, 0), ((14, 640, 64, 2048, 10), 1, 1), ((1, 4096, 8, 14336, 2), 0, 0), ((8, 2048, 64, 1408, 6), 1, 1)]
     src = tmp_path / "rules.cpp"
     src.write_text('#include "bm_dispatch_rules.h"\n#include <cstdio>\nint main() {\n  int bad = 0;\n' + "".join(
         '  { bm_layer_desc d{}; d.T = %d; d.d = %d; d.E = %d; d.F = %d; d.K = %d; d.dtype = BM_BF16;\n'
