@@ -885,6 +885,7 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
     const int nbatch = ksteps / U;
     static_assert((NW * 64) % (NB * 16) == 0, "a thread adds up logits of one expert only");
     const int my_e = tid % (NB * 16);
+    const float my_bias = (p.bias != nullptr && my_e < p.E) ? p.bias[my_e] : 0.0f;
 
     for (int tile = tile_begin; tile < tile_end; ++tile) {
         const int t0 = tile * p.tile_tokens;
@@ -1015,16 +1016,17 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                 part[i * STRIDE + e] = p.logits[(size_t)t0 * p.E + idx];
             }
         } else {
-            const float my_bias = (p.bias != nullptr && my_e < p.E) ? p.bias[my_e] : 0.0f;
             float sum[2][ROWS_PER];
+            constexpr bool BOTH = NS == KW;              // the waves' tiles of 32 tokens fit side by side: both blocks at once
+            constexpr int SLOT = BOTH ? TILE : 16 * STRIDE, ROUNDS = (KW + NS2 - 1) / NS2;
 #pragma unroll
             for (int tb = 0; tb < 2; ++tb) {
                 if (tb == 1 && !two) break;
-                if (tb == 1) __syncthreads();            // the first block's slots have been read
+                if (tb == 1 && !BOTH) __syncthreads();   // the first block's slots have been read
 #pragma unroll
-                for (int r = 0; r < (KW + NS2 - 1) / NS2; ++r) {
+                for (int r = 0; r < ROUNDS; ++r) {
                     if (kw / NS2 == r) {
-                        float *mine = part + (kw % NS2) * (16 * STRIDE);
+                        float *mine = part + (kw % NS2) * SLOT + (BOTH ? tb * 16 * STRIDE : 0);
 #pragma unroll
                         for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
@@ -1033,12 +1035,22 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
                                 *q = (r == 0 ? 0.0f : *q) + acc[tb][nb][v];
                             }
                     }
-                    __syncthreads();
+                    if (!BOTH) __syncthreads();
                 }
+                if (BOTH) continue;
 #pragma unroll
                 for (int j = 0; j < ROWS_PER; ++j)
                     if (my_i + j * STEP < 16)
-                        sum[tb][j] = add_slots<NS2, NS2>(part + (my_i + j * STEP) * STRIDE + my_e, 16 * STRIDE) + my_bias;
+                        sum[tb][j] = add_slots<NS2, NS2>(part + (my_i + j * STEP) * STRIDE + my_e, SLOT) + my_bias;
+            }
+            if (BOTH) {
+                __syncthreads();
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+                    for (int j = 0; j < ROWS_PER; ++j)
+                        if ((tb == 0 || two) && my_i + j * STEP < 16)
+                            sum[tb][j] = add_slots<NS2, NS2>(part + (tb * 16 + my_i + j * STEP) * STRIDE + my_e, SLOT) + my_bias;
             }
             // the first two slots become the logit tile (a thread writes only where it alone has read)
 #pragma unroll
