@@ -8,11 +8,12 @@ from helpers import DeviceLayer, HostLayer, err_metric
 
 pytestmark = pytest.mark.gpu
 
-# fp32 sums over at most 512 values in blocks of at most 32: measured errors are below 1e-6, the bound is the suite's
+# fp32 sums over at most 512 values: measured errors are below 1e-6, the bound is the suite's (test_gpu_f32_chains.py
+# has the long reductions, with one close to the measured error)
 TOL = 1e-5
 
-# (overrides, tokens): group sizes around 16, 32 and 64 rows, more than one 64-row tile of a group, both row-tile
-# heights of the table, expert counts of every front kernel, widths that are no multiple of 64, 4 (outputs) or
+# (overrides, tokens): group sizes around 16, 32 and 64 rows, more than one 64-row tile of a group (the table lists a live
+# group once, whatever the layer's average), expert counts of every front kernel, widths that are no multiple of 64, 4 (outputs) or
 # 32 (reductions: the row-by-row kernel and the front kernel's checked loads), shared experts
 CASES = [
     (dict(E=4, K=1, n_resident=1, R=3, H=3), 1),
