@@ -241,7 +241,9 @@ int bm_permute_by_expert(const bm_layer_desc *desc, const int32_t *ids_remapped,
  * the workspace given, so their y can differ in rounding with the workspace's
  * size.)  dbg may be NULL.
  * bf16: MFMA with fp32 accumulation, h and o held in bf16 between the two
- * projections; fp32: fp32 FMA throughout. */
+ * projections; fp32: fp32 products and sums throughout (matrix instructions, the
+ * sums as trees; widths that are no multiple of 32 and arrays off a 16-byte
+ * boundary row by row). */
 int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *weights,
                    const uint64_t *residency_bitmap, const int32_t *buddy_table, void *y,
                    void *workspace, size_t workspace_bytes, const bm_debug_out *dbg,

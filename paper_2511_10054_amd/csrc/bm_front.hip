@@ -2,18 +2,21 @@
 // substitution (Section 4, Algorithm 1) and the stable grouping of the
 // surviving assignments by expert.
 //
-// Tokens are processed in tiles of TILE_T = 32 (16 for small bf16 batches, see
-// front_tile_tokens).  One workgroup owns one tile:
+// Tokens are processed in tiles of TILE_T = 32 (16 for fp32 and for bf16 batches
+// of up to 8160 tokens, see front_tile_tokens).  One workgroup owns one tile:
 // its waves split the hidden dimension for the router product (MFMA,
-// for bf16 and fp32), the partial logits meet in LDS, then each wave ranks
-// whole tokens (one expert per lane), 32 lanes walk Algorithm 1 for the 32
-// tokens, and the tile's per-expert histogram goes to global memory.  A
-// one-workgroup scan turns the histograms into group offsets, per-tile bases
-// and the row-tile table of the grouped GEMMs; a scatter kernel then places
-// every assignment (rank inside the tile by counting earlier equal keys, so
-// the order is the stable one and no atomics decide a position).  Small batches
-// get offsets and placement from one workgroup instead (group_small_kernel), or
-// from the front kernel itself (FUSED).
+// for bf16 and fp32; few tokens and many experts: in a launch of its own), the
+// partial logits meet in LDS, then each wave ranks
+// whole tokens (one expert per lane), Algorithm 1 runs on eight lanes per token
+// (remap_tile; more than eight slots, or priorities: a lane walks the slots),
+// and the tile's per-expert histogram goes to global memory.  One kernel, or a
+// one-workgroup scan and a scatter kernel for large histograms, turns the
+// histograms into group offsets, the row-tile table of the grouped GEMMs and the
+// position of every assignment (rank inside the tile from its expert's
+// assignment set, so the order is the stable one and no atomics decide a
+// position).  Small batches get offsets and placement from one workgroup instead
+// (group_small_kernel), or from the front kernel itself (FUSED, or the tail of a
+// single tile).
 #include "bm_dispatch_rules.h"
 #include "bm_kernels.h"
 
@@ -32,12 +35,6 @@ __device__ __forceinline__ bool test_bit(const uint64_t (&m)[W], int b) {
         wv = (b >> 6) == i ? mi : wv;    // indexed one, which puts the array into scratch memory
     }
     return (wv >> (b & 63)) & 1ull;
-}
-template <int W>
-__device__ __forceinline__ void set_bit(uint64_t (&m)[W], int b) {
-    const uint64_t bit = 1ull << (b & 63);
-#pragma unroll
-    for (int i = 0; i < W; ++i) m[i] |= (W == 1 || (b >> 6) == i) ? bit : 0ull;
 }
 
 // Gates in front of the substitution (Section 3.1: TAE, Eq. 1, and probability margin;
@@ -177,8 +174,8 @@ __device__ __forceinline__ int replacement_budget_of_eight(int K, int k, uint32_
 // moves on to its row's next entry (all slots before it are final then, so this is the order of the algorithm;
 // mostly no or one turn).  The budget, from gates evaluated once per token, keeps the first so many substitutes in
 // slot order.  Without U_t and gates any number of slots goes that way, a lane per assignment; so does a single slot per
-// token, compiled for it (KC = 1; 1 of 64 experts behind the gates, 1024 / 16384 tokens: 5.5 8.2 us, in eight lanes 8.2 10.7).  (Substitution of
-// 3001 tokens of 8 out of 128 experts with U_t: 6.5 us against 12 us with the walk.)
+// token, compiled for it (KC = 1; 1 of 64 experts behind the gates, 1024 / 16384 tokens: 5.5 8.2 us, in eight lanes 8.2 10.7).
+// (bm_buddy_remap of 4096 tokens of 8 out of 128 experts with U_t: 9.0 us; 28 us with all of it in a lane's walk.)
 constexpr int PICK_RESIDENT = 1 << 24, PICK_CANDIDATE = 1 << 25, PICK_VALID = 1 << 26;
 
 template <int W, int KC = 0>
@@ -507,7 +504,7 @@ __device__ void tile_epilogue(const FrontParams &p, float *logits, int stride, i
 #pragma unroll
     for (int i = 0; i < EC; ++i) resident[i] = s.bitmap[i];
     if (p.flags & (BM_REMAP_UNIQUE | BM_GATE_ANY | BM_PSI_TOKEN)) {
-        // Algorithm 1 proper (and its per-token gates and priorities): a lane walks its token's slots in order
+        // Algorithm 1 proper, with its per-token gates and priorities
         uint32_t *accept = reinterpret_cast<uint32_t *>(s.lut);
         for (int e = tid; e < E; e += blockDim.x) accept[e] = acceptable_entries<EC>(tab + (size_t)e * p.R, H, E, resident);
         __syncthreads();
@@ -1088,8 +1085,8 @@ __global__ void __launch_bounds__(NW * 64) front_bf16_kernel(FrontParams p) {
 // 16 tokens, which reads the whole router matrix through one unit (bf16, 128 experts: 8 of 18 us) and, in fp32,
 // multiplies 16 x 128 x 2048 on it (14 us of matrix instructions, plus the sums between them).  Here a workgroup
 // takes 16 tokens x 16 experts, its 8 waves split the hidden dimension; the front kernel then starts from the
-// logits.  Same operand layouts, k-step batches and order of additions as there, so the same bits.  Qwen3-shaped layer: fp32, 128 tokens 48 us -> 11 + 10 us; bf16, 8 tokens
-// 17 us -> 5 + 10 us.
+// logits.  Same operand layouts, k-step batches and order of additions as there, so the same bits.  Qwen3-shaped layer:
+// fp32, 128 tokens 48 us -> 11 + 10 us; bf16, 8 tokens 17 us -> 5 + 10 us.
 // ---------------------------------------------------------------------------
 constexpr int ROUTER_NW = 8;
 
@@ -1331,7 +1328,7 @@ __global__ void __launch_bounds__(NW * 64) front_f32_kernel(FrontParams p) {
 // ---------------------------------------------------------------------------
 // Stand-alone substitution kernel: tiles of 64 tokens; table, acceptable entries and ids in LDS.  Bound by latency.
 // With the distribution gate every workgroup reads all routed ids for the request set (no scratch memory, no
-// grid-wide wait): 16 bytes per load, eight loads in flight per lane (3001 tokens of 8 out of 128 experts: 15 us; 62 us
+// grid-wide wait): 16 bytes per load, eight loads in flight per lane (3001 tokens of 8 out of 128 experts: 8.8 us; 62 us
 // with one 4-byte load in flight, the buddy rows scanned entry by entry and a whole walk per lane).
 // A single workgroup stores the counters, several add theirs to zeros (launch_remap).
 // ---------------------------------------------------------------------------
