@@ -20,6 +20,8 @@
 #include "bm_dispatch_rules.h"
 #include "bm_kernels.h"
 
+#include <type_traits>
+
 namespace bm {
 
 // ---------------------------------------------------------------------------
@@ -134,23 +136,28 @@ __device__ __forceinline__ int replacement_budget_of_eight(int K, int k, uint32_
     int budget = (flags & BM_REPLACE_BUDGET) ? rho : 0x7fffffff;
     if (flags & (BM_GATE_TAE | BM_GATE_MARGIN)) {
         const int first = KC == 1 ? lane_id() : lane_id() & 56;
-        float v[8], sum = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = __shfl(wk, first + j, WAVE);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) sum = j < K ? sum + v[j] : sum;
-        const float mine = k < K ? wk / sum : 0.0f;
-        const float term = mine > 0.0f ? mine * logf(mine) : 0.0f;
         float h = 0.0f, p1 = 0.0f, p2 = 0.0f;
+        auto evaluate = [&](auto slots) {                // the first so many lanes, K of them with a slot
+            constexpr int N = decltype(slots)::value;
+            float v[N], sum = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float pj = __shfl(mine, first + j, WAVE), tj = __shfl(term, first + j, WAVE);
-            if (j >= K) continue;
-            h -= tj;
-            const float lo = fminf(p1, pj);
-            p1 = fmaxf(p1, pj);
-            p2 = fmaxf(p2, lo);
-        }
+            for (int j = 0; j < N; ++j) v[j] = __shfl(wk, first + j, WAVE);
+#pragma unroll
+            for (int j = 0; j < N; ++j) sum = j < K ? sum + v[j] : sum;
+            const float mine = k < K ? wk / sum : 0.0f;
+            const float term = mine > 0.0f ? mine * logf(mine) : 0.0f;
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const float pj = __shfl(mine, first + j, WAVE), tj = __shfl(term, first + j, WAVE);
+                if (j >= K) continue;
+                h -= tj;
+                const float lo = fminf(p1, pj);
+                p1 = fmaxf(p1, pj);
+                p2 = fmaxf(p2, lo);
+            }
+        };
+        if (K <= 2) evaluate(std::integral_constant<int, KC == 1 ? 1 : 2>{});
+        else evaluate(std::integral_constant<int, 8>{});
         const float tae = K > 1 ? h / logf((float)K) : 0.0f;
         if ((flags & BM_GATE_TAE) && tae <= tau) budget = 0;
         if ((flags & BM_GATE_MARGIN) && (p1 - p2) >= gamma) budget = 0;
@@ -184,7 +191,7 @@ __device__ __forceinline__ void remap_tile(int ntok, int K_, int E, int R, uint3
                                            int32_t *ids, float *w, unsigned long long *used, int32_t *stats,
                                            const PsiSource &psi) {
     const int tid = threadIdx.x, K = KC != 0 ? KC : K_, n = ntok * K;
-    const bool unique = (flags & BM_REMAP_UNIQUE) != 0;
+    const bool unique = (flags & BM_REMAP_UNIQUE) != 0 && K > 1;       // (a single slot's own id is not resident, so no candidate)
     const bool tied = unique || (flags & BM_GATE_ANY) != 0;
     if (psi.q == nullptr && (!tied || K <= 8)) {
         const int per = tied && KC != 1 ? 8 : K, total = ntok * per;   // lanes per token
@@ -196,7 +203,7 @@ __device__ __forceinline__ void remap_tile(int ntok, int K_, int E, int R, uint3
             const int32_t *row = table + (size_t)(valid ? e : 0) * R;
             uint32_t m = valid && !res ? accept[e] : 0u;               // entries left to try; the candidate is the lowest
             int cand = m != 0u ? row[__builtin_ctz(m)] : -1;
-            if (unique && KC != 1) {                                   // (a single slot's own id is not resident, so no candidate)
+            if (unique) {
                 int held[8], other[8];                                 // from lane ^ 0 .. lane ^ 7
                 lanes_of_eight(valid ? e : -1, held);
                 auto skip_held = [&]() {                               // the token's original ids stay in U_t
@@ -503,7 +510,7 @@ __device__ void tile_epilogue(const FrontParams &p, float *logits, int stride, i
     uint64_t resident[EC];
 #pragma unroll
     for (int i = 0; i < EC; ++i) resident[i] = s.bitmap[i];
-    if (p.flags & (BM_REMAP_UNIQUE | BM_GATE_ANY | BM_PSI_TOKEN)) {
+    if ((p.flags & (BM_GATE_ANY | BM_PSI_TOKEN)) || ((p.flags & BM_REMAP_UNIQUE) && K > 1)) {
         // Algorithm 1 proper, with its per-token gates and priorities
         uint32_t *accept = reinterpret_cast<uint32_t *>(s.lut);
         for (int e = tid; e < E; e += blockDim.x) accept[e] = acceptable_entries<EC>(tab + (size_t)e * p.R, H, E, resident);

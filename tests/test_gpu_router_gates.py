@@ -51,3 +51,16 @@ def test_priorities_behind_the_router_launch(name, over, T):
     assert ref["stats"]["bypassed"] == 0 and ref["stats"]["n_substituted"] > 0
     out, ref = _check(host, q, 8.0, False, beta=closed)
     assert ref["stats"]["bypassed"] == 1 and ref["stats"]["n_substituted"] == 0
+
+
+# one slot a token: U_t never decides (a non-resident expert is no candidate), the gates see one weight; one tile and several
+@pytest.mark.parametrize("name,over", [("c2_mixtral_decode", dict(d=256, F=256, K=1)), ("c4_qwen3", dict(d=256, F=128, E=65, K=1, n_resident=30)),
+                                       ("c1_tiny", dict(K=1))])
+@pytest.mark.parametrize("T", [1, 16, 40])
+def test_one_slot_per_token_in_the_layer(name, over, T):
+    spec = workloads.scaled(name, **over)
+    print("one slot in the layer", name, over, T, flush=True)
+    host = HostLayer(spec, T)
+    for unique in (False, True):
+        for gates in (dict(), dict(tau=0.5), dict(gamma=0.5), dict(gamma=1.5), dict(rho=0), dict(tau=-0.5, rho=1), dict(beta=1.5), dict(beta=0.0)):
+            _check_layer(host, unique, **gates)
