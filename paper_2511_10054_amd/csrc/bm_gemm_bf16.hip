@@ -14,9 +14,8 @@
 // Kernels, in the order the launchers prefer them:
 //   grouped_gemm_mixed_k64w      persistent, k-steps of 64 with whole-line direct-to-LDS loads,
 //                                v_mfma_f32_16x16x32_bf16; 256-row tiles plus one 128-row tile for a group's
-//                                rest of at most 128 rows, both heights in one launch
-//   grouped_gemm256_k64w         the same tile loop on 256-row tiles only, with a reduction-split tail: the
-//                                down projection of long reductions
+//                                rest of at most 128 rows, both heights in one launch; the down projection of
+//                                long reductions cuts what does not fill a round along the reduction
 //   grouped_gemm256_dma          BM = 256, k-steps of 32 (reduction not a multiple of 64, offsets beyond
 //                                32 bits, or a device that is not the full part)
 //   grouped_gemm_bf16_kernel     BM = 128, 4 waves, register-staged double buffer, for groups too small
@@ -419,32 +418,54 @@ constexpr int P_PART = 256 * 64;                       // bf16 elements per part
 #define BM_WAIT_VM_LGKM(vm, lgkm) \
     __builtin_amdgcn_s_waitcnt(((vm) & 15) | (7 << 4) | ((lgkm) << 8) | (((vm) >> 4) << 14))
 
-// The tail of the persistent schedule.  An XCD's workgroups (stride of them) take its tiles round by
-// round; when the last round is not full its `rem` tiles would keep rem workgroups busy for a whole tile
-// time while the others idle.  For the down projection (long reduction, few rounds) each of those tiles
-// is instead cut along the reduction into S = stride / rem chunks, one per workgroup; the chunks leave
-// fp32 partial tiles in scratch memory and splitk_fixup_kernel adds them in chunk order.
-struct TailSplit {
-    int full;     // tiles of this XCD done in complete rounds
-    int rem;      // tiles left for the last, partial round
-    int S;        // chunks per tail tile (1: not split)
-};
-__device__ __forceinline__ TailSplit tail_split(int total, int per_xcd, int xcd, int stride, int KT, bool allowed) {
-    TailSplit t;
-    const int valid = max(0, min(per_xcd, total - xcd * per_xcd));
-    t.full = valid / stride * stride;
-    t.rem = valid - t.full;
-    t.S = 1;
-    // worth it only for long reductions: a chunk costs a 256 KB partial tile written and read back, which
-    // a tile of fewer than 64 k-steps does not take long enough to repay
-    if (allowed && t.rem > 0 && KT >= 64) {
-        t.S = min(stride / t.rem, 8);
-        while (t.S > 1 && KT / t.S < 16) --t.S;
-        if (t.S < 1) t.S = 1;
+// One XCD's share of a launch that runs both tile heights.  Its workgroups (stride of them) take its 256-row tiles round by
+// round, then its 128-row tiles (SmallTileDealer).  SPLIT: the 256-row tiles that do not fill a round (R of them) and the
+// 128-row tiles are cut along the reduction into S pieces each, so that the last round is short; the pieces
+// leave fp32 partial tiles in scratch memory and split_fixup_kernel adds them up.  All tiles are cut at the same places and
+// first pieces go out before second ones, because workgroups that run together share panels in the XCD's L2 only
+// while they are at the same k: pieces of equal cost laid end to end (every workgroup at a k of its own)
+// fetch 64 KB a k-step from outside the XCD, 2.4 us at the 28 GB/s that a unit gets there.
+constexpr int SPLIT_COST = 160, SPLIT_COST_PART = 40;   // of partial tiles and their sums, in twentieths of a 256-row k-step
+constexpr int SPLIT_MAX = 8;                           // most pieces of a tile
+constexpr int SPLIT_TILE_FLOATS = 256 * 256;           // a partial 256-row tile; a 128-row tile takes half
+constexpr int SPLIT_XCD_TILES = K64_CUS / K64_XCDS;    // partial 256-row tiles that an XCD has scratch for
+struct XcdWork {
+    int big0, small0;    // first 256-row and 128-row tile of this XCD
+    int nb, ns;          // number of either
+    int full;            // 256-row tiles that are not cut
+    int S;               // pieces of the others and of the 128-row tiles
+    __device__ __forceinline__ void init(int total_big, int total_small, int KT, int xcd, int stride, bool split) {
+        big0 = total_big * xcd / K64_XCDS; nb = total_big * (xcd + 1) / K64_XCDS - big0;
+        small0 = total_small * xcd / K64_XCDS; ns = total_small * (xcd + 1) / K64_XCDS - small0;
+        full = nb;
+        S = 1;
+        if (split) cut(choose(KT, stride), stride);
     }
-    return t;
-}
-constexpr int SPLIT_TILE_FLOATS = 256 * 256;
+    __device__ __forceinline__ void cut(int pieces, int stride) {
+        S = pieces;
+        full = S > 1 ? nb / stride * stride : nb;
+    }
+    __device__ __forceinline__ int choose(int KT, int stride) const {
+        const int R = nb % stride;
+        int S = 1;
+        int best = 1 << 30;
+        for (int s = 1; s <= SPLIT_MAX && KT / s >= 16 && R * s + (ns * s + 1) / 2 <= SPLIT_XCD_TILES; ++s) {
+            // load of the lighter and the heavier workgroups once the pieces are dealt out; a k-step of 256 rows counts 20, of 128 rows 13
+            const int n = R * s, h = n % stride, l = stride - h;
+            int light = n / stride * 20, heavy = light + (h ? 20 : 0);
+            for (int left = ns * s; left > 0;) {
+                if (h == 0 || light <= heavy) { light += 13; left -= l; }
+                else { heavy += 13; left -= h; }
+            }
+            const int t = max(light, heavy) * (KT / s) + (s > 1 ? SPLIT_COST + SPLIT_COST_PART * s : 0);
+            if (t < best) { best = t; S = s; }
+        }
+        return S;
+    }
+};
+
+// number of 128-row tiles: none where the plain table lists every tile
+__device__ __forceinline__ int small_tiles(const GemmParams &p) { return p.mixed ? p.n_mtiles_s[0] : 0; }
 
 // table[idx] for a wave-uniform idx through the scalar cache.  Written out by hand because the compiler
 // uses scalar loads only for memory it can prove unwritten since the kernel began; behind the first
@@ -458,27 +479,43 @@ __device__ __forceinline__ int scalar_load_i32(const int32_t *table, int idx) {
     return v;
 }
 
-// SPLIT: compile the reduction-split tail in (kept out of the other instantiations: its write-out of raw
-// accumulators costs registers that short tiles cannot afford to spill around)
-// MI: 16-row blocks per wave.  MI = 8 is the 256-row tile described above; MI = 4 is a 128-row tile on the
-// same ring (the activation part fills half of its slot: four loads per wave and k-step instead of eight,
-// 32 MFMAs per k slice instead of 64, the weight part unchanged), for layers whose groups are mostly
-// smaller than a 256-row tile.
-//
-// PHASE: 0 - every row tile of the table has the height of this instantiation.  1 and 2 - one launch runs
-// both heights (grouped_gemm_mixed_k64w_bf16_kernel): a group's rows are cut into 256-row tiles, and a rest
-// of at most 128 rows becomes a 128-row tile; every workgroup first takes its share of the 256-row tiles
-// (phase 1, the plain persistent order), then its share of the 128-row tiles (phase 2), which are dealt out
-// so that the workgroups that got one 256-row tile fewer catch up first (next_small_tile).
+// The two tile loops of a launch (grouped_gemm_mixed_k64w_bf16_kernel): a group's rows are cut into 256-row tiles
+// (k64w_body), and a rest of at most 128 rows becomes a 128-row tile (k64s_body).  A workgroup takes its share of the
+// 256-row tiles, the plain persistent order, and its share of the 128-row tiles, which are dealt out so that the
+// workgroups that got one 256-row tile fewer catch up first (SmallTileDealer).  SPLIT: cut tiles are compiled in.
 __shared__ __attribute__((aligned(1024))) uint16_t k64w_smem[5 * P_PART];        // 160 KB: the whole LDS
 
-template <bool DUAL, bool SPLIT, int MI, int PHASE>
-__device__ __forceinline__ void k64w_body(const GemmParams &p) {
+// A piece of a cut tile is done: the wave leaves its fp32 accumulators in scratch memory for split_fixup_kernel
+// (accumulator tile by accumulator tile, 16 bytes a lane; blocks of dead rows are left out).  Read one
+// accumulator tile at a time, by hand: copies of all of them in vector registers spill.
+// Scratch of piece c of the cut tile t of an XCD, 256-row tiles first.
+__device__ __forceinline__ float *partial_tile(float *splitk, const XcdWork &x, int xcd, int t, int c) {
+    const int R = x.nb - x.full;
+    return splitk + (size_t)xcd * (SPLIT_XCD_TILES * SPLIT_TILE_FLOATS) +
+           (t < R ? (size_t)(t * x.S + c) * SPLIT_TILE_FLOATS : (size_t)(2 * R * x.S + (t - R) * x.S + c) * (SPLIT_TILE_FLOATS / 2));
+}
+template <int RB, int CB>
+__device__ __forceinline__ void store_partial(float *dst, const f32x4 (&acc)[RB][CB], int wave_row0, int row_end) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        if (wave_row0 + i * 16 >= row_end) continue;
+#pragma unroll
+        for (int j = 0; j < CB; ++j)
+        {
+            f32x4 x;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x[v]) : "a"(acc[i][j][v]));
+            *(BM_GLOBAL f32x4 *)(dst + (i * CB + j) * 256 + lane * 4) = x;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+template <bool DUAL, bool SPLIT>
+__device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &work) {
     uint16_t *const smem = k64w_smem;
-    static_assert(MI == 8 || MI == 4, "tile height is 256 or 128 rows");
-    static_assert(PHASE == 0 || (!SPLIT && MI == (PHASE == 1 ? 8 : 4)), "mixed heights: 256-row tiles first, then 128-row tiles");
-    static_assert(!SPLIT || MI == 8, "the reduction-split tail exists for 256-row tiles only");
-    constexpr int TM = MI * 32;                            // rows per tile
+    constexpr int MI = 8;                                  // 16-row blocks per wave
     constexpr int NM = MI * 8;                             // MFMAs per k slice of 32
     constexpr int NR = MI + 8;                             // fragment reads per k slice
     const int tid = threadIdx.x, lane = tid & 63;
@@ -492,48 +529,32 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
     // logical tiles with stride (workgroups per XCD), so the workgroups that run together on an XCD work
     // on consecutive logical tiles (see tile_of) and a workgroup keeps its compute unit: the next tile's
     // first loads fly while the finished tile is written out, and nothing is relaunched.
-    const int32_t *const mt_group = PHASE == 2 ? p.mt_group_s : p.mt_group;
-    const int32_t *const mt_row0 = PHASE == 2 ? p.mt_row0_s : p.mt_row0;
-    const int n_mt = PHASE == 2 ? p.n_mtiles_s[0] : p.n_mtiles[0];
+    const int n_mt = p.n_mtiles[0];
     const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
-    const int total = n_mt * n_nt;
-    const int per_xcd = (total + 7) >> 3;
     const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, slot = blockIdx.x >> 3;
     const int N = p.N, Kd = p.Kd;
     const int KT = Kd / 64;
-    const TailSplit ts = tail_split(total, per_xcd, xcd, stride, KT, SPLIT && p.splitk != nullptr);
-    SmallTileDealer dealer;
-    if (PHASE == 2) {
-        const int total_big = p.n_mtiles[0] * n_nt, per_xcd_big = (total_big + 7) >> 3;
-        dealer.init(max(0, min(per_xcd_big, total_big - xcd * per_xcd_big)), max(0, min(per_xcd, total - xcd * per_xcd)),
-                    stride, slot);
-    }
-    int idx = slot;                                    // next tile of the complete rounds
-    bool tail_pending = ts.rem > 0;
+    // Gate/up: the reduction is walked as a circle that each XCD enters elsewhere (see k64s_body); inside an XCD the
+    // workgroups stay in step, because they share panels.  The down projection of few column tiles shares panels between
+    // XCDs as well (Mixtral-shaped, 1024 tokens: 336 us in step, 345 not).
+    const int rot = DUAL ? xcd * KT >> 3 : 0;
+    auto rotated = [&](int k) { const int r = k + rot; return r >= KT ? r - KT : r; };
+    const int R = work.nb - work.full;                 // tiles that are cut
+    const int n_items = work.full + R * work.S;
+    int idx = slot;                                    // next item of this workgroup
     int kbeg = 0, kend = KT;                           // k-steps of the item whose loads are being issued
-    bool partial = false;                              // that item is a chunk of a split tile
     int item_tile = 0;
-// next work item of this workgroup -> item_tile, kbeg, kend, partial; false when there is none
+// next work item of this workgroup -> item_tile, kbeg, kend; false when there is none
 #define BM_NEXT_ITEM(ok_)                                                                          \
     {                                                                                              \
-        ok_ = false;                                                                               \
-        if (PHASE == 2) {                                                                          \
-            ok_ = dealer.next(item_tile);                                                          \
-            kbeg = 0; kend = KT; partial = false;                                                  \
-        } else if (idx < ts.full) {                                                                       \
-            item_tile = idx; kbeg = 0; kend = KT; partial = false; idx += stride; ok_ = true;      \
-        } else if (tail_pending) {                                                                 \
-            tail_pending = false;                                                                  \
-            if (ts.S >= 2) {                                                                       \
-                if (slot < ts.rem * ts.S) {                                                        \
-                    const int c_ = slot % ts.S;                                                    \
-                    item_tile = ts.full + slot / ts.S;                                             \
-                    kbeg = c_ * KT / ts.S; kend = (c_ + 1) * KT / ts.S; partial = true; ok_ = true; \
-                }                                                                                  \
-            } else if (slot < ts.rem) {                                                            \
-                item_tile = ts.full + slot; kbeg = 0; kend = KT; partial = false; ok_ = true;      \
-            }                                                                                      \
+        ok_ = idx < n_items;                                                                       \
+        item_tile = idx; kbeg = 0; kend = KT;                                                      \
+        if (SPLIT && ok_ && idx >= work.full && work.S > 1) {                                      \
+            const int c_ = (idx - work.full) / R;                                                  \
+            item_tile = idx - c_ * R;                                                              \
+            kbeg = c_ * KT / work.S; kend = (c_ + 1) * KT / work.S;                                \
         }                                                                                          \
+        idx += stride;                                                                             \
     }
     bool have;
     BM_NEXT_ITEM(have);
@@ -559,8 +580,9 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
     int row0, row_end, n0;                             // of the tile whose loads are being issued
     int g_n, row0_n, row_end_n, n0_n;                  // of the tile looked up last (BM_LOOKUP)
                                                        // (the source rows of its activation loads: in v255)
-    bool n_more = false, n_partial = false;            // the item the loads move on to next, found a k-step
+    bool n_more = false;                               // the item the loads move on to next, found a k-step
     int n_kbeg = 0, n_kend = 0;                        // before they do
+    int load_tile;                                     // the tile whose loads are being issued (XCD's own number)
 
 // Load instruction j of a wave fills the 1 KB block (4*j + wave) of a part: 8 tile rows of 128 bytes.  Lane i
 // supplies row 8*block + i/8 and LDS slot i%8 of it, i.e. global piece (i % 8) ^ ((row >> 1) & 7).
@@ -586,8 +608,8 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
     {                                                                                              \
         int mt_, nt_;                                                                              \
         tile_of((lid_), n_mt, n_nt, mt_, nt_);                                                     \
-        g_n = scalar_load_i32(mt_group, mt_);                                                      \
-        row0_n = scalar_load_i32(mt_row0, mt_);                                                    \
+        g_n = scalar_load_i32(p.mt_group, mt_);                                                     \
+        row0_n = scalar_load_i32(p.mt_row0, mt_);                                                   \
         row_end_n = scalar_load_i32(p.offsets, g_n + 1);                                           \
         n0_n = __builtin_amdgcn_readfirstlane(nt_) * (DUAL ? 128 : 256);                           \
         int lane_ = lane;                                                                          \
@@ -627,7 +649,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
 // load j_ of the activation part (A) / weight part (B) of k-step tile_ into slot_
 #define BM_DMA_AT(base_, off_, slot_, tile_, j_)                                                   \
     __builtin_amdgcn_global_load_lds(                                                              \
-        (const BM_GLOBAL void *)(reinterpret_cast<const char *>((base_) + min((tile_), kend - 1) * 64) + (off_)), \
+        (const BM_GLOBAL void *)(reinterpret_cast<const char *>((base_) + rotated(min((tile_), kend - 1)) * 64) + (off_)), \
         (BM_LDS void *)(smem + (slot_) * P_PART + wave * 512 + (j_) * 2048), 16, 0, 0)
 #define BM_DMA_A(slot_, tile_, j_) BM_DMA_AT(a, oa[j_], slot_, tile_, j_)
 #define BM_DMA_B(slot_, tile_, j_) BM_DMA_AT(((j_) < 4 ? base_b0 : base_b1), ob[j_], slot_, tile_, j_)
@@ -685,7 +707,8 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
                 : "+a"(acc[(m_) >> 3][(m_) & 7]) : "v"(fb_[(m_) & 7]), "v"(fa_[(m_) >> 3]));       \
     }
 
-    BM_LOOKUP(xcd * per_xcd + item_tile);
+    BM_LOOKUP(work.big0 + item_tile);
+    load_tile = item_tile;
     BM_WAIT_VM_LGKM(0, 0);                             // the row_map load, which the compiler does not wait for
     BM_ADOPT();
     BM_PROLOGUE();
@@ -698,7 +721,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
     BM_WAIT_VMCNT(8 + MI);
     for (;;) {
         const int t_row0 = row0, t_row_end = row_end, t_n0 = n0;    // the tile being multiplied
-        const bool t_partial = partial;
+        const int t_tile = load_tile;
         const int t_kbeg = kbeg, t_kend = kend;
         bool more = false;                             // the loads have moved on to a next item (uniform)
         // One tile: accumulators cleared, then the k-steps.  Written as a macro so that the down projection
@@ -772,16 +795,15 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
             if (kt == t_kend - 3) {                                                                                   \
                 more = n_more;                                                                                        \
                 if (more) {                                                                                           \
-                    kbeg = n_kbeg; kend = n_kend; partial = n_partial;                                                \
+                    kbeg = n_kbeg; kend = n_kend; load_tile = item_tile;                                               \
                     BM_ADOPT();                                                                                       \
                 }                                                                                                     \
             } else if (kt == t_kend - 4) {    /* every item has at least 4 k-steps */                                  \
                 const int kb_ = kbeg, ke_ = kend;                                                                     \
-                const bool pa_ = partial;                                                                             \
                 BM_NEXT_ITEM(n_more);                                                                                 \
-                n_kbeg = kbeg; n_kend = kend; n_partial = partial;                                                    \
-                kbeg = kb_; kend = ke_; partial = pa_;                                                                \
-                if (n_more) BM_LOOKUP(xcd * per_xcd + item_tile);                                                     \
+                n_kbeg = kbeg; n_kend = kend;                                                                         \
+                kbeg = kb_; kend = ke_;                                                                               \
+                if (n_more) BM_LOOKUP(work.big0 + item_tile);                                                         \
             }                                                                                                         \
         }                                                                                                             \
     }
@@ -798,27 +820,18 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
         // The tile is done.  The slot A(last k-step) sat in is free for every wave since the barrier in
         // the middle of that k-step; it stages the write-out while the next tile's loads land elsewhere.
 
-        if (!live) {                                   // nothing but padding rows: nothing to write
+        const bool t_partial = SPLIT && t_kend - t_kbeg < KT;
+        if (!live && !t_partial) {                     // nothing but padding rows: nothing to write
             if (!more) break;
             continue;
         }
         // last MFMA of the tile -> first read of an accumulator (see BM_MFMA1): acc[MI - 1][7] is the last MFMA's
         // accumulator, every other one is at least one MFMA (16 cycles) older
         asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[MI - 1][7]));
-        if (SPLIT && t_partial) {
-            // chunk of a split tile: the fp32 accumulators go to this workgroup's scratch tile as they are
-            // (accumulator tile, lane: 16-byte stores, contiguous over the lanes)
-            // (the address advances store by store behind an optimisation barrier: 64 addresses computed
-            // up front cost registers, and the spills land in the main loop)
-            float *dst = p.splitk + (size_t)(xcd * stride + slot) * SPLIT_TILE_FLOATS + wave * (64 * 256) + lane * 4;
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    *(BM_GLOBAL f32x4 *)dst = acc[i][j];
-                    dst += 256;
-                    asm volatile("" : "+v"(dst));
-                }
+        if (t_partial) {
+            if (live)
+                store_partial<MI, 8>(partial_tile(p.splitk, work, xcd, t_tile - work.full, (t_kbeg * work.S + KT - 1) / KT) + wave * (MI * 8 * 256), acc,
+                                     t_row0 + wm * (MI * 16), t_row_end);
             if (!more) break;
             continue;
         }
@@ -926,78 +939,362 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p) {
 #undef BM_MFMA1
 }
 
-template <bool DUAL, bool SPLIT, int MI = 8>
-__global__ void __launch_bounds__(256) grouped_gemm256_k64w_bf16_kernel(GemmParams p) {
-    k64w_body<DUAL, SPLIT, MI, 0>(p);
+// ---------------------------------------------------------------------------
+// 128 x 256 tile, the only user of its weight panel: bound by streaming that panel from memory.
+//   Stages: a k-step is 48 KB (weight rows, then activation rows) and LDS holds three of them; the loads of
+//   k-step kt + 3 go out in the second half of k-step kt, once its fragments are in registers, and are waited for
+//   in the middle of k-step kt + 2: 24 loads (24 KB) a wave in flight, twice what the 256-row ring leaves them.
+//   Waves: each owns 64 weight rows and all 128 activation rows, so a weight fragment is read from LDS once.
+//   Streaming: the weights are loaded non-temporally (they are not read again, and would push activations and
+//   router matrix out of the L2: Qwen3-shaped layer at 512 tokens, gate/up 85 -> 79 us, the next front kernel 19.4 -> 15.6),
+//   and the tiles of an XCD enter the reduction at 32 different places and walk it as a circle: weight rows lie a
+//   multiple of 4 KB apart in many layers, and workgroups in step all ask the same memory channels (256 units reading
+//   panels of 256 rows of 4 / 8 KB: 4.2 TB/s in step, 5.9 / 6.1 TB/s from 32 places, 6.5 / 6.7 non-temporally too; 1.5 KB
+//   rows 4.6 -> 5.5, 28 KB rows 6.0 -> 7.0).  What an XCD misses in its L2 comes at 7 TB/s for the whole chip, from the
+//   memory-side cache as well.
+// Kernel times, 128-row tiles on the 256-row ring | here, us: Mixtral-shaped 256 tokens gate/up 292 | 250, Qwen3-shaped 512
+// tokens 88 | 79 and 52 | 52, 2048 tokens 150 | 137, DeepSeek-shaped 128 tokens 53 | 46 and 36 | 33.
+// Hazards around the assembly MFMA as in k64w_body.
+// ---------------------------------------------------------------------------
+constexpr int DMA_STREAM = 2;                              // cache policy of a load that is not read again (nt)
+
+template <bool DUAL, bool SPLIT>
+__device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &work) {
+    constexpr int RB = 8;                                  // 16-row blocks of the tile
+    uint16_t *const smem = k64w_smem;
+    constexpr int NJ = 4;                                  // 16-column weight blocks per wave (DUAL: two of each matrix)
+    constexpr int NA = RB / 2;                             // activation loads per wave and k-step
+    constexpr int NL = NA + 8;                             // loads per wave and k-step
+    constexpr int STAGE = (256 + RB * 16) * 64;            // bf16 elements of a stage: weight rows, then activation rows
+    constexpr int NS = 3;                                  // stages
+    constexpr int NM = RB * NJ;                            // MFMAs per k slice of 32
+    constexpr int NR = RB + NJ;                            // fragment reads per k slice
+    static_assert(NS * STAGE + 4 * 1024 * 2 <= 5 * P_PART, "the stages leave 4 KB per wave for the write-out");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, quad = lane >> 4;
+    const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
+    const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, slot = blockIdx.x >> 3;
+    const int N = p.N, Kd = p.Kd;
+    const int KT = Kd / 64;
+    int rot = 0, rot_n = 0;                                // where the tile whose loads are being issued enters the reduction
+    auto rotated = [&](int k) { const int r = k + rot; return r >= KT ? r - KT : r; };
+    SmallTileDealer dealer;
+    dealer.init((work.nb - work.full) * work.S + work.full, work.ns * work.S, stride, slot);
+    int item = 0, kbeg = 0, kend = KT;
+#define BM_NEXT_ITEM(ok_, kb_, ke_)                                                                \
+    {                                                                                              \
+        kb_ = 0; ke_ = KT;                                                                         \
+        ok_ = dealer.next(item);                                                                   \
+        if (SPLIT && ok_ && work.S > 1) {                                                          \
+            const int c_ = item / work.ns;                                                         \
+            item -= c_ * work.ns;                                                                  \
+            kb_ = c_ * KT / work.S; ke_ = (c_ + 1) * KT / work.S;                                  \
+        }                                                                                          \
+    }
+    bool n_more;
+    BM_NEXT_ITEM(n_more, kbeg, kend);
+    if (!n_more) return;
+    const uint16_t *a = static_cast<const uint16_t *>(p.a);
+    uint16_t *c = static_cast<uint16_t *>(p.c);
+    int fa_off[2], fb_off[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int pc = ((4 * s + quad) ^ ((r16 >> 1) & 7)) << 3;
+        fa_off[s] = 256 * 64 + r16 * 64 + pc;
+        fb_off[s] = (DUAL ? (wave * 32 + r16) : (wave * 64 + r16)) * 64 + pc;
+    }
+    f32x4 acc[RB][NJ];
+    bf16x8 f0a[RB], f0b[NJ], f1a[RB], f1b[NJ];
+    uint32_t oa[NA], ob[8];
+    const uint16_t *base_b0, *base_b1;
+    int row0, row_end, n0;
+    int g_n, row0_n, row_end_n, n0_n;
+#define BM_LOOKUP(lid_)                                                                            \
+    {                                                                                              \
+        const int id_ = __builtin_amdgcn_readfirstlane(lid_);                                      \
+        const int mt_ = id_ / n_nt;                                                                \
+        g_n = scalar_load_i32(p.mt_group_s, mt_);                                                  \
+        row0_n = scalar_load_i32(p.mt_row0_s, mt_);                                                \
+        row_end_n = scalar_load_i32(p.offsets, g_n + 1);                                           \
+        n0_n = (id_ - mt_ * n_nt) * (DUAL ? 128 : 256);                                            \
+        rot_n = (((id_ - work.small0) * 5) & 31) * KT >> 5;                                        \
+        int lane_ = lane;                                                                          \
+        asm volatile("" : "+v"(lane_));                                                            \
+        const int r_ = 8 * (4 * (lane_ >> 3) + wave) + (lane_ & 7);                                \
+        const int pos_ = min(row0_n + r_, row_end_n - 1);                                          \
+        if (p.row_map)                                                                             \
+            asm volatile("global_load_dword v255, %0, %1" : : "v"(pos_ * 4), "s"(p.row_map) : "v255", "memory"); \
+        else                                                                                       \
+            asm volatile("v_mov_b32 v255, %0" : : "v"(pos_) : "v255");                             \
+    }
+#define BM_ADOPT()                                                                                 \
+    {                                                                                              \
+        row0 = row0_n; row_end = row_end_n; n0 = n0_n; rot = rot_n;                                \
+        if (g_n < p.E) {                                                                           \
+            base_b0 = static_cast<const uint16_t *>(p.b0) + (size_t)g_n * N * Kd;                  \
+            base_b1 = DUAL ? static_cast<const uint16_t *>(p.b1) + (size_t)g_n * N * Kd : base_b0; \
+        } else {                                                                                   \
+            base_b0 = static_cast<const uint16_t *>(p.sb0) + (size_t)(g_n - p.E) * N * Kd;         \
+            base_b1 = DUAL ? static_cast<const uint16_t *>(p.sb1) + (size_t)(g_n - p.E) * N * Kd : base_b0; \
+        }                                                                                          \
+        int lane_ = lane, rmv_;                                                                    \
+        asm volatile("" : "+v"(lane_));                                                            \
+        asm volatile("v_mov_b32 %0, v255" : "=v"(rmv_));                                           \
+        _Pragma("unroll") for (int j = 0; j < 8; ++j) {                                            \
+            const int r_ = 8 * (4 * j + wave) + (lane_ >> 3);                                      \
+            const int piece_ = (lane_ & 7) ^ ((r_ >> 1) & 7);                                      \
+            if (j < NA) {                                                                          \
+                const int src_ = __builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane_ >> 3)), rmv_);   \
+                oa[j] = ((uint32_t)src_ * (uint32_t)Kd + piece_ * 8) * 2u;                         \
+            }                                                                                      \
+            const int n_ = DUAL ? min(n0 + (r_ & 127), N - 1) : min(n0 + r_, N - 1);               \
+            ob[j] = ((uint32_t)n_ * (uint32_t)Kd + piece_ * 8) * 2u;                               \
+        }                                                                                          \
+    }
+#define BM_DMA_AT(base_, off_, dst_, tile_, aux_)                                                  \
+    __builtin_amdgcn_global_load_lds(                                                              \
+        (const BM_GLOBAL void *)(reinterpret_cast<const char *>((base_) + rotated(min((tile_), kend - 1)) * 64) + (off_)), \
+        (BM_LDS void *)(smem + (dst_) + wave * 512), 16, 0, aux_)
+// load j_ of NL of k-step tile_ into stage st_: the weight rows first
+#define BM_DMA(st_, tile_, j_)                                                                     \
+    {                                                                                              \
+        if ((j_) < 8) BM_DMA_AT(((j_) < 4 ? base_b0 : base_b1), ob[(j_) & 7], (st_) * STAGE + (j_) * 2048, tile_, DMA_STREAM); \
+        else BM_DMA_AT(a, oa[((j_) - 8) % NA], (st_) * STAGE + 256 * 64 + ((j_) - 8) * 2048, tile_, 0); \
+    }
+#define BM_LD(ptr_) as_bf16x8(*reinterpret_cast<const u32x4 *>(ptr_))
+#define BM_BOFF(j_) (DUAL ? (((j_) >> 1) * 8192 + ((j_) & 1) * 1024) : (j_) * 1024)
+// fragment read d_ of NR, in the order the MFMAs need them: a0 b0..b3 a1..
+#define BM_RD(d_, fa_, fb_, st_, s_)                                                               \
+    {                                                                                              \
+        const uint16_t *sp_ = smem + (st_) * STAGE;                                                \
+        if ((d_) == 0) fa_[0] = BM_LD(sp_ + fa_off[s_]);                                           \
+        else if ((d_) <= NJ) fb_[((d_) - 1) % NJ] = BM_LD(sp_ + fb_off[s_] + BM_BOFF((d_) - 1));   \
+        else fa_[((d_) - NJ) % RB] = BM_LD(sp_ + fa_off[s_] + ((d_) - NJ) * 1024);                 \
+    }
+#define BM_MFMA1(m_, fa_, fb_)                                                                     \
+    {                                                                                              \
+        if (DUAL)                                                                                  \
+            asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"                                          \
+                : "+a"(acc[(m_) / NJ][(m_) % NJ]) : "v"(fa_[(m_) / NJ]), "v"(fb_[(m_) % NJ]));     \
+        else                                                                                       \
+            asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"                                          \
+                : "+a"(acc[(m_) / NJ][(m_) % NJ]) : "v"(fb_[(m_) % NJ]), "v"(fa_[(m_) / NJ]));     \
+    }
+
+    BM_LOOKUP(work.small0 + item);
+    int load_item = item;
+    BM_WAIT_VM_LGKM(0, 0);
+    BM_ADOPT();
+#pragma unroll
+    for (int t = 0; t < NS; ++t)
+#pragma unroll
+        for (int j = 0; j < NL; ++j) BM_DMA(t, kbeg + t, j)
+    int st = 0;                                        // stage of k-step kt
+    BM_WAIT_VMCNT(NL * (NS - 1));
+    for (;;) {
+        const int t_row0 = row0, t_row_end = row_end, t_n0 = n0, t_tile = load_item;    // the tile being multiplied
+        const int t_kbeg = kbeg, t_kend = kend;
+        int n_kbeg, n_kend;
+        BM_NEXT_ITEM(n_more, n_kbeg, n_kend);
+        if (n_more) BM_LOOKUP(work.small0 + item);
+        bool more = false;
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
+        asm volatile("s_nop 7" : "+a"(acc[0][0]));
+        BM_BARE_BARRIER();
+#pragma unroll
+        for (int d = 0; d < NR; ++d) BM_RD(d, f0a, f0b, st, 0)
+        for (int kt = t_kbeg; kt < t_kend; ++kt) {
+            const int kl = more ? kbeg + (kt + NS - t_kend) : kt + NS;
+            const int stn = st == NS - 1 ? 0 : st + 1;
+            BM_WAIT_VM_LGKM(63, 0);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                BM_MFMA1(m, f0a, f0b);
+                if (m < 2 * NR && (m & 1) == 0) BM_RD(m >> 1, f1a, f1b, st, 1)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            BM_WAIT_VM_LGKM(NL * (NS - 2), 0);
+            BM_BARE_BARRIER();
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                BM_MFMA1(m, f1a, f1b);
+                if (m * NL / NM != (m + 1) * NL / NM) BM_DMA(st, kl, m * NL / NM)
+                if (m < 2 * NR && (m & 1) == 0) BM_RD(m >> 1, f0a, f0b, stn, 0)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            st = stn;
+            if (kt == t_kend - NS - 1) {
+                more = n_more;
+                if (more) {
+                    if (t_kend - t_kbeg < 2 * NS - 1) BM_WAIT_VM_LGKM(0, 0);
+                    kbeg = n_kbeg; kend = n_kend; load_item = item;
+                    BM_ADOPT();
+                }
+            }
+        }
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[RB - 1][NJ - 1]));
+        if (SPLIT && t_kend - t_kbeg < KT) {
+            store_partial<RB, NJ>(partial_tile(p.splitk, work, xcd, work.nb - work.full + t_tile, (t_kbeg * work.S + KT - 1) / KT) +
+                                      wave * (RB * NJ * 256), acc, t_row0, t_row_end);
+            if (!more) break;
+            continue;
+        }
+        if (DUAL) {
+            constexpr int SD = 20;
+            uint32_t *stage = reinterpret_cast<uint32_t *>(smem + NS * STAGE) + wave * 1024;
+            int lane_w = lane;
+            asm volatile("" : "+v"(lane_w));
+            const int r16 = lane_w & 15, quad = lane_w >> 4;
+            const bool odd = lane_w & 1;
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                    for (int v = 0; v < 4; v += 2) {
+                        float g0, g1, u0, u1;
+                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(g0) : "a"(acc[i][j][v]));
+                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(g1) : "a"(acc[i][j][v + 1]));
+                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u0) : "a"(acc[i][2 + j][v]));
+                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u1) : "a"(acc[i][2 + j][v + 1]));
+                        const float x0 = silu(g0) * u0;
+                        const float x1 = silu(g1) * u1;
+                        const float send = odd ? x0 : x1;
+                        const float recv = __builtin_bit_cast(
+                            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, true));
+                        const uint32_t pk = odd ? pack_bf16x2(recv, x1) : pack_bf16x2(x0, recv);
+                        const int lrow = 4 * quad + v + (odd ? 1 : 0);
+                        stage[lrow * SD + j * 8 + (r16 >> 1)] = pk;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const int lrow = lane_w >> 2, pc = lane_w & 3;
+                const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
+                const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * 32 + pc * 8;
+                if (row < t_row_end && col < N) stg128(&c[(size_t)row * N + col], val);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            constexpr int SD = 36;
+            uint32_t *stage = reinterpret_cast<uint32_t *>(smem + NS * STAGE) + wave * 1024;
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    float x[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) x[v] = acc[i][j][v];
+                    u32x2 pk;
+                    pk[0] = pack_bf16x2(x[0], x[1]);
+                    pk[1] = pack_bf16x2(x[2], x[3]);
+                    *reinterpret_cast<u32x2 *>(stage + r16 * SD + j * 8 + 2 * quad) = pk;
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int q = lane + 64 * t;
+                    const int lrow = q >> 3, pc = q & 7;
+                    const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
+                    const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * 64 + pc * 8;
+                    if (row < t_row_end && col < N) stg128(&c[(size_t)row * N + col], val);
+                }
+            }
+        }
+        if (!more) break;
+    }
+    BM_WAIT_VM_LGKM(0, 0);
+#undef BM_LOOKUP
+#undef BM_NEXT_ITEM
+#undef BM_ADOPT
+#undef BM_DMA_AT
+#undef BM_DMA
+#undef BM_LD
+#undef BM_BOFF
+#undef BM_RD
+#undef BM_MFMA1
 }
 
-// Both tile heights in one launch (see k64w_body): p.mt_group / mt_row0 / n_mtiles list the 256-row tiles,
-// p.mt_group_s / mt_row0_s / n_mtiles_s the 128-row tiles.
-template <bool DUAL>
+// Both tile heights in one launch: p.mt_group / mt_row0 / n_mtiles list the 256-row tiles, p.mt_group_s / mt_row0_s /
+// n_mtiles_s the 128-row tiles.
+template <bool DUAL, bool SPLIT>
 __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmParams p) {
+    const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
+    XcdWork work;
+    work.init(p.n_mtiles[0] * n_nt, small_tiles(p) * n_nt, p.Kd / 64, blockIdx.x & 7, gridDim.x >> 3, SPLIT);
+    if (SPLIT && blockIdx.x < K64_XCDS && threadIdx.x == 0) p.split_pieces[blockIdx.x] = work.S;
     // A 128-row tile is the only user of its weight panel (a group has at most one), so it streams from
     // memory at a third of a 256-row tile's arithmetic intensity.  When there are many of them (at least a
     // quarter of the 256-row tiles' number) every other workgroup takes its 128-row tiles first, so that the
     // streaming is spread over the launch instead of bunched at its end (Qwen3-shaped layer, 2048 tokens:
     // gate/up 141 -> 133 us); with few of them that order only delays 256-row tiles (Mixtral-shaped prefill
     // + 1 %, 1024 tokens + 3 %).
-    const bool small_first = p.n_mtiles_s[0] * 4 >= p.n_mtiles[0] && ((blockIdx.x >> 3) & 1);
+    const bool small_first = small_tiles(p) * 4 >= p.n_mtiles[0] && ((blockIdx.x >> 3) & 1);
     if (small_first) {
-        k64w_body<DUAL, false, 4, 2>(p);
+        k64s_body<DUAL, SPLIT>(p, work);
         __syncthreads();      // the last write-out's staging area becomes the next phase's first load target
-        k64w_body<DUAL, false, 8, 1>(p);
+        k64w_body<DUAL, SPLIT>(p, work);
     } else {
-        k64w_body<DUAL, false, 8, 1>(p);
+        k64w_body<DUAL, SPLIT>(p, work);
         __syncthreads();
-        k64w_body<DUAL, false, 4, 2>(p);
+        k64s_body<DUAL, SPLIT>(p, work);
     }
 }
 
-// Adds the chunks of every split tail tile in chunk order and writes the bf16 result (see TailSplit).
-// Grid 8 XCDs x 16 slices of a tile x 16 tail tiles, the XCD fastest: workgroups are dealt round-robin to the XCDs, so
-// a tile's chunks are read where they were written and partly still sit in that XCD's L2.  A workgroup handles one
-// sixteenth of a tile - the accumulator tiles (i, j) with i * 8 + j in [4 * slice, 4 * slice + 4) - with the chunk
-// writers' thread -> element mapping, so that the reduction itself is spread over the chip.
-__global__ void __launch_bounds__(256) splitk_fixup_kernel(GemmParams p) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1, r16 = lane & 15, quad = lane >> 4;
-    const int n_mt = p.n_mtiles[0];
-    const int n_nt = (p.N + 255) / 256;
-    const int total = n_mt * n_nt;
-    const int per_xcd = (total + 7) >> 3;
-    const int xcd = blockIdx.x & 7, slice = (blockIdx.x >> 3) & 15, t = blockIdx.x >> 7, stride = p.splitk_stride;
-    const TailSplit ts = tail_split(total, per_xcd, xcd, stride, p.Kd / 64, true);
-    if (ts.S < 2 || t >= ts.rem) return;
+// Adds up the pieces of every cut tile of the down projection, in their order along the reduction, and writes the bf16 result.
+// Grid 8 XCDs x 16 slices of a tile x cut tiles, the XCD fastest: workgroups are dealt round-robin to the XCDs, so a
+// tile's pieces are read where they were written and partly still sit in that XCD's L2.  A workgroup handles one slice - four
+// accumulator tiles of each of the writers' waves - with the writers' thread -> element mapping, so that the sums are
+// spread over the chip.
+constexpr int FIXUP_TILES = 32;                        // most cut tiles of an XCD: 2 to 8 pieces each of at least 128 KB
+__global__ void __launch_bounds__(256) split_fixup_kernel(GemmParams p) {
+    const int xcd = blockIdx.x & 7, slice = (blockIdx.x >> 3) & 15, tile = blockIdx.x >> 7, stride = p.split_stride;
+    const int n_nt = (p.N + 255) / 256, n_mt = p.n_mtiles[0];
+    XcdWork work;
+    const int n = p.split_pieces[xcd];                     // S, as the workgroups of the launch before chose it
+    if (n == 1) return;
+    work.init(n_mt * n_nt, small_tiles(p) * n_nt, p.Kd / 64, xcd, stride, false);
+    work.cut(n, stride);
+    const int R = work.nb - work.full;
+    const bool big = tile < R;
+    if (tile >= R + work.ns || (!big && slice >= 8)) return;
     int mt, nt;
-    tile_of(xcd * per_xcd + ts.full + t, n_mt, n_nt, mt, nt);
-    const int g = p.mt_group[mt];
-    const int row0 = p.mt_row0[mt], row_end = p.offsets[g + 1], n0 = nt * 256, N = p.N;
-    uint16_t *c = static_cast<uint16_t *>(p.c);
-    const float *src = p.splitk + (size_t)(xcd * stride + t * ts.S) * SPLIT_TILE_FLOATS + wave * (64 * 256) + lane * 4;
-    // all loads of the workgroup's share go out before the first sum (S <= 8 chunks, tail_split): one
-    // round trip to memory instead of one per chunk
-    f32x4 part[4][8];
+    if (big) tile_of(work.big0 + work.full + tile, n_mt, n_nt, mt, nt);
+    else { mt = (work.small0 + tile - R) / n_nt; nt = (work.small0 + tile - R) % n_nt; }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, quad = lane >> 4;
+    const int g = big ? p.mt_group[mt] : p.mt_group_s[mt];
+    const int i = big ? slice >> 1 : slice;                // row block inside the wave's part of the tile
+    const int row0 = (big ? p.mt_row0[mt] + (wave >> 1) * 128 : p.mt_row0_s[mt]) + i * 16, row_end = p.offsets[g + 1], N = p.N;
+    if (row0 >= row_end) return;
+    const size_t ofs = (size_t)wave * (big ? 64 * 256 : 32 * 256) + (big ? i * 8 + (slice & 1) * 4 : i * 4) * 256 + lane * 4;
+    // all loads go out before the first sum: one round trip to memory instead of one per piece
+    f32x4 part[SPLIT_MAX][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int c = 0; c < SPLIT_MAX; ++c)
+        if (c < n) {
+            const float *src = partial_tile(p.splitk, work, xcd, tile, c) + ofs;
 #pragma unroll
-        for (int ch = 0; ch < 8; ++ch)
-            if (ch < ts.S)
-                part[q][ch] = *(const BM_GLOBAL f32x4 *)(src + (size_t)ch * SPLIT_TILE_FLOATS + (slice * 4 + q) * 256);
+            for (int q = 0; q < 4; ++q) part[c][q] = *(const BM_GLOBAL f32x4 *)(src + q * 256);
+        }
+    uint16_t *out = static_cast<uint16_t *>(p.c);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int ij = slice * 4 + q, i = ij >> 3, j = ij & 7;
-        f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+        f32x4 sum = part[0][q];
 #pragma unroll
-        for (int ch = 0; ch < 8; ++ch)
-            if (ch < ts.S) sum += part[q][ch];
+        for (int c = 1; c < SPLIT_MAX; ++c)
+            if (c < n) sum += part[c][q];
         // transposed accumulator tiles: the lane holds columns 4 * quad .. + 3 of row r16
-        const int n = n0 + wn * 128 + j * 16 + 4 * quad;
-        const int row = row0 + wm * 128 + i * 16 + r16;
-        if (row < row_end && n < N) {
+        const int col = nt * 256 + (big ? (wave & 1) * 128 + ((slice & 1) * 4 + q) * 16 : wave * 64 + q * 16) + 4 * quad;
+        const int row = row0 + r16;
+        if (row < row_end && col < N) {
             u32x2 pk;
             pk[0] = pack_bf16x2(sum[0], sum[1]);
             pk[1] = pack_bf16x2(sum[2], sum[3]);
-            *(BM_GLOBAL u32x2 *)(&c[(size_t)row * N + n]) = pk;
+            *(BM_GLOBAL u32x2 *)(&out[(size_t)row * N + col]) = pk;
         }
     }
 }
@@ -1042,7 +1339,7 @@ static bool k64_ok(const GemmParams &p) {
 
 int launch_gateup_bf16(const GemmParams &p, hipStream_t st) {
     if (p.mixed && k64_ok(p))
-        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<true>), dim3(persistent_grid(p, true)), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<true, false>), dim3(persistent_grid(p, true)), dim3(256), 0, st, p);
     else if (p.mixed)
         return -1;                // the caller asks for both tile heights only where the persistent kernel runs
     else if (p.BM == 256)
@@ -1056,15 +1353,15 @@ int launch_gateup_bf16(const GemmParams &p, hipStream_t st) {
 bool down_split_tail(int Kd) { return Kd / 64 >= 64; }
 
 int launch_down_bf16(const GemmParams &p, hipStream_t st) {
-    if (p.mixed && k64_ok(p)) {
-        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false>), dim3(persistent_grid(p, false)), dim3(256), 0, st, p);
+    if (p.BM == 256 && k64_ok(p) && p.splitk != nullptr && down_split_tail(p.Kd)) {
+        GemmParams q = p;
+        q.split_stride = K64_CUS / K64_XCDS;
+        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false, true>), dim3(K64_CUS), dim3(256), 0, st, q);
+        hipLaunchKernelGGL(split_fixup_kernel, dim3(K64_XCDS * 16 * FIXUP_TILES), dim3(256), 0, st, q);
+    } else if (p.mixed && k64_ok(p)) {
+        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false, false>), dim3(persistent_grid(p, false)), dim3(256), 0, st, p);
     } else if (p.mixed) {
         return -1;
-    } else if (p.BM == 256 && p.splitk != nullptr && down_split_tail(p.Kd) && k64_ok(p)) {
-        GemmParams q = p;
-        q.splitk_stride = persistent_grid(p, false) >> 3;
-        hipLaunchKernelGGL((grouped_gemm256_k64w_bf16_kernel<false, true>), dim3(persistent_grid(p, false)), dim3(256), 0, st, q);
-        hipLaunchKernelGGL(splitk_fixup_kernel, dim3(16 * 8 * 16), dim3(256), 0, st, q);
     } else if (p.BM == 256) {
         hipLaunchKernelGGL((grouped_gemm256_dma_bf16_kernel<false>), dim3(grid_for(p, false)), dim3(256), 0, st, p);
     } else {

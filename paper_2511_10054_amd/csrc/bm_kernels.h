@@ -92,8 +92,9 @@ struct GemmParams {
     const int32_t *mt_group, *mt_row0, *n_mtiles, *offsets;
     int mixed;                    // both tile heights in one launch: the table above lists the 256-row tiles and
     const int32_t *mt_group_s, *mt_row0_s, *n_mtiles_s;   // ... this one the 128-row tiles
-    float *splitk;                // scratch for the reduction-split tail of the down projection (or null)
-    int splitk_stride;            // workgroups per XCD of the launch that wrote it
+    float *splitk;                // scratch for the partial tiles of tiles that are cut along the reduction, or null: none is
+    int32_t *split_pieces;        // [K64_XCDS] pieces of a cut tile, XCD by XCD, as the launch that cuts them chose
+    int split_stride;             // workgroups per XCD of that launch
 };
 
 // Skinny (decode) projections: one weight-row block per wave, see bm_skinny_bf16.hip.
