@@ -63,9 +63,8 @@ __global__ void __launch_bounds__(256) rowwise_f32_kernel(GemmParams p) {
 //
 // What bounds it: groups of at most ~30 rows are bound by streaming their weights once, larger ones by the fp32
 // matrix rate.  The kernel it replaces (one workgroup per row, each wave a weight row at a time) read an expert's
-// weights once per ROW: 2790 + 2630 us for the two projections of the Qwen3-shaped layer at 128 tokens; here 142 to 162 +
-// 87 to 98 us by process (floors 90 and 48: 599 and 322 MB read at 6.7 TB/s).  Counters: 4.1 and 3.6 TB/s with the matrix
-// unit busy 47 % and 37 % of the time, no bank conflicts: groups of a few rows, which stream, and groups of tens of rows,
+// weights once per ROW: 2790 + 2630 us for the two projections of the Qwen3-shaped layer at 128 tokens; here 127 + 78 us
+// (floors 90 and 48: 599 and 322 MB read at 6.7 TB/s).  Groups of a few rows, which stream, and groups of tens of rows,
 // which multiply, take turns on a unit.
 //
 //  - Weights are the first MFMA operand, activations the second: a lane ends up with four consecutive output
@@ -84,6 +83,13 @@ __global__ void __launch_bounds__(256) rowwise_f32_kernel(GemmParams p) {
 //    row; this way no level is longer than the chains of the kernel it replaces (Kd / 64 values per lane and a tree
 //    over the lanes), and the error against 64 bits is no larger.  Short reductions, where that tree was most of
 //    the sum, take CHAIN = 1; from 1024 on CHAIN = 2 spares a third of the additions.
+//  - Weights of a group that one row tile covers are not read again: they are loaded non-temporally (AUX = 2), and the units
+//    of an XCD enter the reduction at 32 different places and walk it as a circle (rot; the tree's shape stays): weight
+//    rows lie a multiple of 4 KB apart in many layers, and workgroups in step all ask the same memory channels.
+//    Qwen3-shaped layer at 16 tokens 76 + 42 -> 64 + 38 us, DeepSeek-shaped at 8 tokens 74 + 30 -> 59 + 27.
+//  - Three waves a SIMD are asked for, not left to happen: with room for more registers the compiler puts the MFMA results
+//    into accumulator registers and copies each of them out for the tree, as many instructions as the tree itself
+//    (8 experts of 256 rows, d = 2048, F = 4096: 783 + 401 -> 718 + 367 us; Qwen3-shaped at 128 tokens 143 + 90 -> 127 + 78).
 // Needs Kd % 32 == 0.
 // ---------------------------------------------------------------------------
 #define BM_LDS __attribute__((address_space(3)))
@@ -91,9 +97,9 @@ constexpr int F32_ROWS = 64;            // activation rows per tile
 constexpr int F32_STAGES = 3;           // 48 KB: three workgroups per unit (4 or 5 stages leave two: gate/up 162 / 164 us against 150)
 constexpr int F32_CHUNKS = 8;           // row tiles of a group that run side by side
 
-template <bool DUAL, int NBT, int CHAIN>
+template <bool DUAL, int NBT, int CHAIN, int AUX>
 __device__ __forceinline__ void f32_tile(const GemmParams &p, float *smem, const float *b0, const float *b1,
-                                         int row0, int row_end, int n0) {
+                                         int row0, int row_end, int n0, int rot) {
     constexpr int S = F32_STAGES;
     constexpr int AROWS = 16 * NBT;
     constexpr int STAGE = (AROWS + 64) * 32;                     // floats
@@ -125,11 +131,12 @@ __device__ __forceinline__ void f32_tile(const GemmParams &p, float *smem, const
     }
 #define BM_F32_LOAD(kt_, slot_)                                                                               \
     {                                                                                                         \
-        const int k_ = min((kt_), KT - 1) * 32;                                                               \
+        const int kr_ = min((kt_), KT - 1) + rot;                                                             \
+        const int k_ = (kr_ >= KT ? kr_ - KT : kr_) * 32;                                                     \
         float *st_ = smem + (slot_) * STAGE;                                                                  \
         _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                         \
             __builtin_amdgcn_global_load_lds((const BM_GLOBAL void *)(pb[j] + k_),                            \
-                (BM_LDS void *)(st_ + (AROWS + j * 32 + wave * 8) * 32), 16, 0, 0);                           \
+                (BM_LDS void *)(st_ + (AROWS + j * 32 + wave * 8) * 32), 16, 0, AUX);                         \
         _Pragma("unroll") for (int j = 0; j < NA; ++j)                                                        \
             __builtin_amdgcn_global_load_lds((const BM_GLOBAL void *)(pa[j] + k_),                            \
                                              (BM_LDS void *)(st_ + la[j]), 16, 0, 0);                         \
@@ -227,7 +234,7 @@ __host__ __device__ __forceinline__ int f32_units(int chunk, int groups, int max
 }
 
 template <bool DUAL, int CHAIN>
-__global__ void __launch_bounds__(256) grouped_gemm_f32_kernel(GemmParams p, int chunks, int groups, int max_rows) {
+__global__ void __launch_bounds__(256, 3) grouped_gemm_f32_kernel(GemmParams p, int chunks, int groups, int max_rows) {
     __shared__ __attribute__((aligned(1024))) float smem[F32_STAGES * (F32_ROWS + 64) * 32];
     constexpr int BLK = DUAL ? 32 : 64;
     const int n_nt = (p.N + BLK - 1) / BLK;
@@ -244,11 +251,17 @@ __global__ void __launch_bounds__(256) grouped_gemm_f32_kernel(GemmParams p, int
     const size_t gofs = (size_t)(g < p.E ? g : g - p.E) * p.N * p.Kd;
     const float *b0 = static_cast<const float *>(g < p.E ? p.b0 : p.sb0) + gofs;
     const float *b1 = DUAL ? static_cast<const float *>(g < p.E ? p.b1 : p.sb1) + gofs : b0;
+    const int rot = (((unit >> 3) * 5) & 31) * (p.Kd >> 5) >> 5;
+    const bool once = end - p.offsets[g] <= F32_ROWS;
     for (int row0 = p.offsets[g] + chunk * F32_ROWS; row0 < end; row0 += chunks * F32_ROWS) {
         const int row_end = min(end, row0 + F32_ROWS), n_rows = row_end - row0;
-        if (n_rows <= 16) f32_tile<DUAL, 1, CHAIN>(p, smem, b0, b1, row0, row_end, nt * BLK);
-        else if (n_rows <= 32) f32_tile<DUAL, 2, CHAIN>(p, smem, b0, b1, row0, row_end, nt * BLK);
-        else f32_tile<DUAL, 4, CHAIN>(p, smem, b0, b1, row0, row_end, nt * BLK);
+#define BM_F32_TILE(NBT_)                                                                                             \
+    if (once) f32_tile<DUAL, NBT_, CHAIN, 2>(p, smem, b0, b1, row0, row_end, nt * BLK, rot);                                \
+    else f32_tile<DUAL, NBT_, CHAIN, 0>(p, smem, b0, b1, row0, row_end, nt * BLK, rot)
+        if (n_rows <= 16) { BM_F32_TILE(1); }
+        else if (n_rows <= 32) { BM_F32_TILE(2); }
+        else { BM_F32_TILE(4); }
+#undef BM_F32_TILE
         __syncthreads();                               // the next tile's loads go where the halves met
     }
 }
