@@ -4,11 +4,16 @@
 namespace bm {
 
 // ---------------------------------------------------------------------------
-// Aggregation: a gather per token in slot order, then the shared experts, so
-// the floating-point sum has one fixed order.
+// Aggregation: a gather per token in slot order, then the shared experts, so the floating-point sum has one fixed
+// order.  Rows are fetched several at a time before they are added (in that order): one 16-byte load in flight per
+// thread does not keep the memory system busy, and in a small batch every load is a round trip of its own; a dropped
+// slot reads row 0 and is skipped.
 // ---------------------------------------------------------------------------
-template <bool O_BF16>
-__global__ void __launch_bounds__(256) combine_kernel(CombineParams p) {
+
+// bf16 rows (tiled path): eight columns a thread.  NT: non-temporal loads, for more rows than the 256 MB memory-side cache
+// holds (us without | with: 268 MB 55 | 47, 196 MB 35 | 36, 134 MB 24.3 | 25.6, 20 MB 7.5 | 8.7).
+template <bool NT>
+__global__ void __launch_bounds__(256) combine_bf16_kernel(CombineParams p) {
     __shared__ int s_pos[BM_MAX_K + 8];
     __shared__ float s_w[BM_MAX_K + 8];
     const int t = blockIdx.x, tid = threadIdx.x;
@@ -21,57 +26,29 @@ __global__ void __launch_bounds__(256) combine_kernel(CombineParams p) {
         s_w[tid] = 1.0f;
     }
     __syncthreads();
-    const bool vec = (p.d & 7) == 0;
     for (int j0 = tid * 8; j0 < p.d; j0 += blockDim.x * 8) {
         float acc[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = 0.0f;
-        if (O_BF16) {
-            // rows are fetched four at a time before they are added (in slot order): one 16-byte load in
-            // flight per thread does not keep the memory system busy; a dropped slot reads row 0 with weight 0
-            for (int k0 = 0; k0 < nsrc; k0 += 4) {
-                u32x4 v[4];
-                float wk[4];
+        for (int k0 = 0; k0 < nsrc; k0 += 4) {
+            u32x4 v[4];
+            float wk[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int k = k0 + u;
-                    const int pos = k < nsrc ? s_pos[k] : -1;
-                    wk[u] = pos >= 0 ? s_w[k] : 0.0f;
-                    v[u] = ldg128(static_cast<const uint16_t *>(p.o) + (size_t)max(pos, 0) * p.d + j0);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (k0 + u >= nsrc || s_pos[k0 + u] < 0) continue;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        acc[2 * i] = fmaf(wk[u], bf16_to_f32((uint16_t)(v[u][i] & 0xffffu)), acc[2 * i]);
-                        acc[2 * i + 1] = fmaf(wk[u], bf16_to_f32((uint16_t)(v[u][i] >> 16)), acc[2 * i + 1]);
-                    }
-                }
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + u;
+                const int pos = k < nsrc ? s_pos[k] : -1;
+                wk[u] = pos >= 0 ? s_w[k] : 0.0f;
+                const uint16_t *src = static_cast<const uint16_t *>(p.o) + (size_t)max(pos, 0) * p.d + j0;
+                v[u] = NT ? __builtin_nontemporal_load((const BM_GLOBAL u32x4 *)src) : ldg128(src);
             }
-        }
-        for (int k = 0; !O_BF16 && k < nsrc; ++k) {
-            const int pos = s_pos[k];
-            if (pos < 0) continue;
-            const float wk = s_w[k];
-            {
-                // partial sums of the split reduction are added in slice order first
-                float o[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) o[i] = 0.0f;
-                for (int sl = 0; sl < p.ksplit; ++sl) {
-                    const float *src = static_cast<const float *>(p.o) + sl * p.slice_stride + (size_t)pos * p.d + j0;
-                    if (vec) {
-                        const f32x4 lo = *(const BM_GLOBAL f32x4 *)src, hi = *(const BM_GLOBAL f32x4 *)(src + 4);
+            for (int u = 0; u < 4; ++u) {
+                if (k0 + u >= nsrc || s_pos[k0 + u] < 0) continue;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) { o[i] += lo[i]; o[4 + i] += hi[i]; }
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) if (j0 + i < p.d) o[i] += src[i];
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    acc[2 * i] = fmaf(wk[u], bf16_to_f32((uint16_t)(v[u][i] & 0xffffu)), acc[2 * i]);
+                    acc[2 * i + 1] = fmaf(wk[u], bf16_to_f32((uint16_t)(v[u][i] >> 16)), acc[2 * i + 1]);
                 }
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[i] = fmaf(wk, o[i], acc[i]);
             }
         }
         if (p.y_f32) {
@@ -85,6 +62,69 @@ __global__ void __launch_bounds__(256) combine_kernel(CombineParams p) {
             out.z = pack_bf16x2(acc[4], acc[5]);
             out.w = pack_bf16x2(acc[6], acc[7]);
             stg128(static_cast<uint16_t *>(p.y) + (size_t)t * p.d + j0, out);
+        }
+    }
+}
+
+// fp32 rows (streaming path and fp32 layers), ksplit slices of each, added in slice order first: VEC (4 or 1) columns a
+// thread, so that a small batch is spread over more units.  Bound by two dependent round trips to memory (one row at a
+// time, eight columns a thread | here, us: Mixtral-shaped layer 64 tokens 5.6 | 4.6, Qwen3-shaped 8 tokens 5.8 | 5.5,
+// fp32 128 tokens 7.4 | 6.1).
+template <int VEC>
+__global__ void __launch_bounds__(256) combine_f32_kernel(CombineParams p) {
+    typedef __attribute__((ext_vector_type(VEC))) float fvec;
+    __shared__ int s_pos[BM_MAX_K + 8];
+    __shared__ float s_w[BM_MAX_K + 8];
+    const int t = blockIdx.x, tid = threadIdx.x;
+    const int nsrc = p.K + p.n_shared;
+    if (tid < p.K) {
+        s_pos[tid] = p.inv_perm[(size_t)t * p.K + tid];
+        s_w[tid] = p.w[(size_t)t * p.K + tid];
+    } else if (tid < nsrc) {
+        s_pos[tid] = p.offsets[p.E + (tid - p.K)] + t;
+        s_w[tid] = 1.0f;
+    }
+    __syncthreads();
+    const int j0 = (blockIdx.y * 256 + tid) * VEC;
+    if (j0 >= p.d) return;
+    constexpr int U = 8;                                // loads in flight
+    const int n = nsrc * p.ksplit;                      // (row, slice) pairs, slices fastest
+    fvec acc = 0.0f, o = 0.0f;
+    int k = 0, sl = 0, kl = 0, sll = 0;                 // pair that is added next, pair that is loaded next
+    for (int i0 = 0; i0 < n; i0 += U) {
+        fvec v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = i0 + u < n;
+            const float *src = static_cast<const float *>(p.o) + (in ? sll * p.slice_stride + (size_t)max(s_pos[kl], 0) * p.d : 0) + j0;
+            v[u] = *(const BM_GLOBAL fvec *)src;
+            if (in && ++sll == p.ksplit) { sll = 0; ++kl; }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i0 + u >= n) break;
+            o += v[u];
+            if (++sl == p.ksplit) {
+                if (s_pos[k] >= 0)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(s_w[k], o[i], acc[i]);
+                o = 0.0f;
+                sl = 0;
+                ++k;
+            }
+        }
+    }
+    if (p.y_f32) {
+        *(BM_GLOBAL fvec *)(static_cast<float *>(p.y) + (size_t)t * p.d + j0) = acc;
+    } else {
+        uint16_t *y = static_cast<uint16_t *>(p.y) + (size_t)t * p.d + j0;
+        if (VEC == 4) {
+            u32x2 out;
+            out[0] = pack_bf16x2(acc[0], acc[VEC > 1 ? 1 : 0]);
+            out[1] = pack_bf16x2(acc[VEC > 2 ? 2 : 0], acc[VEC > 3 ? 3 : 0]);
+            *(BM_GLOBAL u32x2 *)y = out;
+        } else {
+            stg16(y, f32_to_bf16(acc[0]));
         }
     }
 }
@@ -122,8 +162,13 @@ int launch_stream_read(const void *src, size_t bytes, uint32_t *sink, hipStream_
 
 int launch_combine(const CombineParams &p, bool o_bf16, hipStream_t st) {
     if (p.T > 0) {
-        if (o_bf16) hipLaunchKernelGGL(combine_kernel<true>, dim3(p.T), dim3(256), 0, st, p);
-        else hipLaunchKernelGGL(combine_kernel<false>, dim3(p.T), dim3(256), 0, st, p);
+        const bool vec = p.d % 4 == 0 && aligned16(p.y);
+        const int cols = vec ? 1024 : 256;
+        const bool large = (size_t)p.T * (p.K + p.n_shared) * p.d * 2 > (size_t)224 << 20;
+        if (o_bf16 && large) hipLaunchKernelGGL(combine_bf16_kernel<true>, dim3(p.T), dim3(256), 0, st, p);
+        else if (o_bf16) hipLaunchKernelGGL(combine_bf16_kernel<false>, dim3(p.T), dim3(256), 0, st, p);
+        else if (vec) hipLaunchKernelGGL(combine_f32_kernel<4>, dim3(p.T, (p.d + cols - 1) / cols), dim3(256), 0, st, p);
+        else hipLaunchKernelGGL(combine_f32_kernel<1>, dim3(p.T, (p.d + cols - 1) / cols), dim3(256), 0, st, p);
     }
     return launch_status(__func__);
 }

@@ -316,7 +316,7 @@ static void launch_skinny_q(const SkinnyParams &p, hipStream_t st) {
 template <bool DUAL, int NBT, bool PACKED, int NWV, int CH>
 __device__ __forceinline__ void skinny_lds_pass(const SkinnyParams &p, const uint16_t *w0, const uint16_t *w1,
                                                 u32x4 *xs, u32x4 *wst, int row_begin, int row_end, int k_begin,
-                                                int k_end, int n0, int kslice, bool active) {
+                                                int k_end, int n0, int kslice, bool active, int rot) {
     constexpr int KSTEP = 512 * (DUAL ? 2 : 1);         // packed copy: weight elements between consecutive k-steps
     constexpr int XW = CH / NWV;                        // k-steps of a chunk each wave stages
     BM_OPAQUE_PTR(w0);
@@ -383,11 +383,12 @@ __device__ __forceinline__ void skinny_lds_pass(const SkinnyParams &p, const uin
             _Pragma("unroll") for (int tb = 0; tb < NBT; ++tb)                             \
                 xs[(((buf_) * CH + XW * wave + 2 * li) * NBT + tb) * 64 + wslot[j]] = xr[(li * 2 + j) * NBT + tb];
 
-    BM_LOAD_X(k_begin);
+    int kn = k_begin + (rot % nch) * (CH * 32);             // chunk that is loaded next
+    BM_LOAD_X(kn);
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
-        s0[u] = BM_LOADW(w0, wl0, u, k_begin);
-        if (DUAL) s1[u] = BM_LOADW(w1, wl1, u, k_begin);
+        s0[u] = BM_LOADW(w0, wl0, u, kn);
+        if (DUAL) s1[u] = BM_LOADW(w1, wl1, u, kn);
     }
     BM_STORE_X(0);
     __syncthreads();
@@ -396,7 +397,8 @@ __device__ __forceinline__ void skinny_lds_pass(const SkinnyParams &p, const uin
 // unconditional inside the steady-state loop (see the note on wait counts in the kernel above)
 #define BM_CHUNK(c_, REFILL_)                                                                        \
     {                                                                                                \
-        const int kn_ = k_begin + ((c_) + 1) * (CH * 32);                                            \
+        kn = kn + CH * 32 == k_end ? k_begin : kn + CH * 32;                                         \
+        const int kn_ = kn;                                                                          \
         if (REFILL_) { BM_LOAD_X(kn_); }                                                             \
         {                                                                                            \
             const u32x4 *xc = xs + (size_t)((c_) & 1) * CH * NBT * 64 + rslot;                       \
@@ -485,14 +487,19 @@ __device__ __forceinline__ void skinny_lds_item(const SkinnyParams &p, u32x4 *xs
         if (DUAL) w1 = static_cast<const uint16_t *>(g < p.E ? p.b1 : p.sb1) + gofs + (size_t)n0 * p.Kd;
     }
     u32x4 *wst = wstage + (PACKED ? 0 : wave * (DUAL ? 256 : 128));
+    // Gate/up: an XCD's workgroups enter the reduction at different chunks and walk it as a circle.  Weight rows lie a
+    // multiple of 4 KB apart in many layers, and workgroups in step ask the same memory channels, more or less so by where the
+    // weights lie (us, by process, in step | from different chunks: Mixtral-shaped 32 tokens 182 to 194 | 177, DeepSeek-shaped 8
+    // tokens 30 to 34 | 28, Qwen3-shaped 16 tokens 31 to 35 | 31, 128 tokens 52 to 60 | 52).  The down projections: no gain.
+    const int rot = DUAL ? (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) >> 3 : 0;
     constexpr int PASS_ROWS = 16 * MAXNBT;
     for (int rb = row_begin; rb < row_end; rb += PASS_ROWS) {
         const int re = min(row_end, rb + PASS_ROWS);
         const int n_rows = re - rb;
-        if (MAXNBT == 1 || n_rows <= 16) skinny_lds_pass<DUAL, 1, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
-        else if (MAXNBT == 2 || n_rows <= 32) skinny_lds_pass<DUAL, 2, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
-        else if (MAXNBT == 4 || n_rows <= 64) skinny_lds_pass<DUAL, 4, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
-        else skinny_lds_pass<DUAL, MAXNBT, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active);
+        if (MAXNBT == 1 || n_rows <= 16) skinny_lds_pass<DUAL, 1, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active, rot);
+        else if (MAXNBT == 2 || n_rows <= 32) skinny_lds_pass<DUAL, 2, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active, rot);
+        else if (MAXNBT == 4 || n_rows <= 64) skinny_lds_pass<DUAL, 4, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active, rot);
+        else skinny_lds_pass<DUAL, MAXNBT, PACKED, NWV, CH>(p, w0, w1, xs, wst, rb, re, k_begin, k_end, n0, kslice, active, rot);
         __syncthreads();                              // the next pass restages the LDS buffers
     }
 }
