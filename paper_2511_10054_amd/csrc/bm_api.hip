@@ -37,6 +37,7 @@ constexpr int SKINNY_MANY_MAX_AVG = 28;   // ... rows per group from which it ta
 constexpr int SKINNY_MANY_AVG_ROWS = 13;  // ... and rows per group above which it takes the others
 constexpr int SKINNY_UNFIT_ROWS = 16;  // total rows when the widths do not fit its fast kernels but do fit the persistent tiled kernel
 constexpr int SKINNY_KSPLIT = 8;
+constexpr long long STREAM_BYTES = 256ll << 20;   // a layer whose weights the memory-side cache holds does not stream them past it
 
 // Shapes both projections of which fit the persistent k-step-64 kernel: reduction widths that are multiples
 // of 64 and at least 256, operands within 32-bit byte offsets.
@@ -641,6 +642,7 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
     gp.c = at<void>(ws, L.h);
     gp.N = desc->F; gp.Kd = desc->d; gp.E = E; gp.n_groups = G; gp.max_mtiles = L.mtiles_max; gp.BM = sp.BM;
     gp.mt_group = sp.mt_group; gp.mt_row0 = sp.mt_row0; gp.n_mtiles = sp.n_mtiles; gp.offsets = sp.offsets;
+    gp.stream = (bf16 ? 6ll : 12ll) * G * desc->d * desc->F > STREAM_BYTES ? 1 : 0;
     GemmParams dp = gp;
     auto use_mixed = [&](GemmParams &q) {
         q.mixed = 1; q.BM = 256;

@@ -945,9 +945,11 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
 //   k-step kt + 3 go out in the second half of k-step kt, once its fragments are in registers, and are waited for
 //   in the middle of k-step kt + 2: 24 loads (24 KB) a wave in flight, twice what the 256-row ring leaves them.
 //   Waves: each owns 64 weight rows and all 128 activation rows, so a weight fragment is read from LDS once.
-//   Streaming: the weights are loaded non-temporally (they are not read again, and would push activations and
+//   Streaming: the weights are loaded non-temporally (STREAM; they are not read again, and would push activations and
 //   router matrix out of the L2: Qwen3-shaped layer at 512 tokens, gate/up 85 -> 79 us, the next front kernel 19.4 -> 15.6),
-//   and the tiles of an XCD enter the reduction at 32 different places and walk it as a circle: weight rows lie a
+//   unless the layer's weights are few enough to stay in the 256 MB memory-side cache until its next call (us, plain |
+//   non-temporal: 64 experts, d = F = 512, 101 MB, 3000 tokens 24.3 | 26.0, d = 1024, F = 512, 201 MB 48 + 30 | 52 + 33; 48
+//   experts, d = F = 1024, 302 MB, level); and the tiles of an XCD enter the reduction at 32 different places and walk it as a circle: weight rows lie a
 //   multiple of 4 KB apart in many layers, and workgroups in step all ask the same memory channels (256 units reading
 //   panels of 256 rows of 4 / 8 KB: 4.2 TB/s in step, 5.9 / 6.1 TB/s from 32 places, 6.5 / 6.7 non-temporally too; 1.5 KB
 //   rows 4.6 -> 5.5, 28 KB rows 6.0 -> 7.0).  What an XCD misses in its L2 comes at 7 TB/s for the whole chip, from the
@@ -958,7 +960,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
 // ---------------------------------------------------------------------------
 constexpr int DMA_STREAM = 2;                              // cache policy of a load that is not read again (nt)
 
-template <bool DUAL, bool SPLIT>
+template <bool DUAL, bool SPLIT, bool STREAM>
 __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &work) {
     constexpr int RB = 8;                                  // 16-row blocks of the tile
     uint16_t *const smem = k64w_smem;
@@ -1059,7 +1061,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
 // load j_ of NL of k-step tile_ into stage st_: the weight rows first
 #define BM_DMA(st_, tile_, j_)                                                                     \
     {                                                                                              \
-        if ((j_) < 8) BM_DMA_AT(((j_) < 4 ? base_b0 : base_b1), ob[(j_) & 7], (st_) * STAGE + (j_) * 2048, tile_, DMA_STREAM); \
+        if ((j_) < 8) BM_DMA_AT(((j_) < 4 ? base_b0 : base_b1), ob[(j_) & 7], (st_) * STAGE + (j_) * 2048, tile_, STREAM ? DMA_STREAM : 0); \
         else BM_DMA_AT(a, oa[((j_) - 8) % NA], (st_) * STAGE + 256 * 64 + ((j_) - 8) * 2048, tile_, 0); \
     }
 #define BM_LD(ptr_) as_bf16x8(*reinterpret_cast<const u32x4 *>(ptr_))
@@ -1221,7 +1223,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
 
 // Both tile heights in one launch: p.mt_group / mt_row0 / n_mtiles list the 256-row tiles, p.mt_group_s / mt_row0_s /
 // n_mtiles_s the 128-row tiles.
-template <bool DUAL, bool SPLIT>
+template <bool DUAL, bool SPLIT, bool STREAM>
 __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmParams p) {
     const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
     XcdWork work;
@@ -1235,13 +1237,13 @@ __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmP
     // + 1 %, 1024 tokens + 3 %).
     const bool small_first = small_tiles(p) * 4 >= p.n_mtiles[0] && ((blockIdx.x >> 3) & 1);
     if (small_first) {
-        k64s_body<DUAL, SPLIT>(p, work);
+        k64s_body<DUAL, SPLIT, STREAM>(p, work);
         __syncthreads();      // the last write-out's staging area becomes the next phase's first load target
         k64w_body<DUAL, SPLIT>(p, work);
     } else {
         k64w_body<DUAL, SPLIT>(p, work);
         __syncthreads();
-        k64s_body<DUAL, SPLIT>(p, work);
+        k64s_body<DUAL, SPLIT, STREAM>(p, work);
     }
 }
 
@@ -1337,9 +1339,16 @@ static bool k64_ok(const GemmParams &p) {
            (unsigned long long)p.N * p.Kd * 2 < lim;
 }
 
+template <bool DUAL>
+static void launch_mixed(const GemmParams &p, hipStream_t st) {
+    const dim3 grid(persistent_grid(p, DUAL));
+    if (p.stream) hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<DUAL, false, true>), grid, dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<DUAL, false, false>), grid, dim3(256), 0, st, p);
+}
+
 int launch_gateup_bf16(const GemmParams &p, hipStream_t st) {
     if (p.mixed && k64_ok(p))
-        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<true, false>), dim3(persistent_grid(p, true)), dim3(256), 0, st, p);
+        launch_mixed<true>(p, st);
     else if (p.mixed)
         return -1;                // the caller asks for both tile heights only where the persistent kernel runs
     else if (p.BM == 256)
@@ -1356,10 +1365,10 @@ int launch_down_bf16(const GemmParams &p, hipStream_t st) {
     if (p.BM == 256 && k64_ok(p) && p.splitk != nullptr && down_split_tail(p.Kd)) {
         GemmParams q = p;
         q.split_stride = K64_CUS / K64_XCDS;
-        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false, true>), dim3(K64_CUS), dim3(256), 0, st, q);
+        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false, true, true>), dim3(K64_CUS), dim3(256), 0, st, q);
         hipLaunchKernelGGL(split_fixup_kernel, dim3(K64_XCDS * 16 * FIXUP_TILES), dim3(256), 0, st, q);
     } else if (p.mixed && k64_ok(p)) {
-        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false, false>), dim3(persistent_grid(p, false)), dim3(256), 0, st, p);
+        launch_mixed<false>(p, st);
     } else if (p.mixed) {
         return -1;
     } else if (p.BM == 256) {

@@ -83,7 +83,8 @@ __global__ void __launch_bounds__(256) rowwise_f32_kernel(GemmParams p) {
 //    row; this way no level is longer than the chains of the kernel it replaces (Kd / 64 values per lane and a tree
 //    over the lanes), and the error against 64 bits is no larger.  Short reductions, where that tree was most of
 //    the sum, take CHAIN = 1; from 1024 on CHAIN = 2 spares a third of the additions.
-//  - Weights of a group that one row tile covers are not read again: they are loaded non-temporally (AUX = 2), and the units
+//  - Weights of a group that one row tile covers are not read again: they are loaded non-temporally (AUX = 2; unless the
+//    memory-side cache holds all of the layer's weights until its next call), and the units
 //    of an XCD enter the reduction at 32 different places and walk it as a circle (rot; the tree's shape stays): weight
 //    rows lie a multiple of 4 KB apart in many layers, and workgroups in step all ask the same memory channels.
 //    Qwen3-shaped layer at 16 tokens 76 + 42 -> 64 + 38 us, DeepSeek-shaped at 8 tokens 74 + 30 -> 59 + 27.
@@ -252,7 +253,7 @@ __global__ void __launch_bounds__(256, 3) grouped_gemm_f32_kernel(GemmParams p, 
     const float *b0 = static_cast<const float *>(g < p.E ? p.b0 : p.sb0) + gofs;
     const float *b1 = DUAL ? static_cast<const float *>(g < p.E ? p.b1 : p.sb1) + gofs : b0;
     const int rot = (((unit >> 3) * 5) & 31) * (p.Kd >> 5) >> 5;
-    const bool once = end - p.offsets[g] <= F32_ROWS;
+    const bool once = p.stream && end - p.offsets[g] <= F32_ROWS;
     for (int row0 = p.offsets[g] + chunk * F32_ROWS; row0 < end; row0 += chunks * F32_ROWS) {
         const int row_end = min(end, row0 + F32_ROWS), n_rows = row_end - row0;
 #define BM_F32_TILE(NBT_)                                                                                             \
