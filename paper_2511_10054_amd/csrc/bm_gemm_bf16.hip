@@ -464,6 +464,23 @@ struct XcdWork {
     }
 };
 
+// Column tiles of the 128-row tiles.  A launch of fewer tiles than units - few live groups, narrow matrices - cuts 256-row
+// tiles into halves and every tile into as many column tiles, BLK columns apart, as give each unit one: a tile's time is
+// that of its loads, and a unit alone gets 50 GB/s and more from memory, so narrower tiles on more units end sooner
+// (us: FIGURES).
+struct SmallPlan {
+    int halved;          // 256-row tiles cut into halves: all or none of them
+    int cols;            // column tiles
+    __device__ __forceinline__ SmallPlan(int n_big, int n_small, int n_nt, int n_blk, int units, bool may) {
+        const int tiles = 2 * n_big + n_small;
+        halved = 0; cols = n_nt;
+        if (may && tiles > 0 && tiles * n_nt <= units) {
+            halved = n_big;
+            cols = min(units / tiles, n_blk);
+        }
+    }
+};
+
 // number of 128-row tiles: none where the plain table lists every tile
 __device__ __forceinline__ int small_tiles(const GemmParams &p) { return p.mixed ? p.n_mtiles_s[0] : 0; }
 
@@ -961,7 +978,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
 constexpr int DMA_STREAM = 2;                              // cache policy of a load that is not read again (nt)
 
 template <bool DUAL, bool SPLIT, bool STREAM>
-__device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &work) {
+__device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &work, const SmallPlan &plan) {
     constexpr int RB = 8;                                  // 16-row blocks of the tile
     uint16_t *const smem = k64w_smem;
     constexpr int NJ = 4;                                  // 16-column weight blocks per wave (DUAL: two of each matrix)
@@ -975,10 +992,12 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, quad = lane >> 4;
-    const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
+    constexpr int BLK = DUAL ? 16 : 32;                    // columns by which the width of a tile varies
     const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, slot = blockIdx.x >> 3;
     const int N = p.N, Kd = p.Kd;
     const int KT = Kd / 64;
+    const bool WIDE = plan.halved == 0 && plan.cols == (DUAL ? (N + 127) / 128 : (N + 255) / 256);   // column tiles of full width
+    const int cols = plan.cols, n_blk = N / BLK, n_halves = 2 * plan.halved * cols;   // items that are halves of 256-row tiles
     int rot = 0, rot_n = 0;                                // where the tile whose loads are being issued enters the reduction
     auto rotated = [&](int k) { const int r = k + rot; return r >= KT ? r - KT : r; };
     SmallTileDealer dealer;
@@ -1010,17 +1029,20 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
     bf16x8 f0a[RB], f0b[NJ], f1a[RB], f1b[NJ];
     uint32_t oa[NA], ob[8];
     const uint16_t *base_b0, *base_b1;
-    int row0, row_end, n0;
-    int g_n, row0_n, row_end_n, n0_n;
+    int row0, row_end, n0, n_end;
+    int g_n, row0_n, row_end_n, n0_n, n_end_n;
 #define BM_LOOKUP(lid_)                                                                            \
     {                                                                                              \
         const int id_ = __builtin_amdgcn_readfirstlane(lid_);                                      \
-        const int mt_ = id_ / n_nt;                                                                \
-        g_n = scalar_load_i32(p.mt_group_s, mt_);                                                  \
-        row0_n = scalar_load_i32(p.mt_row0_s, mt_);                                                \
+        const bool half_ = id_ < n_halves;             /* the halves of a tile follow each other */ \
+        const int q_ = half_ ? id_ >> 1 : id_ - n_halves;                                          \
+        const int mt_ = q_ / cols, ct_ = q_ - mt_ * cols;                                          \
+        g_n = scalar_load_i32(half_ ? p.mt_group : p.mt_group_s, mt_);                             \
+        row0_n = scalar_load_i32(half_ ? p.mt_row0 : p.mt_row0_s, mt_) + (half_ ? (id_ & 1) * 128 : 0); \
         row_end_n = scalar_load_i32(p.offsets, g_n + 1);                                           \
-        n0_n = (id_ - mt_ * n_nt) * (DUAL ? 128 : 256);                                            \
-        rot_n = (((id_ - work.small0) * 5) & 31) * KT >> 5;                                        \
+        n0_n = WIDE ? ct_ * (DUAL ? 128 : 256) : __builtin_amdgcn_readfirstlane(ct_ * n_blk / cols) * BLK; \
+        n_end_n = WIDE ? min(n0_n + (DUAL ? 128 : 256), N) : __builtin_amdgcn_readfirstlane((ct_ + 1) * n_blk / cols) * BLK; \
+        rot_n = (((half_ ? q_ : id_ - work.small0) * 5) & 31) * KT >> 5;                           \
         int lane_ = lane;                                                                          \
         asm volatile("" : "+v"(lane_));                                                            \
         const int r_ = 8 * (4 * (lane_ >> 3) + wave) + (lane_ & 7);                                \
@@ -1032,7 +1054,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
     }
 #define BM_ADOPT()                                                                                 \
     {                                                                                              \
-        row0 = row0_n; row_end = row_end_n; n0 = n0_n; rot = rot_n;                                \
+        row0 = row0_n; row_end = row_end_n; n0 = n0_n; n_end = n_end_n; rot = rot_n;               \
         if (g_n < p.E) {                                                                           \
             base_b0 = static_cast<const uint16_t *>(p.b0) + (size_t)g_n * N * Kd;                  \
             base_b1 = DUAL ? static_cast<const uint16_t *>(p.b1) + (size_t)g_n * N * Kd : base_b0; \
@@ -1050,7 +1072,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
                 const int src_ = __builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane_ >> 3)), rmv_);   \
                 oa[j] = ((uint32_t)src_ * (uint32_t)Kd + piece_ * 8) * 2u;                         \
             }                                                                                      \
-            const int n_ = DUAL ? min(n0 + (r_ & 127), N - 1) : min(n0 + r_, N - 1);               \
+            const int n_ = DUAL ? min(n0 + (r_ & 127), n_end - 1) : min(n0 + r_, n_end - 1);       \
             ob[j] = ((uint32_t)n_ * (uint32_t)Kd + piece_ * 8) * 2u;                               \
         }                                                                                          \
     }
@@ -1095,7 +1117,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
     int st = 0;                                        // stage of k-step kt
     BM_WAIT_VMCNT(NL * (NS - 1));
     for (;;) {
-        const int t_row0 = row0, t_row_end = row_end, t_n0 = n0, t_tile = load_item;    // the tile being multiplied
+        const int t_row0 = row0, t_row_end = row_end, t_n0 = n0, t_n_end = n_end, t_tile = load_item;   // the tile being multiplied
         const int t_kbeg = kbeg, t_kend = kend;
         int n_kbeg, n_kend;
         BM_NEXT_ITEM(n_more, n_kbeg, n_kend);
@@ -1179,7 +1201,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
                 const int lrow = lane_w >> 2, pc = lane_w & 3;
                 const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
                 const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * 32 + pc * 8;
-                if (row < t_row_end && col < N) stg128(&c[(size_t)row * N + col], val);
+                if (row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
@@ -1203,7 +1225,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
                     const int lrow = q >> 3, pc = q & 7;
                     const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
                     const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * 64 + pc * 8;
-                    if (row < t_row_end && col < N) stg128(&c[(size_t)row * N + col], val);
+                    if (row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
                 }
             }
         }
@@ -1227,7 +1249,8 @@ template <bool DUAL, bool SPLIT, bool STREAM>
 __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmParams p) {
     const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
     XcdWork work;
-    work.init(p.n_mtiles[0] * n_nt, small_tiles(p) * n_nt, p.Kd / 64, blockIdx.x & 7, gridDim.x >> 3, SPLIT);
+    const SmallPlan plan(p.n_mtiles[0], small_tiles(p), n_nt, p.N / (DUAL ? 16 : 32), gridDim.x, !SPLIT);
+    work.init((p.n_mtiles[0] - plan.halved) * n_nt, (2 * plan.halved + small_tiles(p)) * plan.cols, p.Kd / 64, blockIdx.x & 7, gridDim.x >> 3, SPLIT);
     if (SPLIT && blockIdx.x < K64_XCDS && threadIdx.x == 0) p.split_pieces[blockIdx.x] = work.S;
     // A 128-row tile is the only user of its weight panel (a group has at most one), so it streams from
     // memory at a third of a 256-row tile's arithmetic intensity.  When there are many of them (at least a
@@ -1237,13 +1260,13 @@ __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmP
     // + 1 %, 1024 tokens + 3 %).
     const bool small_first = small_tiles(p) * 4 >= p.n_mtiles[0] && ((blockIdx.x >> 3) & 1);
     if (small_first) {
-        k64s_body<DUAL, SPLIT, STREAM>(p, work);
+        k64s_body<DUAL, SPLIT, STREAM>(p, work, plan);
         __syncthreads();      // the last write-out's staging area becomes the next phase's first load target
         k64w_body<DUAL, SPLIT>(p, work);
     } else {
         k64w_body<DUAL, SPLIT>(p, work);
         __syncthreads();
-        k64s_body<DUAL, SPLIT, STREAM>(p, work);
+        k64s_body<DUAL, SPLIT, STREAM>(p, work, plan);
     }
 }
 
@@ -1341,7 +1364,7 @@ static bool k64_ok(const GemmParams &p) {
 
 template <bool DUAL>
 static void launch_mixed(const GemmParams &p, hipStream_t st) {
-    const dim3 grid(persistent_grid(p, DUAL));
+    const dim3 grid(K64_CUS);
     if (p.stream) hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<DUAL, false, true>), grid, dim3(256), 0, st, p);
     else hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<DUAL, false, false>), grid, dim3(256), 0, st, p);
 }

@@ -15,13 +15,20 @@ namespace bm {
 // bit twice, ids out of range set none; neighbouring lanes own different words, so that a popular expert's bits do
 // not queue on one), then counts every pair (pivot i, expert j) as the population count of
 // the two sets' intersection and adds it to the global int64 totals; the pair (i, i) is the activation count.
-// Bound by latency: one read of the chunk's ids, two barriers, the LDS reads of a thread's pairs (4 pivots: 6.8 us for
-// 4096 tokens of 8 out of 128 experts; 8 pivots 7.9, 16 pivots 15.3; 6.4 without the global atomics).  The kernel it
+// Bound by latency: one read of the chunk's ids, two barriers, the LDS reads of a thread's pairs (4 pivots: 5.8 us for
+// 4096 tokens of 8 out of 128 experts).  The kernel it
 // replaces walked a token per wave with lane permutes and flushed a whole triangle every 64 tokens: 41 us.
-constexpr int CO_TOK = 1024, CO_ROWS = 4, CO_WORDS = CO_TOK / 64;
+// CO_TOK = 512 halves the chain of a workgroup (sets to clear, bits to set that meet in a bank, words of a pair to count) and
+// doubles the additions to the totals: better while those are few or the tokens' slots many (us, 1024 | 512: 128 experts, 8 a
+// token, 1000 / 4096 tokens 6.6 7.0 | 4.8 5.8, 8192 / 16384 tokens 0.96, 0.99 of the time; 5 a token, 2048 / 4096 / 8192
+// tokens 0.89, 0.91, 1.09; 64 experts 0.92, 1.03, 1.24; 16 experts 0.72 to 0.95 at every size).
+constexpr int CO_ROWS = 4;
+static bool coact_short_chunks(int T, int K, int E) { return T <= 2048 || E <= 16 || (K >= 8 && T <= 8192); }
 
+template <int CO_TOK>
 __global__ void __launch_bounds__(CO_TOK) coact_kernel(const int32_t *ids, int T, int K, int E, unsigned long long *A,
                                                        unsigned long long *M) {
+    constexpr int CO_WORDS = CO_TOK / 64;
     __shared__ unsigned long long bits[BM_MAX_E][CO_WORDS + 1];         // padded: rows start in different banks
     constexpr int PAIRS = CO_ROWS * BM_MAX_E / CO_TOK;                  // pairs of a thread
     const int tid = threadIdx.x, row0 = blockIdx.x * CO_ROWS;
@@ -44,7 +51,7 @@ __global__ void __launch_bounds__(CO_TOK) coact_kernel(const int32_t *ids, int T
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 if ((unsigned)e[i] < (unsigned)E)
-                    atomicOr(reinterpret_cast<unsigned *>(bits[e[i]]) + (tid & 31), 1u << (tid >> 5));
+                    atomicOr(reinterpret_cast<unsigned *>(bits[e[i]]) + tid % (2 * CO_WORDS), 1u << tid / (2 * CO_WORDS));
         }
         __syncthreads();
 #pragma unroll
@@ -138,11 +145,15 @@ __global__ void __launch_bounds__(BM_MAX_E) buddy_build_kernel(const long long *
 
 int launch_coactivation(const int32_t *ids, int T, int K, int E, long long *A, long long *M, hipStream_t st) {
     if (T > 0) {
-        // up to two workgroups per unit; those of a longer batch walk several chunks before they add their counts up
-        const int rows = (E + CO_ROWS - 1) / CO_ROWS, chunks = T / CO_TOK + (T % CO_TOK ? 1 : 0), most = 512 / rows;
+        // up to two workgroups per unit (four of the short ones); those of a longer batch walk several chunks before they
+        // add their counts up
+        const bool brief = coact_short_chunks(T, K, E);
+        const int tok = brief ? 512 : 1024, rows = (E + CO_ROWS - 1) / CO_ROWS;
+        const int chunks = T / tok + (T % tok ? 1 : 0), most = 512 * 1024 / tok / rows;
         const dim3 grid(rows, chunks < most ? chunks : most);
-        hipLaunchKernelGGL(coact_kernel, grid, dim3(CO_TOK), 0, st, ids, T, K, E,
-                           reinterpret_cast<unsigned long long *>(A), reinterpret_cast<unsigned long long *>(M));
+        unsigned long long *a = reinterpret_cast<unsigned long long *>(A), *m = reinterpret_cast<unsigned long long *>(M);
+        if (brief) hipLaunchKernelGGL(coact_kernel<512>, grid, dim3(512), 0, st, ids, T, K, E, a, m);
+        else hipLaunchKernelGGL(coact_kernel<1024>, grid, dim3(1024), 0, st, ids, T, K, E, a, m);
     }
     return launch_status(__func__);
 }
