@@ -465,18 +465,24 @@ struct XcdWork {
 };
 
 // Column tiles of the 128-row tiles.  A launch of fewer tiles than units - few live groups, narrow matrices - cuts 256-row
-// tiles into halves and every tile into as many column tiles, BLK columns apart, as give each unit one: a tile's time is
-// that of its loads, and a unit alone gets 50 GB/s and more from memory, so narrower tiles on more units end sooner
-// (us: FIGURES).
+// tiles into halves and every tile into as many column tiles, 16 (DUAL) or 32 columns up, as give each unit one: a k-step
+// takes as long as its loads, and tiles of at most half the width have a loop of their own whose k-step is 32 KB instead of 48
+// and four deep (the shortest reductions, which are over before it gets going, keep the wide one).  Kernel times, us, tiles of
+// full width | narrower | with the narrow loop: 495 tokens, 5 experts of d = 1792, F = 256 38 + 12 | 25 + 9 | 17 + 9; 900 tokens,
+// 12 experts of d = 1024, F = 512 28 + 17 | 20 + 12 | 14 + 9; 300 tokens, 3 experts of d = 3072, F = 1024 59 + 25 | 42 + 18 | 28 +
+// 13; DeepSeek-shaped 17 / 32 / 128 tokens, down projection 30 30 34 | 24 25 28 | 19 25 28.  Twice as many tiles as units were
+// no better cut (Qwen3-shaped, 512 tokens: 378 tiles 80 us, 504 narrower ones 88).
 struct SmallPlan {
     int halved;          // 256-row tiles cut into halves: all or none of them
     int cols;            // column tiles
-    __device__ __forceinline__ SmallPlan(int n_big, int n_small, int n_nt, int n_blk, int units, bool may) {
+    bool narrow;         // they are at most half as wide as a tile can be
+    __device__ __forceinline__ SmallPlan(int n_big, int n_small, int n_nt, int n_blk, int KT, int units, bool may) {
         const int tiles = 2 * n_big + n_small;
-        halved = 0; cols = n_nt;
+        halved = 0; cols = n_nt; narrow = false;
         if (may && tiles > 0 && tiles * n_nt <= units) {
             halved = n_big;
             cols = min(units / tiles, n_blk);
+            narrow = n_blk <= 4 * cols && KT >= 6;
         }
     }
 };
@@ -977,17 +983,21 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
 // ---------------------------------------------------------------------------
 constexpr int DMA_STREAM = 2;                              // cache policy of a load that is not read again (nt)
 
-template <bool DUAL, bool SPLIT, bool STREAM>
+template <bool DUAL, bool SPLIT, bool STREAM, int NJ>
 __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &work, const SmallPlan &plan) {
     constexpr int RB = 8;                                  // 16-row blocks of the tile
     uint16_t *const smem = k64w_smem;
-    constexpr int NJ = 4;                                  // 16-column weight blocks per wave (DUAL: two of each matrix)
+    static_assert(NJ == 4 || NJ == 2, "16-column weight blocks per wave (DUAL: half of them of either matrix)");
+    constexpr int NB = 2 * NJ;                             // weight loads per wave and k-step
+    constexpr int BROWS = 64 * NJ;                         // weight rows of the tile
     constexpr int NA = RB / 2;                             // activation loads per wave and k-step
-    constexpr int NL = NA + 8;                             // loads per wave and k-step
-    constexpr int STAGE = (256 + RB * 16) * 64;            // bf16 elements of a stage: weight rows, then activation rows
-    constexpr int NS = 3;                                  // stages
+    constexpr int NL = NA + NB;                            // loads per wave and k-step
+    constexpr int STAGE = (BROWS + RB * 16) * 64;           // bf16 elements of a stage: weight rows, then activation rows
+    constexpr int NS = NJ == 4 ? 3 : 4;                    // stages
     constexpr int NM = RB * NJ;                            // MFMAs per k slice of 32
     constexpr int NR = RB + NJ;                            // fragment reads per k slice
+    constexpr int RSTEP = NM >= 2 * NR ? 2 : 1;            // MFMAs per fragment read
+    static_assert(NR * RSTEP <= NM, "every fragment is read under the slice before its own");
     static_assert(NS * STAGE + 4 * 1024 * 2 <= 5 * P_PART, "the stages leave 4 KB per wave for the write-out");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -996,7 +1006,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
     const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, slot = blockIdx.x >> 3;
     const int N = p.N, Kd = p.Kd;
     const int KT = Kd / 64;
-    const bool WIDE = plan.halved == 0 && plan.cols == (DUAL ? (N + 127) / 128 : (N + 255) / 256);   // column tiles of full width
+    const bool WIDE = NJ == 4 && plan.cols == (DUAL ? (N + 127) / 128 : (N + 255) / 256);   // column tiles of full width
     const int cols = plan.cols, n_blk = N / BLK, n_halves = 2 * plan.halved * cols;   // items that are halves of 256-row tiles
     int rot = 0, rot_n = 0;                                // where the tile whose loads are being issued enters the reduction
     auto rotated = [&](int k) { const int r = k + rot; return r >= KT ? r - KT : r; };
@@ -1022,12 +1032,12 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         const int pc = ((4 * s + quad) ^ ((r16 >> 1) & 7)) << 3;
-        fa_off[s] = 256 * 64 + r16 * 64 + pc;
-        fb_off[s] = (DUAL ? (wave * 32 + r16) : (wave * 64 + r16)) * 64 + pc;
+        fa_off[s] = BROWS * 64 + r16 * 64 + pc;
+        fb_off[s] = (wave * (DUAL ? NJ * 8 : NJ * 16) + r16) * 64 + pc;
     }
     f32x4 acc[RB][NJ];
     bf16x8 f0a[RB], f0b[NJ], f1a[RB], f1b[NJ];
-    uint32_t oa[NA], ob[8];
+    uint32_t oa[NA], ob[NB];
     const uint16_t *base_b0, *base_b1;
     int row0, row_end, n0, n_end;
     int g_n, row0_n, row_end_n, n0_n, n_end_n;
@@ -1040,8 +1050,8 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
         g_n = scalar_load_i32(half_ ? p.mt_group : p.mt_group_s, mt_);                             \
         row0_n = scalar_load_i32(half_ ? p.mt_row0 : p.mt_row0_s, mt_) + (half_ ? (id_ & 1) * 128 : 0); \
         row_end_n = scalar_load_i32(p.offsets, g_n + 1);                                           \
-        n0_n = WIDE ? ct_ * (DUAL ? 128 : 256) : __builtin_amdgcn_readfirstlane(ct_ * n_blk / cols) * BLK; \
-        n_end_n = WIDE ? min(n0_n + (DUAL ? 128 : 256), N) : __builtin_amdgcn_readfirstlane((ct_ + 1) * n_blk / cols) * BLK; \
+        n0_n = WIDE ? ct_ * (DUAL ? BROWS / 2 : BROWS) : __builtin_amdgcn_readfirstlane(ct_ * n_blk / cols) * BLK; \
+        n_end_n = WIDE ? min(n0_n + (DUAL ? BROWS / 2 : BROWS), N) : __builtin_amdgcn_readfirstlane((ct_ + 1) * n_blk / cols) * BLK; \
         rot_n = (((half_ ? q_ : id_ - work.small0) * 5) & 31) * KT >> 5;                           \
         int lane_ = lane;                                                                          \
         asm volatile("" : "+v"(lane_));                                                            \
@@ -1065,15 +1075,17 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
         int lane_ = lane, rmv_;                                                                    \
         asm volatile("" : "+v"(lane_));                                                            \
         asm volatile("v_mov_b32 %0, v255" : "=v"(rmv_));                                           \
-        _Pragma("unroll") for (int j = 0; j < 8; ++j) {                                            \
+        _Pragma("unroll") for (int j = 0; j < (NA > NB ? NA : NB); ++j) {                                          \
             const int r_ = 8 * (4 * j + wave) + (lane_ >> 3);                                      \
             const int piece_ = (lane_ & 7) ^ ((r_ >> 1) & 7);                                      \
             if (j < NA) {                                                                          \
                 const int src_ = __builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane_ >> 3)), rmv_);   \
                 oa[j] = ((uint32_t)src_ * (uint32_t)Kd + piece_ * 8) * 2u;                         \
             }                                                                                      \
-            const int n_ = DUAL ? min(n0 + (r_ & 127), n_end - 1) : min(n0 + r_, n_end - 1);       \
-            ob[j] = ((uint32_t)n_ * (uint32_t)Kd + piece_ * 8) * 2u;                               \
+            if (j < NB) {                                                                          \
+                const int n_ = min(n0 + (DUAL ? r_ % (BROWS / 2) : r_), n_end - 1);                \
+                ob[j] = ((uint32_t)n_ * (uint32_t)Kd + piece_ * 8) * 2u;                           \
+            }                                                                                      \
         }                                                                                          \
     }
 #define BM_DMA_AT(base_, off_, dst_, tile_, aux_)                                                  \
@@ -1083,11 +1095,11 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
 // load j_ of NL of k-step tile_ into stage st_: the weight rows first
 #define BM_DMA(st_, tile_, j_)                                                                     \
     {                                                                                              \
-        if ((j_) < 8) BM_DMA_AT(((j_) < 4 ? base_b0 : base_b1), ob[(j_) & 7], (st_) * STAGE + (j_) * 2048, tile_, STREAM ? DMA_STREAM : 0); \
-        else BM_DMA_AT(a, oa[((j_) - 8) % NA], (st_) * STAGE + 256 * 64 + ((j_) - 8) * 2048, tile_, 0); \
+        if ((j_) < NB) BM_DMA_AT(((j_) < NJ ? base_b0 : base_b1), ob[(j_) % NB], (st_) * STAGE + (j_) * 2048, tile_, STREAM ? DMA_STREAM : 0); \
+        else BM_DMA_AT(a, oa[((j_) - NB) % NA], (st_) * STAGE + BROWS * 64 + ((j_) - NB) * 2048, tile_, 0); \
     }
 #define BM_LD(ptr_) as_bf16x8(*reinterpret_cast<const u32x4 *>(ptr_))
-#define BM_BOFF(j_) (DUAL ? (((j_) >> 1) * 8192 + ((j_) & 1) * 1024) : (j_) * 1024)
+#define BM_BOFF(j_) (DUAL ? ((j_) / (NJ / 2) * (BROWS * 32) + (j_) % (NJ / 2) * 1024) : (j_) * 1024)
 // fragment read d_ of NR, in the order the MFMAs need them: a0 b0..b3 a1..
 #define BM_RD(d_, fa_, fb_, st_, s_)                                                               \
     {                                                                                              \
@@ -1140,7 +1152,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
 #pragma unroll
             for (int m = 0; m < NM; ++m) {
                 BM_MFMA1(m, f0a, f0b);
-                if (m < 2 * NR && (m & 1) == 0) BM_RD(m >> 1, f1a, f1b, st, 1)
+                if (m % RSTEP == 0 && m / RSTEP < NR) BM_RD(m / RSTEP, f1a, f1b, st, 1)
                 __builtin_amdgcn_sched_barrier(0);
             }
             BM_WAIT_VM_LGKM(NL * (NS - 2), 0);
@@ -1149,7 +1161,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
             for (int m = 0; m < NM; ++m) {
                 BM_MFMA1(m, f1a, f1b);
                 if (m * NL / NM != (m + 1) * NL / NM) BM_DMA(st, kl, m * NL / NM)
-                if (m < 2 * NR && (m & 1) == 0) BM_RD(m >> 1, f0a, f0b, stn, 0)
+                if (m % RSTEP == 0 && m / RSTEP < NR) BM_RD(m / RSTEP, f0a, f0b, stn, 0)
                 __builtin_amdgcn_sched_barrier(0);
             }
             st = stn;
@@ -1170,6 +1182,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
             continue;
         }
         if (DUAL) {
+            constexpr int OC = NJ / 2;                  // 16-column output blocks per wave
             constexpr int SD = 20;
             uint32_t *stage = reinterpret_cast<uint32_t *>(smem + NS * STAGE) + wave * 1024;
             int lane_w = lane;
@@ -1179,14 +1192,14 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < OC; ++j) {
 #pragma unroll
                     for (int v = 0; v < 4; v += 2) {
                         float g0, g1, u0, u1;
                         asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(g0) : "a"(acc[i][j][v]));
                         asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(g1) : "a"(acc[i][j][v + 1]));
-                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u0) : "a"(acc[i][2 + j][v]));
-                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u1) : "a"(acc[i][2 + j][v + 1]));
+                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u0) : "a"(acc[i][OC + j][v]));
+                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u1) : "a"(acc[i][OC + j][v + 1]));
                         const float x0 = silu(g0) * u0;
                         const float x1 = silu(g1) * u1;
                         const float send = odd ? x0 : x1;
@@ -1198,10 +1211,10 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                const int lrow = lane_w >> 2, pc = lane_w & 3;
+                const int lrow = lane_w / (2 * OC) % 16, pc = lane_w % (2 * OC);
                 const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
-                const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * 32 + pc * 8;
-                if (row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
+                const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * (16 * OC) + pc * 8;
+                if (lane_w < 32 * OC && row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
@@ -1220,11 +1233,11 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
                     *reinterpret_cast<u32x2 *>(stage + r16 * SD + j * 8 + 2 * quad) = pk;
                 }
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
+                for (int t = 0; t < NJ / 2; ++t) {
                     const int q = lane + 64 * t;
-                    const int lrow = q >> 3, pc = q & 7;
+                    const int lrow = q / (2 * NJ), pc = q % (2 * NJ);
                     const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
-                    const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * 64 + pc * 8;
+                    const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * (16 * NJ) + pc * 8;
                     if (row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
                 }
             }
@@ -1249,7 +1262,7 @@ template <bool DUAL, bool SPLIT, bool STREAM>
 __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmParams p) {
     const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
     XcdWork work;
-    const SmallPlan plan(p.n_mtiles[0], small_tiles(p), n_nt, p.N / (DUAL ? 16 : 32), gridDim.x, !SPLIT);
+    const SmallPlan plan(p.n_mtiles[0], small_tiles(p), n_nt, p.N / (DUAL ? 16 : 32), p.Kd / 64, gridDim.x, !SPLIT);
     work.init((p.n_mtiles[0] - plan.halved) * n_nt, (2 * plan.halved + small_tiles(p)) * plan.cols, p.Kd / 64, blockIdx.x & 7, gridDim.x >> 3, SPLIT);
     if (SPLIT && blockIdx.x < K64_XCDS && threadIdx.x == 0) p.split_pieces[blockIdx.x] = work.S;
     // A 128-row tile is the only user of its weight panel (a group has at most one), so it streams from
@@ -1258,15 +1271,19 @@ __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmP
     // streaming is spread over the launch instead of bunched at its end (Qwen3-shaped layer, 2048 tokens:
     // gate/up 141 -> 133 us); with few of them that order only delays 256-row tiles (Mixtral-shaped prefill
     // + 1 %, 1024 tokens + 3 %).
+    if (!SPLIT && plan.narrow) {
+        k64s_body<DUAL, SPLIT, STREAM, 2>(p, work, plan);
+        return;
+    }
     const bool small_first = small_tiles(p) * 4 >= p.n_mtiles[0] && ((blockIdx.x >> 3) & 1);
     if (small_first) {
-        k64s_body<DUAL, SPLIT, STREAM>(p, work, plan);
+        k64s_body<DUAL, SPLIT, STREAM, 4>(p, work, plan);
         __syncthreads();      // the last write-out's staging area becomes the next phase's first load target
         k64w_body<DUAL, SPLIT>(p, work);
     } else {
         k64w_body<DUAL, SPLIT>(p, work);
         __syncthreads();
-        k64s_body<DUAL, SPLIT, STREAM>(p, work, plan);
+        k64s_body<DUAL, SPLIT, STREAM, 4>(p, work, plan);
     }
 }
 

@@ -42,3 +42,20 @@ def test_tiled_layer_matches_oracle(over, T):
         e = err_metric(out["y"], ref["y"])
         print("   err", e, flush=True)
         assert e <= 2e-2, e                                          # bf16 rounding of h, o and y: the suite's bound
+
+
+# launches of fewer tiles than units: every tile in as many column tiles as give each unit one, of 16 (32) columns up and of
+# unequal widths, 256-row tiles in halves; tiles of at most half the width run on the narrow loop, from 6 k-steps on
+FEW = [
+    (dict(d=256, F=256, E=3, K=1, n_resident=3, R=2, H=2), 300),
+    (dict(d=384, F=384, E=3, K=1, n_resident=2, R=2, H=2), 300),
+    (dict(d=448, F=1344, E=4, K=2, n_resident=2, R=3, H=3), 260),
+    (dict(d=1792, F=256, E=6, K=1, n_resident=5), 495),
+    (dict(d=576, F=704, E=10, K=2, n_resident=6, n_shared=2), 131),
+    (dict(d=2048, F=1408, E=16, K=4, n_resident=10, n_shared=1), 70),
+]
+
+
+@pytest.mark.parametrize("over,T", FEW)
+def test_launches_of_few_tiles_match_oracle(over, T):
+    test_tiled_layer_matches_oracle(over, T)
