@@ -994,10 +994,6 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
     constexpr int NL = NA + NB;                            // loads per wave and k-step
     constexpr int STAGE = (BROWS + RB * 16) * 64;           // bf16 elements of a stage: weight rows, then activation rows
     constexpr int NS = NJ == 4 ? 3 : 4;                    // stages
-    constexpr int NM = RB * NJ;                            // MFMAs per k slice of 32
-    constexpr int NR = RB + NJ;                            // fragment reads per k slice
-    constexpr int RSTEP = NM >= 2 * NR ? 2 : 1;            // MFMAs per fragment read
-    static_assert(NR * RSTEP <= NM, "every fragment is read under the slice before its own");
     static_assert(NS * STAGE + 4 * 1024 * 2 <= 5 * P_PART, "the stages leave 4 KB per wave for the write-out");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1143,37 +1139,50 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
                 for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
         asm volatile("s_nop 7" : "+a"(acc[0][0]));
         BM_BARE_BARRIER();
-#pragma unroll
-        for (int d = 0; d < NR; ++d) BM_RD(d, f0a, f0b, st, 0)
-        for (int kt = t_kbeg; kt < t_kend; ++kt) {
-            const int kl = more ? kbeg + (kt + NS - t_kend) : kt + NS;
-            const int stn = st == NS - 1 ? 0 : st + 1;
-            BM_WAIT_VM_LGKM(63, 0);
-#pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                BM_MFMA1(m, f0a, f0b);
-                if (m % RSTEP == 0 && m / RSTEP < NR) BM_RD(m / RSTEP, f1a, f1b, st, 1)
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            BM_WAIT_VM_LGKM(NL * (NS - 2), 0);
-            BM_BARE_BARRIER();
-#pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                BM_MFMA1(m, f1a, f1b);
-                if (m * NL / NM != (m + 1) * NL / NM) BM_DMA(st, kl, m * NL / NM)
-                if (m % RSTEP == 0 && m / RSTEP < NR) BM_RD(m / RSTEP, f0a, f0b, stn, 0)
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            st = stn;
-            if (kt == t_kend - NS - 1) {
-                more = n_more;
-                if (more) {
-                    if (t_kend - t_kbeg < 2 * NS - 1) BM_WAIT_VM_LGKM(0, 0);
-                    kbeg = n_kbeg; kend = n_kend; load_item = item;
-                    BM_ADOPT();
-                }
-            }
-        }
+        // The k-steps, on the first RBL_ row blocks: a tile of at most 64 rows leaves the others out of the matrix work, the
+        // fragment reads and the write-out (not of the loads: the waits count them): what they do not draw lets the others
+        // clock higher (layers, us: DeepSeek-shaped 32 tokens 83 -> 80, Qwen3-shaped 512 / 2048 tokens 159 272 -> 155 261).  The
+        // narrow loop does without: its launches are short, and the larger kernel costs them as much as it gives.
+#define BM_TILE_LOOP(RBL_)                                                                                            \
+    {                                                                                                                 \
+        constexpr int NM = (RBL_) * NJ;                        /* MFMAs per k slice of 32 */                          \
+        constexpr int NR = (RBL_) + NJ;                        /* fragment reads per k slice */                       \
+        constexpr int RSTEP = NM >= 2 * NR ? 2 : 1;            /* MFMAs per fragment read */                          \
+        static_assert(NR * RSTEP <= NM, "every fragment is read under the slice before its own");                     \
+        _Pragma("unroll") for (int d = 0; d < NR; ++d) BM_RD(d, f0a, f0b, st, 0)                                      \
+        for (int kt = t_kbeg; kt < t_kend; ++kt) {                                                                    \
+            const int kl = more ? kbeg + (kt + NS - t_kend) : kt + NS;                                                \
+            const int stn = st == NS - 1 ? 0 : st + 1;                                                                \
+            BM_WAIT_VM_LGKM(63, 0);                                                                                   \
+            _Pragma("unroll") for (int m = 0; m < NM; ++m) {                                                          \
+                BM_MFMA1(m, f0a, f0b);                                                                                \
+                if (m % RSTEP == 0 && m / RSTEP < NR) BM_RD(m / RSTEP, f1a, f1b, st, 1)                               \
+                __builtin_amdgcn_sched_barrier(0);                                                                    \
+            }                                                                                                         \
+            BM_WAIT_VM_LGKM(NL * (NS - 2), 0);                                                                        \
+            BM_BARE_BARRIER();                                                                                        \
+            _Pragma("unroll") for (int m = 0; m < NM; ++m) {                                                          \
+                BM_MFMA1(m, f1a, f1b);                                                                                \
+                _Pragma("unroll") for (int j = m * NL / NM; j < (m + 1) * NL / NM; ++j) BM_DMA(st, kl, j)             \
+                if (m % RSTEP == 0 && m / RSTEP < NR) BM_RD(m / RSTEP, f0a, f0b, stn, 0)                              \
+                __builtin_amdgcn_sched_barrier(0);                                                                    \
+            }                                                                                                         \
+            st = stn;                                                                                                 \
+            if (kt == t_kend - NS - 1) {                                                                              \
+                more = n_more;                                                                                        \
+                if (more) {                                                                                           \
+                    if (t_kend - t_kbeg < 2 * NS - 1) BM_WAIT_VM_LGKM(0, 0);                                          \
+                    kbeg = n_kbeg; kend = n_kend; load_item = item;                                                   \
+                    BM_ADOPT();                                                                                       \
+                }                                                                                                     \
+            }                                                                                                         \
+        }                                                                                                             \
+    }
+        if (NJ == 4 && t_row_end - t_row0 <= RB * 8) BM_TILE_LOOP(RB / 2)
+        else BM_TILE_LOOP(RB)
+#undef BM_TILE_LOOP
+        // last MFMA -> first read of an accumulator, whichever of the two loops ran (see k64w_body)
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[RB / 2 - 1][NJ - 1]), "+a"(acc[RB - 1][NJ - 1]));
         asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[RB - 1][NJ - 1]));
         if (SPLIT && t_kend - t_kbeg < KT) {
             store_partial<RB, NJ>(partial_tile(p.splitk, work, xcd, work.nb - work.full + t_tile, (t_kbeg * work.S + KT - 1) / KT) +
@@ -1191,6 +1200,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
             const bool odd = lane_w & 1;
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
+                if (NJ == 4 && t_row0 + i * 16 >= t_row_end) break;
 #pragma unroll
                 for (int j = 0; j < OC; ++j) {
 #pragma unroll
@@ -1222,6 +1232,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
             uint32_t *stage = reinterpret_cast<uint32_t *>(smem + NS * STAGE) + wave * 1024;
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
+                if (NJ == 4 && t_row0 + i * 16 >= t_row_end) break;
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
                     float x[4];
