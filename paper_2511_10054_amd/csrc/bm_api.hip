@@ -5,7 +5,6 @@
 #include "bm_dispatch_rules.h"
 #include "bm_device_shape.h"
 
-#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <mutex>
@@ -30,11 +29,8 @@ using namespace bm;
 
 constexpr size_t ALIGN = 256;
 constexpr int MAX_SHARED = 8;
-constexpr int SKINNY_MAX_ROWS = 256;   // total rows up to which the weight-streaming path is used,
+constexpr int SKINNY_MAX_ROWS = 256;   // total rows up to which the weight-streaming path is always used,
 constexpr int SKINNY_AVG_ROWS = 16;    // ... and rows per group (averaged over all experts) likewise
-constexpr int SKINNY_MANY_TILES = 512; // layers of so many 128-column tiles, all groups together, fill the tiled path sooner:
-constexpr int SKINNY_MANY_MAX_AVG = 28;   // ... rows per group from which it takes batches of up to SKINNY_MAX_ROWS rows,
-constexpr int SKINNY_MANY_AVG_ROWS = 13;  // ... and rows per group above which it takes the others
 constexpr int SKINNY_UNFIT_ROWS = 16;  // total rows when the widths do not fit its fast kernels but do fit the persistent tiled kernel
 constexpr int SKINNY_KSPLIT = 8;
 constexpr long long STREAM_BYTES = 256ll << 20;   // a layer whose weights the memory-side cache holds does not stream them past it
@@ -87,16 +83,10 @@ constexpr long long NARROW_UNFIT_BYTES = 16ll << 20;
 // fallbacks: there the persistent tiled kernel is faster from 4 tokens on (4 / 8 / 32 tokens: 0.064 / 0.071 /
 // 0.089 against 0.068 / 0.082 / 0.101 ms), so the streaming path keeps only batches of at most 16 rows, unless
 // the two-wave kernel takes the shape (narrow_shape).
-// Streaming | tiled where both widths fit, us: Mixtral-shaped layer (896 column tiles of all experts) 64 / 96 / 112 / 128
-// tokens, public weights 338 364 373 411 | 341 354 355 356, packed 311 340 346 364 | 345 354 351 357 (which of the two the
-// weights are is not known when the workspace is sized); Qwen3-shaped (768) 128 / 192 / 224 / 256 tokens 112 134 145 153 |
-// 132 135 139 140; with few column tiles the tiled path leaves units without one: 16 experts, K = 2, d = F = 2048 (256) at
-// 128 tokens 80 | 90, 64 experts, K = 4, d = F = 1024 (512) at 128 / 256 tokens 69 85 | 79 85, 4 experts, K = 1, d = F =
-// 3072 (96) at 128 tokens 84 | 113, 8 experts, K = 2, d = 2048, F = 4096 (256) 89 | 89.
-// compact: the path that needs less scratch, the streaming one up to SKINNY_MAX_ROWS rows, else the tiled one.
-bool many_tiles(const bm_layer_desc *d) {
-    return k64_shape(d) && (long long)(d->E + (d->n_shared > 0 ? d->n_shared : 0)) * ((d->F + 127) / 128) >= SKINNY_MANY_TILES;
-}
+// Streaming | tiled, us: Mixtral-shaped layer 64 / 96 / 112 / 128 tokens, public weights 338 364 373 411 | 341 354 355 356,
+// packed 311 340 346 364 | 345 354 351 357; Qwen3-shaped 128 / 192 / 224 / 256 tokens 112 134 145 153 | 132 135 139 140.
+// The batches at the upper end would be faster tiled, but that path holds the down projection's output in bf16 until
+// the aggregation, the streaming one in fp32 (error against 64 bits 0.0029 | 0.0023), so the lines stay where they are.
 bool use_skinny(const bm_layer_desc *d, bool compact) {
     if (d->dtype != BM_BF16) return false;
     const int ns = d->n_shared > 0 ? d->n_shared : 0;
@@ -104,10 +94,8 @@ bool use_skinny(const bm_layer_desc *d, bool compact) {
     const bool fit = d->d % 256 == 0 && d->F % 256 == 0;
     if (!fit && k64_shape(d))
         return rows <= SKINNY_UNFIT_ROWS || (!compact && narrow_shape(d) && d->T <= NARROW_UNFIT_T && rows * (2ll * d->F + 4ll * d->d) <= NARROW_UNFIT_BYTES);
-    const int groups = d->E + ns;
-    const bool many = many_tiles(d);
-    if (rows <= SKINNY_MAX_ROWS) return !many || compact || rows < (long long)SKINNY_MANY_MAX_AVG * groups;
-    return fit && !(many && compact) && rows <= (long long)(many ? SKINNY_MANY_AVG_ROWS : SKINNY_AVG_ROWS) * groups;
+    if (rows <= SKINNY_MAX_ROWS) return true;
+    return fit && rows <= (long long)SKINNY_AVG_ROWS * (d->E + ns);
 }
 // Reduction slices of the decode down projection (each slice is a workgroup
 // whose 4 waves split it once more): prefer a count that fits the
@@ -215,16 +203,7 @@ Layout make_layout(const bm_layer_desc *d, bool compact = false) {
     L.probs = take(((d->flags & BM_PSI_TOKEN) && (d->flags & BM_GATE_DIST)) ? (size_t)d->T * d->E * 4 : 0);
     const size_t F = d->F > 0 ? d->F : 0;
     L.h = take((size_t)L.rows_max * F * esz);
-    size_t o_bytes = L.skinny ? (size_t)L.ksplit * L.rows_max * d->d * 4 : (size_t)L.rows_max * d->d * esz;
-    if (!L.skinny && !compact && d->dtype == BM_BF16 && many_tiles(d)) {
-        // a workspace sized for this batch also takes the largest one that streams, whose fp32 output is larger
-        bm_layer_desc s = *d;
-        s.T = SKINNY_MANY_AVG_ROWS * G / (d->K + n_shared);
-        const size_t streamed = (size_t)s.T * (d->K + n_shared);
-        if (s.T < d->T && streamed > SKINNY_MAX_ROWS && use_skinny(&s, false))
-            o_bytes = std::max(o_bytes, skinny_ksplit(&s, false) * streamed * d->d * 4);
-    }
-    L.o = take(o_bytes);
+    L.o = take(L.skinny ? (size_t)L.ksplit * L.rows_max * d->d * 4 : (size_t)L.rows_max * d->d * esz);
     // fp32 partial tiles of the down projection: one 256 x 256 tile per workgroup of the launch
     L.has_splitk = !L.skinny && k64_shape(d) && down_split_tail(d->F);
     L.splitk = take(L.has_splitk ? (size_t)K64_CUS * 256 * 256 * 4 : 0);   // a launch has at most K64_CUS workgroups

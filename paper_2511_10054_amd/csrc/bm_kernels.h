@@ -150,7 +150,7 @@ bool grouping_small(long long assignments, int E);   // launch_grouping takes th
 int launch_gateup_bf16(const GemmParams &p, hipStream_t st);   // c = silu(a b0^T) * (a b1^T), bf16
 int launch_down_bf16(const GemmParams &p, hipStream_t st);     // c = a b0^T, bf16
 bool persistent_device();       // the current device has the shape the persistent prefill kernels are laid out for
-bool down_split_tail(int Kd);   // the down projection of this reduction width may use p.splitk (its split tail)
+bool down_split_tail(int Kd);   // the down projection of this reduction width may use p.splitk (tiles cut along the reduction)
 
 // fp32 projections (the row-tile table lists each live group once); max_rows bounds the rows of all groups
 int launch_gateup_f32(const GemmParams &p, int max_rows, int T, hipStream_t st);

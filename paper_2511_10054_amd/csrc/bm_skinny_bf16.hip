@@ -583,7 +583,7 @@ __device__ __forceinline__ PItem p_setup(const SkinnyParams &p, int it, int NRB,
 // number): the stride of the item walk is then a multiple of the blocks per group, so a workgroup meets the
 // same 16-row blocks - 16 columns of the layer output each - in every live group.  It keeps its finished
 // 16-column slices of every row in LDS instead of writing them out, and once through adds them up per token
-// the way combine_kernel does (slot order, then the shared experts: the same operations in the same order,
+// the way combine_f32_kernel does (slot order, then the shared experts: the same operations in the same order,
 // so the same bits) and writes the layer output: no launch, and no round trip through memory, for the
 // aggregation.
 constexpr int P_COMB_ROWS = 160;                       // rows (assignments + shared-expert rows) the fused form holds
@@ -616,7 +616,7 @@ __global__ void __launch_bounds__(512) skinny_p_kernel(SkinnyParams p) {
     const int NRB = p.N >> 4;
     const int n_items = p.n_mtiles[0] * NRB;
     __shared__ float comb[COMBINE ? P_COMB_BLOCKS * P_COMB_ROWS * 16 : 1];   // [block][row][16 columns]
-// the layer output for this workgroup's 16-column blocks from the slices in comb (see combine_kernel)
+// the layer output for this workgroup's 16-column blocks from the slices in comb (see combine_f32_kernel)
 #define BM_COMBINE_OUT(HAVE_)                                                                           \
     {                                                                                                   \
         const int nbl_ = NRB / (int)gridDim.x;                                                          \
