@@ -983,6 +983,75 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
 // ---------------------------------------------------------------------------
 constexpr int DMA_STREAM = 2;                              // cache policy of a load that is not read again (nt)
 
+// Write-out of a 128-row tile, or of its first 16 * RBL rows: 16 rows at a time through the wave's own 4 KB of LDS (stage)
+// into 16-byte stores, as in k64w_body.  wcol0: first output column of the wave.
+template <bool DUAL, int RBL, int NJ>
+__device__ __forceinline__ void k64s_write(const f32x4 (&acc)[RBL][NJ], uint32_t *stage, uint16_t *c, int N, int t_row0, int t_row_end, int wcol0,
+                                           int t_n_end, int lane) {
+    if (DUAL) {
+        constexpr int OC = NJ / 2;                  // 16-column output blocks per wave
+        constexpr int SD = 20;
+        int lane_w = lane;
+        asm volatile("" : "+v"(lane_w));
+        const int r16 = lane_w & 15, quad = lane_w >> 4;
+        const bool odd = lane_w & 1;
+#pragma unroll
+        for (int i = 0; i < RBL; ++i) {
+            if (NJ == 4 && t_row0 + i * 16 >= t_row_end) break;
+#pragma unroll
+            for (int j = 0; j < OC; ++j) {
+#pragma unroll
+                for (int v = 0; v < 4; v += 2) {
+                    float g0, g1, u0, u1;
+                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(g0) : "a"(acc[i][j][v]));
+                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(g1) : "a"(acc[i][j][v + 1]));
+                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u0) : "a"(acc[i][OC + j][v]));
+                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u1) : "a"(acc[i][OC + j][v + 1]));
+                    const float x0 = silu(g0) * u0;
+                    const float x1 = silu(g1) * u1;
+                    const float send = odd ? x0 : x1;
+                    const float recv = __builtin_bit_cast(
+                        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, true));
+                    const uint32_t pk = odd ? pack_bf16x2(recv, x1) : pack_bf16x2(x0, recv);
+                    const int lrow = 4 * quad + v + (odd ? 1 : 0);
+                    stage[lrow * SD + j * 8 + (r16 >> 1)] = pk;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const int lrow = lane_w / (2 * OC) % 16, pc = lane_w % (2 * OC);
+            const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
+            const int row = t_row0 + i * 16 + lrow, col = wcol0 + pc * 8;
+            if (lane_w < 32 * OC && row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        constexpr int SD = 36;
+        const int r16 = lane & 15, quad = lane >> 4;
+#pragma unroll
+        for (int i = 0; i < RBL; ++i) {
+            if (NJ == 4 && t_row0 + i * 16 >= t_row_end) break;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                float x[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x[v]) : "a"(acc[i][j][v]));
+                u32x2 pk;
+                pk[0] = pack_bf16x2(x[0], x[1]);
+                pk[1] = pack_bf16x2(x[2], x[3]);
+                *reinterpret_cast<u32x2 *>(stage + r16 * SD + j * 8 + 2 * quad) = pk;
+            }
+#pragma unroll
+            for (int t = 0; t < NJ / 2; ++t) {
+                const int q = lane + 64 * t;
+                const int lrow = q / (2 * NJ), pc = q % (2 * NJ);
+                const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
+                const int row = t_row0 + i * 16 + lrow, col = wcol0 + pc * 8;
+                if (row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
+            }
+        }
+    }
+}
+
 template <bool DUAL, bool SPLIT, bool STREAM, int NJ>
 __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &work, const SmallPlan &plan) {
     constexpr int RB = 8;                                  // 16-row blocks of the tile
@@ -1031,7 +1100,6 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
         fa_off[s] = BROWS * 64 + r16 * 64 + pc;
         fb_off[s] = (wave * (DUAL ? NJ * 8 : NJ * 16) + r16) * 64 + pc;
     }
-    f32x4 acc[RB][NJ];
     bf16x8 f0a[RB], f0b[NJ], f1a[RB], f1b[NJ];
     uint32_t oa[NA], ob[NB];
     const uint16_t *base_b0, *base_b1;
@@ -1131,24 +1199,22 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
         BM_NEXT_ITEM(n_more, n_kbeg, n_kend);
         if (n_more) BM_LOOKUP(work.small0 + item);
         bool more = false;
-#pragma unroll
-        for (int i = 0; i < RB; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
-        asm volatile("s_nop 7" : "+a"(acc[0][0]));
-        BM_BARE_BARRIER();
         // The k-steps, on the first RBL_ row blocks: a tile of at most 64 rows leaves the others out of the matrix work, the
         // fragment reads and the write-out (not of the loads: the waits count them): what they do not draw lets the others
         // clock higher (layers, us: DeepSeek-shaped 32 tokens 83 -> 80, Qwen3-shaped 512 / 2048 tokens 159 272 -> 155 261).  The
         // narrow loop does without: its launches are short, and the larger kernel costs them as much as it gives.
-#define BM_TILE_LOOP(RBL_)                                                                                            \
+#define BM_TILE(RBL_)                                                                                            \
     {                                                                                                                 \
         constexpr int NM = (RBL_) * NJ;                        /* MFMAs per k slice of 32 */                          \
         constexpr int NR = (RBL_) + NJ;                        /* fragment reads per k slice */                       \
         constexpr int RSTEP = NM >= 2 * NR ? 2 : 1;            /* MFMAs per fragment read */                          \
         static_assert(NR * RSTEP <= NM, "every fragment is read under the slice before its own");                     \
+        f32x4 acc[RBL_][NJ];                                                                                          \
+        _Pragma("unroll") for (int i = 0; i < (RBL_); ++i)                                                            \
+            _Pragma("unroll") for (int j = 0; j < NJ; ++j)                                                            \
+                _Pragma("unroll") for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;                                    \
+        asm volatile("s_nop 7" : "+a"(acc[0][0]));                                                                    \
+        BM_BARE_BARRIER();                                                                                            \
         _Pragma("unroll") for (int d = 0; d < NR; ++d) BM_RD(d, f0a, f0b, st, 0)                                      \
         for (int kt = t_kbeg; kt < t_kend; ++kt) {                                                                    \
             const int kl = more ? kbeg + (kt + NS - t_kend) : kt + NS;                                                \
@@ -1177,82 +1243,20 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
                 }                                                                                                     \
             }                                                                                                         \
         }                                                                                                             \
+        /* last MFMA -> first access to an accumulator (see k64w_body).  Each loop has its own accumulators and its own */\
+        /* write-out: joined behind the two loops, the compiler moves accumulators to other registers in front of */  \
+        /* the wait, wherever it stands and whichever of them it is tied to */                                        \
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[(RBL_) - 1][NJ - 1]));                                         \
+        if (SPLIT && t_kend - t_kbeg < KT)                                                                            \
+            store_partial<(RBL_), NJ>(partial_tile(p.splitk, work, xcd, work.nb - work.full + t_tile,                 \
+                                                   (t_kbeg * work.S + KT - 1) / KT) + wave * (RB * NJ * 256), acc, t_row0, t_row_end);\
+        else                                                                                                          \
+            k64s_write<DUAL, (RBL_), NJ>(acc, reinterpret_cast<uint32_t *>(smem + NS * STAGE) + wave * 1024, c, N, t_row0, t_row_end,\
+                                         t_n0 + wave * (DUAL ? 8 : 16) * NJ, t_n_end, lane);                          \
     }
-        if (NJ == 4 && t_row_end - t_row0 <= RB * 8) BM_TILE_LOOP(RB / 2)
-        else BM_TILE_LOOP(RB)
-#undef BM_TILE_LOOP
-        // last MFMA -> first read of an accumulator, whichever of the two loops ran (see k64w_body)
-        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[RB / 2 - 1][NJ - 1]), "+a"(acc[RB - 1][NJ - 1]));
-        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[RB - 1][NJ - 1]));
-        if (SPLIT && t_kend - t_kbeg < KT) {
-            store_partial<RB, NJ>(partial_tile(p.splitk, work, xcd, work.nb - work.full + t_tile, (t_kbeg * work.S + KT - 1) / KT) +
-                                      wave * (RB * NJ * 256), acc, t_row0, t_row_end);
-            if (!more) break;
-            continue;
-        }
-        if (DUAL) {
-            constexpr int OC = NJ / 2;                  // 16-column output blocks per wave
-            constexpr int SD = 20;
-            uint32_t *stage = reinterpret_cast<uint32_t *>(smem + NS * STAGE) + wave * 1024;
-            int lane_w = lane;
-            asm volatile("" : "+v"(lane_w));
-            const int r16 = lane_w & 15, quad = lane_w >> 4;
-            const bool odd = lane_w & 1;
-#pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                if (NJ == 4 && t_row0 + i * 16 >= t_row_end) break;
-#pragma unroll
-                for (int j = 0; j < OC; ++j) {
-#pragma unroll
-                    for (int v = 0; v < 4; v += 2) {
-                        float g0, g1, u0, u1;
-                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(g0) : "a"(acc[i][j][v]));
-                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(g1) : "a"(acc[i][j][v + 1]));
-                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u0) : "a"(acc[i][OC + j][v]));
-                        asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(u1) : "a"(acc[i][OC + j][v + 1]));
-                        const float x0 = silu(g0) * u0;
-                        const float x1 = silu(g1) * u1;
-                        const float send = odd ? x0 : x1;
-                        const float recv = __builtin_bit_cast(
-                            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, true));
-                        const uint32_t pk = odd ? pack_bf16x2(recv, x1) : pack_bf16x2(x0, recv);
-                        const int lrow = 4 * quad + v + (odd ? 1 : 0);
-                        stage[lrow * SD + j * 8 + (r16 >> 1)] = pk;
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                const int lrow = lane_w / (2 * OC) % 16, pc = lane_w % (2 * OC);
-                const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
-                const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * (16 * OC) + pc * 8;
-                if (lane_w < 32 * OC && row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-            constexpr int SD = 36;
-            uint32_t *stage = reinterpret_cast<uint32_t *>(smem + NS * STAGE) + wave * 1024;
-#pragma unroll
-            for (int i = 0; i < RB; ++i) {
-                if (NJ == 4 && t_row0 + i * 16 >= t_row_end) break;
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    float x[4];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) x[v] = acc[i][j][v];
-                    u32x2 pk;
-                    pk[0] = pack_bf16x2(x[0], x[1]);
-                    pk[1] = pack_bf16x2(x[2], x[3]);
-                    *reinterpret_cast<u32x2 *>(stage + r16 * SD + j * 8 + 2 * quad) = pk;
-                }
-#pragma unroll
-                for (int t = 0; t < NJ / 2; ++t) {
-                    const int q = lane + 64 * t;
-                    const int lrow = q / (2 * NJ), pc = q % (2 * NJ);
-                    const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
-                    const int row = t_row0 + i * 16 + lrow, col = t_n0 + wave * (16 * NJ) + pc * 8;
-                    if (row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
-                }
-            }
-        }
+        if (NJ == 4 && t_row_end - t_row0 <= RB * 8) BM_TILE(RB / 2)
+        else BM_TILE(RB)
+#undef BM_TILE
         if (!more) break;
     }
     BM_WAIT_VM_LGKM(0, 0);
