@@ -243,7 +243,12 @@ int bm_permute_by_expert(const bm_layer_desc *desc, const int32_t *ids_remapped,
  * bf16: MFMA with fp32 accumulation, h and o held in bf16 between the two
  * projections; fp32: fp32 products and sums throughout (matrix instructions, the
  * sums as trees; widths that are no multiple of 32 and arrays off a 16-byte
- * boundary row by row). */
+ * boundary row by row).
+ * Equal calls give equal bits.  fp32: a token's y is the same bits whatever batch
+ * it is part of.  bf16: y can differ in rounding with the rest of the batch - its
+ * size chooses the kernels, and in a batch of prefill size the tile that a row falls
+ * into says where the sum over the reduction starts and, for F >= 4096, into which
+ * pieces it is cut; two equal tokens of one such batch can differ so as well. */
 int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *weights,
                    const uint64_t *residency_bitmap, const int32_t *buddy_table, void *y,
                    void *workspace, size_t workspace_bytes, const bm_debug_out *dbg,

@@ -252,7 +252,8 @@ __global__ void __launch_bounds__(256, 3) grouped_gemm_f32_kernel(GemmParams p, 
     const size_t gofs = (size_t)(g < p.E ? g : g - p.E) * p.N * p.Kd;
     const float *b0 = static_cast<const float *>(g < p.E ? p.b0 : p.sb0) + gofs;
     const float *b1 = DUAL ? static_cast<const float *>(g < p.E ? p.b1 : p.sb1) + gofs : b0;
-    const int rot = (((unit >> 3) * 5) & 31) * (p.Kd >> 5) >> 5;
+    // (by expert and output columns, not by the unit's number: a token's bits then do not depend on the rest of the batch)
+    const int rot = (((g * ((n_nt + 7) >> 3) + (nt >> 3)) * 5) & 31) * (p.Kd >> 5) >> 5;
     const bool once = p.stream && end - p.offsets[g] <= F32_ROWS;
     for (int row0 = p.offsets[g] + chunk * F32_ROWS; row0 < end; row0 += chunks * F32_ROWS) {
         const int row_end = min(end, row0 + F32_ROWS), n_rows = row_end - row0;

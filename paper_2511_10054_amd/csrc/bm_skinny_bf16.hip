@@ -491,7 +491,8 @@ __device__ __forceinline__ void skinny_lds_item(const SkinnyParams &p, u32x4 *xs
     // multiple of 4 KB apart in many layers, and workgroups in step ask the same memory channels, more or less so by where the
     // weights lie (us, by process, in step | from different chunks: Mixtral-shaped 32 tokens 182 to 194 | 177, DeepSeek-shaped 8
     // tokens 30 to 34 | 28, Qwen3-shaped 16 tokens 31 to 35 | 31, 128 tokens 52 to 60 | 52).  The down projections: no gain.
-    const int rot = DUAL ? (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) >> 3 : 0;
+    // By the group, not by its slot in the list, so that a row's bits do not depend on which other groups are live.
+    const int rot = DUAL ? (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * g)) >> 3 : 0;
     constexpr int PASS_ROWS = 16 * MAXNBT;
     for (int rb = row_begin; rb < row_end; rb += PASS_ROWS) {
         const int re = min(row_end, rb + PASS_ROWS);
