@@ -660,10 +660,8 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
         _Pragma("unroll") for (int j = 0; j < 8; ++j) {                                            \
             const int r_ = 8 * (4 * j + wave) + (lane_ >> 3);                                      \
             const int piece_ = (lane_ & 7) ^ ((r_ >> 1) & 7);                                      \
-            if (j < MI) {                                                                          \
-                const int src_ = __builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane_ >> 3)), rmv_);   \
-                oa[j] = ((uint32_t)src_ * (uint32_t)Kd + piece_ * 8) * 2u;                         \
-            }                                                                                      \
+            const int src_ = __builtin_amdgcn_ds_bpermute(4 * (8 * j + (lane_ >> 3)), rmv_);       \
+            oa[j] = ((uint32_t)src_ * (uint32_t)Kd + piece_ * 8) * 2u;                             \
             /* DUAL: rows 0-127 of the part are W_gate rows (loads 0-3), rows 128-255 W_up rows (4-7) */ \
             const int n_ = DUAL ? min(n0 + (r_ & 127), N - 1) : min(n0 + r_, N - 1);               \
             ob[j] = ((uint32_t)n_ * (uint32_t)Kd + piece_ * 8) * 2u;                               \
@@ -713,7 +711,9 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
 //     wait to all 64 accumulators instead made the allocator spill 128 registers);
 //   - last MFMA of a tile (acc[MI - 1][7]) -> first read of an accumulator by another instruction (write-out,
 //     partial-tile store): an 8-pass MFMA result needs 11 wait states (18 for a 16-pass one); 32 are
-//     inserted where the write-out starts.  Every other accumulator's MFMA is at least 16 cycles older.
+//     inserted where the write-out starts.  Every other accumulator's MFMA is at least 16 cycles older.  The write-outs
+//     read accumulators through assembly statements (volatile, so in order behind the wait): where the compiler reads them by
+//     itself it also moves the accumulator that the wait is tied to, in front of the wait.
 // Inside the loop an accumulator is next touched by its own MFMA 63 instructions later (same register as
 // destination and third operand), which the MFMA pipeline interlocks by itself.
 // Down projection: the weight fragment is the first operand, so the product comes out transposed, i.e. a
@@ -794,7 +794,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
                 for (int m = 0; m < NM; ++m) {                                                                        \
                     if (COMPUTE_) BM_MFMA1(m, f0a, f0b);                                                              \
                     if ((COMPUTE_) && m < 2 * NR && (m & 1) == 0) BM_RD(m >> 1, f1a, f1b, sa_, sb_)                   \
-                    if (MI == 8 ? (m & 7) == 5 : (m & 3) == 1) BM_DMA_B(sAp, kl, MI == 8 ? m >> 3 : m >> 2);          \
+                    if ((m & 7) == 5) BM_DMA_B(sAp, kl, m >> 3);                                                      \
                     __builtin_amdgcn_sched_barrier(0);                                                                \
                 }                                                                                                     \
             }                                                                                                         \
@@ -830,14 +830,13 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
             }                                                                                                         \
         }                                                                                                             \
     }
-        // Down projection: a tile of at most 128 rows leaves the two waves of the lower row half nothing but
-        // padding.  They keep their share of the loads, the waits and the barriers - the same instruction
+        // Down projection of 256-row tiles alone (SPLIT; a launch of both heights has no such tile): a tile of at most
+        // 128 rows leaves the two waves of the lower row half nothing but padding.  They keep their share of the loads, the waits and the barriers - the same instruction
         // stream minus every MFMA and fragment read - and skip the write-out: the chip runs these kernels
         // against its power limit, and what the idle matrix cores do not draw lets the others clock higher
-        // (Qwen3-shaped layer, 41 % padding: down projection -6 %).  The gate/up instantiation keeps the single
-        // loop (a second copy costs it registers and 2 % of its time).
-        const bool live = DUAL || !(wm == 1 && t_row_end - t_row0 <= MI * 16);
-        if (DUAL || live) BM_TILE_LOOP(true)
+        // (Qwen3-shaped layer, 41 % padding: down projection -6 %).
+        const bool live = !SPLIT || !(wm == 1 && t_row_end - t_row0 <= MI * 16);
+        if (!SPLIT || live) BM_TILE_LOOP(true)
         else BM_TILE_LOOP(false)
 #undef BM_TILE_LOOP
         // The tile is done.  The slot A(last k-step) sat in is free for every wave since the barrier in
@@ -927,7 +926,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
                 for (int j = 0; j < OC; ++j) {
                     float x[4];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) x[v] = acc[i][j][v];
+                    for (int v = 0; v < 4; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x[v]) : "a"(acc[i][j][v]));
                     u32x2 pk;
                     pk[0] = pack_bf16x2(x[0], x[1]);
                     pk[1] = pack_bf16x2(x[2], x[3]);
@@ -1027,28 +1026,37 @@ __device__ __forceinline__ void k64s_write(const f32x4 (&acc)[RBL][NJ], uint32_t
     } else {
         constexpr int SD = 36;
         const int r16 = lane & 15, quad = lane >> 4;
-#pragma unroll
-        for (int i = 0; i < RBL; ++i) {
-            if (NJ == 4 && t_row0 + i * 16 >= t_row_end) break;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                float x[4];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x[v]) : "a"(acc[i][j][v]));
-                u32x2 pk;
-                pk[0] = pack_bf16x2(x[0], x[1]);
-                pk[1] = pack_bf16x2(x[2], x[3]);
-                *reinterpret_cast<u32x2 *>(stage + r16 * SD + j * 8 + 2 * quad) = pk;
-            }
+        u32x4 val[2][NJ / 2];                       // a block's pieces are stored once the next block's are on their way
+        auto store = [&](int i) {
 #pragma unroll
             for (int t = 0; t < NJ / 2; ++t) {
                 const int q = lane + 64 * t;
-                const int lrow = q / (2 * NJ), pc = q % (2 * NJ);
-                const u32x4 val = *reinterpret_cast<const u32x4 *>(stage + lrow * SD + pc * 4);
-                const int row = t_row0 + i * 16 + lrow, col = wcol0 + pc * 8;
-                if (row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val);
+                const int row = t_row0 + i * 16 + q / (2 * NJ), col = wcol0 + q % (2 * NJ) * 8;
+                if (row < t_row_end && col < t_n_end) stg128(&c[(size_t)row * N + col], val[i & 1][t]);
             }
+        };
+#pragma unroll
+        for (int i = 0; i < RBL; ++i) {
+            if (t_row0 + i * 16 < t_row_end) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    float x[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x[v]) : "a"(acc[i][j][v]));
+                    u32x2 pk;
+                    pk[0] = pack_bf16x2(x[0], x[1]);
+                    pk[1] = pack_bf16x2(x[2], x[3]);
+                    *reinterpret_cast<u32x2 *>(stage + r16 * SD + j * 8 + 2 * quad) = pk;
+                }
+#pragma unroll
+                for (int t = 0; t < NJ / 2; ++t) {
+                    const int q = lane + 64 * t;
+                    val[i & 1][t] = *reinterpret_cast<const u32x4 *>(stage + q / (2 * NJ) * SD + q % (2 * NJ) * 4);
+                }
+            }
+            if (i > 0) store(i - 1);
         }
+        store(RBL - 1);
     }
 }
 
