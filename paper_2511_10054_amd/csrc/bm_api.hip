@@ -33,7 +33,6 @@ constexpr int SKINNY_MAX_ROWS = 256;   // total rows up to which the weight-stre
 constexpr int SKINNY_AVG_ROWS = 16;    // ... and rows per group (averaged over all experts) likewise
 constexpr int SKINNY_UNFIT_ROWS = 16;  // total rows when the widths do not fit its fast kernels but do fit the persistent tiled kernel
 constexpr int SKINNY_KSPLIT = 8;
-constexpr long long STREAM_BYTES = 256ll << 20;   // a layer whose weights the memory-side cache holds does not stream them past it
 
 // Shapes both projections of which fit the persistent k-step-64 kernel: reduction widths that are multiples
 // of 64 and at least 256, operands within 32-bit byte offsets.
@@ -197,7 +196,7 @@ Layout make_layout(const bm_layer_desc *d, bool compact = false) {
     L.n_mtiles_b = take(mixed ? 16 : 0);
     L.mt_group_s = take(mixed ? (size_t)G * 4 : 0);
     L.mt_row0_s = take(mixed ? (size_t)G * 4 : 0);
-    L.n_mtiles_s = take(mixed ? 16 + 4 * K64_XCDS : 0);    // and the number of pieces that each XCD cuts tiles into
+    L.n_mtiles_s = take(mixed ? 16 + 4 * K64_XCDS : 0);    // tiles, rows, live groups; then the pieces that each XCD cuts tiles into
     L.stats = take(32);
     // every expert's probability per token: only when the substitution runs apart from the router kernel
     L.probs = take(((d->flags & BM_PSI_TOKEN) && (d->flags & BM_GATE_DIST)) ? (size_t)d->T * d->E * 4 : 0);
@@ -621,7 +620,7 @@ int bm_moe_forward(const bm_layer_desc *desc, const void *x, const bm_weights *w
     gp.c = at<void>(ws, L.h);
     gp.N = desc->F; gp.Kd = desc->d; gp.E = E; gp.n_groups = G; gp.max_mtiles = L.mtiles_max; gp.BM = sp.BM;
     gp.mt_group = sp.mt_group; gp.mt_row0 = sp.mt_row0; gp.n_mtiles = sp.n_mtiles; gp.offsets = sp.offsets;
-    gp.stream = (bf16 ? 6ll : 12ll) * G * desc->d * desc->F > STREAM_BYTES ? 1 : 0;
+    gp.cached_groups = cached_groups(desc);
     GemmParams dp = gp;
     auto use_mixed = [&](GemmParams &q) {
         q.mixed = 1; q.BM = 256;

@@ -53,6 +53,16 @@ inline bool narrow_down(const bm_layer_desc *d, bool compact) {
     return narrow_down_whole(d, compact) && !quarter_split_projection(d, d->d, d->F);
 }
 
+// Most live groups whose three matrices the 256 MB memory-side cache holds until the layer's next call.  The tiled kernels
+// load weights that are read once non-temporally where a batch has more live groups than that (a count that the grouping leaves on
+// the device: most experts of a layer may be absent).  us, plain | non-temporal, warm, bf16: 16 of 64 experts resident, d = F = 1024, 101 MB
+// of 403, 600 / 1500 / 3000 tokens 54 69 96 | 57 72 102; 24 of 96, d = 1024, F = 512, 75 MB of 302, 1000 / 3000 tokens 57 73 |
+// 59 75; 48 of 48, d = F = 1024, 302 MB, level; Qwen3-shaped, 604 MB, 512 tokens gate/up 85 | 79.
+constexpr long long MEMORY_SIDE_CACHE = 256ll << 20;
+inline int cached_groups(const bm_layer_desc *d) {
+    return (int)(MEMORY_SIDE_CACHE / ((d->dtype == BM_BF16 ? 6ll : 12ll) * d->d * d->F));
+}
+
 // Tokens of a tile of the stand-alone substitution kernel, and the most tokens that a single workgroup takes.  It stores
 // the counters itself and needs no launch in front of it that zeroes them (1.8 us), but takes the tiles one after the
 // other.  One workgroup | one per tile, us: 8 of 128 experts, no ties between a token's slots, 65 / 128 / 192 tokens 5.9

@@ -634,7 +634,7 @@ __device__ void write_mixed_tile_tables(const ScanParams &p, const int32_t *star
     if (wave != nw - 1) return;
     const int G = p.E + p.n_shared;
     constexpr int PER = (BM_MAX_E + 8 + 63) / 64;
-    int nb[PER], ns[PER], sum_b = 0, sum_s = 0;
+    int nb[PER], ns[PER], sum_b = 0, sum_s = 0;        // sum_s: 128-row tiles, and live groups from bit 16 on
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const int g = lane * PER + i;
@@ -643,10 +643,10 @@ __device__ void write_mixed_tile_tables(const ScanParams &p, const int32_t *star
         nb[i] = (n >> 8) + (rest > 128 ? 1 : 0);
         ns[i] = (rest >= 1 && rest <= 128) ? 1 : 0;
         sum_b += nb[i];
-        sum_s += ns[i];
+        sum_s += ns[i] + (n > 0 ? 1 << 16 : 0);
     }
     int tot_b, tot_s;
-    int run_b = wave_excl_scan(sum_b, tot_b), run_s = wave_excl_scan(sum_s, tot_s);
+    int run_b = wave_excl_scan(sum_b, tot_b), run_s = wave_excl_scan(sum_s, tot_s) & 0xffff;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const int g = lane * PER + i;
@@ -663,7 +663,7 @@ __device__ void write_mixed_tile_tables(const ScanParams &p, const int32_t *star
     }
     if (lane == 0) {
         p.n_mtiles_b[0] = tot_b; p.n_mtiles_b[1] = start[G];
-        p.n_mtiles_s[0] = tot_s; p.n_mtiles_s[1] = start[G];
+        p.n_mtiles_s[0] = tot_s & 0xffff; p.n_mtiles_s[1] = start[G]; p.n_mtiles_s[2] = tot_s >> 16;
     }
 }
 

@@ -969,9 +969,8 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
 //   Waves: each owns 64 weight rows and all 128 activation rows, so a weight fragment is read from LDS once.
 //   Streaming: the weights are loaded non-temporally (STREAM; they are not read again, and would push activations and
 //   router matrix out of the L2: Qwen3-shaped layer at 512 tokens, gate/up 85 -> 79 us, the next front kernel 19.4 -> 15.6),
-//   unless the layer's weights are few enough to stay in the 256 MB memory-side cache until its next call (us, plain |
-//   non-temporal: 64 experts, d = F = 512, 101 MB, 3000 tokens 24.3 | 26.0, d = 1024, F = 512, 201 MB 48 + 30 | 52 + 33; 48
-//   experts, d = F = 1024, 302 MB, level); and the tiles of an XCD enter the reduction at 32 different places and walk it as a circle: weight rows lie a
+//   unless those of the live groups are few enough to stay in the 256 MB memory-side cache until the next call (cached_groups);
+//   and the tiles of an XCD enter the reduction at 32 different places and walk it as a circle: weight rows lie a
 //   multiple of 4 KB apart in many layers, and workgroups in step all ask the same memory channels (256 units reading
 //   panels of 256 rows of 4 / 8 KB: 4.2 TB/s in step, 5.9 / 6.1 TB/s from 32 places, 6.5 / 6.7 non-temporally too; 1.5 KB
 //   rows 4.6 -> 5.5, 28 KB rows 6.0 -> 7.0).  What an XCD misses in its L2 comes at 7 TB/s for the whole chip, from the
@@ -1281,7 +1280,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
 
 // Both tile heights in one launch: p.mt_group / mt_row0 / n_mtiles list the 256-row tiles, p.mt_group_s / mt_row0_s /
 // n_mtiles_s the 128-row tiles.
-template <bool DUAL, bool SPLIT, bool STREAM>
+template <bool DUAL, bool SPLIT, bool MAY_STREAM>
 __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmParams p) {
     const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
     XcdWork work;
@@ -1294,19 +1293,29 @@ __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmP
     // streaming is spread over the launch instead of bunched at its end (Qwen3-shaped layer, 2048 tokens:
     // gate/up 141 -> 133 us); with few of them that order only delays 256-row tiles (Mixtral-shaped prefill
     // + 1 %, 1024 tokens + 3 %).
+    // MAY_STREAM: all of the layer's groups together outgrow the memory-side cache; whether the live ones do is known here.  (Layers
+    // that never do have a kernel without the second copies: 0.8 us of 50 in launches of short reductions.)
+    // The cut down projection streams whatever the size of its weights: d = 1024 .. 2048, F = 4096 .. 5120, 50 to 130 MB, warm,
+    // 200 to 1000 tokens: the same to 1 % either way.
+    const bool stream = SPLIT || (MAY_STREAM && p.n_mtiles_s[2] > p.cached_groups);
     if (!SPLIT && plan.narrow) {
-        k64s_body<DUAL, SPLIT, STREAM, 2>(p, work, plan);
+        if (stream) k64s_body<DUAL, SPLIT, true, 2>(p, work, plan);
+        else k64s_body<DUAL, SPLIT, false, 2>(p, work, plan);
         return;
     }
     const bool small_first = small_tiles(p) * 4 >= p.n_mtiles[0] && ((blockIdx.x >> 3) & 1);
+    const auto small = [&]() {
+        if (stream) k64s_body<DUAL, SPLIT, true, 4>(p, work, plan);
+        else k64s_body<DUAL, SPLIT, false, 4>(p, work, plan);
+    };
     if (small_first) {
-        k64s_body<DUAL, SPLIT, STREAM, 4>(p, work, plan);
+        small();
         __syncthreads();      // the last write-out's staging area becomes the next phase's first load target
         k64w_body<DUAL, SPLIT>(p, work);
     } else {
         k64w_body<DUAL, SPLIT>(p, work);
         __syncthreads();
-        k64s_body<DUAL, SPLIT, STREAM, 4>(p, work, plan);
+        small();
     }
 }
 
@@ -1397,9 +1406,10 @@ static bool k64_ok(const GemmParams &p) {
 
 template <bool DUAL>
 static void launch_mixed(const GemmParams &p, hipStream_t st) {
-    const dim3 grid(K64_CUS);
-    if (p.stream) hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<DUAL, false, true>), grid, dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<DUAL, false, false>), grid, dim3(256), 0, st, p);
+    if (p.n_groups > p.cached_groups)
+        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<DUAL, false, true>), dim3(K64_CUS), dim3(256), 0, st, p);
+    else
+        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<DUAL, false, false>), dim3(K64_CUS), dim3(256), 0, st, p);
 }
 
 int launch_gateup_bf16(const GemmParams &p, hipStream_t st) {
@@ -1421,8 +1431,6 @@ int launch_down_bf16(const GemmParams &p, hipStream_t st) {
     if (p.BM == 256 && k64_ok(p) && p.splitk != nullptr && down_split_tail(p.Kd)) {
         GemmParams q = p;
         q.split_stride = K64_CUS / K64_XCDS;
-        // (streamed past the memory-side cache whatever their size: d = 1024 .. 2048, F = 4096 .. 5120, 50 to 130 MB of
-        // weights, warm, 200 to 1000 tokens: the same to 1 % either way)
         hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false, true, true>), dim3(K64_CUS), dim3(256), 0, st, q);
         hipLaunchKernelGGL(split_fixup_kernel, dim3(K64_XCDS * 16 * FIXUP_TILES), dim3(256), 0, st, q);
     } else if (p.mixed && k64_ok(p)) {

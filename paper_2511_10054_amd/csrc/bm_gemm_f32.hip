@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(256) rowwise_f32_kernel(GemmParams p) {
 //    over the lanes), and the error against 64 bits is no larger.  Short reductions, where that tree was most of
 //    the sum, take CHAIN = 1; from 1024 on CHAIN = 2 spares a third of the additions.
 //  - Weights of a group that one row tile covers are not read again: they are loaded non-temporally (AUX = 2; unless the
-//    memory-side cache holds all of the layer's weights until its next call), and the units
+//    memory-side cache holds the weights of all live groups until the layer's next call), and the units
 //    of an XCD enter the reduction at 32 different places and walk it as a circle (rot; the tree's shape stays): weight
 //    rows lie a multiple of 4 KB apart in many layers, and workgroups in step all ask the same memory channels.
 //    Qwen3-shaped layer at 16 tokens 76 + 42 -> 64 + 38 us, DeepSeek-shaped at 8 tokens 74 + 30 -> 59 + 27.
@@ -254,7 +254,7 @@ __global__ void __launch_bounds__(256, 3) grouped_gemm_f32_kernel(GemmParams p, 
     const float *b1 = DUAL ? static_cast<const float *>(g < p.E ? p.b1 : p.sb1) + gofs : b0;
     // (by expert and output columns, not by the unit's number: a token's bits then do not depend on the rest of the batch)
     const int rot = (((g * ((n_nt + 7) >> 3) + (nt >> 3)) * 5) & 31) * (p.Kd >> 5) >> 5;
-    const bool once = p.stream && end - p.offsets[g] <= F32_ROWS;
+    const bool once = p.n_mtiles[0] > p.cached_groups && end - p.offsets[g] <= F32_ROWS;
     for (int row0 = p.offsets[g] + chunk * F32_ROWS; row0 < end; row0 += chunks * F32_ROWS) {
         const int row_end = min(end, row0 + F32_ROWS), n_rows = row_end - row0;
 #define BM_F32_TILE(NBT_)                                                                                             \

@@ -93,7 +93,7 @@ struct GemmParams {
     int mixed;                    // both tile heights in one launch: the table above lists the 256-row tiles and
     const int32_t *mt_group_s, *mt_row0_s, *n_mtiles_s;   // ... this one the 128-row tiles
     float *splitk;                // scratch for the partial tiles of tiles that are cut along the reduction, or null: none is
-    int stream;                   // the layer's weights outgrow the memory-side cache: those read once are loaded non-temporally
+    int cached_groups;            // most live groups whose weights the memory-side cache holds: of more, weights read once are loaded non-temporally
     int32_t *split_pieces;        // [K64_XCDS] pieces of a cut tile, XCD by XCD, as the launch that cuts them chose
     int split_stride;             // workgroups per XCD of that launch
 };
