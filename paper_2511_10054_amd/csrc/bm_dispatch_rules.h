@@ -74,6 +74,15 @@ inline int remap_one_workgroup_tokens(int K, uint32_t flags) {
     return K <= 8 && !(flags & BM_PSI_TOKEN) ? 96 : REMAP_TOK;
 }
 
+// Co-activation counts in chunks of 512 tokens instead of 1024: better while the additions to the totals are few or the tokens'
+// slots many.  Time of 512 over 1024, calls of a captured graph (from Python a call takes 7.3 us to issue, more than most of these
+// run), at 1000 / 2048 / 4096 / 8192 / 16384 tokens: up to 8 slots of 8 or 16 experts .90 .89 .90 .93 1.00 (32768: 1.11); 4 slots of
+// 64 experts .91 .97 1.07 1.23 1.38, of 256 .95 .98 1.07 1.20 1.05; 8 slots of 16 experts .71 .71 .71 .74 .78, of 64 .74 .78 .85
+// .99 1.16, of 128 .75 .80 .88 1.02 1.08, of 256 .81 .87 1.00 1.15 .94 (8192 tokens 12.1 us in chunks of 1024).
+inline bool coact_short_chunks(int T, int K, int E) {
+    return T <= 2048 || (K >= 8 ? (long long)T * E <= 1 << 19 : E <= 16 && T <= 16384);
+}
+
 // Words between the assignment sets of consecutive experts in LDS, for A assignments (bit a % 64 of word a / 64).  Long sets
 // lie an odd number of words apart: at 16 or 32 words the same word of every expert's set is in one bank (grouping of
 // 1024 / 2048 assignments of 16 experts 6.0 13.8 us, an odd number 4.6 6.1; layers of 8 experts, 2048 assignments 45.4 -> 41.0).

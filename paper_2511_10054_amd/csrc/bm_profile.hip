@@ -6,6 +6,7 @@
 //                       frequency threshold
 //
 // Both are exact integer work up to one fp64 comparison per list entry.
+#include "bm_dispatch_rules.h"
 #include "bm_kernels.h"
 
 namespace bm {
@@ -19,11 +20,8 @@ namespace bm {
 // 4096 tokens of 8 out of 128 experts).  The kernel it
 // replaces walked a token per wave with lane permutes and flushed a whole triangle every 64 tokens: 41 us.
 // CO_TOK = 512 halves the chain of a workgroup (sets to clear, bits to set that meet in a bank, words of a pair to count) and
-// doubles the additions to the totals: better while those are few or the tokens' slots many (us, 1024 | 512: 128 experts, 8 a
-// token, 1000 / 4096 tokens 6.6 7.0 | 4.8 5.8, 8192 / 16384 tokens 0.96, 0.99 of the time; 5 a token, 2048 / 4096 / 8192
-// tokens 0.89, 0.91, 1.09; 64 experts 0.92, 1.03, 1.24; 16 experts 0.72 to 0.95 at every size).
+// doubles the additions to the totals; which it takes: coact_short_chunks.
 constexpr int CO_ROWS = 4;
-static bool coact_short_chunks(int T, int K, int E) { return T <= 2048 || E <= 16 || (K >= 8 && T <= 8192); }
 
 template <int CO_TOK>
 __global__ void __launch_bounds__(CO_TOK) coact_kernel(const int32_t *ids, int T, int K, int E, unsigned long long *A,
