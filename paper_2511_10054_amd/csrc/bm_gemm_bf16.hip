@@ -25,24 +25,11 @@
 // 16-byte slots (measured: zero bank-conflict cycles).
 #include "bm_kernels.h"
 #include "bm_device_shape.h"
-#include "bm_tile_dealer.h"
+#include "bm_tile_schedule.h"
 
 namespace bm {
 
 constexpr int G_BN = 256, G_BK = 64;
-
-// Logical tile id -> (row tile, column tile).  The 32 workgroups that run together on one XCD (its
-// 32 compute units take consecutive ids) form a block of GM row tiles x 32/GM column tiles, so they
-// share GM activation tiles and 32/GM weight panels in that XCD's L2 instead of 32 + 1.
-constexpr int G_GM = 4;
-__device__ __forceinline__ void tile_of(int lid, int n_mt, int n_nt, int &mt, int &nt) {
-    const int per_group = G_GM * n_nt;
-    const int group = lid / per_group, in_group = lid - group * per_group;
-    const int first = group * G_GM;
-    const int gsize = min(n_mt - first, G_GM);
-    nt = in_group / gsize;
-    mt = first + (in_group - nt * gsize);
-}
 
 __device__ __forceinline__ int lds_slot(int row, int piece) { return row * G_BK + ((piece ^ ((row >> 1) & 7)) << 3); }
 
@@ -418,75 +405,6 @@ constexpr int P_PART = 256 * 64;                       // bf16 elements per part
 #define BM_WAIT_VM_LGKM(vm, lgkm) \
     __builtin_amdgcn_s_waitcnt(((vm) & 15) | (7 << 4) | ((lgkm) << 8) | (((vm) >> 4) << 14))
 
-// One XCD's share of a launch that runs both tile heights.  Its workgroups (stride of them) take its 256-row tiles round by
-// round, then its 128-row tiles (SmallTileDealer).  SPLIT: the 256-row tiles that do not fill a round (R of them) and the
-// 128-row tiles are cut along the reduction into S pieces each, so that the last round is short; the pieces
-// leave fp32 partial tiles in scratch memory and split_fixup_kernel adds them up.  All tiles are cut at the same places and
-// first pieces go out before second ones, because workgroups that run together share panels in the XCD's L2 only
-// while they are at the same k: pieces of equal cost laid end to end (every workgroup at a k of its own)
-// fetch 64 KB a k-step from outside the XCD, 2.4 us at the 28 GB/s that a unit gets there.
-constexpr int SPLIT_COST = 160, SPLIT_COST_PART = 40;   // of partial tiles and their sums, in twentieths of a 256-row k-step
-constexpr int SPLIT_MAX = 8;                           // most pieces of a tile
-constexpr int SPLIT_TILE_FLOATS = 256 * 256;           // a partial 256-row tile; a 128-row tile takes half
-constexpr int SPLIT_XCD_TILES = K64_CUS / K64_XCDS;    // partial 256-row tiles that an XCD has scratch for
-struct XcdWork {
-    int big0, small0;    // first 256-row and 128-row tile of this XCD
-    int nb, ns;          // number of either
-    int full;            // 256-row tiles that are not cut
-    int S;               // pieces of the others and of the 128-row tiles
-    __device__ __forceinline__ void init(int total_big, int total_small, int KT, int xcd, int stride, bool split) {
-        big0 = total_big * xcd / K64_XCDS; nb = total_big * (xcd + 1) / K64_XCDS - big0;
-        small0 = total_small * xcd / K64_XCDS; ns = total_small * (xcd + 1) / K64_XCDS - small0;
-        full = nb;
-        S = 1;
-        if (split) cut(choose(KT, stride), stride);
-    }
-    __device__ __forceinline__ void cut(int pieces, int stride) {
-        S = pieces;
-        full = S > 1 ? nb / stride * stride : nb;
-    }
-    __device__ __forceinline__ int choose(int KT, int stride) const {
-        const int R = nb % stride;
-        int S = 1;
-        int best = 1 << 30;
-        for (int s = 1; s <= SPLIT_MAX && KT / s >= 16 && R * s + (ns * s + 1) / 2 <= SPLIT_XCD_TILES; ++s) {
-            // load of the lighter and the heavier workgroups once the pieces are dealt out; a k-step of 256 rows counts 20, of 128 rows 13
-            const int n = R * s, h = n % stride, l = stride - h;
-            int light = n / stride * 20, heavy = light + (h ? 20 : 0);
-            for (int left = ns * s; left > 0;) {
-                if (h == 0 || light <= heavy) { light += 13; left -= l; }
-                else { heavy += 13; left -= h; }
-            }
-            const int t = max(light, heavy) * (KT / s) + (s > 1 ? SPLIT_COST + SPLIT_COST_PART * s : 0);
-            if (t < best) { best = t; S = s; }
-        }
-        return S;
-    }
-};
-
-// Column tiles of the 128-row tiles.  A launch of fewer tiles than units - few live groups, narrow matrices - cuts 256-row
-// tiles into halves and every tile into as many column tiles, 16 (DUAL) or 32 columns up, as give each unit one: a k-step
-// takes as long as its loads, and tiles of at most half the width have a loop of their own whose k-step is 32 KB instead of 48
-// and four deep (the shortest reductions, which are over before it gets going, keep the wide one).  Kernel times, us, tiles of
-// full width | narrower | with the narrow loop: 495 tokens, 5 experts of d = 1792, F = 256 38 + 12 | 25 + 9 | 17 + 9; 900 tokens,
-// 12 experts of d = 1024, F = 512 28 + 17 | 20 + 12 | 14 + 9; 300 tokens, 3 experts of d = 3072, F = 1024 59 + 25 | 42 + 18 | 28 +
-// 13; DeepSeek-shaped 17 / 32 / 128 tokens, down projection 30 30 34 | 24 25 28 | 19 25 28.  Twice as many tiles as units were
-// no better cut (Qwen3-shaped, 512 tokens: 378 tiles 80 us, 504 narrower ones 88).
-struct SmallPlan {
-    int halved;          // 256-row tiles cut into halves: all or none of them
-    int cols;            // column tiles
-    bool narrow;         // they are at most half as wide as a tile can be
-    __device__ __forceinline__ SmallPlan(int n_big, int n_small, int n_nt, int n_blk, int KT, int units, bool may) {
-        const int tiles = 2 * n_big + n_small;
-        halved = 0; cols = n_nt; narrow = false;
-        if (may && tiles > 0 && tiles * n_nt <= units) {
-            halved = n_big;
-            cols = min(units / tiles, n_blk);
-            narrow = n_blk <= 4 * cols && KT >= 6;
-        }
-    }
-};
-
 // number of 128-row tiles: none where the plain table lists every tile
 __device__ __forceinline__ int small_tiles(const GemmParams &p) { return p.mixed ? p.n_mtiles_s[0] : 0; }
 
@@ -508,15 +426,14 @@ __device__ __forceinline__ int scalar_load_i32(const int32_t *table, int idx) {
 // workgroups that got one 256-row tile fewer catch up first (SmallTileDealer).  SPLIT: cut tiles are compiled in.
 __shared__ __attribute__((aligned(1024))) uint16_t k64w_smem[5 * P_PART];        // 160 KB: the whole LDS
 
+// scratch of piece c of the cut tile t of an XCD
+__device__ __forceinline__ float *partial_tile(float *splitk, const XcdWork &x, int xcd, int t, int c) {
+    return splitk + (size_t)xcd * (SPLIT_XCD_TILES * SPLIT_TILE_FLOATS) + x.partial_offset(t, c);
+}
+
 // A piece of a cut tile is done: the wave leaves its fp32 accumulators in scratch memory for split_fixup_kernel
 // (accumulator tile by accumulator tile, 16 bytes a lane; blocks of dead rows are left out).  Read one
 // accumulator tile at a time, by hand: copies of all of them in vector registers spill.
-// Scratch of piece c of the cut tile t of an XCD, 256-row tiles first.
-__device__ __forceinline__ float *partial_tile(float *splitk, const XcdWork &x, int xcd, int t, int c) {
-    const int R = x.nb - x.full;
-    return splitk + (size_t)xcd * (SPLIT_XCD_TILES * SPLIT_TILE_FLOATS) +
-           (t < R ? (size_t)(t * x.S + c) * SPLIT_TILE_FLOATS : (size_t)(2 * R * x.S + (t - R) * x.S + c) * (SPLIT_TILE_FLOATS / 2));
-}
 template <int RB, int CB>
 __device__ __forceinline__ void store_partial(float *dst, const f32x4 (&acc)[RB][CB], int wave_row0, int row_end) {
     const int lane = threadIdx.x & 63;
@@ -573,9 +490,9 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
         ok_ = idx < n_items;                                                                       \
         item_tile = idx; kbeg = 0; kend = KT;                                                      \
         if (SPLIT && ok_ && idx >= work.full && work.S > 1) {                                      \
-            const int c_ = (idx - work.full) / R;                                                  \
+            const int c_ = work.big_piece(idx);                                                    \
             item_tile = idx - c_ * R;                                                              \
-            kbeg = c_ * KT / work.S; kend = (c_ + 1) * KT / work.S;                                \
+            work.piece(c_, kbeg, kend);                                                            \
         }                                                                                          \
         idx += stride;                                                                             \
     }
@@ -852,7 +769,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
         asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[MI - 1][7]));
         if (t_partial) {
             if (live)
-                store_partial<MI, 8>(partial_tile(p.splitk, work, xcd, t_tile - work.full, (t_kbeg * work.S + KT - 1) / KT) + wave * (MI * 8 * 256), acc,
+                store_partial<MI, 8>(partial_tile(p.splitk, work, xcd, t_tile - work.full, work.piece_at(t_kbeg)) + wave * (MI * 8 * 256), acc,
                                      t_row0 + wm * (MI * 16), t_row_end);
             if (!more) break;
             continue;
@@ -1090,9 +1007,9 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
         kb_ = 0; ke_ = KT;                                                                         \
         ok_ = dealer.next(item);                                                                   \
         if (SPLIT && ok_ && work.S > 1) {                                                          \
-            const int c_ = item / work.ns;                                                         \
+            const int c_ = work.small_piece(item);                                                 \
             item -= c_ * work.ns;                                                                  \
-            kb_ = c_ * KT / work.S; ke_ = (c_ + 1) * KT / work.S;                                  \
+            work.piece(c_, kb_, ke_);                                                              \
         }                                                                                          \
     }
     bool n_more;
@@ -1256,7 +1173,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
         asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[(RBL_) - 1][NJ - 1]));                                         \
         if (SPLIT && t_kend - t_kbeg < KT)                                                                            \
             store_partial<(RBL_), NJ>(partial_tile(p.splitk, work, xcd, work.nb - work.full + t_tile,                 \
-                                                   (t_kbeg * work.S + KT - 1) / KT) + wave * (RB * NJ * 256), acc, t_row0, t_row_end);\
+                                                   work.piece_at(t_kbeg)) + wave * (RB * NJ * 256), acc, t_row0, t_row_end);\
         else                                                                                                          \
             k64s_write<DUAL, (RBL_), NJ>(acc, reinterpret_cast<uint32_t *>(smem + NS * STAGE) + wave * 1024, c, N, t_row0, t_row_end,\
                                          t_n0 + wave * (DUAL ? 8 : 16) * NJ, t_n_end, lane);                          \
@@ -1324,7 +1241,6 @@ __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmP
 // tile's pieces are read where they were written and partly still sit in that XCD's L2.  A workgroup handles one slice - four
 // accumulator tiles of each of the writers' waves - with the writers' thread -> element mapping, so that the sums are
 // spread over the chip.
-constexpr int FIXUP_TILES = 32;                        // most cut tiles of an XCD: 2 to 8 pieces each of at least 128 KB
 __global__ void __launch_bounds__(256) split_fixup_kernel(GemmParams p) {
     const int xcd = blockIdx.x & 7, slice = (blockIdx.x >> 3) & 15, tile = blockIdx.x >> 7, stride = p.split_stride;
     const int n_nt = (p.N + 255) / 256, n_mt = p.n_mtiles[0];

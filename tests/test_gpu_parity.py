@@ -177,8 +177,8 @@ LAYER_CASES = [
     ("c3_mixtral_prefill", dict(d=256, F=320), 600),
     ("c5_deepseek", dict(d=256, F=384, E=16, n_resident=6), 700),
     ("c5_deepseek", dict(d=256, F=256, E=16, n_resident=6), 900),     # four k-steps in both projections
-    # long reduction of the down projection (the reduction-split tail itself needs more than 256 tiles: it is
-    # covered by the full-size Mixtral prefill test)
+    # long reduction of the down projection, 256-row tiles only: those that do not fill a round of an XCD are cut along it
+    # (more such layers, with 128-row tiles among them, in test_gpu_tiled_edges.py)
     ("c3_mixtral_prefill", dict(d=256, F=4096), 2300),
     # the two projections on different tile heights (each walks its own row-tile table): 128-row gate/up tiles
     # with 256-row down tiles, short and long reduction

@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 # (overrides, tokens): reductions of 4 to 11 k-steps (an item's first loads, its look-up and its hand-over fall together
 # in the shortest), widths that end inside a column tile, groups of a few rows to a few 256-row tiles with rests on both sides of
 # 128, many groups, shared experts; then reductions of 64 and more k-steps, whose tiles are cut: both heights
-# (below 128 routed rows an expert on average) and 256 rows only, one to sixteen column tiles, pieces of unequal length
+# (below 128 routed rows an expert on average) and 256 rows only, one to sixteen column tiles, pieces of unequal length; up
+# to 65 k-steps 3 and 4 pieces, then 6 and 7 of 256- and 128-row tiles, 7 of 256-row tiles alone, 8 of both heights, 8 of unequal
+# length of 128-row tiles alone
 CASES = [
     (dict(d=256, F=256, E=4, K=2, n_resident=4), 150),
     (dict(d=320, F=448, E=4, K=2, n_resident=2), 257),
@@ -25,6 +27,10 @@ CASES = [
     (dict(d=1024, F=4160, E=8, K=2, n_resident=5), 530),
     (dict(d=4096, F=4096, E=8, K=2, n_resident=5), 150),
     (dict(d=256, F=4096, E=4, K=2, n_resident=4), 700),
+    (dict(d=512, F=8192, E=8, K=2, n_resident=5), 300),
+    (dict(d=512, F=8256, E=4, K=2, n_resident=4), 300),
+    (dict(d=256, F=16384, E=16, K=2, n_resident=12), 300),
+    (dict(d=256, F=16448, E=8, K=2, n_resident=5), 120),
 ]
 
 
