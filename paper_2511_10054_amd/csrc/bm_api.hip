@@ -29,20 +29,7 @@ using namespace bm;
 
 constexpr size_t ALIGN = 256;
 constexpr int MAX_SHARED = 8;
-constexpr int SKINNY_MAX_ROWS = 256;   // total rows up to which the weight-streaming path is always used,
-constexpr int SKINNY_AVG_ROWS = 16;    // ... and rows per group (averaged over all experts) likewise
-constexpr int SKINNY_UNFIT_ROWS = 16;  // total rows when the widths do not fit its fast kernels but do fit the persistent tiled kernel
 constexpr int SKINNY_KSPLIT = 8;
-
-// Shapes both projections of which fit the persistent k-step-64 kernel: reduction widths that are multiples
-// of 64 and at least 256, operands within 32-bit byte offsets.
-bool k64_shape(const bm_layer_desc *d) {
-    const unsigned long long lim = 1ull << 32;
-    const int ns = d->n_shared > 0 ? d->n_shared : 0;
-    const unsigned long long rows = (unsigned long long)d->T * (d->K + ns) + 256ull * (d->E + ns);
-    return d->dtype == BM_BF16 && d->d % 64 == 0 && d->F % 64 == 0 && d->d >= 256 && d->F >= 256 &&
-           (unsigned long long)d->T * d->d * 2 < lim && rows * d->F * 2 < lim && (unsigned long long)d->F * d->d * 2 < lim;
-}
 
 // Row tiles of a grouped projection (down: the down projection, else gate/up): TILES_MIXED, or the single
 // tile height 256 / 128.  On the persistent kernel (k64_shape on a device of the expected shape) a launch
@@ -65,37 +52,6 @@ int tile_mode(const bm_layer_desc *d, bool down, bool persistent) {
     return large ? 256 : 128;
 }
 
-// Widths that are multiples of 128 but not of 256 take the two-wave streaming kernel (bm_dispatch_rules.h) instead of the
-// tiled path up to 16 tokens
-// (DeepSeek-shaped layer, F = 1408, at 3 / 8 / 16 / 32 tokens: tiled .061 .077 .080 .087, two-wave streaming .053
-// .062 .070 .089), as long as its fp32 down-projection output is small (the tiled path's is bf16).  A call whose
-// workspace has no room for that output keeps the tiled path (plan_layout): one that is sized for the largest batch
-// of a serving loop, of 17 to 25 tokens for instance, takes every smaller batch.
-constexpr int NARROW_UNFIT_T = 16;
-constexpr long long NARROW_UNFIT_BYTES = 16ll << 20;
-
-// Few rows per group: every expert group is decode-sized and the projections are bound by reading the
-// weights once.  Up to 256 rows in all, or up to 16 rows per expert on average (Qwen3-shaped layer, 128
-// experts, 64 / 128 / 256 tokens: 0.11 / 0.13 / 0.16 ms against 0.14 / 0.15 / 0.16 ms on the tiled path), when
-// both widths fit the fast streaming kernels (multiples of 256).  Widths that do not (DeepSeek-shaped layer,
-// F = 1408, whose shared experts take every token as well) leave the streaming path to its slower
-// fallbacks: there the persistent tiled kernel is faster from 4 tokens on (4 / 8 / 32 tokens: 0.064 / 0.071 /
-// 0.089 against 0.068 / 0.082 / 0.101 ms), so the streaming path keeps only batches of at most 16 rows, unless
-// the two-wave kernel takes the shape (narrow_shape).
-// Streaming | tiled, us: Mixtral-shaped layer 64 / 96 / 112 / 128 tokens, public weights 338 364 373 411 | 341 354 355 356,
-// packed 311 340 346 364 | 345 354 351 357; Qwen3-shaped 128 / 192 / 224 / 256 tokens 112 134 145 153 | 132 135 139 140.
-// The batches at the upper end would be faster tiled, but that path holds the down projection's output in bf16 until
-// the aggregation, the streaming one in fp32 (error against 64 bits 0.0029 | 0.0023), so the lines stay where they are.
-bool use_skinny(const bm_layer_desc *d, bool compact) {
-    if (d->dtype != BM_BF16) return false;
-    const int ns = d->n_shared > 0 ? d->n_shared : 0;
-    const long long rows = (long long)d->T * (d->K + ns);
-    const bool fit = d->d % 256 == 0 && d->F % 256 == 0;
-    if (!fit && k64_shape(d))
-        return rows <= SKINNY_UNFIT_ROWS || (!compact && narrow_shape(d) && d->T <= NARROW_UNFIT_T && rows * (2ll * d->F + 4ll * d->d) <= NARROW_UNFIT_BYTES);
-    if (rows <= SKINNY_MAX_ROWS) return true;
-    return fit && rows <= (long long)SKINNY_AVG_ROWS * (d->E + ns);
-}
 // Reduction slices of the decode down projection (each slice is a workgroup
 // whose 4 waves split it once more): prefer a count that fits the
 // quarter-split kernel, else up to 8 slices of at least 16 k-steps.
