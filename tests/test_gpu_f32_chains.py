@@ -30,3 +30,25 @@ def test_long_fp32_reductions(d, F, T):
     e = err_metric(out["y"], ref["y"])
     print("   err", e, flush=True)
     assert e <= TOL, e
+
+
+# Live groups whose weights outgrow the 256 MB memory-side cache (csrc/bm_dispatch_rules.h): groups of at most 64 rows, one row tile,
+# load them non-temporally, by copies of the tiles of their own, larger groups do not.  One group of 270 MB with chains of two,
+# two of 178 MB (a shared expert, which takes every token as well) with chains of one in either projection.  The bound is the one
+# above: a reduction of 15968 values has three more levels of folds than one of 2048 (measured: up to 1.2e-6).
+@pytest.mark.parametrize("d,F,n_shared", [(2048, 11008, 0), (928, 15968, 1), (15968, 928, 1)])
+def test_fp32_weights_past_the_memory_side_cache(d, F, n_shared):
+    assert (1 + n_shared) * 12 * d * F > 256 << 20
+    spec = workloads.scaled("c1_tiny", d=d, F=F, E=4, K=1, n_resident=1, R=3, H=3, n_shared=n_shared)
+    host = dev = None
+    for T in (1, 16, 17, 32, 33, 64, 65, 130):
+        print("fp32 past the cache", d, F, T, flush=True)
+        host = HostLayer(spec, T, only_resident=True, poison=True, base=host)
+        rows = np.unique([0, T // 2, T - 1])                         # tokens are independent: the oracle takes three
+        ref = host.oracle_forward(oracle, rows=rows)
+        dev = DeviceLayer(host, base=dev)
+        out = dev.forward()
+        np.testing.assert_array_equal(out["ids_remapped"][rows], ref["ids_remapped"])
+        e = err_metric(out["y"][rows], ref["y"])
+        print("   err", e, flush=True)
+        assert e <= TOL, e
