@@ -11,7 +11,8 @@ namespace bm {
 // ---------------------------------------------------------------------------
 
 // bf16 rows (tiled path): eight columns a thread.  NT: non-temporal loads, for more rows than the 256 MB memory-side cache
-// holds (us without | with: 268 MB 55 | 47, 196 MB 35 | 36, 134 MB 24.3 | 25.6, 20 MB 7.5 | 8.7).
+// holds beside the rest (us without | with: 268 MB 55 | 47, 196 MB 35 | 36, 134 MB 24.3 | 25.6, 20 MB 7.5 | 8.7: the line,
+// 224 MB, lies between the two largest).  The rows of dropped slots are counted: how many there are only the device knows.
 template <bool NT>
 __global__ void __launch_bounds__(256) combine_bf16_kernel(CombineParams p) {
     __shared__ int s_pos[BM_MAX_K + 8];

@@ -893,7 +893,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
 //   rows 4.6 -> 5.5, 28 KB rows 6.0 -> 7.0).  What an XCD misses in its L2 comes at 7 TB/s for the whole chip, from the
 //   memory-side cache as well.
 // Kernel times, 128-row tiles on the 256-row ring | here, us: Mixtral-shaped 256 tokens gate/up 292 | 250, Qwen3-shaped 512
-// tokens 88 | 79 and 52 | 52, 2048 tokens 150 | 137, DeepSeek-shaped 128 tokens 53 | 46 and 36 | 33.
+// tokens 88 | 79 and 52 | 52, 2048 tokens 156 | 148, DeepSeek-shaped 128 tokens 53 | 46 and 36 | 33.
 // Hazards around the assembly MFMA as in k64w_body.
 // ---------------------------------------------------------------------------
 constexpr int DMA_STREAM = 2;                              // cache policy of a load that is not read again (nt)

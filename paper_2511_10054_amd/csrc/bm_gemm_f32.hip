@@ -63,7 +63,7 @@ __global__ void __launch_bounds__(256) rowwise_f32_kernel(GemmParams p) {
 //
 // What bounds it: groups of at most ~30 rows are bound by streaming their weights once, larger ones by the fp32
 // matrix rate.  The kernel it replaces (one workgroup per row, each wave a weight row at a time) read an expert's
-// weights once per ROW: 2790 + 2630 us for the two projections of the Qwen3-shaped layer at 128 tokens; here 127 + 78 us
+// weights once per ROW: 2790 + 2630 us for the two projections of the Qwen3-shaped layer at 128 tokens; here 123 to 148 + 75 to 85 us by inputs
 // (floors 90 and 48: 599 and 322 MB read at 6.7 TB/s).  Groups of a few rows, which stream, and groups of tens of rows,
 // which multiply, take turns on a unit.
 //

@@ -356,8 +356,9 @@ def test_front_end_kernels_stay_out_of_scratch_memory(tmp_path):
 def test_prefill_kernels_keep_the_hand_managed_register_to_themselves(tmp_path):
     """The persistent prefill kernels park the pending result of one vector load in v255, a register the
     compiler does not manage (csrc/bm_gemm_bf16.hip, BM_LOOKUP / BM_ADOPT): the compiler's own values must
-    stay below it, and it may appear in the hand-written statements only.  The same kernels must not spill:
-    a reload from scratch memory waits for every load and store in flight.  Checked on the assembly the
+    stay below it, and it may appear in the hand-written statements only.  The same kernels must not spill
+    vector registers: a reload from scratch memory waits for every load and store in flight.  (Scalar registers they do spill, to
+    lanes of a vector register, which touches no memory.)  Checked on the assembly the
     build's compiler emits for the build's flags (own code, device side only)."""
     import re
     import subprocess
