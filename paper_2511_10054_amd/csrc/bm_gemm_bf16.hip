@@ -466,12 +466,12 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
     const int r16 = lane & 15, quad = lane >> 4;           // MFMA 16x16x32: row (or column) and k eighth
 
     // Persistent: workgroup b serves the XCD it was dealt to (b % 8) and walks that XCD's share of the
-    // logical tiles with stride (workgroups per XCD), so the workgroups that run together on an XCD work
+    // logical tiles with stride XCD_WGS, so the workgroups that run together on an XCD work
     // on consecutive logical tiles (see tile_of) and a workgroup keeps its compute unit: the next tile's
     // first loads fly while the finished tile is written out, and nothing is relaunched.
     const int n_mt = p.n_mtiles[0];
     const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
-    const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, slot = blockIdx.x >> 3;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int N = p.N, Kd = p.Kd;
     const int KT = Kd / 64;
     // Gate/up: the reduction is walked as a circle that each XCD enters elsewhere (see k64s_body); inside an XCD the
@@ -494,7 +494,7 @@ __device__ __forceinline__ void k64w_body(const GemmParams &p, const XcdWork &wo
             item_tile = idx - c_ * R;                                                              \
             work.piece(c_, kbeg, kend);                                                            \
         }                                                                                          \
-        idx += stride;                                                                             \
+        idx += XCD_WGS;                                                                            \
     }
     bool have;
     BM_NEXT_ITEM(have);
@@ -992,7 +992,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, quad = lane >> 4;
     constexpr int BLK = DUAL ? 16 : 32;                    // columns by which the width of a tile varies
-    const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3, slot = blockIdx.x >> 3;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int N = p.N, Kd = p.Kd;
     const int KT = Kd / 64;
     const bool WIDE = NJ == 4 && plan.cols == (DUAL ? (N + 127) / 128 : (N + 255) / 256);   // column tiles of full width
@@ -1000,7 +1000,7 @@ __device__ __forceinline__ void k64s_body(const GemmParams &p, const XcdWork &wo
     int rot = 0, rot_n = 0;                                // where the tile whose loads are being issued enters the reduction
     auto rotated = [&](int k) { const int r = k + rot; return r >= KT ? r - KT : r; };
     SmallTileDealer dealer;
-    dealer.init((work.nb - work.full) * work.S + work.full, work.ns * work.S, stride, slot);
+    dealer.init((work.nb - work.full) * work.S + work.full, work.ns * work.S, XCD_WGS, slot);
     int item = 0, kbeg = 0, kend = KT;
 #define BM_NEXT_ITEM(ok_, kb_, ke_)                                                                \
     {                                                                                              \
@@ -1201,8 +1201,8 @@ template <bool DUAL, bool SPLIT, bool MAY_STREAM>
 __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmParams p) {
     const int n_nt = DUAL ? (p.N + 127) / 128 : (p.N + 255) / 256;
     XcdWork work;
-    const SmallPlan plan(p.n_mtiles[0], small_tiles(p), n_nt, p.N / (DUAL ? 16 : 32), p.Kd / 64, gridDim.x, !SPLIT);
-    work.init((p.n_mtiles[0] - plan.halved) * n_nt, (2 * plan.halved + small_tiles(p)) * plan.cols, p.Kd / 64, blockIdx.x & 7, gridDim.x >> 3, SPLIT);
+    const SmallPlan plan(p.n_mtiles[0], small_tiles(p), n_nt, p.N / (DUAL ? 16 : 32), p.Kd / 64, K64_CUS, !SPLIT);
+    work.init((p.n_mtiles[0] - plan.halved) * n_nt, (2 * plan.halved + small_tiles(p)) * plan.cols, p.Kd / 64, blockIdx.x & 7, SPLIT);
     if (SPLIT && blockIdx.x < K64_XCDS && threadIdx.x == 0) p.split_pieces[blockIdx.x] = work.S;
     // A 128-row tile is the only user of its weight panel (a group has at most one), so it streams from
     // memory at a third of a 256-row tile's arithmetic intensity.  When there are many of them (at least a
@@ -1242,13 +1242,13 @@ __global__ void __launch_bounds__(256) grouped_gemm_mixed_k64w_bf16_kernel(GemmP
 // accumulator tiles of each of the writers' waves - with the writers' thread -> element mapping, so that the sums are
 // spread over the chip.
 __global__ void __launch_bounds__(256) split_fixup_kernel(GemmParams p) {
-    const int xcd = blockIdx.x & 7, slice = (blockIdx.x >> 3) & 15, tile = blockIdx.x >> 7, stride = p.split_stride;
+    const int xcd = blockIdx.x & 7, slice = (blockIdx.x >> 3) & 15, tile = blockIdx.x >> 7;
     const int n_nt = (p.N + 255) / 256, n_mt = p.n_mtiles[0];
     XcdWork work;
     const int n = p.split_pieces[xcd];                     // S, as the workgroups of the launch before chose it
     if (n == 1) return;
-    work.init(n_mt * n_nt, small_tiles(p) * n_nt, p.Kd / 64, xcd, stride, false);
-    work.cut(n, stride);
+    work.init(n_mt * n_nt, small_tiles(p) * n_nt, p.Kd / 64, xcd, false);
+    work.cut(n);
     const int R = work.nb - work.full;
     const bool big = tile < R;
     if (tile >= R + work.ns || (!big && slice >= 8)) return;
@@ -1345,10 +1345,9 @@ bool down_split_tail(int Kd) { return Kd / 64 >= 64; }
 
 int launch_down_bf16(const GemmParams &p, hipStream_t st) {
     if (p.BM == 256 && k64_ok(p) && p.splitk != nullptr && down_split_tail(p.Kd)) {
-        GemmParams q = p;
-        q.split_stride = K64_CUS / K64_XCDS;
-        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false, true, true>), dim3(K64_CUS), dim3(256), 0, st, q);
-        hipLaunchKernelGGL(split_fixup_kernel, dim3(K64_XCDS * 16 * FIXUP_TILES), dim3(256), 0, st, q);
+        hipLaunchKernelGGL((grouped_gemm_mixed_k64w_bf16_kernel<false, true, true>), dim3(K64_CUS), dim3(256), 0, st, p);
+        const int tiles = p.mixed ? FIXUP_TILES : FIXUP_TILES_256;
+        hipLaunchKernelGGL(split_fixup_kernel, dim3(K64_XCDS * 16 * tiles), dim3(256), 0, st, p);
     } else if (p.mixed && k64_ok(p)) {
         launch_mixed<false>(p, st);
     } else if (p.mixed) {

@@ -95,7 +95,6 @@ struct GemmParams {
     float *splitk;                // scratch for the partial tiles of tiles that are cut along the reduction, or null: none is
     int cached_groups;            // most live groups whose weights the memory-side cache holds: of more, weights read once are loaded non-temporally
     int32_t *split_pieces;        // [K64_XCDS] pieces of a cut tile, XCD by XCD, as the launch that cuts them chose
-    int split_stride;             // workgroups per XCD of that launch
 };
 
 // Skinny (decode) projections: one weight-row block per wave, see bm_skinny_bf16.hip.

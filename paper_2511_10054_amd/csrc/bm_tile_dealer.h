@@ -4,8 +4,10 @@
 
 #if defined(__HIPCC__)
 #define BM_HOST_DEVICE __host__ __device__ __forceinline__
+#define BM_UNROLL _Pragma("unroll")
 #else
 #define BM_HOST_DEVICE inline
+#define BM_UNROLL
 #endif
 
 namespace bm {

@@ -20,44 +20,47 @@ BM_HOST_DEVICE void tile_of(int lid, int n_mt, int n_nt, int &mt, int &nt) {
     mt = first + (in_group - nt * gsize);
 }
 
-// One XCD's share of a launch that runs both tile heights.  Its workgroups (stride of them) take its 256-row tiles round by
+// One XCD's share of a launch that runs both tile heights.  Its workgroups (XCD_WGS of them) take its 256-row tiles round by
 // round, then its 128-row tiles (SmallTileDealer).  SPLIT: the 256-row tiles that do not fill a round (R of them) and the
 // 128-row tiles are cut along the reduction into S pieces each, so that the last round is short; the pieces
 // leave fp32 partial tiles in scratch memory and split_fixup_kernel adds them up.  All tiles are cut at the same places and
 // first pieces go out before second ones, because workgroups that run together share panels in the XCD's L2 only
 // while they are at the same k: pieces of equal cost laid end to end (every workgroup at a k of its own)
 // fetch 64 KB a k-step from outside the XCD, 2.4 us at the 28 GB/s that a unit gets there.
+constexpr int XCD_WGS = K64_CUS / K64_XCDS;            // workgroups of a launch that an XCD gets
 constexpr int SPLIT_COST = 160, SPLIT_COST_PART = 40;   // of partial tiles and their sums, in twentieths of a 256-row k-step
 constexpr int SPLIT_MAX = 8;                           // most pieces of a tile
 constexpr int SPLIT_TILE_FLOATS = 256 * 256;           // a partial 256-row tile; a 128-row tile takes half
-constexpr int SPLIT_XCD_TILES = K64_CUS / K64_XCDS;    // partial 256-row tiles that an XCD has scratch for
-constexpr int FIXUP_TILES = 32;                        // most cut tiles of an XCD: 2 to 8 pieces each of at least 128 KB
+constexpr int SPLIT_XCD_TILES = XCD_WGS;               // partial 256-row tiles that an XCD has scratch for
+// most cut tiles of an XCD, 2 to 8 pieces each: in a launch of both heights, of 256-row tiles alone
+constexpr int FIXUP_TILES = SPLIT_XCD_TILES, FIXUP_TILES_256 = SPLIT_XCD_TILES / 2;
 struct XcdWork {
     int big0, small0;    // first 256-row and 128-row tile of this XCD
     int nb, ns;          // number of either
     int full;            // 256-row tiles that are not cut
     int S;               // pieces of the others and of the 128-row tiles
     int KT;              // k-steps of the reduction
-    BM_HOST_DEVICE void init(int total_big, int total_small, int KT_, int xcd, int stride, bool split) {
+    BM_HOST_DEVICE void init(int total_big, int total_small, int KT_, int xcd, bool split) {
         big0 = total_big * xcd / K64_XCDS; nb = total_big * (xcd + 1) / K64_XCDS - big0;
         small0 = total_small * xcd / K64_XCDS; ns = total_small * (xcd + 1) / K64_XCDS - small0;
         full = nb;
         S = 1;
         KT = KT_;
-        if (split) cut(choose(stride), stride);
+        if (split) cut(choose());
     }
-    BM_HOST_DEVICE void cut(int pieces, int stride) {
+    BM_HOST_DEVICE void cut(int pieces) {
         S = pieces;
-        full = S > 1 ? nb / stride * stride : nb;
+        full = S > 1 ? nb / XCD_WGS * XCD_WGS : nb;
     }
-    BM_HOST_DEVICE int choose(int stride) const {
-        const int R = nb % stride;
+    BM_HOST_DEVICE int choose() const {
+        const int R = nb % XCD_WGS;
         int S = 1;
         int best = 1 << 30;
-        for (int s = 1; s <= SPLIT_MAX && KT / s >= 16 && R * s + (ns * s + 1) / 2 <= SPLIT_XCD_TILES; ++s) {
+        // (unrolled, and with a constant number of workgroups, so that it divides by constants: it runs before a launch's first load)
+        BM_UNROLL for (int s = 1; s <= SPLIT_MAX && KT / s >= 16 && R * s + (ns * s + 1) / 2 <= SPLIT_XCD_TILES; ++s) {
             // load of the lighter and the heavier workgroups once the pieces are dealt out; a k-step of 256 rows counts 20, of 128 rows 13
-            const int n = R * s, h = n % stride, l = stride - h;
-            int light = n / stride * 20, heavy = light + (h ? 20 : 0);
+            const int n = R * s, h = n % XCD_WGS, l = XCD_WGS - h;
+            int light = n / XCD_WGS * 20, heavy = light + (h ? 20 : 0);
             for (int left = ns * s; left > 0;) {
                 if (h == 0 || light <= heavy) { light += 13; left -= l; }
                 else { heavy += 13; left -= h; }
